@@ -377,10 +377,11 @@ a3_status a3_chunk_cache_load_q8(const a3_layout *layout, const int *chunk_start
  * Process-wide integers, read when a call is made; value < 0 restores the library's own choice.  Names:
  *   "attn_wgs"        workgroups (shares of the work) per KV head in a3_fused_attention, 1 .. 1024
  *   "attn_item_cost"  start-up cost of a row tile, in 64-key steps, that the shares are balanced with, 0 .. 64
- *   "proj_ntw"        row-tile width (2, 3, 4: 128, 192, 256 rows) of the projection GEMM; set, it also sends
- *                     calls with few rows to that kernel instead of the weight-streaming one
- *   "proj_k64"        0: the projection's main loop on 64-byte instead of 128-byte row pieces
- *   "gemm_tb", "gemm_k64"   the same two for the GEMMs of a3_block_tail
+ *   "proj_ntw"        tile of the projection GEMM (2, 3, 4: 256 weight rows x 128, 192, 256 rows; 5, 6, 7: 128 weight
+ *                     rows x 192, 128, 64 rows); set, it also sends calls with few rows to that kernel instead of
+ *                     the weight-streaming one
+ *   "gemm_tb"         the same tiles for the GEMMs of a3_block_tail; set, their reduction is not split
+ *   "proj_k64", "gemm_k64"   accepted, without effect (there is one way to fetch the rows)
  * A value must not change between a3_attention_plan and the a3_fused_attention_planned calls that use its plan:
  * if "attn_wgs" does, the plan lies elsewhere in the workspace, the kernels of the planned call notice (the
  * plan records the value it was made with at a fixed place) and leave `out` untouched.

@@ -7,20 +7,16 @@
 // The paper names H in one clause (layer normalisation and feed-forward network applied to the attention
 // output); this is the pre-norm block of the model families it evaluates.
 //
-// bf16: three launches of one row-tiled MFMA GEMM (weights [out, in], both operands reduction-contiguous)
-// with two epilogues -- "add to the residual row" and "silu(gate) * up" -- and two launches of a
-// one-wave-per-row RMSNorm.  The GEMM main loop is the one of the Q/K/V projection: 256 weight rows x
-// 64*TB activation rows per workgroup, direct-to-LDS loads into a ring of 32-wide k-slabs, every
-// fragment read and every load issued singly behind an MFMA.  For the gated pair a wave's 128 weight
-// rows are 64 gate rows and the 64 up rows of the same features, so gate and up of one output meet in
-// one lane and the activation is formed on the fp32 accumulators.
+// bf16: three launches of the row-tiled MFMA GEMM of a3_gemm_pp.h (weights [out, in], both operands
+// reduction-contiguous) with the epilogues "add to the residual row", "silu(gate) * up" on the fp32 accumulators
+// (gate and up of one output meet in one lane) and "store the partial product", and RMSNorm kernels.
 // fp32: plain LDS-tiled FMA kernels (correctness configuration, not tuned).
 #include "a3_internal.h"
-#include "a3_gemm_tile.h"
+#include "a3_gemm_pp.h"
 
 namespace {
 
-enum { EPI_RESID = 0, EPI_SWIGLU = 1 };
+enum { EPI_RESID = 0, EPI_SWIGLU = 1, EPI_PART = 2 };
 
 // ---------------------------------------------------------------------------------------
 // RMSNorm: one wave per row, two passes over the row (the second is served by the cache)
@@ -59,120 +55,165 @@ rms_norm_kernel(const T *x, const int *__restrict__ in_idx, const T *__restrict_
 // bf16 MFMA GEMM with the two epilogues
 // ---------------------------------------------------------------------------------------
 struct gemm_args {
-  const bf16_t *a;       // activation rows [*, K]
-  const int *a_idx;      // row i of the product reads activation row a_idx[i] (NULL: row i)
+  const bf16_t *a;       // activation rows [n_rows, K]
   int n_rows;
   const bf16_t *w0;      // [N, K]; EPI_SWIGLU: the gate weights
   const bf16_t *w1;      // EPI_SWIGLU: the up weights [N, K]
   bf16_t *out;           // EPI_RESID: [*, N], row out_idx[i] += product row i; EPI_SWIGLU: [n_rows, N]
   const int *out_idx;
   int K, N;
-  int n_ftiles, n_tok_tiles;
+  float *part;           // EPI_PART: [splits, n_rows, N] partial products
+  int splits;
+  int n_wtiles, n_tok_tiles, group;
 };
 
-template <int TB, int EPI, bool K64>
-__global__ void __launch_bounds__(256, (TB == 2 && !K64) ? 2 : 1)
+template <class P, int EPI>
+__global__ void __launch_bounds__(512)
 gemm_bf16_kernel(gemm_args a) {
-  constexpr int kTokTile = 64 * TB;
-  constexpr int kFeat = EPI == EPI_RESID ? 256 : 128;        // output features per workgroup
+  constexpr int IB = P::kIB, JB = P::kJB;
+  // output features per workgroup and per wave group (EPI_SWIGLU: half 0 of a group's rows are gate rows, half 1 the up
+  // rows of the same features)
+  constexpr int kFeat = EPI == EPI_SWIGLU ? P::BM / 2 : P::BM, kFeatGrp = kFeat / 2;
   extern __shared__ __align__(16) unsigned char lds[];
+  int wt, xt;
+  if (!gemm_tile_of(a.n_wtiles, a.n_tok_tiles, a.group, blockIdx.x, wt, xt)) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, lg = lane >> 4, grp = wave >> 2, wn = wave & 3;
 
-  // consecutive workgroup ids go to different XCDs; all row tiles of one feature tile stay on one XCD
-  const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
-  const int ft = xcd + 8 * (q / a.n_tok_tiles), tt = q % a.n_tok_tiles;
-  if (ft >= a.n_ftiles) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, lhi = lane >> 5;
-  const int fh = wave & 1, th = wave >> 1;
-
-  const int tok0 = tt * kTokTile + th * 32 * TB;
-
-  // ---- the product.  EPI_RESID: weight-tile row r is weight row kFeat ft + r.  EPI_SWIGLU: rows 0..63 of a
-  // wave's half are the gate rows of its 64 features, rows 64..127 the up rows of the same features.
-  f32x16 acc[4][TB];
-  gemm_tile_mainloop<TB, K64>(
-      acc, lds, a.K,
-      [&](int row) -> const bf16_t * {
-        if (EPI == EPI_RESID) return a.w0 + (size_t)min(kFeat * ft + row, a.N - 1) * a.K;
-        const int r = row & 127;
-        const int f = min(kFeat * ft + 64 * (row >> 7) + (r & 63), a.N - 1);
-        return (r < 64 ? a.w0 : a.w1) + (size_t)f * a.K;
+  // slabs of this workgroup's share of the reduction (EPI_PART: blockIdx.y of a.splits nearly equal ones)
+  int s0 = 0, ns = a.K / 64;
+  if (EPI == EPI_PART) {
+    const int all = ns, b = all / a.splits, rem = all - b * a.splits, y = blockIdx.y;
+    s0 = y * b + min(y, rem);
+    ns = b + (y < rem ? 1 : 0);
+  }
+  f32x4 acc[IB][JB];
+  P::mainloop(
+      acc, lds, ns,
+      [&](int r0) -> const char * {
+        int q = 0, f;
+        if (EPI == EPI_SWIGLU) P::row_of(r0 % (16 * IB), q, f);
+        return reinterpret_cast<const char *>((q ? a.w1 : a.w0) + (size_t)wt * kFeat * a.K + 64 * s0);
       },
-      [&](int row) -> const bf16_t * {
-        const int m = min(tt * kTokTile + row, a.n_rows - 1);    // clamp: computed but never stored
-        return a.a + (size_t)(a.a_idx ? a.a_idx[m] : m) * a.K;
+      [&](int r) -> uint32_t {
+        int q, f;
+        P::row_of(r % (16 * IB), q, f);
+        f += (r / (16 * IB)) * kFeatGrp + (EPI == EPI_SWIGLU ? 0 : 8 * IB * q);
+        return (uint32_t)min(f, a.N - 1 - wt * kFeat) * (uint32_t)a.K * 2u;
+      },
+      [&](int) -> const char * { return reinterpret_cast<const char *>(a.a + (size_t)xt * P::BN * a.K + 64 * s0); },
+      [&](int r) -> uint32_t {
+        return (uint32_t)min(r, a.n_rows - 1 - xt * P::BN) * (uint32_t)a.K * 2u;   // clamp: computed but never stored
       });
 
-  // ---- epilogue ----------------------------------------------------------------------------------------
-  // Each wave turns its fp32 tile through its own piece of the now free LDS, one 32-row block at a time
-  // ([32 rows][128 weight rows], row stride 528 bytes).  Read back, a lane holds weight rows 4c..4c+3 and
-  // 64+4c..64+4c+3 of one activation row and 16 lanes cover that row: global accesses are whole runs.
-  __syncthreads();
-  const int fblock = EPI == EPI_RESID ? kFeat * ft + 128 * fh : kFeat * ft + 64 * fh;   // first output feature
-  if (fblock >= a.N) return;
-  constexpr int kEpiStride = 528;
-  unsigned char *epi = lds + wave * (32 * kEpiStride);
-  const int ec = lane & 15, er = lane >> 4;
-  int orow[TB][8];
+  // ---- epilogue: a lane holds L consecutive features of half 0 and of half 1 of one row; four lanes cover 64 or 128
+  // consecutive bytes of a bf16 row
+  constexpr int L = P::L;
+  const int feat = wt * kFeat + grp * kFeatGrp;                  // first feature of the group
+  if (feat >= a.N) return;
 #pragma unroll
-  for (int tb = 0; tb < TB; ++tb)
+  for (int j = 0; j < JB; ++j) {
+    const int tok = xt * P::BN + 16 * (JB * wn + j) + l16;
+    float lo[L], hi[L];
+    if constexpr (EPI == EPI_RESID) {
+      const int row = tok < a.n_rows ? (a.out_idx ? a.out_idx[tok] : tok) : -1;
+      bf16_t *p = a.out + (size_t)max(row, 0) * a.N + feat + L * lg;
+      bf16x8 rl[L / 8], rh[L / 8];
+      if (row >= 0) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int tok = tok0 + tb * 32 + er + 4 * j;
-      orow[tb][j] = tok < a.n_rows ? (a.out_idx ? a.out_idx[tok] : tok) : -1;
-    }
-#pragma unroll
-  for (int tb = 0; tb < TB; ++tb) {
-    // accumulator block (fb, tb), register r of this lane: weight row 32 fb + 8 (r/4) + 4 lhi + r%4, row l32
-#pragma unroll
-    for (int fb = 0; fb < 4; ++fb)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        f32x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc[fb][tb][4 * q4 + e];
-        *reinterpret_cast<f32x4 *>(epi + l32 * kEpiStride + (32 * fb + 8 * q4 + 4 * lhi) * 4) = v;
-      }
-    if (EPI == EPI_RESID) {
-      bf16x4 rl[8], rh[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (orow[tb][j] >= 0) {
-          const bf16_t *p = a.out + (size_t)orow[tb][j] * a.N + fblock;
-          rl[j] = *reinterpret_cast<const bf16x4 *>(p + 4 * ec);
-          rh[j] = *reinterpret_cast<const bf16x4 *>(p + 64 + 4 * ec);
+        for (int e = 0; e < L / 8; ++e) {
+          rl[e] = *reinterpret_cast<const bf16x8 *>(p + 8 * e);
+          rh[e] = *reinterpret_cast<const bf16x8 *>(p + 8 * IB + 8 * e);
         }
+      }
+      gemm_lane_values<IB, JB>(acc, j, lo, hi);
+      if (row >= 0) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int row = er + 4 * j;
-        const f32x4 lo = *reinterpret_cast<const f32x4 *>(epi + row * kEpiStride + ec * 16);
-        const f32x4 hi = *reinterpret_cast<const f32x4 *>(epi + row * kEpiStride + 256 + ec * 16);
-        if (orow[tb][j] >= 0) {
-          bf16_t *p = a.out + (size_t)orow[tb][j] * a.N + fblock;
-          bf16x4 vlo, vhi;
+        for (int e = 0; e < L / 8; ++e) {
+          bf16x8 vl, vh;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            vlo[e] = a3_f2bf(a3_bf2f(rl[j][e]) + lo[e]);
-            vhi[e] = a3_f2bf(a3_bf2f(rh[j][e]) + hi[e]);
+          for (int u = 0; u < 8; ++u) {
+            vl[u] = a3_f2bf(a3_bf2f(rl[e][u]) + lo[8 * e + u]);
+            vh[u] = a3_f2bf(a3_bf2f(rh[e][u]) + hi[8 * e + u]);
           }
-          *reinterpret_cast<bf16x4 *>(p + 4 * ec) = vlo;
-          *reinterpret_cast<bf16x4 *>(p + 64 + 4 * ec) = vhi;
+          *reinterpret_cast<bf16x8 *>(p + 8 * e) = vl;
+          *reinterpret_cast<bf16x8 *>(p + 8 * IB + 8 * e) = vh;
+        }
+      }
+    } else if constexpr (EPI == EPI_SWIGLU) {
+      gemm_lane_values<IB, JB>(acc, j, lo, hi);                  // gate, up
+      if (tok < a.n_rows) {
+        bf16_t *p = a.out + (size_t)tok * a.N + feat + L * lg;
+#pragma unroll
+        for (int e = 0; e < L; e += 8) {
+          bf16x8 v;
+#pragma unroll
+          for (int u = 0; u < 8; ++u) v[u] = a3_f2bf(lo[e + u] / (1.0f + __expf(-lo[e + u])) * hi[e + u]);
+          *reinterpret_cast<bf16x8 *>(p + e) = v;
         }
       }
     } else {
+      gemm_lane_values<IB, JB>(acc, j, lo, hi);
+      if (tok < a.n_rows) {
+        float *p = a.part + ((size_t)blockIdx.y * a.n_rows + tok) * a.N + feat + L * lg;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int row = er + 4 * j;
-        const f32x4 gt = *reinterpret_cast<const f32x4 *>(epi + row * kEpiStride + ec * 16);         // gate
-        const f32x4 up = *reinterpret_cast<const f32x4 *>(epi + row * kEpiStride + 256 + ec * 16);   // up
-        if (orow[tb][j] >= 0) {
-          bf16x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = a3_f2bf(gt[e] / (1.0f + __expf(-gt[e])) * up[e]);
-          *reinterpret_cast<bf16x4 *>(a.out + (size_t)orow[tb][j] * a.N + fblock + 4 * ec) = v;
+        for (int e = 0; e < L; e += 4) {
+          *reinterpret_cast<f32x4 *>(p + e) = f32x4{lo[e], lo[e + 1], lo[e + 2], lo[e + 3]};
+          *reinterpret_cast<f32x4 *>(p + 8 * IB + e) = f32x4{hi[e], hi[e + 1], hi[e + 2], hi[e + 3]};
         }
       }
     }
+  }
+}
+
+// Rows of a product whose reduction was split: residual row += the partial rows in share order (one rounding), then the
+// RMSNorm of the new row.  One workgroup per row; the row stays in registers between the two (up to 8 vectors a thread).
+constexpr int kSumNormThreads = 256, kSumNormVecs = 8;
+__global__ void __launch_bounds__(kSumNormThreads)
+sum_norm_kernel(const float *__restrict__ part, int splits, int n_rows, bf16_t *resid, const int *__restrict__ idx,
+                const bf16_t *__restrict__ g, float eps, bf16_t *out, const int *__restrict__ out_idx, int h) {
+  __shared__ float red[kSumNormThreads / 64];
+  const int i = blockIdx.x, row = idx ? idx[i] : i, dst = out_idx ? out_idx[i] : i;
+  bf16_t *rr = resid + (size_t)row * h;
+  float x[kSumNormVecs][8], ss = 0.f;
+#pragma unroll
+  for (int v = 0; v < kSumNormVecs; ++v) {
+    const int c = (v * kSumNormThreads + threadIdx.x) * 8;
+    if (c >= h) break;
+    const bf16x8 r = *reinterpret_cast<const bf16x8 *>(rr + c);
+    float t[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) t[e] = 0.f;
+    for (int s = 0; s < splits; ++s) {
+      const float *p = part + ((size_t)s * n_rows + i) * h + c;
+      const f32x4 a = *reinterpret_cast<const f32x4 *>(p), b = *reinterpret_cast<const f32x4 *>(p + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { t[e] += a[e]; t[4 + e] += b[e]; }
+    }
+    bf16x8 y;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      y[e] = a3_f2bf(a3_bf2f(r[e]) + t[e]);
+      x[v][e] = a3_bf2f(y[e]);
+      ss = fmaf(x[v][e], x[v][e], ss);
+    }
+    *reinterpret_cast<bf16x8 *>(rr + c) = y;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  ss = (red[0] + red[1]) + (red[2] + red[3]);
+  const float inv = 1.0f / sqrtf(ss / (float)h + eps);
+#pragma unroll
+  for (int v = 0; v < kSumNormVecs; ++v) {
+    const int c = (v * kSumNormThreads + threadIdx.x) * 8;
+    if (c >= h) break;
+    const bf16x8 w = *reinterpret_cast<const bf16x8 *>(g + c);
+    bf16x8 y;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = a3_f2bf(x[v][e] * inv * a3_bf2f(w[e]));
+    *reinterpret_cast<bf16x8 *>(out + (size_t)dst * h + c) = y;
   }
 }
 
@@ -236,56 +277,35 @@ gemm_f32_kernel(gemm_args_f32 a) {
   }
 }
 
-// rows per workgroup (64 TB): useful rows / padded rows x how evenly the workgroups fill 256 CUs (the
-// busiest CU sets the time; two co-resident 128-row workgroups share their CU's matrix pipes) x a bonus
-// for the lower cache traffic of larger tiles
-int pick_tb(int n_rows, int n_ftiles) {
-  int best_tb = 2;
-  double best = -1.0;
-  for (int c = 2; c <= 4; ++c) {
-    const int tiles = (n_rows + 64 * c - 1) / (64 * c);
-    const long wgs = (long)tiles * n_ftiles;
-    const long rounds = (wgs + 255) / 256;
-    const double fill = (double)wgs / (double)(rounds * 256L);
-    const double pad = (double)n_rows / (double)(tiles * 64 * c);
-    const double traffic = 256.0 * 64 * c / (256.0 + 64 * c) / 128.0;
-    const double score = pad * fill * (0.5 + 0.5 * traffic);
-    if (score > best) { best = score; best_tb = c; }
-  }
-  return best_tb;
+template <int EPI>
+a3_status gemm_bf16_launch(const gemm_args &a0, int tile, hipStream_t st, const char *who) {
+  return gemm_with_tile(tile, [&](auto t) -> a3_status {
+    using P = decltype(t);
+    auto kern = gemm_bf16_kernel<P, EPI>;
+    static a3_once_per_device lds_once;
+    if (a3_once(lds_once, [&]() { return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P::kLdsBytes); }) != hipSuccess)
+      return a3_fail(A3_ERR_HIP, "%s: cannot raise the dynamic LDS limit", who);
+    gemm_args a = a0;
+    const int feat = EPI == EPI_SWIGLU ? P::BM / 2 : P::BM;
+    a.n_wtiles = (a.N + feat - 1) / feat;
+    a.n_tok_tiles = (a.n_rows + P::BN - 1) / P::BN;
+    a.group = gemm_tile_group(a.n_wtiles, a.n_tok_tiles);
+    hipLaunchKernelGGL(kern, dim3(gemm_tile_grid(a.n_wtiles, a.n_tok_tiles, a.group), EPI == EPI_PART ? a.splits : 1), dim3(512),
+                       P::kLdsBytes, st, a);
+    A3_CHECK_LAUNCH(who);
+    return A3_OK;
+  });
 }
 
-template <int EPI>
-a3_status gemm_bf16_launch(const gemm_args &a0, hipStream_t st, const char *who) {
-  gemm_args a = a0;
-  a.n_ftiles = EPI == EPI_RESID ? (a.N + 255) / 256 : (a.N + 127) / 128;
-  int tb = pick_tb(a.n_rows, a.n_ftiles);
-  { const int t = a3_knob(A3_KNOB_GEMM_TB); if (t >= 2 && t <= 4) tb = t; }   // tuning value "gemm_tb"
-  a.n_tok_tiles = (a.n_rows + 64 * tb - 1) / (64 * tb);
-  // 128-byte row pieces whenever K allows (tuning value "gemm_k64" = 0: the 64-byte loop)
-  bool k64 = a.K % 64 == 0;
-  if (a3_knob(A3_KNOB_GEMM_K64) == 0) k64 = false;
-  static a3_once_per_device lds_once;
-  const hipError_t once_err = a3_once(lds_once, []() {
-    hipError_t e1 = hipFuncSetAttribute((const void *)gemm_bf16_kernel<2, EPI, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_tile_lds_bytes(2));
-    hipError_t e2 = hipFuncSetAttribute((const void *)gemm_bf16_kernel<3, EPI, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_tile_lds_bytes(3));
-    hipError_t e3 = hipFuncSetAttribute((const void *)gemm_bf16_kernel<4, EPI, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_tile_lds_bytes(4));
-    hipError_t e4 = hipFuncSetAttribute((const void *)gemm_bf16_kernel<3, EPI, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_tile_lds_bytes_k64(3));
-    hipError_t e5 = hipFuncSetAttribute((const void *)gemm_bf16_kernel<4, EPI, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_tile_lds_bytes_k64(4));
-    hipError_t e6 = hipFuncSetAttribute((const void *)gemm_bf16_kernel<2, EPI, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_tile_lds_bytes_k64(2));
-    for (hipError_t e : {e1, e2, e3, e4, e5, e6}) if (e != hipSuccess) return e;
-    return hipSuccess;
-  });
-  if (once_err != hipSuccess) return a3_fail(A3_ERR_HIP, "%s: cannot raise the dynamic LDS limit", who);
-  const unsigned grid = 8u * (unsigned)((a.n_ftiles + 7) / 8) * (unsigned)a.n_tok_tiles;
-  if (tb == 2 && k64) hipLaunchKernelGGL((gemm_bf16_kernel<2, EPI, true>), dim3(grid), dim3(256), gemm_tile_lds_bytes_k64(2), st, a);
-  else if (tb == 2) hipLaunchKernelGGL((gemm_bf16_kernel<2, EPI, false>), dim3(grid), dim3(256), gemm_tile_lds_bytes(2), st, a);
-  else if (tb == 3 && k64) hipLaunchKernelGGL((gemm_bf16_kernel<3, EPI, true>), dim3(grid), dim3(256), gemm_tile_lds_bytes_k64(3), st, a);
-  else if (tb == 3) hipLaunchKernelGGL((gemm_bf16_kernel<3, EPI, false>), dim3(grid), dim3(256), gemm_tile_lds_bytes(3), st, a);
-  else if (k64) hipLaunchKernelGGL((gemm_bf16_kernel<4, EPI, true>), dim3(grid), dim3(256), gemm_tile_lds_bytes_k64(4), st, a);
-  else hipLaunchKernelGGL((gemm_bf16_kernel<4, EPI, false>), dim3(grid), dim3(256), gemm_tile_lds_bytes(4), st, a);
-  A3_CHECK_LAUNCH(who);
-  return A3_OK;
+int tile_of_knob(int tile) {
+  const int t = gemm_tile_of_knob(a3_knob(A3_KNOB_GEMM_TB));
+  return t >= 0 ? t : tile;
+}
+
+constexpr int kMaxSplits = 8;
+// fp32 partial results of a residual GEMM of H(.) when its reduction is split (0: it is not)
+size_t split_bytes(const gemm_tile_choice &c, int n_rows, int h) {
+  return c.splits > 1 ? (size_t)c.splits * n_rows * h * sizeof(float) : 0;
 }
 
 template <int EPI>
@@ -311,13 +331,24 @@ a3_status rms_norm_launch(const a3_layout *L, const void *x, const int *in_idx, 
 
 size_t elem_bytes(const a3_layout *L) { return L->dtype == A3_BF16 ? 2 : 4; }
 
+// without partial results
+size_t tail_base_bytes(const a3_layout *L, int ffn, int n_rows) {
+  const size_t e = elem_bytes(L);
+  return a3_align_up((size_t)n_rows * L->hidden * e, 256) + a3_align_up((size_t)n_rows * ffn * e, 256) + 256;
+}
+
 }  // namespace
 
 extern "C" size_t a3_block_tail_ws_bytes(const a3_layout *L, int ffn, int n_rows) {
   if (L == nullptr || ffn <= 0 || n_rows < 0 || L->hidden <= 0) return 0;
   if (L->dtype != A3_BF16 && L->dtype != A3_F32) return 0;
-  const size_t e = elem_bytes(L);
-  return a3_align_up((size_t)n_rows * L->hidden * e, 256) + a3_align_up((size_t)n_rows * ffn * e, 256) + 256;
+  size_t part = 0;
+  if (L->dtype == A3_BF16 && n_rows > 0) {
+    const size_t p0 = split_bytes(gemm_choose_tile(L->hidden, n_rows, L->n_q_heads * L->head_dim / 64, kMaxSplits), n_rows, L->hidden);
+    const size_t p1 = split_bytes(gemm_choose_tile(L->hidden, n_rows, ffn / 64, kMaxSplits), n_rows, L->hidden);
+    part = p0 > p1 ? p0 : p1;
+  }
+  return tail_base_bytes(L, ffn, n_rows) + a3_align_up(part, 256);
 }
 
 extern "C" a3_status a3_rms_norm(const a3_layout *L, const void *x, const int *row_idx, int n_rows, const void *g,
@@ -359,36 +390,50 @@ extern "C" a3_status a3_block_tail(const a3_layout *L, const void *attn_out, con
                "a3_block_tail: bf16 needs hidden %% 128 == 0, ffn %% 64 == 0, heads x head_dim %% 32 == 0 (got %d, %d, %d)",
                h, f, qd);
   A3_REQUIRE(ws != nullptr, A3_ERR_WORKSPACE, "a3_block_tail: workspace is NULL");
-  const size_t need = a3_block_tail_ws_bytes(L, f, n_act);
+  const size_t need = tail_base_bytes(L, f, n_act);
   A3_REQUIRE(ws_bytes >= need, A3_ERR_WORKSPACE, "a3_block_tail: workspace %zu bytes, need %zu", ws_bytes, need);
   hipStream_t st = (hipStream_t)stream;
   a3_ws_cursor cur(ws, ws_bytes);
   void *normed = cur.take((size_t)n_act * h * elem_bytes(L));
   void *act = cur.take((size_t)n_act * f * elem_bytes(L));
 
-  // r1 = r0 + O Wo^T
   if (L->dtype == A3_BF16) {
-    gemm_args a{(const bf16_t *)attn_out, nullptr, n_act, (const bf16_t *)w->wo, nullptr, (bf16_t *)resid, act_idx, qd, h, 0, 0};
-    if ((s = gemm_bf16_launch<EPI_RESID>(a, st, "a3_block_tail")) != A3_OK) return s;
-  } else {
-    gemm_args_f32 a{(const float *)attn_out, nullptr, n_act, (const float *)w->wo, nullptr, (float *)resid, act_idx, qd, h};
-    if ((s = gemm_f32_launch<EPI_RESID>(a, st, "a3_block_tail")) != A3_OK) return s;
+    // A residual GEMM and the norm behind it: in one pass over the reduction and a norm kernel, or - where too few tiles
+    // would be left to fill the chip - with the reduction split over workgroups and a kernel that sums, adds and norms.
+    auto resid_norm = [&](const bf16_t *x, const void *weight, int K, const void *g, bf16_t *out, const int *out_idx) -> a3_status {
+      gemm_args a{x, n_act, (const bf16_t *)weight, nullptr, (bf16_t *)resid, act_idx, K, h, nullptr, 1, 0, 0, 0};
+      gemm_tile_choice c = gemm_choose_tile(h, n_act, K / 64, h <= 8 * kSumNormThreads * kSumNormVecs ? kMaxSplits : 1);
+      const size_t room = ws_bytes > need ? ws_bytes - need : 0;   // a caller's smaller workspace: one pass
+      if (a3_knob(A3_KNOB_GEMM_TB) >= 0 || split_bytes(c, n_act, h) > room) c = gemm_choose_tile(h, n_act, K / 64, 1);
+      c.tile = tile_of_knob(c.tile);
+      a3_status e;
+      if (c.splits == 1) {
+        if ((e = gemm_bf16_launch<EPI_RESID>(a, c.tile, st, "a3_block_tail")) != A3_OK) return e;
+        return rms_norm_launch(L, resid, act_idx, g, w->eps, out, out_idx, n_act, st, "a3_block_tail");
+      }
+      a.part = (float *)((char *)ws + a3_align_up(cur.off, 256));
+      a.splits = c.splits;
+      if ((e = gemm_bf16_launch<EPI_PART>(a, c.tile, st, "a3_block_tail")) != A3_OK) return e;
+      hipLaunchKernelGGL(sum_norm_kernel, dim3(n_act), dim3(kSumNormThreads), 0, st, a.part, c.splits, n_act, (bf16_t *)resid, act_idx,
+                         (const bf16_t *)g, w->eps, out, out_idx, h);
+      A3_CHECK_LAUNCH("a3_block_tail");
+      return A3_OK;
+    };
+    // r1 = r0 + O Wo^T, n1 = RMSNorm(r1; g_post) (compact)
+    if ((s = resid_norm((const bf16_t *)attn_out, w->wo, qd, w->g_post, (bf16_t *)normed, nullptr)) != A3_OK) return s;
+    // act = silu(n1 Wg^T) * (n1 Wu^T)
+    gemm_args a{(const bf16_t *)normed, n_act, (const bf16_t *)w->w_gate, (const bf16_t *)w->w_up, (bf16_t *)act, nullptr, h, f, nullptr, 1, 0, 0, 0};
+    if ((s = gemm_bf16_launch<EPI_SWIGLU>(a, tile_of_knob(gemm_choose_tile(2 * f, n_act, h / 64, 1).tile), st, "a3_block_tail")) != A3_OK) return s;
+    // r2 = r1 + act Wd^T, x' = RMSNorm(r2; g_next) at the rows' own places
+    return resid_norm((const bf16_t *)act, w->w_down, f, w->g_next, (bf16_t *)hidden_next, act_idx);
   }
-  // n1 = RMSNorm(r1; g_post), compact
+  gemm_args_f32 a{(const float *)attn_out, nullptr, n_act, (const float *)w->wo, nullptr, (float *)resid, act_idx, qd, h};
+  if ((s = gemm_f32_launch<EPI_RESID>(a, st, "a3_block_tail")) != A3_OK) return s;
   if ((s = rms_norm_launch(L, resid, act_idx, w->g_post, w->eps, normed, nullptr, n_act, st, "a3_block_tail")) != A3_OK)
     return s;
-  // act = silu(n1 Wg^T) * (n1 Wu^T);  r2 = r1 + act Wd^T
-  if (L->dtype == A3_BF16) {
-    gemm_args a{(const bf16_t *)normed, nullptr, n_act, (const bf16_t *)w->w_gate, (const bf16_t *)w->w_up, (bf16_t *)act, nullptr, h, f, 0, 0};
-    if ((s = gemm_bf16_launch<EPI_SWIGLU>(a, st, "a3_block_tail")) != A3_OK) return s;
-    gemm_args b{(const bf16_t *)act, nullptr, n_act, (const bf16_t *)w->w_down, nullptr, (bf16_t *)resid, act_idx, f, h, 0, 0};
-    if ((s = gemm_bf16_launch<EPI_RESID>(b, st, "a3_block_tail")) != A3_OK) return s;
-  } else {
-    gemm_args_f32 a{(const float *)normed, nullptr, n_act, (const float *)w->w_gate, (const float *)w->w_up, (float *)act, nullptr, h, f};
-    if ((s = gemm_f32_launch<EPI_SWIGLU>(a, st, "a3_block_tail")) != A3_OK) return s;
-    gemm_args_f32 b{(const float *)act, nullptr, n_act, (const float *)w->w_down, nullptr, (float *)resid, act_idx, f, h};
-    if ((s = gemm_f32_launch<EPI_RESID>(b, st, "a3_block_tail")) != A3_OK) return s;
-  }
-  // x' = RMSNorm(r2; g_next) at the rows' own places
+  gemm_args_f32 u{(const float *)normed, nullptr, n_act, (const float *)w->w_gate, (const float *)w->w_up, (float *)act, nullptr, h, f};
+  if ((s = gemm_f32_launch<EPI_SWIGLU>(u, st, "a3_block_tail")) != A3_OK) return s;
+  gemm_args_f32 b{(const float *)act, nullptr, n_act, (const float *)w->w_down, nullptr, (float *)resid, act_idx, f, h};
+  if ((s = gemm_f32_launch<EPI_RESID>(b, st, "a3_block_tail")) != A3_OK) return s;
   return rms_norm_launch(L, resid, act_idx, w->g_next, w->eps, hidden_next, act_idx, n_act, st, "a3_block_tail");
 }

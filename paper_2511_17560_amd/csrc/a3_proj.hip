@@ -2,33 +2,20 @@
 //
 //   Q = RoPE_p(x Wq^T + bq),  K = RoPE_p(x Wk^T + bk),  V = x Wv^T + bv        p = position of the row
 //
-// bf16: a row-gathering MFMA GEMM.  One workgroup computes one head (128 output features) for
-// 128 listed rows.  The weight tile is the MFMA "row" operand and the gathered hidden rows
-// the "column" operand, so a lane ends up holding, for ONE token, 4 consecutive features per
-// accumulator quad and all 128 features of the head across its 4 accumulator blocks: both
-// RoPE pairings (adjacent coordinates, or i with i+64) are lane-local and the rotation runs in
-// the epilogue on the fp32 accumulators, before the single rounding to bf16.
+// bf16: a row-gathering MFMA GEMM (main loop: a3_gemm_pp.h), the weights as the MFMA "row" operand and the gathered
+// hidden rows as the "column" operand.  Both RoPE pairings (adjacent coordinates, or i with i + 64) end up lane-local
+// and the rotation runs in the epilogue on the fp32 accumulators, before the single rounding to bf16.
 // fp32: a plain LDS-tiled FMA kernel (correctness configuration, not tuned).
 #include <stdlib.h>
 
 #include "a3_internal.h"
-#include "a3_gemm_tile.h"
+#include "a3_gemm_pp.h"
 
 namespace {
 
 // ---------------------------------------------------------------------------------------
 // bf16 MFMA kernel
 // ---------------------------------------------------------------------------------------
-// The 128 B/clk LDS feeds at most one 16-byte fragment read per 32x32x16 MFMA issued on the CU,
-// so a wave has to reuse every fragment several times.  A wave therefore owns one head
-// (128 features = 4 blocks) x 32*TB listed rows (TB = 2, 3 or 4 blocks): (4 + TB) fragment reads
-// per 4*TB MFMAs, accumulators in up to 256 registers, one wave per SIMD.  The workgroup is
-// 2 (heads) x 2 (row halves) waves: 256 features x 64*TB rows, both operands staged through LDS
-// with full 128-byte row segments per 8 lanes.  TB is chosen per launch: larger tiles need less
-// LDS and L2 traffic per flop, smaller ones fill the 256 CUs better.
-// Loads go from global memory straight into LDS (global_load_lds, 16 bytes per lane, no staging
-// registers), three 32-wide k-slabs ahead of the MFMAs in a ring of four LDS stages; rows are
-// unpadded and the 16-byte pieces of a row are XOR-swizzled against bank conflicts.
 constexpr int kHeadDim = 128;
 struct proj_args {
   const bf16_t *hidden;
@@ -40,7 +27,7 @@ struct proj_args {
   const int *tok_pos;
   const float2 *pos_cs;
   int K, Hq, Hkv, rope_layout;
-  int n_pairs, n_tok_tiles;
+  int n_heads, n_wtiles, n_tok_tiles, group;
   int scatter_kv;        // K and V go to row row_idx[i] of their output (the caches) instead of row i
 };
 
@@ -54,145 +41,119 @@ __device__ __forceinline__ head_sel select_head(int h, int Hq, int Hkv) {
   return r;
 }
 
-template <int TB, bool K64>
-__global__ void __launch_bounds__(256, TB == 2 ? 2 : 1)
+// The heads that have an output, in the order Q, K, V (a Q-only or K/V-only call has fewer tiles, not idle ones).
+__device__ __forceinline__ head_sel active_head(const proj_args &a, int i) {
+  head_sel r;
+  r.which = 0; r.head = i; r.heads_out = a.Hq;
+  const int n0 = a.out[0] ? a.Hq : 0, n1 = a.out[1] ? a.Hkv : 0;
+  if (i >= n0) { r.which = 1; r.head = i - n0; r.heads_out = a.Hkv; }
+  if (i >= n0 + n1) { r.which = 2; r.head = i - n0 - n1; }
+  return r;
+}
+
+// IB = 8: a workgroup holds two heads, one per wave group; IB = 4: one head, group g its features 32 g .. and 64 + 32 g ..
+template <class P>
+__global__ void __launch_bounds__(512)
 proj_bf16_kernel(proj_args a) {
-  constexpr int kTokTile = 64 * TB;
+  constexpr int IB = P::kIB, JB = P::kJB;
   extern __shared__ __align__(16) unsigned char lds[];
+  int wt, xt;
+  if (!gemm_tile_of(a.n_wtiles, a.n_tok_tiles, a.group, blockIdx.x, wt, xt)) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, lg = lane >> 4, grp = wave >> 2, wn = wave & 3;
+  constexpr int kHeadsWg = IB == 8 ? 2 : 1;
 
-  // workgroup -> (head pair, row tile).  Consecutive workgroup ids go to different XCDs; all row
-  // tiles of one head pair are kept on one XCD so its L2 holds that pair's weights.
-  const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
-  const int hp = xcd + 8 * (q / a.n_tok_tiles), tt = q % a.n_tok_tiles;
-  if (hp >= a.n_pairs) return;
-  const int n_heads = a.Hq + 2 * a.Hkv;
-  {
-    // a pair whose two heads both have no output (Q-only or K/V-only calls) has nothing to do
-    const head_sel h0 = select_head(min(2 * hp, n_heads - 1), a.Hq, a.Hkv);
-    const head_sel h1 = select_head(min(2 * hp + 1, n_heads - 1), a.Hq, a.Hkv);
-    if (a.out[h0.which] == nullptr && (2 * hp + 1 >= n_heads || a.out[h1.which] == nullptr)) return;
-  }
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, lhi = lane >> 5;
-  const int fh = wave & 1, th = wave >> 1;
-
-  // ---- this wave's head and rows ---------------------------------------------------------------------
-  const int my_head = 2 * hp + fh;
-  const head_sel hs = select_head(min(my_head, n_heads - 1), a.Hq, a.Hkv);
-  bf16_t *__restrict__ out = my_head < n_heads ? a.out[hs.which] : nullptr;
-  const bool compute = out != nullptr;
-  const int tok0 = tt * kTokTile + th * 32 * TB;
-
-  // ---- the product: weight-tile row r is row r % 128 of head 2 hp + r / 128, activation-tile row r the
-  // hidden row of listed row tt * kTokTile + r
-  f32x16 acc[4][TB];
-  gemm_tile_mainloop<TB, K64>(
-      acc, lds, a.K,
-      [&](int row) -> const bf16_t * {
-        const head_sel hsl = select_head(min(2 * hp + (row >> 7), n_heads - 1), a.Hq, a.Hkv);
-        const bf16_t *wb = a.w[hsl.which];
-        int hh = hsl.head;
-        if (wb == nullptr) { wb = a.w[0] ? a.w[0] : (a.w[1] ? a.w[1] : a.w[2]); hh = 0; }   // unused head: any valid tile
-        return wb + ((size_t)hh * kHeadDim + (row & 127)) * a.K;
+  f32x4 acc[IB][JB];
+  P::mainloop(
+      acc, lds, a.K / 64,
+      [&](int r0) -> const char * {                              // (an odd last head is computed twice, stored once)
+        const head_sel hs = active_head(a, min(kHeadsWg * wt + (IB == 8 ? r0 >> 7 : 0), a.n_heads - 1));
+        return reinterpret_cast<const char *>(a.w[hs.which] + (size_t)hs.head * kHeadDim * a.K);
       },
-      [&](int row) -> const bf16_t * {
-        const int m = min(tt * kTokTile + row, a.n_rows - 1);    // clamp: computed but never stored
-        return a.hidden + (size_t)(a.row_idx ? a.row_idx[m] : m) * a.K;
+      [&](int r) -> uint32_t {
+        int q, f;
+        P::row_of(r % (16 * IB), q, f);
+        return (uint32_t)(64 * q + f + (IB == 4 ? 32 * (r / 64) : 0)) * (uint32_t)a.K * 2u;
+      },
+      [&](int) -> const char * { return reinterpret_cast<const char *>(a.hidden); },
+      [&](int r) -> uint32_t {
+        const int m = min(xt * P::BN + r, a.n_rows - 1);         // clamp: computed but never stored
+        return (uint32_t)(a.row_idx ? a.row_idx[m] : m) * (uint32_t)a.K * 2u;
       });
-  // (a wave whose head has no output multiplies all the same: its partner in the pair sets the pace, and
-  // a guard around the MFMAs turns into execution-mask juggling and branches between them)
-  // ---- epilogue: bias, RoPE, one rounding, store -------------------------------------------------------
-  // In the accumulators a lane holds one row and, per register quad, 4 consecutive features: stored
-  // from there, every instruction would touch 64 different cache lines, and the (cos, sin) reads
-  // likewise.  Each wave therefore turns its tile through its own piece of the (now free) LDS, one
-  // 32-row block at a time: fp32 [32 rows][128 features], row stride padded to 528 bytes.  Read back,
-  // a lane holds features 4c..4c+3 and 64+4c..64+4c+3 of one row (both RoPE pairings stay inside the
-  // lane), 16 lanes cover a row, and every global access of the wave is made of whole 128-byte runs.
-  __syncthreads();                                           // every wave's tail loads have landed
-  if (!compute) return;
-  constexpr int kEpiStride = 528;                            // bytes per LDS row: 512 + 16 (bank spread)
-  unsigned char *epi = lds + wave * (32 * kEpiStride);
-  const int which = hs.which, head = hs.head, heads_out = hs.heads_out;
-  const bf16_t *bias = a.bias[which];
-  const int ec = lane & 15, er = lane >> 4;                  // read-back role: chunk of 4 features, row er + 4 j
-  const bool inter = a.rope_layout == A3_ROPE_INTERLEAVED;
-  // rows of this lane in the read-back role and their (cos, sin) table rows, for all blocks at once: the
-  // two dependent index loads of every row are in flight together
-  int src_row[TB][8];
-  const float2 *csrow[TB][8];
+
+  // ---- epilogue: bias, RoPE, one rounding, store ---------------------------------------------------------
+  // A lane holds, of one row, L consecutive features of the head's first half and the L of its second half that belong to
+  // the same lanes: both RoPE pairings are inside the lane, and four lanes cover 64 or 128 consecutive bytes of a row.
+  const int hi_idx = kHeadsWg * wt + (IB == 8 ? grp : 0);
+  if (hi_idx >= a.n_heads) return;
+  const head_sel hs = active_head(a, hi_idx);
+  constexpr int L = P::L;
+  const int f0 = L * lg + (IB == 4 ? 32 * grp : 0);              // lo: features f0 .. f0 + L - 1, hi: 64 + the same
+  const bool inter = a.rope_layout == A3_ROPE_INTERLEAVED, rope = hs.which != 2;
+  bf16_t *__restrict__ out = a.out[hs.which];
+  const bf16_t *bias = a.bias[hs.which];
+  int tok[JB], src[JB], pos[JB];
 #pragma unroll
-  for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int tok = min(tok0 + tb * 32 + er + 4 * j, a.n_rows - 1);
-      src_row[tb][j] = a.row_idx ? a.row_idx[tok] : tok;
-    }
-#pragma unroll
-  for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) csrow[tb][j] = a.pos_cs + (size_t)a.tok_pos[src_row[tb][j]] * (kHeadDim / 2);
-  float bl[4], bh[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    bl[e] = bias ? a3_bf2f(bias[head * kHeadDim + 4 * ec + e]) : 0.f;
-    bh[e] = bias ? a3_bf2f(bias[head * kHeadDim + 64 + 4 * ec + e]) : 0.f;
+  for (int j = 0; j < JB; ++j) {
+    tok[j] = xt * P::BN + 16 * (JB * wn + j) + l16;
+    const int m = min(tok[j], a.n_rows - 1);
+    src[j] = a.row_idx ? a.row_idx[m] : m;
   }
 #pragma unroll
-  for (int tb = 0; tb < TB; ++tb) {
-    // accumulator block (fb, tb), register r of this lane: feature 32 fb + 8 (r/4) + 4 lhi + r%4, row l32
+  for (int j = 0; j < JB; ++j) pos[j] = rope ? a.tok_pos[src[j]] : 0;
 #pragma unroll
-    for (int fb = 0; fb < 4; ++fb)
+  for (int j = 0; j < JB; ++j) {
+    float lo[L], hi[L];
+    // table entries p of the row: interleaved pairs f0 / 2 .. (lo) and 32 + f0 / 2 .. (hi), halves f0 .. f0 + L - 1
+    const float4 *cs = reinterpret_cast<const float4 *>(a.pos_cs + (size_t)pos[j] * (kHeadDim / 2));
+    float4 t[L / 2];
+    if (rope) {
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        f32x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc[fb][tb][4 * q4 + e];
-        *reinterpret_cast<f32x4 *>(epi + l32 * kEpiStride + (32 * fb + 8 * q4 + 4 * lhi) * 4) = v;
-      }
-    // (same wave writes and reads: the compiler's wait for the LDS writes is all the ordering needed)
-    // all (cos, sin) reads of the block first, then the arithmetic and the stores
-    float4 t0[8], t1[8];
-    if (which != 2) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        // interleaved: pairs 2 ec, 2 ec + 1 and 32 + 2 ec, ..; half: pairs 4 ec .. 4 ec + 3
-        t0[j] = *reinterpret_cast<const float4 *>(csrow[tb][j] + (inter ? 2 * ec : 4 * ec));
-        t1[j] = *reinterpret_cast<const float4 *>(csrow[tb][j] + (inter ? 32 + 2 * ec : 4 * ec + 2));
+      for (int e = 0; e < L / 4; ++e) {
+        t[e] = cs[inter ? f0 / 4 + e : f0 / 2 + e];
+        t[L / 4 + e] = cs[inter ? 16 + f0 / 4 + e : f0 / 2 + L / 4 + e];
       }
     }
+    gemm_lane_values<IB, JB>(acc, j, lo, hi);
+    if (bias) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int row = er + 4 * j;
-      const int tok = tok0 + tb * 32 + row;
-      f32x4 lo = *reinterpret_cast<const f32x4 *>(epi + row * kEpiStride + ec * 16);          // features 4 ec ..
-      f32x4 hi = *reinterpret_cast<const f32x4 *>(epi + row * kEpiStride + 256 + ec * 16);    // features 64 + 4 ec ..
+      for (int e = 0; e < L; ++e) {
+        lo[e] += a3_bf2f(bias[hs.head * kHeadDim + f0 + e]);
+        hi[e] += a3_bf2f(bias[hs.head * kHeadDim + 64 + f0 + e]);
+      }
+    }
+    if (rope) {
+      if (inter) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { lo[e] += bl[e]; hi[e] += bh[e]; }
-      if (which != 2) {
-        const float4 c0 = t0[j], c1 = t1[j];
-        if (inter) {
-          f32x4 x = lo;
-          lo[0] = x[0] * c0.x - x[1] * c0.y; lo[1] = x[0] * c0.y + x[1] * c0.x;
-          lo[2] = x[2] * c0.z - x[3] * c0.w; lo[3] = x[2] * c0.w + x[3] * c0.z;
-          x = hi;
-          hi[0] = x[0] * c1.x - x[1] * c1.y; hi[1] = x[0] * c1.y + x[1] * c1.x;
-          hi[2] = x[2] * c1.z - x[3] * c1.w; hi[3] = x[2] * c1.w + x[3] * c1.z;
-        } else {
-          const f32x4 xl = lo, xh = hi;
-          lo[0] = xl[0] * c0.x - xh[0] * c0.y; hi[0] = xl[0] * c0.y + xh[0] * c0.x;
-          lo[1] = xl[1] * c0.z - xh[1] * c0.w; hi[1] = xl[1] * c0.w + xh[1] * c0.z;
-          lo[2] = xl[2] * c1.x - xh[2] * c1.y; hi[2] = xl[2] * c1.y + xh[2] * c1.x;
-          lo[3] = xl[3] * c1.z - xh[3] * c1.w; hi[3] = xl[3] * c1.w + xh[3] * c1.z;
+        for (int e = 0; e < L / 4; ++e)
+#pragma unroll
+          for (int u = 0; u < 4; u += 2) {
+            const float c0 = u ? t[e].z : t[e].x, s0 = u ? t[e].w : t[e].y;
+            const float c1 = u ? t[L / 4 + e].z : t[L / 4 + e].x, s1 = u ? t[L / 4 + e].w : t[L / 4 + e].y;
+            const float x0 = lo[4 * e + u], x1 = lo[4 * e + u + 1], y0 = hi[4 * e + u], y1 = hi[4 * e + u + 1];
+            lo[4 * e + u] = x0 * c0 - x1 * s0; lo[4 * e + u + 1] = x0 * s0 + x1 * c0;
+            hi[4 * e + u] = y0 * c1 - y1 * s1; hi[4 * e + u + 1] = y0 * s1 + y1 * c1;
+          }
+      } else {
+#pragma unroll
+        for (int e = 0; e < L; ++e) {
+          const float c = (e & 1) ? t[e / 2].z : t[e / 2].x, sn = (e & 1) ? t[e / 2].w : t[e / 2].y;
+          const float x = lo[e], y = hi[e];
+          lo[e] = x * c - y * sn;
+          hi[e] = x * sn + y * c;
         }
       }
-      if (tok < a.n_rows) {
-        const int out_row = (a.scatter_kv && which != 0) ? src_row[tb][j] : tok;
-        bf16_t *orow = out + ((size_t)out_row * heads_out + head) * kHeadDim;
-        bf16x4 vlo, vhi;
+    }
+    if (tok[j] < a.n_rows) {
+      const int out_row = (a.scatter_kv && hs.which != 0) ? src[j] : tok[j];
+      bf16_t *p = out + ((size_t)out_row * hs.heads_out + hs.head) * kHeadDim + f0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { vlo[e] = a3_f2bf(lo[e]); vhi[e] = a3_f2bf(hi[e]); }
-        *reinterpret_cast<bf16x4 *>(orow + 4 * ec) = vlo;
-        *reinterpret_cast<bf16x4 *>(orow + 64 + 4 * ec) = vhi;
+      for (int e = 0; e < L; e += 8) {
+        bf16x8 vl, vh;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { vl[u] = a3_f2bf(lo[e + u]); vh[u] = a3_f2bf(hi[e + u]); }
+        *reinterpret_cast<bf16x8 *>(p + e) = vl;
+        *reinterpret_cast<bf16x8 *>(p + 64 + e) = vh;
       }
     }
   }
@@ -574,8 +535,8 @@ static a3_status proj_launch(const a3_layout *L, const void *hidden, const int *
     a.out[0] = (bf16_t *)q_out; a.out[1] = (bf16_t *)k_out; a.out[2] = (bf16_t *)v_out;
     a.tok_pos = L->tok_pos; a.pos_cs = (const float2 *)L->rope_pos_cs;
     a.K = L->hidden; a.Hq = L->n_q_heads; a.Hkv = L->n_kv_heads; a.rope_layout = L->rope_layout;
-    a.n_pairs = (n_heads_total + 1) / 2;
-    a.n_tok_tiles = 0;
+    a.n_heads = n_heads_total;
+    a.n_wtiles = a.n_tok_tiles = a.group = 0;
     a.scatter_kv = scatter_kv;
     const int ntw_knob = a3_knob(A3_KNOB_PROJ_NTW);            // tuning value "proj_ntw": the GEMM kernel in this width
     if (n_rows <= 192 && L->hidden % 64 == 0 && ntw_knob < 0) {
@@ -605,47 +566,24 @@ static a3_status proj_launch(const a3_layout *L, const void *hidden, const int *
       A3_CHECK_LAUNCH("a3_selected_qkv_proj");
       return A3_OK;
     }
-    // rows per workgroup: 128, 192 or 256.  Estimate each choice by (useful rows / padded rows) x (how
-    // evenly the workgroups fill 256 CUs) x a bonus for the lower L2 traffic of larger tiles.
-    int ntw = 2;
-    if (ntw_knob >= 0) ntw = ntw_knob;
-    else {
-      double best = -1.0;
-      for (int c = 2; c <= 4; ++c) {
-        const int tiles = (n_rows + 64 * c - 1) / (64 * c);
-        const long wgs = (long)tiles * a.n_pairs;
-        const int per_cu = c == 2 ? 2 : 1;                    // co-resident workgroups
-        const long rounds = (wgs + 256L * per_cu - 1) / (256L * per_cu);
-        const double fill = (double)wgs / (double)(rounds * 256L * per_cu);
-        const double pad = (double)n_rows / (double)(tiles * 64 * c);
-        const double traffic = 256.0 * 64 * c / (256.0 + 64 * c) / 128.0;   // flop per L2 byte, relative to 256x256
-        const double score = pad * fill * (0.5 + 0.5 * traffic);
-        if (score > best) { best = score; ntw = c; }
-      }
-    }
-    if (ntw < 2 || ntw > 4) ntw = 2;
-    a.n_tok_tiles = (n_rows + 64 * ntw - 1) / (64 * ntw);
-    const unsigned grid = 8u * (unsigned)((a.n_pairs + 7) / 8) * (unsigned)a.n_tok_tiles;
-    // 128-byte row pieces for the 192- and 256-row tiles when the hidden size allows (tuning value "proj_k64" = 0:
-    // the 64-byte loop)
-    bool k64 = ntw >= 3 && L->hidden % 64 == 0;
-    if (a3_knob(A3_KNOB_PROJ_K64) == 0) k64 = false;
-    static a3_once_per_device lds_once;
-    const hipError_t once_err = a3_once(lds_once, []() {
-      hipError_t e1 = hipFuncSetAttribute((const void *)proj_bf16_kernel<2, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_tile_lds_bytes(2));
-      hipError_t e2 = hipFuncSetAttribute((const void *)proj_bf16_kernel<3, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_tile_lds_bytes(3));
-      hipError_t e3 = hipFuncSetAttribute((const void *)proj_bf16_kernel<4, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_tile_lds_bytes(4));
-      hipError_t e4 = hipFuncSetAttribute((const void *)proj_bf16_kernel<3, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_tile_lds_bytes_k64(3));
-      hipError_t e5 = hipFuncSetAttribute((const void *)proj_bf16_kernel<4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)gemm_tile_lds_bytes_k64(4));
-      for (hipError_t e : {e1, e2, e3, e4, e5}) if (e != hipSuccess) return e;
-      return hipSuccess;
+    const int heads_out = (q_out ? L->n_q_heads : 0) + (k_out ? L->n_kv_heads : 0) + (v_out ? L->n_kv_heads : 0);
+    a.n_heads = heads_out;
+    gemm_tile_choice c = gemm_choose_tile(heads_out * kHeadDim, n_rows, L->hidden / 64, 1);
+    if (gemm_tile_of_knob(ntw_knob) >= 0) c.tile = gemm_tile_of_knob(ntw_knob);
+    return gemm_with_tile(c.tile, [&](auto t) -> a3_status {
+      using P = decltype(t);
+      auto kern = proj_bf16_kernel<P>;
+      static a3_once_per_device lds_once;
+      if (a3_once(lds_once, [&]() { return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P::kLdsBytes); }) != hipSuccess)
+        return a3_fail(A3_ERR_HIP, "a3_selected_qkv_proj: cannot raise the dynamic LDS limit");
+      proj_args b = a;
+      b.n_wtiles = P::kIB == 8 ? (heads_out + 1) / 2 : heads_out;
+      b.n_tok_tiles = (n_rows + P::BN - 1) / P::BN;
+      b.group = gemm_tile_group(b.n_wtiles, b.n_tok_tiles);
+      hipLaunchKernelGGL(kern, dim3(gemm_tile_grid(b.n_wtiles, b.n_tok_tiles, b.group)), dim3(512), P::kLdsBytes, st, b);
+      A3_CHECK_LAUNCH("a3_selected_qkv_proj");
+      return A3_OK;
     });
-    if (once_err != hipSuccess) return a3_fail(A3_ERR_HIP, "a3_selected_qkv_proj: cannot raise the dynamic LDS limit");
-    if (ntw == 2) hipLaunchKernelGGL((proj_bf16_kernel<2, false>), dim3(grid), dim3(256), gemm_tile_lds_bytes(2), st, a);
-    else if (ntw == 3 && k64) hipLaunchKernelGGL((proj_bf16_kernel<3, true>), dim3(grid), dim3(256), gemm_tile_lds_bytes_k64(3), st, a);
-    else if (ntw == 3) hipLaunchKernelGGL((proj_bf16_kernel<3, false>), dim3(grid), dim3(256), gemm_tile_lds_bytes(3), st, a);
-    else if (k64) hipLaunchKernelGGL((proj_bf16_kernel<4, true>), dim3(grid), dim3(256), gemm_tile_lds_bytes_k64(4), st, a);
-    else hipLaunchKernelGGL((proj_bf16_kernel<4, false>), dim3(grid), dim3(256), gemm_tile_lds_bytes(4), st, a);
   } else {
     proj_args_f32 a;
     a.hidden = (const float *)hidden; a.row_idx = row_idx; a.n_rows = n_rows;
