@@ -11,10 +11,12 @@
 //                 tile is loaded once per group.  Everything is computed transposed:
 //                     S^T[key][m] = K Q^T          (A = K fragment from LDS, B = Q fragment in registers)
 //                     O^T[d][m]  += V^T P^T        (A = V^T fragment from LDS, B = P^T from the S^T accumulators)
-//                 In this orientation a lane owns ONE query row m: max, sum and rescale are lane-local,
-//                 and 8 consecutive S^T accumulators are exactly one B operand of the second product.
-//                 V is transposed on its way into LDS (4 keys x 8 dims per lane, register transpose)
-//                 with key bits 2 and 3 swapped so that the A operand is a single 16-byte LDS read.
+//                 In this orientation four lanes share ONE query row m, and two blocks of S^T accumulators are
+//                 exactly one B operand of the second product.
+// What bounds the main kernel: power.  16x16x32 matrix instructions, two waves per SIMD in opposite phases: 3230 cycles
+// per 64-key tile and 256 rows against 3580 with one wave's phases overlapping by chance on 32x32x16, at 1.9 GHz;
+// 16K context at r = 10 %: 290 -> 255 us, 64K: 3411 -> 3030 us (1.18 PFLOP/s), seven heads per KV head at 32K: 1597 ->
+// 1400 us.  Leaving out the exponentials, the loads or the fragment reads gives 9, 8 and 4 %.
 // fp32 path: one workgroup per (active row, head), plain FMA (correctness configuration).
 #include <stdlib.h>
 #include <string.h>
@@ -28,11 +30,12 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kD = 128;
 constexpr int kAttnWaves = kTM / 32;   // waves per workgroup: 0-3 also stage the next K/V tile
 constexpr int kAttnThreads = 64 * kAttnWaves;
-constexpr int kKRowBytes = kD * 2;   // K tile  [key][d]   256-byte rows, unpadded; 16-byte pieces XOR-swizzled by key % 16
-constexpr int kVStride = kTK + 8;   // V^T tile [d][key]  row stride in elements (144 B)
-constexpr int kKTile = kTK * kD;     // elements
-constexpr int kVTile = kD * kVStride;
-constexpr size_t kAttnLds = (size_t)2 * (kKTile + kVTile) * sizeof(bf16_t);   // double buffered: 69632 B
+constexpr int kTileBytes = kTK * kD * 2;             // a K or V tile [key][d] in LDS, unpadded 256-byte rows
+constexpr int kStages = 4;                           // of the K ring and of the V ring
+constexpr int kAhead = 4;                            // fragments read ahead of their products
+constexpr int kTableItems = 16;
+constexpr size_t kRingBytes = (size_t)2 * kStages * kTileBytes;
+constexpr size_t kAttnLds = kRingBytes + (size_t)kAttnWaves * kTableItems * 32;   // 132 KB
 
 __global__ void __launch_bounds__(kPlanThreads)
 attn_plan_kernel(attn_plan p, const int *__restrict__ act_idx, int n_act, const int *__restrict__ seg_start,
@@ -55,304 +58,381 @@ struct attn_args {
 
 // v_exp_f32: 2^x, about 1 ulp, -inf -> 0, results below the normal range flush to 0
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-// Combine a value across the two 32-lane halves of the wave with v_permlane32_swap (no LDS round
-// trip): after the swap one result holds the low-half values in every lane and the other the
-// high-half values, so max / sum of the two results is the combined value in all 64 lanes.
-__device__ __forceinline__ float halves_max(float x) {
-  const uint32_t u = __float_as_uint(x);
+// Maximum over the four 16-lane groups of a wave (lanes l, l + 16, l + 32, l + 48), by lane-row swaps
+__device__ __forceinline__ float groups_max(float x) {
+  uint32_t u = __float_as_uint(x);
   auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  u = __float_as_uint(x);
+  r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-__device__ __forceinline__ float halves_sum(float x) {
-  const uint32_t u = __float_as_uint(x);
-  auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ uint32_t pack_lo(uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); }
-__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); }
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 
-// One workgroup per share of a KV head's work: it runs the items of its share in order.
+struct attn_item { int k_begin, k_end, kv_len, m0, m_end, a0, base, nseg; };
+
+// One workgroup per share of a KV head's work: it runs the items of its share in order, their 64-key tiles as one stream.
 __global__ void __launch_bounds__(kAttnThreads, 1)
 attn_bf16_kernel(attn_args a) {
-  extern __shared__ __align__(16) unsigned char lds_raw[];
-  bf16_t *Ks = reinterpret_cast<bf16_t *>(lds_raw);          // [2][64][128], swizzled
-  bf16_t *Vt = Ks + 2 * kKTile;                              // [2][128][kVStride]
-
+  extern __shared__ __align__(16) unsigned char lds[];
   const int g = blockIdx.x % a.Hkv, wg = blockIdx.x / a.Hkv;
   // a plan made with another number of workgroups per head lies elsewhere in the workspace: touch nothing
   if (a.plan.counters[3] != a.plan.max_wgs || wg >= a.plan.counters[2]) return;
   const int item_begin = a.plan.wg_start[wg], item_end = a.plan.wg_start[wg + 1];
+  if (item_begin >= item_end) return;
   const int G = a.Hq / a.Hkv;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, lhi = lane >> 5;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, lg = lane >> 4, grp = wave >> 2;
   const bf16_t *__restrict__ Q = (const bf16_t *)a.q;
-  const bf16_t *__restrict__ K = (const bf16_t *)a.k;
-  const bf16_t *__restrict__ V = (const bf16_t *)a.v;
   const float c2 = a.scale2;
 
-  // K tile: global memory -> LDS directly (global_load_lds, 16 bytes per lane, lane i lands at base + 16 i).
-  // One wave instruction brings 4 keys x 256 B; instruction j of wave w < 4 covers keys 4 (4 j + w) .. +3.
-  // The lane fetches piece (slot ^ key % 16) of its key, so LDS slot s of key r holds piece s ^ (r % 16)
-  // and the 16 keys a quarter wave reads at one piece index touch all 64 banks once.
-  const int dwave = wave & 3;                                // K loads are issued by waves 0..3
-  const int drow = 4 * dwave + (lane >> 4);                  // key of the lane in instruction 0
-  const int dpiece = (lane & 15) ^ (drow & 15);              // (4 (4 j + w) + lane/16) % 16 does not depend on j
-  const uint32_t lds_k = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds_raw;
-  // fragment read: key b*32 + l32, piece 2 ks + lhi -> slot (2 ks + lhi) ^ (l32 % 16)
-  const int kfrag = l32 * kKRowBytes, kswz = (lhi ^ (l32 & 15)) * 16;
-  // V tile: lane = (4 keys, 8 dims), transposed in registers on its way into LDS.
-  // 16 consecutive lanes take 16 different key groups: their 8-byte transposed stores land in 128
-  // contiguous bytes of one V^T row (all 32 LDS banks) instead of 16 rows at a bank-aligned stride
-  // Both tiles are staged by waves 0..3: the SIMD serves the older of its two waves first, so these
-  // waves run ahead of waves 4..7 and would otherwise idle at the barrier of every tile
-  const int vkg = tid & 15, vc = (tid & 255) >> 4;
-  const int vpos = ((4 * vkg) & ~12) | (((4 * vkg) & 4) << 1) | (((4 * vkg) & 8) >> 1);   // swap key bits 2 and 3
-
-  for (int item = item_begin; item < item_end; ++item) {
-    __syncthreads();                                       // the LDS tiles of the previous item are free
-    const int4 it = a.plan.items[item];
+  // ---- items of this workgroup: the first 32 are looked up once, into a table of the wave's own -----------------
+  auto fetch = [&](int i) {
+    const int4 it = a.plan.items[i];
     const int4 ta = a.plan.tile_a[it.x];
-    const int nseg = a.plan.tile_b[it.x].y;
-    const int r = ta.x, m0 = ta.y, kv_len = ta.z, m_end = ta.w;
-    const int k_begin = it.y, k_end = it.z;
-    const int a0 = a.plan.a_lo[r];
-    const int base = a.seg_start[r];
-
-    // this lane's query row
-    const int m = m0 + wave * 32 + l32;
-    const bool valid = m < m_end;
-    const int mc = valid ? m : m_end - 1;
-    const int arow = a0 + mc / G, hq = g * G + mc % G;
-    const int limit = a.act_idx[arow] - base;              // last visible key (request-relative)
-    int wave_min_limit = limit, wave_max_limit = limit;
+    attn_item d;
+    d.nseg = a.plan.tile_b[it.x].y;
+    d.k_begin = it.y; d.k_end = it.z; d.kv_len = ta.z; d.m0 = ta.y; d.m_end = ta.w;
+    d.a0 = a.plan.a_lo[ta.x]; d.base = a.seg_start[ta.x];
+    return d;
+  };
+  attn_item *table = reinterpret_cast<attn_item *>(lds + kRingBytes + wave * (kTableItems * sizeof(attn_item)));
+  if (lane < kTableItems && item_begin + lane < item_end) table[lane] = fetch(item_begin + lane);
+  auto item_at = [&](int i) {
+    attn_item d = i - item_begin < kTableItems ? table[i - item_begin] : fetch(i);
+    int *f = reinterpret_cast<int *>(&d);
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      wave_min_limit = min(wave_min_limit, __shfl_xor(wave_min_limit, off, 64));
-      wave_max_limit = max(wave_max_limit, __shfl_xor(wave_max_limit, off, 64));
+    for (int e = 0; e < 8; ++e) f[e] = __builtin_amdgcn_readfirstlane(f[e]);
+    return d;
+  };
+
+  // ---- loads: both tiles of 64 keys x 256 bytes by direct-to-LDS loads, 4 keys per wave instruction, two instructions
+  // per wave and tile.  K: slot s (16 bytes) of key r holds piece s ^ (r % 16), so that the 16 keys a quarter wave reads at
+  // one piece index touch all 64 banks once.  V: the 32-byte piece p of key r lies at p ^ (r % 8), so that the 8 keys x 32
+  // bytes a half wave hands to the transposing read do.
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
+  const uint32_t pitch = (uint32_t)a.Hkv * kD * sizeof(bf16_t);
+  const int drow = 4 * wave + lg;                            // key of the lane in instruction 0; + 32 in instruction 1
+  const uint32_t key_off = (uint32_t)drow * pitch;
+  const uint32_t kpiece = 16 * (l16 ^ (drow & 15)), vpiece = 32 * ((l16 >> 1) ^ (drow & 7)) + 16 * (l16 & 1);
+  const uint32_t koff0 = key_off + kpiece, koff1 = koff0 + 32 * pitch, voff0 = key_off + vpiece, voff1 = voff0 + 32 * pitch;
+  // K of a tile is requested one tile before its V: l_* the tile whose K comes next, v_* the one before it
+  int l_item = item_begin, l_keys, l_steps, v_keys = kTK;    // visible keys and tiles of the item from this tile on
+  const char *l_kb, *l_vb, *v_vb = nullptr;
+  auto load_from = [&](int i) {
+    const attn_item d = item_at(i);
+    l_keys = d.kv_len - d.k_begin;
+    l_steps = (d.k_end - d.k_begin + kTK - 1) / kTK;
+    const size_t at = ((size_t)(d.base + d.k_begin) * a.Hkv + g) * kD;
+    l_kb = reinterpret_cast<const char *>((const bf16_t *)a.k + at);
+    l_vb = reinterpret_cast<const char *>((const bf16_t *)a.v + at);
+  };
+  // Inline assembly on purpose: the compiler then neither treats these as LDS writes (it would wait for all of them before
+  // every LDS read) nor moves memory accesses across them; the waits for them are the explicit s_waitcnt below.
+  auto dma = [&](const char *base, uint32_t off, uint32_t to) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds_base + to), "v"(off), "s"(base) : "memory");
+  };
+  // keys past the item's last visible one are clamped onto it and masked later; past the last tile of the stream that one
+  // again, unused
+  auto load_half = [&](const char *base, int keys, uint32_t off0, uint32_t off1, uint32_t piece, uint32_t to) {
+    if (keys < kTK) {
+      const uint32_t last = (uint32_t)(keys - 1) * pitch;
+      off0 = min(key_off, last) + piece;
+      off1 = min(key_off + 32 * pitch, last) + piece;
     }
-
-    bf16x8 qf[kD / 16];
-    {
-      const bf16_t *qp = Q + ((size_t)arow * a.Hq + hq) * kD + lhi * 8;
-#pragma unroll
-      for (int ks = 0; ks < kD / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qp + ks * 16);
+    dma(base, off0, to);
+    dma(base, off1, to + 8192);
+  };
+  auto load_k = [&](int stage) { load_half(l_kb, l_keys, koff0, koff1, kpiece, stage * kTileBytes + wave * 1024); };
+  auto load_v = [&](int stage) { load_half(v_vb, v_keys, voff0, voff1, vpiece, (kStages + stage) * kTileBytes + wave * 1024); };
+  auto load_next = [&]() {
+    v_vb = l_vb; v_keys = l_keys;
+    if (--l_steps > 0) {
+      l_kb += kTK * pitch; l_vb += kTK * pitch; l_keys -= kTK;
+    } else if (l_item + 1 < item_end) {
+      load_from(++l_item);
+    } else {
+      l_steps = 1;
     }
+  };
 
-    f32x16 o[4];
+  // ---- rows of an item: lane (l16, lg) holds rows m0 + 32 wave + 16 rb + l16 ---------------------------------------
+  bf16x8 qf[2][4];
+  int limit[2], min_limit, max_limit;                        // last visible key of the rows (request-relative)
+  uint32_t out_row[2], prev_row[2];                          // row of the output, ~0: none
+  attn_item cur;
+  auto load_rows = [&]() {
+    min_limit = 0x7fffffff; max_limit = -1;
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int rb = 0; rb < 2; ++rb) {
+      const int m = cur.m0 + 32 * wave + 16 * rb + l16, mc = min(m, cur.m_end - 1);
+      const int ar = mc / G, arow = cur.a0 + ar, hq = g * G + mc - ar * G;
+      out_row[rb] = (uint32_t)arow * a.Hq + hq;
+      const bf16_t *qp = Q + (size_t)out_row[rb] * kD + lg * 8;
 #pragma unroll
-      for (int x = 0; x < 16; ++x) o[b][x] = 0.f;
-    float row_ref = -INFINITY, row_sum = 0.f;               // exponent reference in raw logit units
-
-    // Next tile staged in registers while the current one is being consumed.  Loads are branch
-    // free (rows past the last visible key are clamped onto it and masked later) so that nothing
-    // forces the loaded registers to be touched before the LDS store at the end of the iteration.
-    uint4 vr_0, vr_1, vr_2, vr_3;
-    const uint32_t pitch_b = (uint32_t)a.Hkv * kD * sizeof(bf16_t);
-    const char *kb = reinterpret_cast<const char *>(K + ((size_t)base * a.Hkv + g) * kD);
-    const char *vb = reinterpret_cast<const char *>(V + ((size_t)base * a.Hkv + g) * kD);
-    const uint32_t k_last = (uint32_t)(kv_len - 1) * pitch_b + dpiece * 16, v_last = (uint32_t)(kv_len - 1) * pitch_b + vc * 16;
-    const uint32_t ko_0 = (uint32_t)drow * pitch_b + dpiece * 16;
-    const uint32_t vo_0 = (uint32_t)(4 * vkg) * pitch_b + vc * 16, vo_1 = vo_0 + pitch_b, vo_2 = vo_0 + 2 * pitch_b,
-                   vo_3 = vo_0 + 3 * pitch_b;
-    // Inline assembly on purpose: the compiler then neither treats these as LDS writes (it would wait
-    // for all of them before every LDS read) nor moves memory accesses across them.  They are issued
-    // right after the V loads of the same tile: the hardware counter the compiler waits on before
-    // using the V registers counts them too, so that wait (which ends at zero, just before the
-    // barrier that publishes the tile) covers them; issued before the V loads they would instead
-    // be waited for at the top of the loop, where the compiler guards the reuse of the V registers.
-#define A3_KDMA(BUF, K0)                                                                                     \
-    _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                          \
-      const char *gp_ = kb + min(ko_0 + ((uint32_t)(K0) + 16u * j) * pitch_b, k_last);                       \
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"                                     \
-                   :: "s"(__builtin_amdgcn_readfirstlane(lds_k + (BUF) * (kKTile * 2) + 4 * (4 * j + dwave) * kKRowBytes)), \
-                      "v"(gp_) : "memory");                                                                  \
+      for (int ds = 0; ds < 4; ++ds) qf[rb][ds] = *reinterpret_cast<const bf16x8 *>(qp + 32 * ds);
+      limit[rb] = a.act_idx[arow] - cur.base;
+      if (m >= cur.m_end) out_row[rb] = ~0u;
     }
-#define A3_GLOAD(K0)                                                                       \
-    {                                                                                      \
-      const uint32_t t_off = (uint32_t)(K0) * pitch_b;                                     \
-      vr_0 = *reinterpret_cast<const uint4 *>(vb + min(vo_0 + t_off, v_last));             \
-      vr_1 = *reinterpret_cast<const uint4 *>(vb + min(vo_1 + t_off, v_last));             \
-      vr_2 = *reinterpret_cast<const uint4 *>(vb + min(vo_2 + t_off, v_last));             \
-      vr_3 = *reinterpret_cast<const uint4 *>(vb + min(vo_3 + t_off, v_last));             \
+    int lo = min(limit[0], limit[1]), hi = max(limit[0], limit[1]);
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) {
+      lo = min(lo, __shfl_xor(lo, off, 64));
+      hi = max(hi, __shfl_xor(hi, off, 64));
     }
-#define A3_V_TRANSPOSE_STORE(VD, W, C)                                                                       \
-    {                                                                                                        \
-      uint2 even = make_uint2(pack_lo(vr_0.C, vr_1.C), pack_lo(vr_2.C, vr_3.C)); /* dim 8vc+2W,   4 keys */  \
-      uint2 odd = make_uint2(pack_hi(vr_0.C, vr_1.C), pack_hi(vr_2.C, vr_3.C));  /* dim 8vc+2W+1, 4 keys */  \
-      *reinterpret_cast<uint2 *>((VD) + (8 * vc + 2 * W) * kVStride + vpos) = even;                          \
-      *reinterpret_cast<uint2 *>((VD) + (8 * vc + 2 * W + 1) * kVStride + vpos) = odd;                       \
-    }
-#define A3_LSTORE(BUF)                                                                                       \
-    {                                                                                                        \
-      bf16_t *vd = Vt + (BUF) * kVTile;                                                                      \
-      A3_V_TRANSPOSE_STORE(vd, 0, x)                                                                         \
-      A3_V_TRANSPOSE_STORE(vd, 1, y)                                                                         \
-      A3_V_TRANSPOSE_STORE(vd, 2, z)                                                                         \
-      A3_V_TRANSPOSE_STORE(vd, 3, w)                                                                         \
-    }
+    min_limit = __builtin_amdgcn_readfirstlane(lo);
+    max_limit = __builtin_amdgcn_readfirstlane(hi);
+  };
 
-    if (k_begin < k_end) {
-      if (wave < 4) {
-        A3_GLOAD(k_begin)
-        A3_KDMA(0, k_begin)
-        A3_LSTORE(0)
-      }
-    }
-    // Everything loaded so far (Q fragments, first tile) has arrived: inside the loop the compiler's
-    // waits then only concern the V registers of the loop itself.  (Its counter arithmetic does not
-    // know about the direct-to-LDS loads; a pending Q load would make it wait for fresh V loads
-    // in the middle of the MFMAs.)
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    int buf = 0;
-    for (int k0 = k_begin; k0 < k_end; k0 += kTK, buf ^= 1) {
-      const bool more = k0 + kTK < k_end;
-      if (wave < 4) {
-        A3_GLOAD(k0 + kTK)                                   // next tile: in flight during everything below
-        if (more) { A3_KDMA(buf ^ 1, k0 + kTK) }
-      }
-      // The tile's keys run up to the last row of the workgroup's 256; a wave whose own rows all end before
-      // the tile has nothing in it (every P would be 0) and only takes part in the staging and the barrier.
-      if (k0 <= wave_max_limit) {
-      const unsigned char *kt = reinterpret_cast<const unsigned char *>(Ks) + buf * (kKTile * 2) + kfrag;
-      const bf16_t *vt = Vt + buf * kVTile + l32 * kVStride + lhi * 8;
-
-      // ---- S^T = K Q^T : two 32-key blocks, K fragments read one step ahead -----------------
-      f32x16 st[2];
+  f32x4 o[8][2], st[4][2];
+  uint32_t pu[2][2][4];                                      // P of the tile before, pairs of bf16, [32 keys][row block]
+  float ref[2], mx[2], nref[2] = {0.f, 0.f};                  // exponent reference and tile maximum in raw logit units; -ref c2
+  f32x4 osum[2];                                             // row sums of P, by the matrix pipe (an all-ones V): every register
+  bf16x8 ones;
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+  for (int e = 0; e < 8; ++e) ones[e] = (bf16_t)1.0f;
+  int prev_item = item_begin, prev_nseg = 0;
+  auto store_rows = [&]() {
 #pragma unroll
-        for (int x = 0; x < 16; ++x) st[b][x] = 0.f;
-      // The scheduling barriers pin the order "reads of step ks + 1, then MFMAs of step ks": left alone
-      // the compiler sinks every read to just before its use and the LDS latency is exposed
-      bf16x8 kf[2][2];
+    for (int rb = 0; rb < 2; ++rb) {
+      const float total = osum[rb][0];
+      if (prev_nseg == 1) {
+        const float inv = 1.0f / total;
+        if (prev_row[rb] != ~0u) {
+          bf16_t *p = (bf16_t *)a.out + (size_t)prev_row[rb] * kD + 4 * lg;
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
-        kf[0][b] = *reinterpret_cast<const bf16x8 *>(kt + b * 32 * kKRowBytes + (0 ^ kswz));
+          for (int db = 0; db < 8; ++db) {
+            bf16x4 v;
 #pragma unroll
-      for (int ks = 0; ks < kD / 16; ++ks) {
-        if (ks + 1 < kD / 16) {
-#pragma unroll
-          for (int b = 0; b < 2; ++b)
-            kf[(ks + 1) & 1][b] = *reinterpret_cast<const bf16x8 *>(kt + b * 32 * kKRowBytes + ((32 * (ks + 1)) ^ kswz));
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          st[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks & 1][b], qf[ks], st[b], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-
-      // first V^T fragments: their LDS latency hides behind the softmax arithmetic
-      bf16x8 vf[2][4];
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-        vf[0][db] = *reinterpret_cast<const bf16x8 *>(vt + db * 32 * kVStride);
-
-      // ---- online softmax for this lane's row (accumulator x of block b: key k0 + 32b + 8(x/4) + 4 lhi + x%4)
-      if (k0 + kTK - 1 > wave_min_limit) {                  // tile touches the causal boundary of some row
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int x = 0; x < 16; ++x) {
-            int key = k0 + 32 * b + 8 * (x >> 2) + 4 * lhi + (x & 3);
-            if (key > limit) st[b][x] = -INFINITY;
+            for (int e = 0; e < 4; ++e) v[e] = a3_f2bf(o[db][rb][e] * inv);
+            *reinterpret_cast<bf16x4 *>(p + 16 * db) = v;
           }
+        }
+      } else {
+        const size_t pr = ((size_t)g * a.plan.max_items + prev_item) * kTM + 32 * wave + 16 * rb + l16;
+        float *p = a.plan.part_o + pr * kD + 4 * lg;
+#pragma unroll
+        for (int db = 0; db < 8; ++db) *reinterpret_cast<f32x4 *>(p + 16 * db) = o[db][rb];
+        if (lg == 0) a.plan.part_ml[pr] = make_float2(ref[rb] * c2, total);
       }
-      float mx = st[0][0];
+    }
+  };
+
+  // ---- fragments: K (16 keys x 32 dims, lane = key l16, piece 4 ds + lg) by one 16-byte read, V^T (16 dims x 32 keys) by two
+  // transposing 8-byte reads: lane (l16, lg) then holds dim l16, keys 4 lg .. + 3 of two 16-key blocks, which is the order in
+  // which the S^T accumulators hold P (accumulator r of key block b: key 16 b + 4 lg + r, row l16)
+  const uint32_t kaddr = l16 * 256 + 16 * (lg ^ l16);
+  const int vkey = 4 * lg + (l16 >> 2);
+  const uint32_t vaddr = vkey * 256 + 32 * (vkey & 7) + 8 * (l16 & 3);
+#define A3_KFRAG(N) fr[(N) % kAhead] = *reinterpret_cast<const bf16x8 *>(kt + (kaddr ^ (64 * ((N) >> 2))) + 4096 * ((N) & 3));
+#define A3_VFRAG(N)                                                                                                    \
+  {                                                                                                                    \
+    typedef __attribute__((address_space(3))) s16x4 *tr_ptr;                                                           \
+    const unsigned char *p_ = vt + (vaddr ^ (32 * ((N) & 7))) + 8192 * ((N) >> 3);                                     \
+    const s16x4 x_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(p_));                                            \
+    const s16x4 y_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(p_ + 4096));                                     \
+    fr[(16 + (N)) % kAhead] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(x_, y_, 0, 1, 2, 3, 4, 5, 6, 7));            \
+  }
+#define A3_FENCE __builtin_amdgcn_sched_barrier(0);
+  bf16x8 fr[kAhead];                                         // fragments in the order K 0 .. 15, V 0 .. 15
+
+  cur = item_at(item_begin);
+  load_rows();
+  prev_row[0] = prev_row[1] = ~0u;
+  load_from(item_begin);
+  __builtin_amdgcn_s_waitcnt(0);
+  load_k(0); load_next();
+  load_k(1); load_v(0); load_next();
+  load_k(2); load_v(1); load_next();
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));                              // this wave's part of K of tiles 0 and 1 has landed
+  __builtin_amdgcn_s_barrier();                                          // ... and everybody's
+  if (grp == 1) __builtin_amdgcn_s_barrier();                            // one phase behind
+
+  // The two waves of a SIMD belong to different groups and run in opposite phases, one barrier apart: while one has the
+  // matrix pipe (S of tile u and P V of tile u - 1), the other does the softmax of its tile on the vector unit.  Group 0
+  // multiplies tile u in phase 2 u, group 1 in phase 2 u + 1.  K of tile u + 3 and V of tile u + 2 are requested in the
+  // vector phase of tile u; at the end of phase 2 u everything up to K of tile u + 1 and V of tile u has landed, one phase
+  // before their first fragments are read.  Beside the matrix pipe a vector instruction takes about 7 cycles of its wave (10.8
+  // an exponential), so the vector phase is kept to the 32 scalings, 32 exponentials and 16 conversions: the row sums are
+  // matrix products, and the maxima are taken between the products of P V.
+  int ring = 0, k0 = cur.k_begin, item = item_begin;         // ring: tile u % 4
+  bool first = true, has_prev = false;
+  bool act = k0 <= max_limit, act_prev = false;              // a wave whose rows all end before a tile leaves its products out
+  {
+    const unsigned char *kt = lds;
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+    for (int n = 0; n < kAhead; ++n) A3_KFRAG(n)
+  }
+#define A3_PV(N)                                                                                                       \
+  {                                                                                                                    \
+    if ((N) == 14) {                                                                                                   \
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));                                                                        \
+      __builtin_amdgcn_s_barrier();                                                                                    \
+      A3_FENCE                                                                                                         \
+    }                                                                                                                  \
+    _Pragma("unroll") for (int rb = 0; rb < 2; ++rb)                                                                   \
+      o[(N) & 7][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[(16 + (N)) % kAhead], A3_P((N) >> 3, rb), o[(N) & 7][rb], 0, 0, 0); \
+    if (((N) & 7) == 4) {                                                                                              \
+      _Pragma("unroll") for (int rb = 0; rb < 2; ++rb)                                                                 \
+        osum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, A3_P((N) >> 3, rb), osum[rb], 0, 0, 0);                 \
+    }                                                                                                                  \
+    A3_FENCE                                                                                                           \
+    if ((N) + kAhead < 16) A3_VFRAG((N) + kAhead)                                                                      \
+    A3_MAX2((N) >> 1, (N) & 1)                                                                                         \
+    A3_FENCE                                                                                                           \
+  }
+  // the N-th pair of S values of a row block, N = 0 .. 7 (key block N / 2, registers 2 (N % 2) and + 1)
+  // (the empty asm statements keep the compiler from moving the arithmetic behind the products)
+#define A3_EXP2(Q)                                                                                                     \
+  {                                                                                                                    \
+    const int b_ = (Q) >> 2, r_ = (Q) & 2, rb_ = (Q) & 1;                                                              \
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));                                                         \
+    bf16x2 t_;                                                                                                         \
+    t_[0] = a3_f2bf(fast_exp2(fmaf(st[b_][rb_][r_], c2, nref[rb_])));                                                  \
+    t_[1] = a3_f2bf(fast_exp2(fmaf(st[b_][rb_][r_ + 1], c2, nref[rb_])));                                              \
+    pu[b_ >> 1][rb_][2 * (b_ & 1) + r_ / 2] = __builtin_bit_cast(uint32_t, t_);                                        \
+    asm volatile("" : "+v"(pu[b_ >> 1][rb_][2 * (b_ & 1) + r_ / 2]));                                                  \
+  }
+#define A3_P(KS, RB) __builtin_bit_cast(bf16x8, u32x4{pu[KS][RB][0], pu[KS][RB][1], pu[KS][RB][2], pu[KS][RB][3]})
+#define A3_MAX2(N, RB) { mx[RB] = fmaxf(fmaxf(mx[RB], st[(N) >> 1][RB][2 * ((N) & 1)]), st[(N) >> 1][RB][2 * ((N) & 1) + 1]); asm volatile("" : "+v"(mx[RB])); }
+  for (;;) {
+    // ---- matrix phase
+    const unsigned char *kt = lds + ring * kTileBytes, *vt = lds + (kStages + ((ring + 3) & 3)) * kTileBytes;
+    A3_FENCE
+    __builtin_amdgcn_s_setprio(1);
+    if (act) {
 #pragma unroll
-        for (int x = 0; x < 16; ++x) mx = fmaxf(mx, st[b][x]);
-      mx = halves_max(mx);
-      // Lazy rescaling: the exponent reference `row_ref` only has to stay within 2^8 of the running
-      // maximum, not equal to it, so the accumulators are rescaled a handful of times per row
-      // instead of whenever the maximum moves (64 multiplies each time).  P then ranges up to 256.
-      if (__any((mx - row_ref) * c2 > 8.0f)) {              // also true for the first visible key (-inf reference)
-        const float new_ref = fmaxf(row_ref, mx);
-        const float alpha = new_ref == -INFINITY ? 1.0f : fast_exp2((row_ref - new_ref) * c2);
-        row_ref = new_ref;
-        row_sum *= alpha;
+      for (int n = 0; n < 16; ++n) {
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+          st[n & 3][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[n % kAhead], qf[rb][n >> 2],
+                                                                  n < 4 ? f32x4{0.f, 0.f, 0.f, 0.f} : st[n & 3][rb], 0, 0, 0);
+        A3_FENCE
+        if (n + kAhead < 16) A3_KFRAG(n + kAhead) else A3_VFRAG(n + kAhead - 16)
+        A3_FENCE
+      }
+      if (k0 + kTK - 1 > min_limit) {                        // tile touches the causal boundary of some row
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
-          for (int x = 0; x < 16; ++x) o[b][x] *= alpha;
-      }
-      const float nref = row_ref == -INFINITY ? 0.f : -row_ref * c2;   // no visible key yet: every P is 0
-      float psum = 0.f;
+          for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int x = 0; x < 16; ++x) {
-          float pv = fast_exp2(fmaf(st[b][x], c2, nref));
-          st[b][x] = pv;
-          psum += pv;
-        }
-      row_sum += psum;                                      // per lane half; halves are added at the end
-
-      // ---- O^T += V^T P^T, V^T fragments read one step ahead ------------------------------------
-#pragma unroll
-      for (int step = 0; step < 4; ++step) {                // step = 2 b + s2: keys 32 b + 16 s2 ..
-        if (step + 1 < 4) {
-#pragma unroll
-          for (int db = 0; db < 4; ++db)
-            vf[(step + 1) & 1][db] = *reinterpret_cast<const bf16x8 *>(vt + db * 32 * kVStride + (step + 1) * 16);
-        }
-        bf16x8 pf;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pf[e] = a3_f2bf(st[step >> 1][8 * (step & 1) + e]);
-#pragma unroll
-        for (int db = 0; db < 4; ++db)
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[step & 1][db], pf, o[db], 0, 0, 0);
-      }
-      }
-      if (more) {
-        if (wave < 4) {
-          A3_LSTORE(buf ^ 1)
-          __builtin_amdgcn_s_waitcnt(0x0f70);               // vmcnt(0): this wave's K loads have landed
-        }
-      }
-      __syncthreads();
-    }
-#undef A3_KDMA
-#undef A3_GLOAD
-#undef A3_LSTORE
-#undef A3_V_TRANSPOSE_STORE
-
-    row_sum = halves_sum(row_sum);
-    if (nseg == 1) {
-      if (valid) {
-        const float inv = 1.0f / row_sum;
-        bf16_t *orow = (bf16_t *)a.out + ((size_t)arow * a.Hq + hq) * kD;
-        // accumulator x of block db: dim 32 db + 8 (x/4) + 4 lhi + x%4
-#pragma unroll
-        for (int db = 0; db < 4; ++db)
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            bf16x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = a3_f2bf(o[db][4 * q4 + e] * inv);
-            *reinterpret_cast<bf16x4 *>(orow + 32 * db + 8 * q4 + 4 * lhi) = v;
-          }
+            for (int r = 0; r < 4; ++r)
+              if (k0 + 16 * b + 4 * lg + r > limit[rb]) st[b][rb][r] = -INFINITY;
       }
     } else {
-      const size_t pidx = (size_t)g * a.plan.max_items + item;
-      const int ml = wave * 32 + l32;
-      float *po = a.plan.part_o + (pidx * kTM + ml) * kD;
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          f32x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = o[db][4 * q4 + e];
-          *reinterpret_cast<f32x4 *>(po + 32 * db + 8 * q4 + 4 * lhi) = v;
-        }
-      if (lhi == 0) a.plan.part_ml[pidx * kTM + ml] = make_float2(row_ref * c2, row_sum);
+      for (int n = 0; n < kAhead; ++n) A3_VFRAG(n)
     }
+    mx[0] = mx[1] = -INFINITY;                               // (of no meaning, and not used, when the tile is left out)
+    A3_FENCE
+    if (act_prev) {
+#pragma unroll
+      for (int n = 0; n < 16; ++n) A3_PV(n)
+    } else {
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
+      __builtin_amdgcn_s_barrier();
+#pragma unroll
+      for (int n = 0; n < 16; ++n) A3_MAX2(n >> 1, n & 1)
+    }
+    __builtin_amdgcn_s_setprio(0);
+    A3_FENCE
+    // ---- vector phase
+    if (first) {
+      if (has_prev) store_rows();
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+#pragma unroll
+        for (int db = 0; db < 8; ++db) o[db][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        osum[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        ref[rb] = -INFINITY;
+        nref[rb] = 0.f;
+      }
+      first = false;
+    }
+    load_k((ring + 3) & 3);
+    load_v((ring + 2) & 3);
+    load_next();
+    if (act) {
+      // Lazy rescaling: the exponent reference only has to stay within 2^8 of the running maximum, not equal to it, so the
+      // accumulators are rescaled a handful of times per row instead of whenever the maximum moves.  P ranges up to 256.
+      const bool redo = __any((mx[0] - ref[0]) * c2 > 8.0f || (mx[1] - ref[1]) * c2 > 8.0f);   // also the first visible key (-inf)
+      if (redo) {
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) {
+          const float new_ref = fmaxf(ref[rb], groups_max(mx[rb]));
+          const float alpha = new_ref == -INFINITY ? 1.0f : fast_exp2((ref[rb] - new_ref) * c2);
+          ref[rb] = new_ref;
+          nref[rb] = new_ref == -INFINITY ? 0.f : -new_ref * c2;                  // no visible key yet: every P is 0
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            osum[rb][r] *= alpha;
+#pragma unroll
+            for (int db = 0; db < 8; ++db) o[db][rb][r] *= alpha;
+          }
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 16; ++q) A3_EXP2(q)
+    }
+    // ---- on to the next tile
+    ring = (ring + 1) & 3;
+    act_prev = act;
+    bool last = false;
+    k0 += kTK;
+    if (k0 >= cur.k_end) {
+      prev_item = item; prev_nseg = cur.nseg;
+      prev_row[0] = out_row[0]; prev_row[1] = out_row[1];
+      has_prev = true;
+      if (++item < item_end) {
+        cur = item_at(item);
+        load_rows();
+        __builtin_amdgcn_s_waitcnt(0);
+        k0 = cur.k_begin;
+        first = true;
+      } else {
+        last = true;
+      }
+    }
+    act = k0 <= max_limit;
+    if (grp == 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
+    {
+      const unsigned char *kt = lds + ring * kTileBytes;
+      A3_FENCE
+#pragma unroll
+      for (int n = 0; n < kAhead; ++n) A3_KFRAG(n)
+      A3_FENCE
+    }
+    __builtin_amdgcn_s_barrier();
+    if (last) break;
   }
+  // ---- P V of the last tile
+  if (act_prev) {
+    const unsigned char *vt = lds + (kStages + ((ring + 3) & 3)) * kTileBytes;
+#pragma unroll
+    for (int n = 0; n < 16; ++n) {
+      A3_VFRAG(n)
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb)
+        o[n & 7][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[(16 + n) % kAhead], A3_P(n >> 3, rb), o[n & 7][rb], 0, 0, 0);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) osum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, A3_P(ks, rb), osum[rb], 0, 0, 0);
+  }
+#undef A3_PV
+#undef A3_P
+#undef A3_EXP2
+#undef A3_MAX2
+#undef A3_KFRAG
+#undef A3_VFRAG
+#undef A3_FENCE
+  if (grp == 0) __builtin_amdgcn_s_barrier();
+  store_rows();
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));                  // the tail loads have landed before LDS is released
 }
 
 // Merges the partial results of tiles that were cut into key segments, in segment order.
@@ -371,22 +451,37 @@ attn_combine_kernel(attn_args a) {
   if (m >= ta.w) return;
   const int arow = a.plan.a_lo[ta.x] + m / G, hq = g * G + m % G;
   const size_t p0 = (size_t)g * a.plan.max_items + tb.x;
-  float M = -INFINITY;
-  for (int s = 0; s < nseg; ++s) M = fmaxf(M, a.plan.part_ml[(p0 + s) * kTM + ml].x);
+  const float2 *ml_p = a.plan.part_ml + p0 * kTM + ml;
+  const float *o_p = a.plan.part_o + (p0 * kTM + ml) * kD + d0;
   float acc[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-  float L = 0.f;
-  for (int s = 0; s < nseg; ++s) {
-    const float2 st = a.plan.part_ml[(p0 + s) * kTM + ml];
-    const float wgt = exp2f(st.x - M);                      // 0 for a segment this row sees nothing of
-    L += st.y * wgt;
-    const f32x4 *po = reinterpret_cast<const f32x4 *>(a.plan.part_o + ((p0 + s) * kTM + ml) * kD + d0);
+  float M = -INFINITY, L = 0.f;
+  // four segments at a time, their loads in flight together (past the last one: that one again, with weight 0)
+  for (int s0 = 0; s0 < nseg; s0 += 4) {
+    float2 st[4];
+    f32x4 v[4][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f32x4 v = po[i];
+    for (int u = 0; u < 4; ++u) {
+      const size_t s = (size_t)min(s0 + u, nseg - 1) * kTM;
+      st[u] = ml_p[s];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[4 * i + e] = fmaf(v[e], wgt, acc[4 * i + e]);
+      for (int i = 0; i < 4; ++i) v[u][i] = *reinterpret_cast<const f32x4 *>(o_p + s * kD + 4 * i);
+    }
+    float m = M;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m = fmaxf(m, st[u].x);
+    const float old = M == -INFINITY ? 0.f : exp2f(M - m);
+    L *= old;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] *= old;
+    M = m;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float wgt = s0 + u < nseg && st[u].x != -INFINITY ? exp2f(st[u].x - M) : 0.f;   // 0: the row sees nothing of it
+      L += st[u].y * wgt;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[i] = fmaf(v[u][i / 4][i % 4], wgt, acc[i]);
     }
   }
   const float inv = 1.0f / L;

@@ -10,6 +10,7 @@ namespace {
 
 constexpr int kTM = 256;            // packed (row, head) pairs per work item: 32 per wave of the attention kernel
 constexpr int kTK = 64;             // keys per tile
+constexpr int kMinSteps = 4;        // key steps of a share, at least (2K context: 37 us with 8, 33 with 4 or less)
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanLdsInts = 4096;  // LDS the plan kernel sets aside for the plan's small arrays (16 KB)
 
@@ -109,7 +110,7 @@ __device__ __forceinline__ void attn_plan_body(const attn_plan &p, const int *ac
 
   // ---- tiles and their running cost -------------------------------------------------------
   // A tile is laid out as `item_cost` units of start-up (fetching its queries and first keys, storing its
-  // result: measured at six to seven key steps) followed by one unit per key step.
+  // result: three to five key steps) followed by one unit per key step.
   int carry = 0;
   for (int base = 0; base < n_tiles; base += kPlanThreads) {
     const int t = base + tid;
@@ -141,7 +142,7 @@ __device__ __forceinline__ void attn_plan_body(const attn_plan &p, const int *ac
   __syncthreads();
 
   // ---- equal shares ------------------------------------------------------------------------
-  int P = (W - n_tiles * item_cost + 7) / 8;                  // at least 8 key steps per share
+  int P = (W - n_tiles * item_cost + kMinSteps - 1) / kMinSteps;
   if (P > wgs_per_head) P = wgs_per_head;
   if (P > p.max_wgs) P = p.max_wgs;
   if (P < 1) P = 1;
@@ -203,7 +204,7 @@ int attn_wgs_per_head(const a3_layout *L) {
 // value "attn_item_cost".
 int attn_item_cost() {
   const int v = a3_knob(A3_KNOB_ATTN_ITEM_COST);
-  return v >= 0 && v <= 64 ? v : 7;
+  return v >= 0 && v <= 64 ? v : 4;
 }
 
 // every tile starts an item, every share boundary inside a tile starts another

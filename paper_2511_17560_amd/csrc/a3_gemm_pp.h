@@ -80,6 +80,7 @@ __device__ __forceinline__ void gemm_lane_values(const f32x4 (&acc)[IB][JB], int
 //
 // Matrix instructions are 16x16x32: with operands that are not all alike this chip's clock under matrix load is set by
 // power, and a loop of nothing but 16x16x32 on N(0, 1) values runs at 2.14 PFLOP/s where 32x32x16 reaches 1.74 - 1.86.
+// (One operand stays from each instruction to the next: 1 - 3 % of the same.)
 template <int IB, int JB, int SW, int SX>
 template <class WBase, class WOff, class XBase, class XOff>
 __device__ __forceinline__ void gemm_pp<IB, JB, SW, SX>::mainloop(f32x4 (&acc)[IB][JB], unsigned char *lds, int n_slabs, WBase w_base, WOff w_off,
@@ -144,7 +145,7 @@ __device__ __forceinline__ void gemm_pp<IB, JB, SW, SX>::mainloop(f32x4 (&acc)[I
   {                                                                                                                     \
     constexpr int step = (kM - kTail) / (NLOADS);                                                                       \
     _Pragma("unroll") for (int m = 0; m < kM; ++m) {                                                                    \
-      const int ks = m / (IB * JB), i = (m / JB) % IB, j = m % JB;                                                      \
+      const int ks = m / (IB * JB), i = (m / JB) % IB, j = i & 1 ? JB - 1 - m % JB : m % JB;                            \
       acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ks][i], xf[ks][j], acc[i][j], 0, 0, 0);                    \
       if (m % step == step - 1 && m / step < (NLOADS)) { const int n = m / step; A3_PP_FENCE LOAD A3_PP_FENCE }         \
       if (m == kM - kTail - 1) { A3_PP_FENCE WAIT __builtin_amdgcn_s_barrier(); A3_PP_FENCE }                           \
