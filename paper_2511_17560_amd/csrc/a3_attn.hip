@@ -17,7 +17,7 @@
 // per 64-key tile and 256 rows against 3580 with one wave's phases overlapping by chance on 32x32x16, at 1.9 GHz;
 // 16K context at r = 10 %: 290 -> 255 us, 64K: 3411 -> 3030 us (1.18 PFLOP/s), seven heads per KV head at 32K: 1597 ->
 // 1400 us.  Leaving out the exponentials, the loads or the fragment reads gives 9, 8 and 4 %.
-// fp32 path: one workgroup per (active row, head), plain FMA (correctness configuration).
+// fp32 path: the fp32 matrix instruction, one workgroup per 16 packed rows.
 #include <stdlib.h>
 #include <string.h>
 
@@ -457,12 +457,12 @@ attn_combine_kernel(attn_args a) {
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
   float M = -INFINITY, L = 0.f;
-  // four segments at a time, their loads in flight together (past the last one: that one again, with weight 0)
-  for (int s0 = 0; s0 < nseg; s0 += 4) {
-    float2 st[4];
-    f32x4 v[4][4];
+  // two segments at a time, their loads in flight together (past the last one: that one again, with weight 0)
+  for (int s0 = 0; s0 < nseg; s0 += 2) {
+    float2 st[2];
+    f32x4 v[2][4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 2; ++u) {
       const size_t s = (size_t)min(s0 + u, nseg - 1) * kTM;
       st[u] = ml_p[s];
 #pragma unroll
@@ -470,14 +470,14 @@ attn_combine_kernel(attn_args a) {
     }
     float m = M;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) m = fmaxf(m, st[u].x);
+    for (int u = 0; u < 2; ++u) m = fmaxf(m, st[u].x);
     const float old = M == -INFINITY ? 0.f : exp2f(M - m);
     L *= old;
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] *= old;
     M = m;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 2; ++u) {
       const float wgt = s0 + u < nseg && st[u].x != -INFINITY ? exp2f(st[u].x - M) : 0.f;   // 0: the row sees nothing of it
       L += st[u].y * wgt;
 #pragma unroll
@@ -496,69 +496,128 @@ attn_combine_kernel(attn_args a) {
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32: one workgroup per (active row, query head)
+// fp32: one workgroup per 16 packed (row, head) pairs of a KV head; its eight waves take every eighth block of 16 keys
+// and merge at the end
 // ---------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
+// fp32 matrix instruction (16x16x4), fragments straight from memory.  S^T[key][m]: register r of lane (l16, lg) is key
+// 4 lg + r, pair l16 - which is the B operand of the r-th product of O^T[d][m] += V^T P^T when lane group lg supplies key
+// 4 lg + r of V; its lane l16 loads coordinates 4 l16 .. + 3 at once, so block e of O holds coordinates 4 (row) + e.
+// (One workgroup per row and head with a thread per key took 50 us for 108 rows x 8 heads x up to 544 keys.)
+constexpr int kF32Waves = 8;
+constexpr size_t kF32Lds(int d) { return (size_t)kF32Waves * 16 * (d * sizeof(float) + sizeof(float2)); }
+template <int D>
+__global__ void __launch_bounds__(64 * kF32Waves)
 attn_f32_kernel(attn_args a) {
-  __shared__ float qs[128];
-  __shared__ float P[256];
-  __shared__ float red[256];
-
-  const int arow = blockIdx.x, hq = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int d = a.d, G = a.Hq / a.Hkv, g = hq / G;
-  const int t = a.act_idx[arow];
-  const int base = a.seg_start[a.tok_req[t]];
-  const int nk = t - base + 1;
+  extern __shared__ __align__(16) float lds_f[];               // [wave][D / 4 rows of 16 pairs] O as float4, then (ref, sum)
+  f32x4 *lds_o = reinterpret_cast<f32x4 *>(lds_f);
+  float2 *lds_ml = reinterpret_cast<float2 *>(lds_f + (size_t)kF32Waves * 16 * D);
+  const int G = a.Hq / a.Hkv, g = blockIdx.y, rows = 16 / G;   // active rows of a workgroup
+  const int a0 = blockIdx.x * rows, a_end = min(a0 + rows, a.n_act);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, lg = lane >> 4;
   const float *__restrict__ Q = (const float *)a.q;
   const float *__restrict__ K = (const float *)a.k;
   const float *__restrict__ V = (const float *)a.v;
-  for (int c = tid; c < d; c += 256) qs[c] = Q[((size_t)arow * a.Hq + hq) * d + c] * a.scale2;
-  __syncthreads();
-
-  const int col = tid % d, slice = tid / d, n_slices = 256 / d;   // d = 64: 4 key slices, d = 128: 2
-  float o_acc = 0.f, row_max = -INFINITY, row_sum = 0.f;
-  for (int k0 = 0; k0 < nk; k0 += 256) {
-    const int key = k0 + tid;
-    float l = -INFINITY;
-    if (key < nk) {
-      const float *kp = K + ((size_t)(base + key) * a.Hkv + g) * d;
-      float dot = 0.f;
-      for (int c = 0; c < d; ++c) dot = fmaf(qs[c], kp[c], dot);
-      l = dot;
-    }
-    red[tid] = l;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-      if (tid < off) red[tid] = fmaxf(red[tid], red[tid + off]);
-      __syncthreads();
-    }
-    const float new_max = fmaxf(row_max, red[0]);
-    __syncthreads();
-    const float p = exp2f(l - new_max);
-    P[tid] = p;
-    red[tid] = p;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-      if (tid < off) red[tid] += red[tid + off];
-      __syncthreads();
-    }
-    const float alpha = exp2f(row_max - new_max);
-    row_sum = row_sum * alpha + red[0];
-    row_max = new_max;
-    float part = 0.f;
-    const int kend = min(256, nk - k0);
-    for (int kk = slice; kk < kend; kk += n_slices)
-      part = fmaf(P[kk], V[((size_t)(base + k0 + kk) * a.Hkv + g) * d + col], part);
-    o_acc = o_acc * alpha + part;
-    __syncthreads();
+  const int arow = min(a0 + l16 / G, a_end - 1), hq = g * G + l16 % G;
+  f32x4 qf[D / 16];
+  {
+    const f32x4 *qp = reinterpret_cast<const f32x4 *>(Q + ((size_t)arow * a.Hq + hq) * D) + lg;
+#pragma unroll
+    for (int c = 0; c < D / 16; ++c) qf[c] = qp[4 * c];
   }
-  red[tid] = o_acc;
-  __syncthreads();
-  if (tid < d) {
-    float sum = 0.f;
-    for (int s = 0; s < n_slices; ++s) sum += red[s * d + tid];
-    ((float *)a.out)[((size_t)arow * a.Hq + hq) * d + tid] = sum / row_sum;
+  const int t = a.act_idx[arow], req = a.tok_req[t];
+  // the rows of one request at a time (rows are ascending: nearly always all of them)
+  for (int b0 = a0; b0 < a_end;) {
+    const int r = a.tok_req[a.act_idx[b0]], base = a.seg_start[r];
+    int b1 = b0;
+    while (b1 < a_end && a.tok_req[a.act_idx[b1]] == r) ++b1;
+    const bool mine = req == r && l16 < (a_end - a0) * G;
+    const int limit = mine ? t - base : -1;                    // last visible key (request-relative)
+    const int n_keys = a.act_idx[b1 - 1] - base + 1;
+    f32x4 o[D / 16];
+#pragma unroll
+    for (int e = 0; e < D / 16; ++e) o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float ref = -INFINITY, sum = 0.f;
+    f32x4 kf[D / 16];
+    auto load_k = [&](int k0) {
+      const f32x4 *kp = reinterpret_cast<const f32x4 *>(K + ((size_t)(base + min(k0 + l16, n_keys - 1)) * a.Hkv + g) * D) + lg;
+#pragma unroll
+      for (int c = 0; c < D / 16; ++c) kf[c] = kp[4 * c];
+    };
+    if (16 * wave < n_keys) load_k(16 * wave);
+    for (int k0 = 16 * wave; k0 < n_keys; k0 += 16 * kF32Waves) {
+      f32x4 vf[4][D / 64];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const f32x4 *vp = reinterpret_cast<const f32x4 *>(V + ((size_t)(base + min(k0 + 4 * lg + e, n_keys - 1)) * a.Hkv + g) * D) + l16;
+#pragma unroll
+        for (int h = 0; h < D / 64; ++h) vf[e][h] = vp[16 * h];
+      }
+      f32x4 c4[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) c4[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < D / 16; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c4[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][e], qf[c][e], c4[e], 0, 0, 0);
+      if (k0 + 16 * kF32Waves < n_keys) load_k(k0 + 16 * kF32Waves);
+      f32x4 p;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        p[e] = k0 + 4 * lg + e <= limit ? ((c4[0][e] + c4[1][e]) + (c4[2][e] + c4[3][e])) * a.scale2 : -INFINITY;
+      float mx = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float new_ref = fmaxf(ref, mx), use = new_ref == -INFINITY ? 0.f : new_ref;
+      const float alpha = exp2f(ref - use);                    // ref = -inf: 0
+      ref = new_ref;
+      sum *= alpha;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { p[e] = exp2f(p[e] - use); sum += p[e]; }
+#pragma unroll
+      for (int e = 0; e < D / 16; ++e)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) o[e][x] *= alpha;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+          for (int x = 0; x < 4; ++x) o[4 * h + x] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e][h][x], p[e], o[4 * h + x], 0, 0, 0);
+    }
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    __syncthreads();                                           // the merge of the request before has been read
+    // register r of block 4 h + x: coordinate 64 h + 4 (4 lg + r) + x
+#pragma unroll
+    for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        lds_o[((size_t)wave * 16 + l16) * (D / 4) + (((h * 4 + lg) * 4 + x) ^ (l16 & 7))] = o[4 * h + x];
+    if (lg == 0) lds_ml[wave * 16 + l16] = make_float2(ref, sum);
+    __syncthreads();
+    // 16 pairs x D / 4 vectors: the waves' results in wave order
+    for (int v = tid; v < 16 * (D / 4); v += 64 * kF32Waves) {
+      const int m = v / (D / 4), c = v % (D / 4);              // c = (h * 4 + lg) * 4 + x
+      const int row = a0 + m / G;
+      if (m >= (a_end - a0) * G || row < b0 || row >= b1) continue;
+      float M = -INFINITY, Z = 0.f;
+#pragma unroll
+      for (int w = 0; w < kF32Waves; ++w) M = fmaxf(M, lds_ml[w * 16 + m].x);
+      f32x4 s4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < kF32Waves; ++w) {
+        const float2 ml = lds_ml[w * 16 + m];
+        const float wgt = exp2f(ml.x - M);                     // 0 for a wave that saw nothing
+        Z += ml.y * wgt;
+        const f32x4 ov = lds_o[((size_t)w * 16 + m) * (D / 4) + (c ^ (m & 7))];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s4[e] = fmaf(ov[e], wgt, s4[e]);
+      }
+      float *op = (float *)a.out + ((size_t)row * a.Hq + g * G + m % G) * D + 64 * (c >> 4) + 16 * ((c >> 2) & 3) + (c & 3);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) op[4 * e] = s4[e] / Z;
+    }
+    b0 = b1;
   }
 }
 
@@ -624,7 +683,15 @@ static a3_status attn_launch(const a3_layout *L, const void *q_act, const int *a
       hipLaunchKernelGGL(attn_combine_kernel, dim3((unsigned)max_tiles, Hkv, kTM / 32), dim3(256), 0, st, a);
     }
   } else if (parts & 2) {
-    hipLaunchKernelGGL(attn_f32_kernel, dim3(n_act, L->n_q_heads), dim3(256), 0, st, a);
+    const int rows = 16 / (L->n_q_heads / L->n_kv_heads);
+    const dim3 grid((n_act + rows - 1) / rows, L->n_kv_heads);
+    static a3_once_per_device lds_once;
+    const hipError_t e = a3_once(lds_once, []() {
+      return hipFuncSetAttribute((const void *)attn_f32_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kF32Lds(128));
+    });
+    if (e != hipSuccess) return a3_fail(A3_ERR_HIP, "a3_fused_attention: %s", hipGetErrorString(e));
+    if (L->head_dim == 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64 * kF32Waves), kF32Lds(64), st, a);
+    else hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(64 * kF32Waves), kF32Lds(128), st, a);
   }
   A3_CHECK_LAUNCH("a3_fused_attention");
   return A3_OK;

@@ -15,7 +15,7 @@
 // one workgroup per CU with its whole run of keys in flight (scores_bf16_kernel).  More rows: a 256-key tile
 // stays in LDS and the waves walk the rows, two workgroups per CU (scores_rows_bf16_kernel).  exp2 with log2(e)
 // folded into the scale.
-// fp32: plain FMA kernels (correctness configuration).
+// fp32: the same two passes on the fp32 matrix instruction.
 #include <mutex>
 
 #include "a3_internal.h"
@@ -80,9 +80,18 @@ scores_question_stats_kernel(scores_args a) {
   const int key0 = a.seg_start[r] + a.ctx_len[r];
   float m = -INFINITY, z = 0.f;
   for (int u = lane; u <= j; u += 64) {
-    const T *kp = K + ((size_t)(key0 + u) * a.Hkv + g) * a.d;
+    // 16-byte loads of both rows (element by element this kernel took 28 us for 64 question tokens x 32 heads)
+    constexpr int V = a3_elem<T>::kVec;
+    typedef T vec_t __attribute__((ext_vector_type(V)));
+    const vec_t *kp = reinterpret_cast<const vec_t *>(K + ((size_t)(key0 + u) * a.Hkv + g) * a.d);
+    const vec_t *qp = reinterpret_cast<const vec_t *>(Q);
     float dot = 0.f;
-    for (int c = 0; c < a.d; ++c) dot = fmaf((float)Q[c], (float)kp[c], dot);
+#pragma unroll 8
+    for (int c = 0; c < a.d / V; ++c) {
+      const vec_t kv = kp[c], qv = qp[c];
+#pragma unroll
+      for (int e = 0; e < V; ++e) dot = fmaf((float)qv[e], (float)kv[e], dot);
+    }
     const float l = dot * a.scale2;
     const float mn = fmaxf(m, l);
     z = z * exp2f(m - mn) + exp2f(l - mn);                     // m = -inf, z = 0 on the first key: 0 * 0
@@ -830,74 +839,86 @@ scores_head_sum_kernel(scores_args a, const int *__restrict__ tok_chunk) {
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32 kernels (any head_dim <= 128)
+// fp32 kernels (head_dim 64 or 128): logits on the fp32 matrix instruction, fragments straight from memory
 // ---------------------------------------------------------------------------------------
-template <int PASS>
+// One workgroup per (64-key tile, KV head, request); a wave owns 16 of the keys and walks the head's rows 16 at a time.
+// 16x16x4 products: a lane's 16-byte load holds four consecutive coordinates of one key or row, one for each of four
+// instructions (which coordinate goes to which does not matter as long as both operands agree).  C[key][row]: register
+// r of lane (l16, lg) is key 4 lg + r, row l16.  (One thread per key and row slice, 64 coordinates deep, took 280 +
+// 188 us for 512 keys x 256 rows.)
+template <int PASS, int D>
 __global__ void __launch_bounds__(256)
 scores_f32_kernel(scores_args a) {
-  __shared__ float Ks[kTileKeys][128 + 1];
-  __shared__ float Qs[4][128];
-  __shared__ float red[4][kTileKeys];
-
-  const int r = blockIdx.y;
-  const int N = a.ctx_len[r];
-  const int i0 = blockIdx.x * kTileKeys;
-  const int tid = threadIdx.x;
-  const int key = tid & 63, slice = tid >> 6;
-  const int s = a.seg_start[r];
-  const int nq = a.q_len[r];
-  if (PASS == 1 && blockIdx.x == 0 && a.scores)
-    for (int j = tid; j < nq; j += 256) a.scores[s + N + j] = -INFINITY;
+  __shared__ float2 red[4][16];                                // PASS 0: (max, sum) of the rows over a wave's keys
+  const int r = blockIdx.z, g = blockIdx.y;
+  const int N = a.ctx_len[r], i0 = blockIdx.x * kTileKeys;
   if (i0 >= N) return;
-  const int d = a.d, G = a.Hq / a.Hkv, Mg = nq * G, qrow0 = a.q_start[r];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, lg = lane >> 4;
+  const int s = a.seg_start[r], G = a.Hq / a.Hkv, Mg = a.q_len[r] * G, qrow0 = a.q_start[r];
   const float *__restrict__ Q = (const float *)a.q;
-  const float *__restrict__ K = (const float *)a.k;
-  float total = 0.f;                     // PASS 1, tid < kTileKeys: the key's score over all heads so far
-
-  for (int g = 0; g < a.Hkv; ++g) {
-    float colsum = 0.f;
-    __syncthreads();
-    for (int i = tid; i < kTileKeys * d; i += 256) {
-      int kr = i / d, c = i % d;
-      int row = min(s + i0 + kr, a.T - 1);
-      Ks[kr][c] = K[((size_t)row * a.Hkv + g) * d + c];
-    }
-    for (int mb = 0; mb < Mg; mb += 4) {
-      const int m = mb + slice;
-      const int mc = m < Mg ? m : Mg - 1;
-      const int row_id = (qrow0 + mc / G) * a.Hq + g * G + mc % G;
-      __syncthreads();
-      for (int c = key; c < d; c += 64) Qs[slice][c] = Q[(size_t)row_id * d + c];
-      __syncthreads();
-      float dot = 0.f;
-      for (int c = 0; c < d; ++c) dot = fmaf(Qs[slice][c], Ks[key][c], dot);
-      float l = (i0 + key < N) ? dot * a.scale2 : -INFINITY;
-      if (PASS == 0) {
-        // (max, sum) over the 64 keys of this tile for row m: wave-wide reduction (one wave per slice)
-        float mx = l;
+  const int key0 = i0 + 16 * wave;                             // first key of the wave
+  f32x4 kf[D / 16];
+  {
+    const f32x4 *kp = reinterpret_cast<const f32x4 *>((const float *)a.k + ((size_t)min(s + key0 + l16, a.T - 1) * a.Hkv + g) * D) + lg;
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-        float e = exp2f(l - mx);
+    for (int c = 0; c < D / 16; ++c) kf[c] = kp[4 * c];
+  }
+  auto row_of = [&](int m) { return (qrow0 + m / G) * a.Hq + g * G + m % G; };
+  f32x4 qf[D / 16];
+  auto load_q = [&](int m0) {
+    const f32x4 *qp = reinterpret_cast<const f32x4 *>(Q + (size_t)row_of(min(m0 + l16, Mg - 1)) * D) + lg;
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) e += __shfl_xor(e, off, 64);
-        if (key == 0 && m < Mg) a.part[(size_t)blockIdx.x * a.total_rows + row_id] = make_float2(mx, e);
-      } else if (m < Mg) {
-        colsum += exp2f(l - a.stats[row_id].x);
-      }
-    }
-    if (PASS == 1) {
-      // this head's column sums: the four row slices in a fixed order, then the heads in order
+    for (int c = 0; c < D / 16; ++c) qf[c] = qp[4 * c];
+  };
+  f32x4 colsum = {0.f, 0.f, 0.f, 0.f};
+  if (Mg > 0) load_q(0);
+  for (int m0 = 0; m0 < Mg; m0 += 16) {
+    const int m = m0 + l16, row = row_of(min(m, Mg - 1));
+    const float stat = PASS == 1 ? a.stats[row].x : 0.f;
+    f32x4 c4[4];                                               // four chains, so that no product waits for the one before
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c4[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < D / 16; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) c4[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][e], qf[c][e], c4[e], 0, 0, 0);
+    if (m0 + 16 < Mg) load_q(m0 + 16);
+    f32x4 l;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      l[e] = key0 + 4 * lg + e < N ? ((c4[0][e] + c4[1][e]) + (c4[2][e] + c4[3][e])) * a.scale2 : -INFINITY;
+    if (PASS == 0) {
+      float mx = fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3]));
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      float z = 0.f;
+      if (mx > -INFINITY) z = (exp2f(l[0] - mx) + exp2f(l[1] - mx)) + (exp2f(l[2] - mx) + exp2f(l[3] - mx));
+      z += __shfl_xor(z, 16, 64);
+      z += __shfl_xor(z, 32, 64);
+      __syncthreads();                                         // the block before has been read
+      if (lg == 0) red[wave][l16] = make_float2(mx, z);
       __syncthreads();
-      red[slice][key] = colsum;
-      __syncthreads();
-      if (tid < kTileKeys && i0 + tid < N) {
-        const float v = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
-        if (a.part_scores) a.part_scores[(size_t)g * a.T + s + i0 + tid] = v;
-        total += v;
+      if (threadIdx.x < 16 && m < Mg) {
+        float mm = -INFINITY, zz = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) mm = fmaxf(mm, red[w][l16].x);   // the first key of a tile is always real
+#pragma unroll
+        for (int w = 0; w < 4; ++w) zz += red[w][l16].y * exp2f(red[w][l16].x - mm);
+        a.part[(size_t)blockIdx.x * a.total_rows + row] = make_float2(mm, zz);
       }
+    } else if (m < Mg) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) colsum[e] += exp2f(l[e] - stat);
     }
   }
-  if (PASS == 1 && a.scores && tid < kTileKeys && i0 + tid < N) a.scores[s + i0 + tid] = total;
+  if (PASS == 1) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+      for (int off = 1; off < 16; off <<= 1) colsum[e] += __shfl_xor(colsum[e], off, 64);
+      if (l16 == 0 && key0 + 4 * lg + e < N) a.part_scores[(size_t)g * a.T + s + key0 + 4 * lg + e] = colsum[e];
+    }
+  }
 }
 
 }  // namespace
@@ -967,7 +988,6 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
   a.stats = (float2 *)cur.take(total_rows * sizeof(float2));
   a.part_scores = (float *)cur.take((size_t)L->n_kv_heads * L->total_tokens * sizeof(float));
   if (votes) a.part_scores = votes;                            // a KV head's column sums are its votes
-  else if (!bf16) a.part_scores = nullptr;                     // fp32 path adds the heads itself
   const int G = L->n_q_heads / L->n_kv_heads;
   a.inv_G = G > 1 ? (uint32_t)(((1ull << 32) + G - 1) / G) : 0u;
   a.causal_q = causal_q;
@@ -1027,14 +1047,16 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
       if (a.merged) hipLaunchKernelGGL(scores_combine_kernel, dim3((unsigned)((total_rows + 15) / 16)), dim3(256), 0, st, a);
       hipLaunchKernelGGL((scores_bf16_kernel<1, false>), grid, dim3(kScoreThreads), kScoresLds, st, a);
     }
-    if (scores)
-      hipLaunchKernelGGL(scores_head_sum_kernel, dim3((L->total_tokens + 255) / 256), dim3(256), 0, st, a, L->tok_chunk);
   } else {
-    const dim3 grid(n_tiles, L->n_req), cgrid((unsigned)((total_rows + 15) / 16));
-    hipLaunchKernelGGL(scores_f32_kernel<0>, grid, dim3(256), 0, st, a);
+    const dim3 grid(n_tiles, L->n_kv_heads, L->n_req), cgrid((unsigned)((total_rows + 15) / 16));
+    if (L->head_dim == 64) hipLaunchKernelGGL((scores_f32_kernel<0, 64>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((scores_f32_kernel<0, 128>), grid, dim3(256), 0, st, a);
     hipLaunchKernelGGL(scores_combine_kernel, cgrid, dim3(256), 0, st, a);
-    hipLaunchKernelGGL(scores_f32_kernel<1>, grid, dim3(256), 0, st, a);
+    if (L->head_dim == 64) hipLaunchKernelGGL((scores_f32_kernel<1, 64>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((scores_f32_kernel<1, 128>), grid, dim3(256), 0, st, a);
   }
+  if (scores)
+    hipLaunchKernelGGL(scores_head_sum_kernel, dim3((L->total_tokens + 255) / 256), dim3(256), 0, st, a, L->tok_chunk);
   A3_CHECK_LAUNCH("a3_question_scores");
   return A3_OK;
 }
