@@ -148,9 +148,12 @@ __device__ __forceinline__ void attn_plan_body(const attn_plan &p, const int *ac
   if (P < 1) P = 1;
   int t0 = 0, cnt = 0;
   long long s_beg = 0, s_end = 0;
+  // (a 64-bit division is some 150 instructions: only where 32 bits do not hold the products)
+  const bool narrow = (long long)(W + 1) * (P + 1) < (1ll << 31);
+  auto quotient = [&](long long a, int b) { return narrow ? (long long)((uint32_t)a / (uint32_t)b) : a / b; };
   if (tid < P && W > 0) {
-    s_beg = (long long)tid * W / P;
-    s_end = (long long)(tid + 1) * W / P;
+    s_beg = quotient((long long)tid * W, P);
+    s_end = quotient((long long)(tid + 1) * W, P);
     if (s_end > s_beg) {
       t0 = upper_bound_i32(tile_pre, n_tiles + 1, (int)s_beg) - 1;      // tile that holds position s_beg
       const int t1 = lower_bound_i32(tile_pre, n_tiles + 1, (int)s_end) - 1;     // ... and position s_end - 1
@@ -174,8 +177,8 @@ __device__ __forceinline__ void attn_plan_body(const attn_plan &p, const int *ac
   // items of a tile = share boundaries strictly inside it + 1; boundary q lies at floor(q W / P)
   for (int t = tid; t < n_tiles; t += kPlanThreads) {
     const long long x = (long long)tile_pre[t] + item_cost, y = tile_pre[t + 1];
-    const long long ub = ((x + 1) * P + W - 1) / W;          // first q with floor(q W / P) > x
-    const long long lb = (y * P + W - 1) / W;                // first q with floor(q W / P) >= y
+    const long long ub = quotient((x + 1) * P + W - 1, W);   // first q with floor(q W / P) > x
+    const long long lb = quotient(y * P + W - 1, W);         // first q with floor(q W / P) >= y
     p.tile_b[t].y = (int)(lb > ub ? lb - ub : 0) + 1;
   }
   if (tid == 0) {

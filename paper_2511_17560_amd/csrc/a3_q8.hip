@@ -87,34 +87,51 @@ expand_q8_kernel(const signed char *__restrict__ rows, T *__restrict__ k_out, T 
 // The quantiser (run once, when a chunk's caches are produced).  One lane: 16 consecutive coordinates of the
 // key and of the value; the head_dim / 16 lanes of a (row, head) are neighbours in a wave and share the maxima.
 // The scale is the float32 rounding of max|x| / 127 taken in float64 and the code the float64 quotient rounded
-// half to even, so that the integer decision is the same as in a float64 reference.
-template <typename T>
-__device__ inline void quantize_run(const T *__restrict__ src, signed char *__restrict__ dst, float *scale_out,
-                                    int per_head, int c) {
-  float v[16];
-  typedef T vec8 __attribute__((ext_vector_type(8)));
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const vec8 in = *reinterpret_cast<const vec8 *>(src + 8 * half);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[8 * half + e] = (float)in[e];
-  }
+// half to even, so that the integer decision is the same as in a float64 reference.  That division is spared
+// nearly always: n = x * (1 / scale) rounded is at most a step off, and x - n * scale formed in one rounding
+// says whether n is the nearest whole number (rounding is monotone and scale / 2 is a float, so a rounded
+// remainder below scale / 2 is a true one below it).  Only a remainder that is not below (a tie, a quotient
+// within 1e-5 of one, NaN) and scales whose reciprocal a float does not hold take the division.
+// FIGURES_HERE
+typedef signed char i8x16 __attribute__((ext_vector_type(16), aligned(8)));
+
+__device__ __forceinline__ float quotient_code(float v, float s) {
+  const double r = s > 0.f ? rint((double)v / (double)s) : 0.0;
+  return (float)fmin(fmax(r, -127.0), 127.0);
+}
+
+__device__ __forceinline__ void quantize_run(const float (&v)[16], signed char *__restrict__ dst, float *scale_out,
+                                             int per_head, int c) {
   float amax = 0.f;
 #pragma unroll
   for (int e = 0; e < 16; ++e) amax = fmaxf(amax, fabsf(v[e]));
   for (int m = 1; m < per_head; m <<= 1) amax = fmaxf(amax, __shfl_xor(amax, m));
   const float s = (float)((double)amax / 127.0);
   if (c == 0) *scale_out = s;
+  const bool normal = s > 1e-30f && s < 1e30f;
+  const float inv = normal ? __builtin_amdgcn_rcpf(s) : 0.f, half = normal ? 0.5f * s : -1.f;
+  constexpr float kMagic = 12582912.f;                         // 1.5 * 2^23: the sum's low bits are the rounded number
+  uint32_t code[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    float m = fmaf(v[e], inv, kMagic);
+    if (!(fabsf(fmaf(kMagic - m, s, v[e])) < half)) m = kMagic + quotient_code(v[e], s);
+    code[e] = __float_as_uint(m);
+  }
+  i8x16 q;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) q[e] = (signed char)code[e];
+  *reinterpret_cast<i8x16 *>(dst) = q;
+}
+
+template <typename T>
+__device__ __forceinline__ void load_run(const T *__restrict__ src, float (&v)[16]) {
+  typedef T vec8 __attribute__((ext_vector_type(8)));
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
-    i8x8 q;
+    const vec8 in = *reinterpret_cast<const vec8 *>(src + 8 * half);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      double r = s > 0.f ? rint((double)v[8 * half + e] / (double)s) : 0.0;
-      r = fmin(fmax(r, -127.0), 127.0);
-      q[e] = (signed char)(int)r;
-    }
-    *reinterpret_cast<i8x8 *>(dst + 8 * half) = q;
+    for (int e = 0; e < 8; ++e) v[8 * half + e] = (float)in[e];
   }
 }
 
@@ -131,8 +148,11 @@ quantize_q8_kernel(const T *__restrict__ k, const T *__restrict__ v, signed char
   const int h = (int)(th % n_heads), kd = n_heads * head_dim;
   signed char *rec = rows + (size_t)t * q8_row_bytes(n_heads, head_dim);
   float *scales = reinterpret_cast<float *>(rec + 2 * kd);
-  quantize_run(k + th * head_dim + 16 * c, rec + h * head_dim + 16 * c, scales + h, per_head, c);
-  quantize_run(v + th * head_dim + 16 * c, rec + kd + h * head_dim + 16 * c, scales + n_heads + h, per_head, c);
+  float xk[16], xv[16];
+  load_run(k + th * head_dim + 16 * c, xk);
+  load_run(v + th * head_dim + 16 * c, xv);
+  quantize_run(xk, rec + h * head_dim + 16 * c, scales + h, per_head, c);
+  quantize_run(xv, rec + kd + h * head_dim + 16 * c, scales + n_heads + h, per_head, c);
 }
 
 }  // namespace

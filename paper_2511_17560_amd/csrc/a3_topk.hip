@@ -1,13 +1,16 @@
 // Step 3 of the A^3 fusion path: Re = top_p(s) (Eq. 3, second line).
 //
 // One workgroup of 16 wavefronts per request.  The k-th largest score is found exactly by a radix
-// select on an order-preserving integer image of the float (8 bits per pass; the passes start at
+// select on an order-preserving integer image of the float (11 bits per pass; the passes start at
 // the highest bit in which the request's smallest and largest key differ), then the rows are
-// compacted in index order with one workgroup-wide prefix sum.  Compacting in index order
+// compacted in index order with ballots and one sum over the waves.  Compacting in index order
 // gives both rules of the selection for free: among equal scores the lowest rows are taken,
 // and the output is ascending.  Integer work only: the result is unique and bit-exact.
-// Requests of up to 36 K rows keep every key in a register of the lane that owns it (a contiguous
-// run of rows per lane); longer ones re-read the scores from global memory in every pass.
+// Requests of up to 68 K rows keep every key in a register of the lane that owns it; longer ones re-read the
+// scores from global memory in every pass.  One compute unit does all of it, so what bounds it is the chain of
+// barriers and the latency between them: TIMES_HERE
+#include <type_traits>
+
 #include "a3_internal.h"
 #include "a3_attn_plan.h"
 
@@ -112,6 +115,20 @@ __device__ __forceinline__ topk_range topk_range_of(const topk_problem &p, const
   return t;
 }
 
+// Eviction extension: keep_idx[g][keep_start[r] + i] for the system-prompt rows (i < skip[r]) and the question rows
+// (the last q_len[r] slots of the request), by the workgroup that ranks the rest.
+__device__ __forceinline__ void write_fixed_rows(const topk_problem &p, int *__restrict__ keep_idx) {
+  const int r = blockIdx.x;
+  int *out = keep_idx + (size_t)blockIdx.y * p.out_stride;
+  const int s = p.seg_start[r], N = p.ctx_len[r], nq = p.q_len[r], sk = p.skip[r];
+  const int o0 = p.sel_start[r], o1 = p.sel_start[r + 1];
+  // (a keep_start that does not match the rule must not send a store outside the list)
+  for (int i = threadIdx.x; i < sk; i += kBlock)
+    if (o0 + i >= 0 && o0 + i < p.out_stride) out[o0 + i] = s + i;
+  for (int j = threadIdx.x; j < nq; j += kBlock)
+    if (o1 - nq + j >= 0 && o1 - nq + j < p.out_stride) out[o1 - nq + j] = s + N + j;
+}
+
 // Requests longer than the register kernel holds: 4 x 8-bit passes from the top byte, every pass
 // re-reads the scores from global memory.
 __global__ void __launch_bounds__(kBlock)
@@ -121,6 +138,7 @@ topk_select_kernel(const float *__restrict__ scores, topk_problem prob, int *__r
   __shared__ uint32_t sh_bin, sh_need;
 
   const int tid = threadIdx.x;
+  if (prob.skip) write_fixed_rows(prob, sel_idx);
   const topk_range rg = topk_range_of(prob, scores, sel_idx);
   const int s = rg.s, N = rg.N, k = rg.k;
   if (k <= 0) return;                    // uniform over the workgroup
@@ -171,152 +189,190 @@ topk_select_kernel(const float *__restrict__ scores, topk_problem prob, int *__r
   }
 }
 
-// KPT = keys per lane (compile-time bound; the request's rows are split into runs of
-// ceil(N / 1024) <= KPT consecutive rows).  The scores are read once, coalesced, into LDS and
-// from there into the registers of their owners; every later step works on registers.
-template <int KPT>
-__device__ __forceinline__ void topk_select_reg_body(const float *__restrict__ scores, const topk_problem &prob,
-                                                     int *__restrict__ sel_idx, uint32_t *keys /* LDS [N + N/32] */) {
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t wave_min[kWaves], wave_max[kWaves];
-  __shared__ int wave_gt[kWaves], wave_eq[kWaves];
-  __shared__ uint32_t sh_bin, sh_need;
+// KPT = keys per lane (compile-time bound).  Wave w owns a contiguous block of 64 * per rows, per <= KPT a multiple
+// of 4; vector q of a lane are the rows 256 q + 4 lane .. + 3 of its wave's block: every load instruction of a wave is
+// 1 KB in one piece, and index order is (wave, q, lane, element).  The blocks are counted from the 16-byte boundary at
+// or below the request's first score, so that every load is aligned wherever the request starts; the vectors that
+// reach over an end of the request are loaded element by element.
+constexpr int kBins = 2048;
+constexpr uint32_t kRankKeys = 256;      // candidates that are ranked directly instead of by another round
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const topk_range rg = topk_range_of(prob, scores, sel_idx);
-  const int s = rg.s, N = rg.N, k = rg.k;
+template <int KPT>
+__device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
+  __shared__ __align__(16) uint32_t hist[kBins];
+  __shared__ uint32_t wave_a[kWaves], wave_b[kWaves];
+  __shared__ uint32_t sh_bin, sh_need, sh_in, sh_key;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int N = rg.N, k = rg.k;
   if (k <= 0) return;                    // uniform over the workgroup
   int *__restrict__ out = rg.out;
   const float *__restrict__ sc = rg.sc;
-
-  const int per = (N + kBlock - 1) / kBlock;                 // <= KPT (checked by the host)
-  const int first = min(N, tid * per), nv = min(N, first + per) - first;
+  const int mis = (int)((reinterpret_cast<uintptr_t>(sc) >> 2) & 3);
+  const int nq = ((N + mis + kBlock - 1) / kBlock + 3) / 4;  // vectors per lane, <= KPT / 4 (checked by the host)
+  const int row0 = wave * 256 * nq + 4 * lane - mis;         // row of key[0]; key[4 q + e]: row0 + 256 q + e
   uint32_t key[KPT];
-  uint32_t mn = 0xffffffffu, mx = 0u;
-  if (per % 4 == 0 && (reinterpret_cast<uintptr_t>(sc) & 15) == 0) {
-    // a lane's run starts on a 16-byte boundary: four scores per load, straight into the registers
+  // (a lane's rows outside [0, N): never counted)
+#define A3_ROW(J) (row0 + 256 * ((J) >> 2) + ((J) & 3))
+#define A3_REAL(J) (((J) >= 4 || row0 >= -(J)) && row0 < N - (256 * ((J) >> 2) + ((J) & 3)))
 #pragma unroll
-    for (int q = 0; q < KPT / 4; ++q) {
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (4 * q < nv) {
-        if (4 * q + 4 <= nv) v = *reinterpret_cast<const float4 *>(sc + first + 4 * q);
-        else {                                               // last lane with scores: the run ends inside this vector
-          v.x = sc[first + 4 * q];
-          if (4 * q + 1 < nv) v.y = sc[first + 4 * q + 1];
-          if (4 * q + 2 < nv) v.z = sc[first + 4 * q + 2];
-        }
+  for (int q = 0; q < KPT / 4; ++q) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    const int i = row0 + 256 * q;
+    if (q < nq && i < N) {
+      if (i >= 0 && i + 4 <= N) v = *reinterpret_cast<const float4 *>(sc + i);
+      else {
+        if (i >= 0) v.x = sc[i];
+        if (i + 1 >= 0 && i + 1 < N) v.y = sc[i + 1];
+        if (i + 2 >= 0 && i + 2 < N) v.z = sc[i + 2];
+        if (i + 3 >= 0 && i + 3 < N) v.w = sc[i + 3];
       }
-      key[4 * q] = score_key(v.x); key[4 * q + 1] = score_key(v.y);
-      key[4 * q + 2] = score_key(v.z); key[4 * q + 3] = score_key(v.w);
     }
-  } else {
-    // coalesced through LDS.  One pad word per 32 keys: a lane reads a contiguous run, and without the pad
-    // the runs of all lanes would start in the same few LDS banks
-    for (int i = tid; i < N; i += kBlock) keys[i + (i >> 5)] = score_key(sc[i]);
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-      const int i = first + min(j, max(nv - 1, 0));
-      key[j] = nv > 0 ? keys[i + (i >> 5)] : 0u;
-    }
+    key[4 * q] = score_key(v.x); key[4 * q + 1] = score_key(v.y);
+    key[4 * q + 2] = score_key(v.z); key[4 * q + 3] = score_key(v.w);
   }
+  for (int i = tid; i < kBins; i += kBlock) hist[i] = 0;
+  uint32_t mn = 0xffffffffu, mx = 0u;
 #pragma unroll
   for (int j = 0; j < KPT; ++j)
-    if (j < nv) { mn = min(mn, key[j]); mx = max(mx, key[j]); }
+    if ((j >> 2) < nq && A3_REAL(j)) { mn = min(mn, key[j]); mx = max(mx, key[j]); }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     mn = min(mn, (uint32_t)__shfl_xor((int)mn, off, 64));
     mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
   }
-  if (lane == 0) { wave_min[wave] = mn; wave_max[wave] = mx; }
+  if (lane == 0) { wave_a[wave] = mn; wave_b[wave] = mx; }
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) { mn = min(mn, wave_min[w]); mx = max(mx, wave_max[w]); }
+  for (int w = 0; w < kWaves; ++w) { mn = min(mn, wave_a[w]); mx = max(mx, wave_b[w]); }
 
   // ---- radix select inside [lo, hi]: the key of the k-th largest score ------------------
   // Invariant: the wanted key lies in [lo, hi] and is the need-th largest of the keys in there.
   uint32_t lo = mn, hi = mx, need = (uint32_t)k;
-  for (;;) {
+  while (hi != lo) {                                         // (equal: every candidate is the same key)
     const uint32_t width = hi - lo;
-    if (width == 0) break;                                   // every candidate is the same key
-    const int shift = max(0, 24 - __clz((int)width));        // (width >> shift) < 256
-    if (tid < 256) hist[tid] = 0;
-    __syncthreads();
+    const int shift = max(0, 21 - __clz((int)width));        // (width >> shift) < kBins
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
       const uint32_t rel = key[j] - lo;
-      if (j < nv && rel <= width) atomicAdd(&hist[rel >> shift], 1u);
+      if ((j >> 2) < nq && A3_REAL(j) && rel <= width) atomicAdd(&hist[rel >> shift], 1u);
     }
     __syncthreads();
-    find_bin(hist, need, &sh_bin, &sh_need);
+    // the bin that holds the need-th largest candidate: suffix sums over the bins, two per thread
+    const uint2 c = *reinterpret_cast<const uint2 *>(hist + 2 * tid);
+    uint32_t suf = c.x + c.y;                                // sum over the lanes >= this one
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t x = __shfl_down(suf, off, 64);
+      if (lane + off < 64) suf += x;
+    }
+    if (lane == 0) wave_a[wave] = suf;
+    __syncthreads();
+    uint32_t above = suf - c.x - c.y;                        // candidates in higher bins
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) above += w > wave ? wave_a[w] : 0u;
+    if (above < need && above + c.y >= need) { sh_bin = 2 * tid + 1; sh_need = need - above; sh_in = c.y; }
+    above += c.y;
+    if (above < need && above + c.x >= need) { sh_bin = 2 * tid; sh_need = need - above; sh_in = c.x; }
+    *reinterpret_cast<uint2 *>(hist + 2 * tid) = make_uint2(0u, 0u);           // for the next round
     __syncthreads();
     lo += sh_bin << shift;
-    hi = min(hi, lo + ((1u << shift) - 1u));
+    hi = lo + min(hi - lo, (1u << shift) - 1u);
     need = sh_need;
-    const uint32_t in_bin = hist[sh_bin];                    // candidates left, need of them wanted
-    __syncthreads();
+    const uint32_t in_bin = sh_in;                           // candidates left, need of them wanted
     if (shift == 0) break;                                   // the bin was a single key
-    if (in_bin <= 64) {
-      // Few candidates left (the usual case after two rounds): they are gathered (in any order: what follows
-      // does not depend on it) and one wave ranks them instead of two more rounds over all lanes.  The key v
-      // with fewer than `need` candidates above it and at least `need` at or above it is the wanted one.
-      uint32_t *cand = hist;                                 // free since the barrier above
+    if (in_bin <= kRankKeys) {
+      // Few candidates left (the usual case after one or two rounds): they are gathered (in any order: what follows
+      // does not depend on it) and ranked directly.  The key v with fewer than `need` candidates above it and at least
+      // `need` at or above it is the wanted one.
+      uint32_t *cand = hist;
+      __syncthreads();                                       // sh_bin and sh_need have been read
       if (tid == 0) sh_bin = 0;
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < KPT; ++j)
-        if (j < nv && key[j] - lo <= hi - lo) cand[atomicAdd(&sh_bin, 1u)] = key[j];
+        if ((j >> 2) < nq && A3_REAL(j) && key[j] - lo <= hi - lo) cand[atomicAdd(&sh_bin, 1u)] = key[j];
       __syncthreads();
-      if (tid < 64) {
+      if (tid < (int)kRankKeys && (wave << 6) < (int)in_bin) {
         const uint32_t mine = tid < (int)in_bin ? cand[tid] : 0u;
         uint32_t gt = 0, ge = 0;
-        for (uint32_t i = 0; i < in_bin; ++i) { const uint32_t c = cand[i]; gt += c > mine; ge += c >= mine; }
+        for (uint32_t i = 0; i < in_bin; ++i) { const uint32_t x = cand[i]; gt += x > mine; ge += x >= mine; }
         // (several lanes hold the wanted key when it occurs more than once: they store the same two numbers)
-        if (tid < (int)in_bin && gt < need && need <= ge) { wave_min[0] = mine; sh_need = need - gt; }
+        if (tid < (int)in_bin && gt < need && need <= ge) { sh_key = mine; sh_need = need - gt; }
       }
       __syncthreads();
-      lo = hi = wave_min[0];
+      lo = hi = sh_key;
       need = sh_need;
       break;
     }
   }
   const uint32_t tau = lo;               // key of the k-th largest; `need` rows equal to it are taken
 
-  // ---- ordered compaction: one scan over (rows above tau, rows equal to tau) per lane -------
-  int cnt_gt = 0, cnt_eq = 0;
+  // ---- ordered compaction: rows above tau and equal to tau per wave, then every row's place from the ballots -------
+  uint32_t n_gt = 0, n_eq = 0;
 #pragma unroll
-  for (int j = 0; j < KPT; ++j) {
-    if (j < nv) { cnt_gt += key[j] > tau; cnt_eq += key[j] == tau; }
-  }
-  int inc_gt = cnt_gt, inc_eq = cnt_eq;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int xg = __shfl_up(inc_gt, off, 64), xe = __shfl_up(inc_eq, off, 64);
-    if (lane >= off) { inc_gt += xg; inc_eq += xe; }
-  }
-  if (lane == 63) { wave_gt[wave] = inc_gt; wave_eq[wave] = inc_eq; }
+  for (int j = 0; j < KPT; ++j)
+    if ((j >> 2) < nq) {
+      n_gt += (uint32_t)__popcll(__ballot(A3_REAL(j) && key[j] > tau));
+      n_eq += (uint32_t)__popcll(__ballot(A3_REAL(j) && key[j] == tau));
+    }
+  __syncthreads();                                           // wave_a, wave_b: free
+  if (lane == 0) { wave_a[wave] = n_gt; wave_b[wave] = n_eq; }
   __syncthreads();
-  int gt_before = inc_gt - cnt_gt, eq_before = inc_eq - cnt_eq;
-  for (int w = 0; w < wave; ++w) { gt_before += wave_gt[w]; eq_before += wave_eq[w]; }
+  uint32_t gt_before = 0, eq_before = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    gt_before += w < wave ? wave_a[w] : 0u;
+    eq_before += w < wave ? wave_b[w] : 0u;
+  }
+  if (n_gt + (eq_before < need ? n_eq : 0u) == 0) return;    // nothing of this wave's block is taken (no barrier follows)
   // rows equal to tau are taken in index order until `need` of them are: min(eq_before, need) of
   // the earlier ones were taken
-  int pos = gt_before + min(eq_before, (int)need);
-  int take_eq = (int)need - eq_before;
-  take_eq = take_eq < 0 ? 0 : (take_eq > cnt_eq ? cnt_eq : take_eq);
+  uint32_t pos = gt_before + min(eq_before, need);
+  const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
-  for (int j = 0; j < KPT; ++j) {
-    if (j < nv) {
-      if (key[j] > tau) out[pos++] = s + first + j;
-      else if (key[j] == tau && take_eq > 0) { out[pos++] = s + first + j; --take_eq; }
+  for (int q = 0; q < KPT / 4; ++q) {
+    if (q < nq) {
+      bool take[4];
+      unsigned long long eq[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        take[e] = A3_REAL(4 * q + e) && key[4 * q + e] > tau;
+        eq[e] = __ballot(A3_REAL(4 * q + e) && key[4 * q + e] == tau);
+      }
+      if (eq[0] | eq[1] | eq[2] | eq[3]) {
+        uint32_t rank = eq_before;                           // rows equal to tau before this one
+#pragma unroll
+        for (int e = 0; e < 4; ++e) rank += (uint32_t)__popcll(eq[e] & below);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool is = (eq[e] >> lane) & 1;
+          take[e] = take[e] || (is && rank < need);
+          rank += is;
+          eq_before += (uint32_t)__popcll(eq[e]);
+        }
+      }
+      uint32_t at = pos;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned long long b = __ballot(take[e]);
+        at += (uint32_t)__popcll(b & below);
+        pos += (uint32_t)__popcll(b);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (take[e]) out[at++] = rg.s + A3_ROW(4 * q + e);
     }
   }
+#undef A3_ROW
+#undef A3_REAL
 }
 
 template <int KPT>
 __global__ void __launch_bounds__(kBlock)
 topk_select_reg_kernel(const float *__restrict__ scores, topk_problem prob, int *__restrict__ sel_idx) {
-  extern __shared__ uint32_t keys[];
-  topk_select_reg_body<KPT>(scores, prob, sel_idx, keys);
+  if (prob.skip) write_fixed_rows(prob, sel_idx);
+  topk_select_reg_body<KPT>(topk_range_of(prob, scores, sel_idx));
 }
 
 // Step 3, the active rows [Re, Q] and the layout of the attention's work in one launch, for a batch of one
@@ -325,12 +381,11 @@ topk_select_reg_kernel(const float *__restrict__ scores, topk_problem prob, int 
 template <int KPT>
 __global__ void __launch_bounds__(kBlock)
 topk_select_plan_kernel(const float *__restrict__ scores, topk_problem prob, int *__restrict__ sel_idx,
-                        int *act_idx, int n_act, attn_plan plan, int G, int wgs_per_head, int item_cost,
-                        int lds_ints /* ints of dynamic LDS */) {
-  extern __shared__ uint32_t keys[];
+                        int *act_idx, int n_act, attn_plan plan, int G, int wgs_per_head, int item_cost) {
   __shared__ int wave_tot[kPlanThreads / 64];
+  __shared__ int small[kPlanLdsInts];
   static_assert(kPlanThreads == kBlock, "one workgroup shape for both parts");
-  topk_select_reg_body<KPT>(scores, prob, sel_idx, keys);
+  topk_select_reg_body<KPT>(topk_range_of(prob, scores, sel_idx));
   __syncthreads();                                           // the selection is written (and has left this CU's L1 path)
   const int k = prob.one_N >= 0 ? prob.one_k : prob.sel_start[1] - prob.sel_start[0];
   const int s = prob.one_N >= 0 ? 0 : prob.seg_start[0], N = prob.one_N >= 0 ? prob.one_N : prob.ctx_len[0];
@@ -339,35 +394,32 @@ topk_select_plan_kernel(const float *__restrict__ scores, topk_problem prob, int
   for (int i = threadIdx.x; k + i < n_act; i += kBlock) act_idx[k + i] = s + N + i;   // the question rows
   __threadfence_block();
   __syncthreads();
-  // (the keys' LDS is free now: it serves as the plan's scratch)
-  attn_plan_body(plan, act_idx, n_act, prob.seg_start, 1, G, wgs_per_head, item_cost, wave_tot,
-                 reinterpret_cast<int *>(keys), lds_ints);
+  attn_plan_body(plan, act_idx, n_act, prob.seg_start, 1, G, wgs_per_head, item_cost, wave_tot, small, kPlanLdsInts);
 }
 
-constexpr int kMaxLdsKeys = 36 * 1024;   // 148.5 KB of padded keys next to the small static arrays
+constexpr int kMaxRegKeys = 68 * 1024 - 3;   // rows of a request in registers, from whatever alignment it starts
+
+// f(std::integral_constant<int, KPT>) for the smallest KPT that holds a request of n rows
+template <typename F>
+void with_keys_per_lane(int n, F &&f) {
+  const int per = (n + 3 + kBlock - 1) / kBlock;
+  if (per <= 4) f(std::integral_constant<int, 4>{});
+  else if (per <= 8) f(std::integral_constant<int, 8>{});
+  else if (per <= 20) f(std::integral_constant<int, 20>{});
+  else if (per <= 36) f(std::integral_constant<int, 36>{});
+  else f(std::integral_constant<int, 68>{});
+}
 
 // One launch of the ranking kernels over grid (requests, heads).
 a3_status topk_launch(const a3_layout *L, const float *scores, const topk_problem &prob, int n_heads, int *sel_idx,
                       hipStream_t st, const char *who) {
   const dim3 grid(L->n_req, n_heads);
-  if (L->max_ctx_len <= kMaxLdsKeys) {
-    const size_t lds = ((size_t)L->max_ctx_len + L->max_ctx_len / 32 + 1) * sizeof(uint32_t);
-    static a3_once_per_device lds_once;
-    const hipError_t once_err = a3_once(lds_once, []() {
-      const int cap = (int)((kMaxLdsKeys + kMaxLdsKeys / 32 + 1) * sizeof(uint32_t));
-      hipError_t e1 = hipFuncSetAttribute((const void *)topk_select_reg_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-      hipError_t e2 = hipFuncSetAttribute((const void *)topk_select_reg_kernel<16>, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-      hipError_t e3 = hipFuncSetAttribute((const void *)topk_select_reg_kernel<36>, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-      return e1 != hipSuccess ? e1 : (e2 != hipSuccess ? e2 : e3);
+  if (L->max_ctx_len <= kMaxRegKeys)
+    with_keys_per_lane(L->max_ctx_len, [&](auto kpt) {
+      hipLaunchKernelGGL(topk_select_reg_kernel<kpt.value>, grid, dim3(kBlock), 0, st, scores, prob, sel_idx);
     });
-    if (once_err != hipSuccess) return a3_fail(A3_ERR_HIP, "%s: cannot raise the dynamic LDS limit", who);
-    const int per = (L->max_ctx_len + kBlock - 1) / kBlock;  // keys per lane of the longest request
-    if (per <= 4) hipLaunchKernelGGL(topk_select_reg_kernel<4>, grid, dim3(kBlock), lds, st, scores, prob, sel_idx);
-    else if (per <= 16) hipLaunchKernelGGL(topk_select_reg_kernel<16>, grid, dim3(kBlock), lds, st, scores, prob, sel_idx);
-    else hipLaunchKernelGGL(topk_select_reg_kernel<36>, grid, dim3(kBlock), lds, st, scores, prob, sel_idx);
-  } else {
+  else
     hipLaunchKernelGGL(topk_select_kernel, grid, dim3(kBlock), 0, st, scores, prob, sel_idx);
-  }
   A3_CHECK_LAUNCH(who);
   return A3_OK;
 }
@@ -398,21 +450,6 @@ pool_votes_kernel(const float *__restrict__ in, float *__restrict__ out, const i
     }
   }
   out[(size_t)blockIdx.y * T + t] = v;
-}
-
-// keep_idx[g][keep_start[r] + i] for the system-prompt rows (i < skip[r]) and the question rows (the last
-// q_len[r] slots of the request)
-__global__ void __launch_bounds__(256)
-evict_fixed_rows_kernel(topk_problem p, int total_keep, int *__restrict__ keep_idx) {
-  const int r = blockIdx.x;
-  int *out = keep_idx + (size_t)blockIdx.y * p.out_stride;
-  const int s = p.seg_start[r], N = p.ctx_len[r], nq = p.q_len[r], sk = p.skip[r];
-  const int o0 = p.sel_start[r], o1 = p.sel_start[r + 1];
-  // (a keep_start that does not match the rule must not send a store outside the list)
-  for (int i = threadIdx.x; i < sk; i += 256)
-    if (o0 + i >= 0 && o0 + i < total_keep) out[o0 + i] = s + i;
-  for (int j = threadIdx.x; j < nq; j += 256)
-    if (o1 - nq + j >= 0 && o1 - nq + j < total_keep) out[o1 - nq + j] = s + N + j;
 }
 
 // out[slot, g, :] = in[keep_idx[g][slot], g, :] for K and V; 16 bytes per lane
@@ -478,7 +515,6 @@ extern "C" a3_status a3_evict_select(const a3_layout *L, const float *votes, con
   }
   const topk_problem prob{L->seg_start, L->ctx_len, keep_start, sys_len, L->q_len, (long)L->total_tokens,
                           (long)total_keep};
-  hipLaunchKernelGGL(evict_fixed_rows_kernel, dim3(L->n_req, L->n_kv_heads), dim3(256), 0, st, prob, total_keep, keep_idx);
   return topk_launch(L, ranked, prob, L->n_kv_heads, keep_idx, st, "a3_evict_select");
 }
 
@@ -515,7 +551,7 @@ extern "C" a3_status a3_topk_select_plan(const a3_layout *L, const float *scores
              "a3_topk_select_plan: total_k %d, n_act %d (of %d rows)", total_k, n_act, L->total_tokens);
   A3_REQUIRE(scores && sel_start && act_idx && (sel_idx || total_k == 0), A3_ERR_INVALID_ARG,
              "a3_topk_select_plan: NULL argument");
-  const bool one = L->n_req == 1 && L->dtype == A3_BF16 && L->max_ctx_len <= kMaxLdsKeys && total_k > 0 && n_act > 0;
+  const bool one = L->n_req == 1 && L->dtype == A3_BF16 && L->max_ctx_len <= kMaxRegKeys && total_k > 0 && n_act > 0;
   if (!one) {
     A3_REQUIRE(sel_idx != act_idx || L->n_req == 1, A3_ERR_INVALID_ARG,
                "a3_topk_select_plan: sel_idx may only be act_idx itself in a batch of one request");
@@ -542,25 +578,11 @@ extern "C" a3_status a3_topk_select_plan(const a3_layout *L, const float *scores
     prob.one_N = L->max_ctx_len;
     prob.one_k = total_k;
   }
-  const size_t lds = ((size_t)L->max_ctx_len + L->max_ctx_len / 32 + 1) * sizeof(uint32_t);
-  static a3_once_per_device lds_once;
-  const hipError_t once_err = a3_once(lds_once, []() {
-    const int cap = (int)((kMaxLdsKeys + kMaxLdsKeys / 32 + 1) * sizeof(uint32_t));
-    hipError_t e1 = hipFuncSetAttribute((const void *)topk_select_plan_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-    hipError_t e2 = hipFuncSetAttribute((const void *)topk_select_plan_kernel<16>, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-    hipError_t e3 = hipFuncSetAttribute((const void *)topk_select_plan_kernel<36>, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-    return e1 != hipSuccess ? e1 : (e2 != hipSuccess ? e2 : e3);
+  const int G = L->n_q_heads / L->n_kv_heads;
+  with_keys_per_lane(L->max_ctx_len, [&](auto kpt) {
+    hipLaunchKernelGGL(topk_select_plan_kernel<kpt.value>, dim3(1), dim3(kBlock), 0, (hipStream_t)stream, scores, prob,
+                       sel_idx, act_idx, n_act, plan, G, plan.max_wgs, attn_item_cost());
   });
-  if (once_err != hipSuccess) return a3_fail(A3_ERR_HIP, "a3_topk_select_plan: cannot raise the dynamic LDS limit");
-  hipStream_t st = (hipStream_t)stream;
-  const int G = L->n_q_heads / L->n_kv_heads, wgs = plan.max_wgs, cost = attn_item_cost();
-  const int per = (L->max_ctx_len + kBlock - 1) / kBlock;
-  if (per <= 4)
-    hipLaunchKernelGGL(topk_select_plan_kernel<4>, dim3(1), dim3(kBlock), lds, st, scores, prob, sel_idx, act_idx, n_act, plan, G, wgs, cost, (int)(lds / sizeof(int)));
-  else if (per <= 16)
-    hipLaunchKernelGGL(topk_select_plan_kernel<16>, dim3(1), dim3(kBlock), lds, st, scores, prob, sel_idx, act_idx, n_act, plan, G, wgs, cost, (int)(lds / sizeof(int)));
-  else
-    hipLaunchKernelGGL(topk_select_plan_kernel<36>, dim3(1), dim3(kBlock), lds, st, scores, prob, sel_idx, act_idx, n_act, plan, G, wgs, cost, (int)(lds / sizeof(int)));
   A3_CHECK_LAUNCH("a3_topk_select_plan");
   return A3_OK;
 }
