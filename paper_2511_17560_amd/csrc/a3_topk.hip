@@ -7,8 +7,8 @@
 // gives both rules of the selection for free: among equal scores the lowest rows are taken,
 // and the output is ascending.  Integer work only: the result is unique and bit-exact.
 // Requests of up to 68 K rows keep every key in a register of the lane that owns it; longer ones re-read the
-// scores from global memory in every pass.  One compute unit does all of it, so what bounds it is the chain of
-// barriers and the latency between them: TIMES_HERE
+// scores from global memory in every pass.  One compute unit does all of it, so what bounds it is the instructions its 16
+// waves issue and the chain of barriers.  With the plan: 2K rows 10.8 us, 16K 21, 32K 33, 64K 49.
 #include <type_traits>
 
 #include "a3_internal.h"
@@ -84,7 +84,7 @@ __device__ __forceinline__ void find_bin(const uint32_t *hist, uint32_t need, ui
 // What one workgroup ranks.  Selection of Eq. 3: the context rows of request blockIdx.x, k from sel_start.
 // Eviction extension (skip != nullptr): blockIdx.y is a KV head with its own score row and output row; the
 // first skip[r] context rows (system prompt) and the question rows are retained anyway and written by
-// another kernel, so the candidates start behind the system prompt, the count leaves them out, and the
+// write_fixed_rows, so the candidates start behind the system prompt, the count leaves them out, and the
 // output starts behind the system prompt's slots.
 struct topk_problem {
   const int *seg_start, *ctx_len, *sel_start;
@@ -211,31 +211,32 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
   const int mis = (int)((reinterpret_cast<uintptr_t>(sc) >> 2) & 3);
   const int nq = ((N + mis + kBlock - 1) / kBlock + 3) / 4;  // vectors per lane, <= KPT / 4 (checked by the host)
   const int row0 = wave * 256 * nq + 4 * lane - mis;         // row of key[0]; key[4 q + e]: row0 + 256 q + e
+  // Keys of scores are at least 1 (score_key is 0 for one NaN alone); a lane's rows outside [0, N) are 0, and no count
+  // below includes 0: no step tests the bounds of a key (with such tests 11.9, 22.6, 35.5 and 57.7 us instead of 10.8, 21.0,
+  // 33.5 and 48.9 at 2K, 16K, 32K and 64K rows, plan included).
   uint32_t key[KPT];
-  // (a lane's rows outside [0, N): never counted)
 #define A3_ROW(J) (row0 + 256 * ((J) >> 2) + ((J) & 3))
-#define A3_REAL(J) (((J) >= 4 || row0 >= -(J)) && row0 < N - (256 * ((J) >> 2) + ((J) & 3)))
 #pragma unroll
   for (int q = 0; q < KPT / 4; ++q) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
     const int i = row0 + 256 * q;
+    key[4 * q] = key[4 * q + 1] = key[4 * q + 2] = key[4 * q + 3] = 0u;
     if (q < nq && i < N) {
-      if (i >= 0 && i + 4 <= N) v = *reinterpret_cast<const float4 *>(sc + i);
-      else {
-        if (i >= 0) v.x = sc[i];
-        if (i + 1 >= 0 && i + 1 < N) v.y = sc[i + 1];
-        if (i + 2 >= 0 && i + 2 < N) v.z = sc[i + 2];
-        if (i + 3 >= 0 && i + 3 < N) v.w = sc[i + 3];
+      if (i >= 0 && i + 4 <= N) {
+        const float4 v = *reinterpret_cast<const float4 *>(sc + i);
+        key[4 * q] = max(score_key(v.x), 1u); key[4 * q + 1] = max(score_key(v.y), 1u);
+        key[4 * q + 2] = max(score_key(v.z), 1u); key[4 * q + 3] = max(score_key(v.w), 1u);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (i + e >= 0 && i + e < N) key[4 * q + e] = max(score_key(sc[i + e]), 1u);
       }
     }
-    key[4 * q] = score_key(v.x); key[4 * q + 1] = score_key(v.y);
-    key[4 * q + 2] = score_key(v.z); key[4 * q + 3] = score_key(v.w);
   }
   for (int i = tid; i < kBins; i += kBlock) hist[i] = 0;
   uint32_t mn = 0xffffffffu, mx = 0u;
 #pragma unroll
   for (int j = 0; j < KPT; ++j)
-    if ((j >> 2) < nq && A3_REAL(j)) { mn = min(mn, key[j]); mx = max(mx, key[j]); }
+    if ((j >> 2) < nq) { mn = min(mn, key[j] - 1u); mx = max(mx, key[j]); }     // (0 - 1: no minimum)
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     mn = min(mn, (uint32_t)__shfl_xor((int)mn, off, 64));
@@ -247,15 +248,16 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
   for (int w = 0; w < kWaves; ++w) { mn = min(mn, wave_a[w]); mx = max(mx, wave_b[w]); }
 
   // ---- radix select inside [lo, hi]: the key of the k-th largest score ------------------
-  // Invariant: the wanted key lies in [lo, hi] and is the need-th largest of the keys in there.
-  uint32_t lo = mn, hi = mx, need = (uint32_t)k;
+  // Invariant: the wanted key lies in [lo, hi] and is the need-th largest of the keys in there.  (lo >= 1: key 0 less lo
+  // lies above hi - lo.)
+  uint32_t lo = mn + 1u, hi = mx, need = (uint32_t)k;
   while (hi != lo) {                                         // (equal: every candidate is the same key)
     const uint32_t width = hi - lo;
     const int shift = max(0, 21 - __clz((int)width));        // (width >> shift) < kBins
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
       const uint32_t rel = key[j] - lo;
-      if ((j >> 2) < nq && A3_REAL(j) && rel <= width) atomicAdd(&hist[rel >> shift], 1u);
+      if ((j >> 2) < nq && rel <= width) atomicAdd(&hist[rel >> shift], 1u);
     }
     __syncthreads();
     // the bin that holds the need-th largest candidate: suffix sums over the bins, two per thread
@@ -291,7 +293,7 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < KPT; ++j)
-        if ((j >> 2) < nq && A3_REAL(j) && key[j] - lo <= hi - lo) cand[atomicAdd(&sh_bin, 1u)] = key[j];
+        if ((j >> 2) < nq && key[j] - lo <= hi - lo) cand[atomicAdd(&sh_bin, 1u)] = key[j];
       __syncthreads();
       if (tid < (int)kRankKeys && (wave << 6) < (int)in_bin) {
         const uint32_t mine = tid < (int)in_bin ? cand[tid] : 0u;
@@ -313,8 +315,8 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
 #pragma unroll
   for (int j = 0; j < KPT; ++j)
     if ((j >> 2) < nq) {
-      n_gt += (uint32_t)__popcll(__ballot(A3_REAL(j) && key[j] > tau));
-      n_eq += (uint32_t)__popcll(__ballot(A3_REAL(j) && key[j] == tau));
+      n_gt += (uint32_t)__popcll(__ballot(key[j] > tau));
+      n_eq += (uint32_t)__popcll(__ballot(key[j] == tau));
     }
   __syncthreads();                                           // wave_a, wave_b: free
   if (lane == 0) { wave_a[wave] = n_gt; wave_b[wave] = n_eq; }
@@ -337,8 +339,8 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
       unsigned long long eq[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        take[e] = A3_REAL(4 * q + e) && key[4 * q + e] > tau;
-        eq[e] = __ballot(A3_REAL(4 * q + e) && key[4 * q + e] == tau);
+        take[e] = key[4 * q + e] > tau;
+        eq[e] = __ballot(key[4 * q + e] == tau);
       }
       if (eq[0] | eq[1] | eq[2] | eq[3]) {
         uint32_t rank = eq_before;                           // rows equal to tau before this one
@@ -365,7 +367,6 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
     }
   }
 #undef A3_ROW
-#undef A3_REAL
 }
 
 template <int KPT>
