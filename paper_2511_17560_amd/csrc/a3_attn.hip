@@ -28,7 +28,7 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kD = 128;
-constexpr int kAttnWaves = kTM / 32;   // waves per workgroup: 0-3 also stage the next K/V tile
+constexpr int kAttnWaves = kTM / 32;   // waves per workgroup, two groups of four in opposite phases
 constexpr int kAttnThreads = 64 * kAttnWaves;
 constexpr int kTileBytes = kTK * kD * 2;             // a K or V tile [key][d] in LDS, unpadded 256-byte rows
 constexpr int kStages = 4;                           // of the K ring and of the V ring
@@ -88,7 +88,7 @@ attn_bf16_kernel(attn_args a) {
   const bf16_t *__restrict__ Q = (const bf16_t *)a.q;
   const float c2 = a.scale2;
 
-  // ---- items of this workgroup: the first 32 are looked up once, into a table of the wave's own -----------------
+  // ---- items of this workgroup: the first kTableItems are looked up once, into a table of the wave's own -----------------
   auto fetch = [&](int i) {
     const int4 it = a.plan.items[i];
     const int4 ta = a.plan.tile_a[it.x];
@@ -436,7 +436,9 @@ attn_bf16_kernel(attn_args a) {
 }
 
 // Merges the partial results of tiles that were cut into key segments, in segment order.
-// One workgroup per (tile, KV head, quarter of the tile's rows); 8 lanes share a row, 16 dims each.
+// One workgroup per (tile, KV head, 32 of the tile's rows); 8 lanes share a row, dims 32 i + 4 lane .. + 3 each, so that
+// one load of theirs covers 128 bytes in one piece (16 dims in a run per lane: 12.4 instead of 11.6 us at 16K, 17.4 instead
+// of 15.8 at 64K).
 __global__ void __launch_bounds__(256)
 attn_combine_kernel(attn_args a) {
   const int t = blockIdx.x, g = blockIdx.y;
@@ -446,7 +448,7 @@ attn_combine_kernel(attn_args a) {
   if (nseg <= 1) return;
   const int4 ta = a.plan.tile_a[t];
   const int G = a.Hq / a.Hkv;
-  const int ml = blockIdx.z * 32 + (threadIdx.x >> 3), d0 = (threadIdx.x & 7) * 16;
+  const int ml = blockIdx.z * 32 + (threadIdx.x >> 3), d0 = (threadIdx.x & 7) * 4;
   const int m = ta.y + ml;
   if (m >= ta.w) return;
   const int arow = a.plan.a_lo[ta.x] + m / G, hq = g * G + m % G;
@@ -466,7 +468,7 @@ attn_combine_kernel(attn_args a) {
       const size_t s = (size_t)min(s0 + u, nseg - 1) * kTM;
       st[u] = ml_p[s];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[u][i] = *reinterpret_cast<const f32x4 *>(o_p + s * kD + 4 * i);
+      for (int i = 0; i < 4; ++i) v[u][i] = *reinterpret_cast<const f32x4 *>(o_p + s * kD + 32 * i);
     }
     float m = M;
 #pragma unroll
@@ -487,11 +489,11 @@ attn_combine_kernel(attn_args a) {
   const float inv = 1.0f / L;
   bf16_t *orow = (bf16_t *)a.out + ((size_t)arow * a.Hq + hq) * kD + d0;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    bf16x8 v;
+  for (int i = 0; i < 4; ++i) {
+    bf16x4 v;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = a3_f2bf(acc[8 * i + e] * inv);
-    *reinterpret_cast<bf16x8 *>(orow + 8 * i) = v;
+    for (int e = 0; e < 4; ++e) v[e] = a3_f2bf(acc[4 * i + e] * inv);
+    *reinterpret_cast<bf16x4 *>(orow + 32 * i) = v;
   }
 }
 
