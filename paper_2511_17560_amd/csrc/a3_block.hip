@@ -290,7 +290,7 @@ a3_status gemm_bf16_launch(const gemm_args &a0, int tile, hipStream_t st, const 
     a.n_wtiles = (a.N + feat - 1) / feat;
     a.n_tok_tiles = (a.n_rows + P::BN - 1) / P::BN;
     a.group = gemm_tile_group(a.n_wtiles, a.n_tok_tiles);
-    hipLaunchKernelGGL(kern, dim3(gemm_tile_grid(a.n_wtiles, a.n_tok_tiles, a.group), EPI == EPI_PART ? a.splits : 1), dim3(512),
+    hipLaunchKernelGGL(kern, dim3(gemm_tile_grid(a.n_wtiles, a.n_tok_tiles), EPI == EPI_PART ? a.splits : 1), dim3(512),
                        P::kLdsBytes, st, a);
     A3_CHECK_LAUNCH(who);
     return A3_OK;

@@ -8,6 +8,7 @@
 #pragma once
 
 #include "a3_internal.h"
+#include "a3_gemm_tiles.h"
 
 namespace {
 
@@ -306,29 +307,7 @@ struct gemm_pl {
   }
 };
 
-// Workgroup -> (weight tile, activation tile).  Consecutive workgroup ids go to different XCDs; an XCD owns every eighth
-// weight tile and walks them in groups of gm, a group's weight tiles fastest, so that the 32 workgroups it runs at a
-// time share about gm weight tiles and 32 / gm activation tiles through its L2.
-__device__ __forceinline__ bool gemm_tile_of(int n_wt, int n_xt, int gm, int id, int &wt, int &xt) {
-  const int xcd = id & 7, q = id >> 3, per = (n_wt + 7) >> 3;
-  const int g = q / (gm * n_xt), r = q - g * (gm * n_xt), cnt = min(gm, per - g * gm);
-  xt = r / cnt;
-  wt = xcd + 8 * (g * gm + r - xt * cnt);
-  return xt < n_xt && wt < n_wt;
-}
-inline unsigned gemm_tile_grid(int n_wt, int n_xt, int gm) {
-  const unsigned per = (unsigned)(n_wt + 7) / 8, groups = (per + gm - 1) / gm;
-  return 8u * groups * gm * (unsigned)n_xt;
-}
-
-// Weight tiles per group of gemm_tile_of: 4 when there are enough activation tiles to fill an XCD beside them.
-inline int gemm_tile_group(int n_wt, int n_xt) {
-  const int per = (n_wt + 7) / 8;
-  return per < 4 ? per : 4;
-}
-
-// ---- choice of the tile --------------------------------------------------------------------------------
-enum gemm_tile_id { GEMM_256x256, GEMM_256x192, GEMM_256x128, GEMM_128x192, GEMM_128x128, GEMM_128x64, GEMM_TILES };
+// ---- the tile as a type (which one: a3_gemm_tiles.h) -----------------------------------------------------
 template <class F>
 static inline a3_status gemm_with_tile(int tile, F f) {
   switch (tile) {
@@ -339,37 +318,6 @@ static inline a3_status gemm_with_tile(int tile, F f) {
     case GEMM_128x128: return f(gemm_pl<4, 2, 5>{});
     default: return f(gemm_pl<4, 1, 6>{});
   }
-}
-// What a tile costs, measured with weights that come from HBM, 332 .. 16448 rows x 4096 .. 28672 weight rows: time of a
-// 64-element slab while the chip is not at its power limit (one workgroup per CU), and the rate of products that the power
-// limit leaves when it is (larger tiles move fewer bytes per product).  Start and end of a workgroup: about 8 us.
-struct gemm_tile_cost { int bm, bn; double us_slab, pflops; };
-constexpr gemm_tile_cost kGemmTileCost[GEMM_TILES] = {{256, 256, 1.03, 1.38}, {256, 192, 0.84, 1.28}, {256, 128, 0.68, 1.10},
-                                                      {128, 192, 0.60, 1.00}, {128, 128, 0.50, 0.85}, {128, 64, 0.37, 0.65}};
-struct gemm_tile_choice { int tile, splits; };
-// tuning values "proj_ntw" and "gemm_tb": -1 (no choice made) or the tile they ask for
-inline int gemm_tile_of_knob(int v) {
-  constexpr int tile[] = {GEMM_256x128, GEMM_256x192, GEMM_256x256, GEMM_128x192, GEMM_128x128, GEMM_128x64};
-  return v >= 2 && v <= 7 ? tile[v - 2] : -1;
-}
-// n_w weight rows, n_x activation rows, `slabs` slabs; up to max_splits ways to split the reduction (each costs a pass over
-// the fp32 partial results at about 3 TB/s, write and read, and a launch).
-inline gemm_tile_choice gemm_choose_tile(int n_w, int n_x, int slabs, int max_splits) {
-  gemm_tile_choice best{GEMM_256x256, 1};
-  double best_us = 1e30;
-  for (int t = 0; t < GEMM_TILES; ++t)
-    for (int sp = 1; sp <= max_splits && sp * 4 <= slabs + 3; sp *= 2) {
-      const gemm_tile_cost &c = kGemmTileCost[t];
-      const long wgs = (long)((n_w + c.bm - 1) / c.bm) * ((n_x + c.bn - 1) / c.bn) * sp;
-      const int s = (slabs + sp - 1) / sp;
-      const double round_us = 8. + s * c.us_slab, power_us = 2. * c.bm * c.bn * 64. * s * 256. / (c.pflops * 1e9);
-      const double last_us = power_us * (wgs % 256) / 256.;
-      double us = (double)(wgs / 256) * (round_us > power_us ? round_us : power_us);
-      if (wgs % 256) us += round_us > last_us ? round_us : last_us;
-      if (sp > 1) us += 4. + 8. * sp * n_w * (double)n_x / 3e6;
-      if (us < best_us) { best_us = us; best.tile = t; best.splits = sp; }
-    }
-  return best;
 }
 
 }  // namespace

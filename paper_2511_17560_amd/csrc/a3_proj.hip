@@ -575,7 +575,7 @@ static a3_status proj_launch(const a3_layout *L, const void *hidden, const int *
       b.n_wtiles = P::kIB == 8 ? (heads_out + 1) / 2 : heads_out;
       b.n_tok_tiles = (n_rows + P::BN - 1) / P::BN;
       b.group = gemm_tile_group(b.n_wtiles, b.n_tok_tiles);
-      hipLaunchKernelGGL(kern, dim3(gemm_tile_grid(b.n_wtiles, b.n_tok_tiles, b.group)), dim3(512), P::kLdsBytes, st, b);
+      hipLaunchKernelGGL(kern, dim3(gemm_tile_grid(b.n_wtiles, b.n_tok_tiles)), dim3(512), P::kLdsBytes, st, b);
       A3_CHECK_LAUNCH("a3_selected_qkv_proj");
       return A3_OK;
     });

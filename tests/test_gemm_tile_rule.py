@@ -1,0 +1,45 @@
+"""Which tile a workgroup of the GEMMs takes (csrc/a3_gemm_tiles.h), compiled for the CPU: every tile exactly once, and no XCD
+(workgroup id % 8) more than one tile ahead of another - a share that is larger than an XCD's 32 CUs costs a second round."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include <vector>
+#include "a3_gemm_tiles.h"
+int main() {
+  for (int n_wt = 1; n_wt <= 150; n_wt += n_wt < 40 ? 1 : 11)
+    for (int n_xt = 1; n_xt <= 66; n_xt += n_xt < 20 ? 1 : 5) {
+      const int gm = gemm_tile_group(n_wt, n_xt), grid = (int)gemm_tile_grid(n_wt, n_xt);
+      std::vector<int> seen(n_wt * n_xt, 0);
+      int per_xcd[8] = {0};
+      for (int id = 0; id < grid; ++id) {
+        int wt = -1, xt = -1;
+        if (!gemm_tile_of(n_wt, n_xt, gm, id, wt, xt)) continue;
+        if (wt < 0 || wt >= n_wt || xt < 0 || xt >= n_xt) return std::printf("%d x %d: tile (%d, %d)\n", n_wt, n_xt, wt, xt), 1;
+        ++seen[wt * n_xt + xt];
+        ++per_xcd[id % 8];
+      }
+      for (int s : seen)
+        if (s != 1) return std::printf("%d x %d: a tile taken %d times\n", n_wt, n_xt, s), 1;
+      for (int x = 0; x < 8; ++x)
+        if (per_xcd[x] > (n_wt * n_xt + 7) / 8) return std::printf("%d x %d: XCD %d takes %d tiles\n", n_wt, n_xt, x, per_xcd[x]), 1;
+    }
+  return 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no C++ compiler")
+def test_every_tile_once_and_evenly_over_the_xcds(tmp_path):
+    src, exe = tmp_path / "tiles.cpp", tmp_path / "tiles"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2511_17560_amd", "csrc"), str(src), "-o", str(exe)],
+                   check=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout
