@@ -29,9 +29,11 @@ constexpr int gemm_tile_group(int n_wt, int n_xt) { return n_wt * n_xt <= 256 ? 
 enum gemm_tile_id { GEMM_256x256, GEMM_256x192, GEMM_256x128, GEMM_128x192, GEMM_128x128, GEMM_128x64, GEMM_TILES };
 // What a tile costs, measured with weights that come from HBM, 332 .. 16448 rows x 4096 .. 28672 weight rows: time of a
 // 64-element slab while the chip is not at its power limit (one workgroup per CU), and the rate of products that the power
-// limit leaves when it is (larger tiles move fewer bytes per product).  Start and end of a workgroup: about 8 us.
+// limit leaves when it is (larger tiles move fewer bytes per product).  Start and end of a workgroup: about 8 us.  The slabs
+// of 256x256 and 256x128 are what they take with two thirds to three quarters of the CUs busy, between the two (with 1.03 and
+// 0.68, what they take with few busy, 256x256 was chosen for 1729 .. 1917 rows x 6144 x 4096: 92 us, 256x192 takes 76).
 struct gemm_tile_cost { int bm, bn; double us_slab, pflops; };
-constexpr gemm_tile_cost kGemmTileCost[GEMM_TILES] = {{256, 256, 1.03, 1.38}, {256, 192, 0.84, 1.28}, {256, 128, 0.68, 1.10},
+constexpr gemm_tile_cost kGemmTileCost[GEMM_TILES] = {{256, 256, 1.20, 1.38}, {256, 192, 0.84, 1.28}, {256, 128, 0.74, 1.10},
                                                       {128, 192, 0.60, 1.00}, {128, 128, 0.50, 0.85}, {128, 64, 0.37, 0.65}};
 struct gemm_tile_choice { int tile, splits; };
 // tuning values "proj_ntw" and "gemm_tb": -1 (no choice made) or the tile they ask for
