@@ -249,13 +249,20 @@ typedef struct a3_block_weights {
   float eps;
 } a3_block_weights;
 
-/* Bytes of workspace a3_block_tail needs for n_rows rows (host only; 0 on a bad argument). */
+/* Bytes of workspace a3_block_tail needs for n_rows rows (host only; 0 on a bad argument).  With few rows the reductions of
+ * its two residual products are split over workgroups, and part of this is room for their partial results: it does not
+ * always grow with n_rows.  A buffer sized for more rows serves a call all the same, as does one that only holds the
+ * intermediate rows (n_rows * (hidden + ffn) elements, each of the two rounded up to 256 bytes, and 256 bytes): the results
+ * are the same bits, only slower where there is no room for the partial results.  One buffer for several row counts: the
+ * largest of their values. */
 size_t a3_block_tail_ws_bytes(const a3_layout *layout, int ffn, int n_rows);
 
 /* H(.) for the active rows.  attn_out: [n_act, n_q_heads, head_dim] as written by a3_fused_attention;
  * act_idx: device int32 [n_act], no duplicates (NULL: rows 0 .. n_act-1).  resid: [total_tokens, hidden],
  * the residual stream; its rows act_idx are read (r0) and overwritten (r2).  hidden_next:
- * [total_tokens, hidden]; its rows act_idx receive x'.  Other rows of both are left alone.
+ * [total_tokens, hidden]; its rows act_idx receive x'.  Other rows of both are left alone.  How the sums of a row are cut
+ * depends on n_act and the shape (not on the workspace): the same row may differ in its last bits between calls of
+ * different n_act, never between calls of the same.
  * bf16 needs hidden % 128 == 0 and ffn % 64 == 0.  Errors: A3_ERR_INVALID_ARG, A3_ERR_UNSUPPORTED,
  * A3_ERR_WORKSPACE before anything is launched. */
 a3_status a3_block_tail(const a3_layout *layout, const void *attn_out, const int *act_idx, int n_act,

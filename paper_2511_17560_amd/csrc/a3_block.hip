@@ -16,7 +16,8 @@
 
 namespace {
 
-enum { EPI_RESID = 0, EPI_SWIGLU = 1, EPI_PART = 2 };
+// EPI_RESID_SUM: EPI_RESID of a product whose reduction is split, the shares one after the other in one workgroup
+enum { EPI_RESID = 0, EPI_SWIGLU = 1, EPI_PART = 2, EPI_RESID_SUM = 3 };
 
 // ---------------------------------------------------------------------------------------
 // RMSNorm: one wave per row, two passes over the row (the second is served by the cache)
@@ -80,31 +81,52 @@ gemm_bf16_kernel(gemm_args a) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, lg = lane >> 4, grp = wave >> 2, wn = wave & 3;
 
-  // slabs of this workgroup's share of the reduction (EPI_PART: blockIdx.y of a.splits nearly equal ones)
+  // share y of the reduction, of a.splits nearly equal ones: its first slab and its slabs
   int s0 = 0, ns = a.K / 64;
-  if (EPI == EPI_PART) {
-    const int all = ns, b = all / a.splits, rem = all - b * a.splits, y = blockIdx.y;
+  auto share = [&](int y) {
+    const int all = a.K / 64, b = all / a.splits, rem = all - b * a.splits;
     s0 = y * b + min(y, rem);
     ns = b + (y < rem ? 1 : 0);
-  }
+  };
   f32x4 acc[IB][JB];
-  P::mainloop(
-      acc, lds, ns,
-      [&](int r0) -> const char * {
-        int q = 0, f;
-        if (EPI == EPI_SWIGLU) P::row_of(r0 % (16 * IB), q, f);
-        return reinterpret_cast<const char *>((q ? a.w1 : a.w0) + (size_t)wt * kFeat * a.K + 64 * s0);
-      },
-      [&](int r) -> uint32_t {
-        int q, f;
-        P::row_of(r % (16 * IB), q, f);
-        f += (r / (16 * IB)) * kFeatGrp + (EPI == EPI_SWIGLU ? 0 : 8 * IB * q);
-        return (uint32_t)min(f, a.N - 1 - wt * kFeat) * (uint32_t)a.K * 2u;
-      },
-      [&](int) -> const char * { return reinterpret_cast<const char *>(a.a + (size_t)xt * P::BN * a.K + 64 * s0); },
-      [&](int r) -> uint32_t {
-        return (uint32_t)min(r, a.n_rows - 1 - xt * P::BN) * (uint32_t)a.K * 2u;   // clamp: computed but never stored
-      });
+  auto product = [&]() {
+    P::mainloop(
+        acc, lds, ns,
+        [&](int r0) -> const char * {
+          int q = 0, f;
+          if (EPI == EPI_SWIGLU) P::row_of(r0 % (16 * IB), q, f);
+          return reinterpret_cast<const char *>((q ? a.w1 : a.w0) + (size_t)wt * kFeat * a.K + 64 * s0);
+        },
+        [&](int r) -> uint32_t {
+          int q, f;
+          P::row_of(r % (16 * IB), q, f);
+          f += (r / (16 * IB)) * kFeatGrp + (EPI == EPI_SWIGLU ? 0 : 8 * IB * q);
+          return (uint32_t)min(f, a.N - 1 - wt * kFeat) * (uint32_t)a.K * 2u;
+        },
+        [&](int) -> const char * { return reinterpret_cast<const char *>(a.a + (size_t)xt * P::BN * a.K + 64 * s0); },
+        [&](int r) -> uint32_t {
+          return (uint32_t)min(r, a.n_rows - 1 - xt * P::BN) * (uint32_t)a.K * 2u;   // clamp: computed but never stored
+        });
+  };
+  if constexpr (EPI == EPI_RESID_SUM) {
+    f32x4 sum[IB][JB] = {};
+    for (int y = 0; y < a.splits; ++y) {                         // the sums sum_norm_kernel forms, in its order
+      share(y);
+      product();
+#pragma unroll
+      for (int i = 0; i < IB; ++i)
+#pragma unroll
+        for (int j = 0; j < JB; ++j) sum[i][j] += acc[i][j];
+      __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+#pragma unroll
+      for (int j = 0; j < JB; ++j) acc[i][j] = sum[i][j];
+  } else {
+    if constexpr (EPI == EPI_PART) share(blockIdx.y);
+    product();
+  }
 
   // ---- epilogue: a lane holds L consecutive features of half 0 and of half 1 of one row; four lanes cover 64 or 128
   // consecutive bytes of a bf16 row
@@ -115,7 +137,7 @@ gemm_bf16_kernel(gemm_args a) {
   for (int j = 0; j < JB; ++j) {
     const int tok = xt * P::BN + 16 * (JB * wn + j) + l16;
     float lo[L], hi[L];
-    if constexpr (EPI == EPI_RESID) {
+    if constexpr (EPI == EPI_RESID || EPI == EPI_RESID_SUM) {
       const int row = tok < a.n_rows ? (a.out_idx ? a.out_idx[tok] : tok) : -1;
       bf16_t *p = a.out + (size_t)max(row, 0) * a.N + feat + L * lg;
       bf16x8 rl[L / 8], rh[L / 8];
@@ -168,6 +190,7 @@ gemm_bf16_kernel(gemm_args a) {
 
 // Rows of a product whose reduction was split: residual row += the partial rows in share order (one rounding), then the
 // RMSNorm of the new row.  One workgroup per row; the row stays in registers between the two (up to 8 vectors a thread).
+// splits = 0: the residual row has its product already.
 constexpr int kSumNormThreads = 256, kSumNormVecs = 8;
 __global__ void __launch_bounds__(kSumNormThreads)
 sum_norm_kernel(const float *__restrict__ part, int splits, int n_rows, bf16_t *resid, const int *__restrict__ idx,
@@ -193,11 +216,11 @@ sum_norm_kernel(const float *__restrict__ part, int splits, int n_rows, bf16_t *
     bf16x8 y;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      y[e] = a3_f2bf(a3_bf2f(r[e]) + t[e]);
+      y[e] = splits > 0 ? a3_f2bf(a3_bf2f(r[e]) + t[e]) : r[e];
       x[v][e] = a3_bf2f(y[e]);
       ss = fmaf(x[v][e], x[v][e], ss);
     }
-    *reinterpret_cast<bf16x8 *>(rr + c) = y;
+    if (splits > 0) *reinterpret_cast<bf16x8 *>(rr + c) = y;
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
@@ -277,24 +300,25 @@ gemm_f32_kernel(gemm_args_f32 a) {
   }
 }
 
+template <class P, int EPI>
+a3_status gemm_bf16_launch_in(gemm_args a, hipStream_t st, const char *who) {
+  auto kern = gemm_bf16_kernel<P, EPI>;
+  static a3_once_per_device lds_once;
+  if (a3_once(lds_once, [&]() { return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P::kLdsBytes); }) != hipSuccess)
+    return a3_fail(A3_ERR_HIP, "%s: cannot raise the dynamic LDS limit", who);
+  const int feat = EPI == EPI_SWIGLU ? P::BM / 2 : P::BM;
+  a.n_wtiles = (a.N + feat - 1) / feat;
+  a.n_tok_tiles = (a.n_rows + P::BN - 1) / P::BN;
+  a.group = gemm_tile_group(a.n_wtiles, a.n_tok_tiles);
+  hipLaunchKernelGGL(kern, dim3(gemm_tile_grid(a.n_wtiles, a.n_tok_tiles), EPI == EPI_PART ? a.splits : 1), dim3(512),
+                     P::kLdsBytes, st, a);
+  A3_CHECK_LAUNCH(who);
+  return A3_OK;
+}
+
 template <int EPI>
-a3_status gemm_bf16_launch(const gemm_args &a0, int tile, hipStream_t st, const char *who) {
-  return gemm_with_tile(tile, [&](auto t) -> a3_status {
-    using P = decltype(t);
-    auto kern = gemm_bf16_kernel<P, EPI>;
-    static a3_once_per_device lds_once;
-    if (a3_once(lds_once, [&]() { return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P::kLdsBytes); }) != hipSuccess)
-      return a3_fail(A3_ERR_HIP, "%s: cannot raise the dynamic LDS limit", who);
-    gemm_args a = a0;
-    const int feat = EPI == EPI_SWIGLU ? P::BM / 2 : P::BM;
-    a.n_wtiles = (a.N + feat - 1) / feat;
-    a.n_tok_tiles = (a.n_rows + P::BN - 1) / P::BN;
-    a.group = gemm_tile_group(a.n_wtiles, a.n_tok_tiles);
-    hipLaunchKernelGGL(kern, dim3(gemm_tile_grid(a.n_wtiles, a.n_tok_tiles), EPI == EPI_PART ? a.splits : 1), dim3(512),
-                       P::kLdsBytes, st, a);
-    A3_CHECK_LAUNCH(who);
-    return A3_OK;
-  });
+a3_status gemm_bf16_launch(const gemm_args &a, int tile, hipStream_t st, const char *who) {
+  return gemm_with_tile(tile, [&](auto t) -> a3_status { return gemm_bf16_launch_in<decltype(t), EPI>(a, st, who); });
 }
 
 int tile_of_knob(int tile) {
@@ -302,8 +326,10 @@ int tile_of_knob(int tile) {
   return t >= 0 ? t : tile;
 }
 
-constexpr int kMaxSplits = 8;
-// fp32 partial results of a residual GEMM of H(.) when its reduction is split (0: it is not)
+// Tile and split of a residual GEMM of H(.): by its shape alone, so that a row's sums do not depend on the workspace.
+constexpr int kMaxSplits = 8, kSumNormMaxHidden = 8 * kSumNormThreads * kSumNormVecs;
+gemm_tile_choice residual_tile(int h, int n_rows, int K) { return gemm_choose_tile(h, n_rows, K / 64, h <= kSumNormMaxHidden ? kMaxSplits : 1); }
+// fp32 partial results of a residual GEMM whose reduction is split (0: it is not)
 size_t split_bytes(const gemm_tile_choice &c, int n_rows, int h) {
   return c.splits > 1 ? (size_t)c.splits * n_rows * h * sizeof(float) : 0;
 }
@@ -344,8 +370,8 @@ extern "C" size_t a3_block_tail_ws_bytes(const a3_layout *L, int ffn, int n_rows
   if (L->dtype != A3_BF16 && L->dtype != A3_F32) return 0;
   size_t part = 0;
   if (L->dtype == A3_BF16 && n_rows > 0) {
-    const size_t p0 = split_bytes(gemm_choose_tile(L->hidden, n_rows, L->n_q_heads * L->head_dim / 64, kMaxSplits), n_rows, L->hidden);
-    const size_t p1 = split_bytes(gemm_choose_tile(L->hidden, n_rows, ffn / 64, kMaxSplits), n_rows, L->hidden);
+    const size_t p0 = split_bytes(residual_tile(L->hidden, n_rows, L->n_q_heads * L->head_dim), n_rows, L->hidden);
+    const size_t p1 = split_bytes(residual_tile(L->hidden, n_rows, ffn), n_rows, L->hidden);
     part = p0 > p1 ? p0 : p1;
   }
   return tail_base_bytes(L, ffn, n_rows) + a3_align_up(part, 256);
@@ -400,22 +426,28 @@ extern "C" a3_status a3_block_tail(const a3_layout *L, const void *attn_out, con
   if (L->dtype == A3_BF16) {
     // A residual GEMM and the norm behind it: in one pass over the reduction and a norm kernel, or - where too few tiles
     // would be left to fill the chip - with the reduction split over workgroups and a kernel that sums, adds and norms.
+    // A workspace without room for the partial results gets the same sums from workgroups that form all shares (slower:
+    // nothing fills the chip then).
     auto resid_norm = [&](const bf16_t *x, const void *weight, int K, const void *g, bf16_t *out, const int *out_idx) -> a3_status {
       gemm_args a{x, n_act, (const bf16_t *)weight, nullptr, (bf16_t *)resid, act_idx, K, h, nullptr, 1, 0, 0, 0};
-      gemm_tile_choice c = gemm_choose_tile(h, n_act, K / 64, h <= 8 * kSumNormThreads * kSumNormVecs ? kMaxSplits : 1);
-      const size_t room = ws_bytes > need ? ws_bytes - need : 0;   // a caller's smaller workspace: one pass
-      if (a3_knob(A3_KNOB_GEMM_TB) >= 0 || split_bytes(c, n_act, h) > room) c = gemm_choose_tile(h, n_act, K / 64, 1);
-      c.tile = tile_of_knob(c.tile);
+      gemm_tile_choice c = residual_tile(h, n_act, K);
+      if (a3_knob(A3_KNOB_GEMM_TB) >= 0) c = {tile_of_knob(c.tile), 1};
       a3_status e;
       if (c.splits == 1) {
         if ((e = gemm_bf16_launch<EPI_RESID>(a, c.tile, st, "a3_block_tail")) != A3_OK) return e;
         return rms_norm_launch(L, resid, act_idx, g, w->eps, out, out_idx, n_act, st, "a3_block_tail");
       }
-      a.part = (float *)((char *)ws + a3_align_up(cur.off, 256));
       a.splits = c.splits;
-      if ((e = gemm_bf16_launch<EPI_PART>(a, c.tile, st, "a3_block_tail")) != A3_OK) return e;
-      hipLaunchKernelGGL(sum_norm_kernel, dim3(n_act), dim3(kSumNormThreads), 0, st, a.part, c.splits, n_act, (bf16_t *)resid, act_idx,
-                         (const bf16_t *)g, w->eps, out, out_idx, h);
+      const bool room = ws_bytes - need >= split_bytes(c, n_act, h);
+      if (room) {
+        a.part = (float *)((char *)ws + a3_align_up(cur.off, 256));
+        e = gemm_bf16_launch<EPI_PART>(a, c.tile, st, "a3_block_tail");
+      } else {
+        e = gemm_bf16_launch_in<gemm_pl<4, 1, 6>, EPI_RESID_SUM>(a, st, "a3_block_tail");
+      }
+      if (e != A3_OK) return e;
+      hipLaunchKernelGGL(sum_norm_kernel, dim3(n_act), dim3(kSumNormThreads), 0, st, a.part, room ? c.splits : 0, n_act, (bf16_t *)resid,
+                         act_idx, (const bf16_t *)g, w->eps, out, out_idx, h);
       A3_CHECK_LAUNCH("a3_block_tail");
       return A3_OK;
     };

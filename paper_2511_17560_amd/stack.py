@@ -41,7 +41,8 @@ def fuse_stack(layout: api.Layout, shape, layers: Sequence[Dict[str, torch.Tenso
     eps = float(shape.rms_eps)
     ffn = int(layers[0]["w_gate"].shape[0])
     ws_attn = layout.workspace(T)
-    ws_tail = torch.empty(max(api.a3_block_tail_ws_bytes(layout, ffn, T), 256), dtype=torch.uint8, device=dev)
+    # (few rows can need more than many: their reductions are split, and the partial results want room)
+    ws_tail = torch.empty(max(*(api.a3_block_tail_ws_bytes(layout, ffn, n) for n in (T, n_act)), 256), dtype=torch.uint8, device=dev)
     x = torch.empty((T, h), dtype=dt, device=dev)
     kept = []
 

@@ -57,10 +57,13 @@ def test_projection_in_every_tile(tile, n, hidden, hq, hkv, tuning):
 
 
 @pytest.mark.parametrize("tile", [None, 2, 3, 4, 5, 6, 7])
-@pytest.mark.parametrize("n,hidden,ffn,heads", [(1, 128, 64, 1), (65, 128, 832, 2), (129, 256, 4160, 3), (257, 384, 1024, 5)])
+@pytest.mark.parametrize("n,hidden,ffn,heads", [(1, 128, 64, 1), (65, 128, 832, 2), (129, 256, 4160, 3), (257, 384, 1024, 5),
+                                                (1, 1024, 4096, 16), (66, 256, 4160, 16), (33, 384, 1984, 15)])
 def test_block_tail_in_every_tile_and_split(tile, n, hidden, ffn, heads, tuning):
-    """With no tile asked for the few tiles of these sizes have their long reductions split (also into unequal shares) when the
-    workspace has room for the partial results, and not when it is only as large as the intermediate rows; both agree."""
+    """With no tile asked for, the reductions of 1920 elements and more are split eight ways here: both residual products' in the
+    last three shapes, the second's in 129 x 256 x 4160 (65 slabs and 30: also into unequal shares); where the workspace only
+    holds the intermediate rows, one workgroup forms all shares.  The result is the same bits in any workspace that is accepted.
+    With a tile asked for nothing is split."""
     if tile is not None:
         tuning("gemm_tb", tile)
     T, eps = 300, 1e-5
@@ -79,11 +82,16 @@ def test_block_tail_in_every_tile_and_split(tile, n, hidden, ffn, heads, tuning)
     want = norm(r2, g2)
     dev = [t.cuda() for t in (wo, g1, wg, wu, wd, g2)]
     small = ((n * hidden * 2 + 255) // 256 + (n * ffn * 2 + 255) // 256) * 256 + 256
-    for size in (api.a3_block_tail_ws_bytes(lay, ffn, n), small):
+    need = api.a3_block_tail_ws_bytes(lay, ffn, n)
+    assert (need > small) == (max(ffn, heads * 128) >= 1920)
+    results = []
+    for size in (need, small, (need + small) // 2, need + (1 << 20)):
         resid, nxt = r0.cuda(), torch.full((T, hidden), 5.0, dtype=torch.bfloat16, device="cuda")
         ws = torch.empty(size, dtype=torch.uint8, device="cuda")
         api.a3_block_tail(lay, o.cuda(), idev(rows), n, *dev, eps, resid, nxt, ws)
         got_r, got_n = resid.double().cpu(), nxt.double().cpu()
+        results.append((got_r, got_n))
+        assert torch.equal(got_r, results[0][0]) and torch.equal(got_n, results[0][1])
         assert float((got_r[at] - r2).abs().max() / r2.abs().max()) <= 2e-2
         assert float((got_n[at] - want).abs().max() / want.abs().max()) <= 2e-2
         rest = np.setdiff1d(np.arange(T), rows.numpy())
