@@ -21,6 +21,8 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "a3_internal.h"
 #include "a3_attn_plan.h"
 
@@ -535,57 +537,86 @@ attn_f32_kernel(attn_args a) {
     const bool mine = req == r && l16 < (a_end - a0) * G;
     const int limit = mine ? t - base : -1;                    // last visible key (request-relative)
     const int n_keys = a.act_idx[b1 - 1] - base + 1;
+    // The product O^T += V^T P^T gives every pair every key of a block, with weight 0 where it sees none: no harm unless V is
+    // infinite or NaN there.  That shows in O, and the wave starts over with each pair adding the keys it sees one by one.
     f32x4 o[D / 16];
+    float ref, sum;
+    auto attend = [&](auto one_by_one) {
 #pragma unroll
-    for (int e = 0; e < D / 16; ++e) o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float ref = -INFINITY, sum = 0.f;
-    f32x4 kf[D / 16];
-    auto load_k = [&](int k0) {
-      const f32x4 *kp = reinterpret_cast<const f32x4 *>(K + ((size_t)(base + min(k0 + l16, n_keys - 1)) * a.Hkv + g) * D) + lg;
+      for (int e = 0; e < D / 16; ++e) o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+      ref = -INFINITY;
+      sum = 0.f;
+      f32x4 kf[D / 16];
+      auto load_k = [&](int k0) {
+        const f32x4 *kp = reinterpret_cast<const f32x4 *>(K + ((size_t)(base + min(k0 + l16, n_keys - 1)) * a.Hkv + g) * D) + lg;
 #pragma unroll
-      for (int c = 0; c < D / 16; ++c) kf[c] = kp[4 * c];
-    };
-    if (16 * wave < n_keys) load_k(16 * wave);
-    for (int k0 = 16 * wave; k0 < n_keys; k0 += 16 * kF32Waves) {
-      f32x4 vf[4][D / 64];
+        for (int c = 0; c < D / 16; ++c) kf[c] = kp[4 * c];
+      };
+      if (16 * wave < n_keys) load_k(16 * wave);
+      for (int k0 = 16 * wave; k0 < n_keys; k0 += 16 * kF32Waves) {
+        f32x4 vf[4][D / 64];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const f32x4 *vp = reinterpret_cast<const f32x4 *>(V + ((size_t)(base + min(k0 + 4 * lg + e, n_keys - 1)) * a.Hkv + g) * D) + l16;
+        for (int e = 0; e < 4; ++e) {
+          const f32x4 *vp = reinterpret_cast<const f32x4 *>(V + ((size_t)(base + min(k0 + 4 * lg + e, n_keys - 1)) * a.Hkv + g) * D) + l16;
 #pragma unroll
-        for (int h = 0; h < D / 64; ++h) vf[e][h] = vp[16 * h];
+          for (int h = 0; h < D / 64; ++h) vf[e][h] = vp[16 * h];
+        }
+        f32x4 c4[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c4[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) c4[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][e], qf[c][e], c4[e], 0, 0, 0);
+        if (k0 + 16 * kF32Waves < n_keys) load_k(k0 + 16 * kF32Waves);
+        f32x4 p;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          p[e] = k0 + 4 * lg + e <= limit ? ((c4[0][e] + c4[1][e]) + (c4[2][e] + c4[3][e])) * a.scale2 : -INFINITY;
+        float mx = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float new_ref = fmaxf(ref, mx), use = new_ref == -INFINITY ? 0.f : new_ref;
+        const float alpha = exp2f(ref - use);                    // ref = -inf: 0
+        ref = new_ref;
+        sum *= alpha;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { p[e] = exp2f(p[e] - use); sum += p[e]; }
+#pragma unroll
+        for (int e = 0; e < D / 16; ++e)
+#pragma unroll
+          for (int x = 0; x < 4; ++x) o[e][x] *= alpha;
+        if constexpr (one_by_one) {
+#pragma unroll 1
+          for (int u = 0; u < 16; ++u) {
+            const float pe = (u & 2) ? ((u & 1) ? p[3] : p[2]) : ((u & 1) ? p[1] : p[0]);
+            const float pu = __shfl(pe, 16 * (u >> 2) + l16, 64);
+            if (k0 + u > limit) continue;
+            const float *vp = V + ((size_t)(base + k0 + u) * a.Hkv + g) * D + 16 * lg;
+#pragma unroll
+            for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+              for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int y = 0; y < 4; ++y) o[4 * h + x][y] = fmaf(pu, vp[64 * h + 4 * y + x], o[4 * h + x][y]);
+          }
+          continue;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) o[4 * h + x] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e][h][x], p[e], o[4 * h + x], 0, 0, 0);
       }
-      f32x4 c4[4];
+    };
+    attend(std::false_type{});
+    float z = 0.f;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) c4[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < D / 16; ++e)
 #pragma unroll
-      for (int c = 0; c < D / 16; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c4[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][e], qf[c][e], c4[e], 0, 0, 0);
-      if (k0 + 16 * kF32Waves < n_keys) load_k(k0 + 16 * kF32Waves);
-      f32x4 p;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        p[e] = k0 + 4 * lg + e <= limit ? ((c4[0][e] + c4[1][e]) + (c4[2][e] + c4[3][e])) * a.scale2 : -INFINITY;
-      float mx = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float new_ref = fmaxf(ref, mx), use = new_ref == -INFINITY ? 0.f : new_ref;
-      const float alpha = exp2f(ref - use);                    // ref = -inf: 0
-      ref = new_ref;
-      sum *= alpha;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { p[e] = exp2f(p[e] - use); sum += p[e]; }
-#pragma unroll
-      for (int e = 0; e < D / 16; ++e)
-#pragma unroll
-        for (int x = 0; x < 4; ++x) o[e][x] *= alpha;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int h = 0; h < D / 64; ++h)
-#pragma unroll
-          for (int x = 0; x < 4; ++x) o[4 * h + x] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e][h][x], p[e], o[4 * h + x], 0, 0, 0);
-    }
+      for (int y = 0; y < 4; ++y) z = fmaf(o[e][y], 0.f, z);
+    if (__any(z != 0.f)) attend(std::true_type{});
     sum += __shfl_xor(sum, 16, 64);
     sum += __shfl_xor(sum, 32, 64);
     __syncthreads();                                           // the merge of the request before has been read

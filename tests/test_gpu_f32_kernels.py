@@ -53,3 +53,37 @@ def test_f32_steps(hq, hkv, d, hidden, chunks, q_lens, half):
     out = torch.zeros((n, hq, d), device="cuda")
     api.a3_fused_attention(lay, dev(res["q_act"]), idev(act), n, dev(res["k_fused"]), dev(res["v_fused"]), out, ws)
     assert max_abs_rel(to_host(out), res["out"]) <= 1e-5
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(1, 1, 64), (4, 2, 128), (7, 1, 64), (16, 1, 128)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_f32_attention_keeps_rows_it_may_not_see_out(hq, hkv, d, bad):
+    """K and V rows that hold no finite value reach the rows that see them and no other: the rows of a 16-row tile share the
+    products, in the block of 16 keys their limit lies in, in later blocks and in blocks of other waves."""
+    n_ctx, lens = 300, 20
+    shape = synth.ModelShape("f32", "f32", 32, hq, hkv, d, 10000.0)
+    w = synth.custom(shape, [[n_ctx], [40]], [lens, 3])
+    lay = api.Layout.from_workload(w)
+    rng = np.random.default_rng(hq + d)
+    k, v = (rng.standard_normal((w.total_tokens, hkv, d)).astype(np.float32) for _ in range(2))
+    second = int(w.seg_start[1])
+    act = np.array([0, 3, 15, 16, 40, 41, 43, 150, 299, 300, 305, 319, second, second + 7, second + 42], np.int32)
+    hidden = np.array([42, 160, 303, second + 8])
+    q = rng.standard_normal((len(act), hq, d)).astype(np.float32)
+    kb, vb = k.copy(), v.copy()
+    kb[hidden], vb[hidden] = bad, bad
+    out = torch.zeros((len(act), hq, d), device="cuda")
+    api.a3_fused_attention(lay, torch.from_numpy(q).cuda(), idev(act), len(act), torch.from_numpy(kb).cuda(), torch.from_numpy(vb).cuda(),
+                           out, lay.workspace(len(act)))
+    got = out.double().cpu().numpy()
+    for i, t in enumerate(act):
+        s = 0 if t < second else second
+        if ((hidden >= s) & (hidden <= t)).any():
+            assert not np.isfinite(got[i]).any()
+            continue
+        for h in range(hq):
+            g = h // (hq // hkv)
+            l = k[s:t + 1, g].astype(np.float64) @ q[i, h].astype(np.float64) / np.sqrt(d)
+            p = np.exp(l - l.max())
+            want = p @ v[s:t + 1, g].astype(np.float64) / p.sum()
+            assert np.abs(got[i, h] - want).max() <= 1e-5 * np.abs(v).max()
