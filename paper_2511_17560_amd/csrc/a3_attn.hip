@@ -191,7 +191,12 @@ attn_bf16_kernel(attn_args a) {
   f32x4 o[8][2], st[4][2];
   uint32_t pu[2][2][4];                                      // P of the tile before, pairs of bf16, [32 keys][row block]
   float ref[2], mx[2], nref[2] = {0.f, 0.f};                  // exponent reference and tile maximum in raw logit units; -ref c2
-  f32x4 osum[2];                                             // row sums of P, by the matrix pipe (an all-ones V): every register
+  // Row sums of P, by the matrix pipe (an all-ones V): every register.  They are fp32 sums of the weights as the product with V
+  // uses them, rounded to bf16: an output is then an exact mean of the values it sees, and the weights' roundings cancel where
+  // values are alike.  Relative error against float64, unrounded weights summed -> these: 8 matching rows of 100 2.04e-3
+  // -> 1.99e-3 at 500 keys, 2.11e-3 -> 2.02e-3 at 2048; plain normal logits 2.20e-3 -> 2.18e-3 and 2.24e-3 -> 2.23e-3; flat logits, one
+  // key with all the weight, and 16K keys and more: the same within 1 %.
+  f32x4 osum[2];
   bf16x8 ones;
 #pragma unroll
   for (int e = 0; e < 8; ++e) ones[e] = (bf16_t)1.0f;
