@@ -41,6 +41,56 @@ def _check(w, act, q, k, v, out, pick):
             assert bool(((got[i, h] - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -8 * vmax).all()), (i, t, h)
 
 
+def test_more_items_than_the_table_holds(tuning):
+    """One workgroup per KV head and 21 and 24 row tiles: a workgroup looks its first 16 items up at its start and every later
+    one in the middle of its stream of loads."""
+    for chunks, q_lens, ratio in (([[1400, 1170]], [33], (50, 100)), ([[600], [37, 500], [9]], [200, 70, 31], (100, 100))):
+        w, act, q, k, v = _inputs(8, 2, chunks, q_lens, ratio, 11)
+        assert len(act) * 4 > 20 * 256
+        lay = api.Layout.from_workload(w)
+        dq, dk, dv, ws = q.cuda(), k.cuda(), v.cuda(), lay.workspace(len(act))
+        outs = []
+        for wgs in (-1, 1):
+            tuning("attn_wgs", wgs)
+            out = torch.zeros_like(dq)
+            api.a3_fused_attention(lay, dq, idev(act), len(act), dk, dv, out, lay.workspace(len(act)))
+            _check(w, act, q, k, v, out, list(range(0, len(act), 29)) + [len(act) - 1])
+            outs.append(out.double().cpu())
+        # with one share nothing is cut and merged: apart only by the rounding of the weights and of the output
+        assert float((outs[0] - outs[1]).abs().max()) <= 2.0 ** -7 * float(v.double().abs().max())
+
+
+def test_plan_too_large_for_lds_many_requests():
+    """The plan's small arrays are looked up in the workspace when they do not fit 4096 integers of LDS: 1100 requests."""
+    rng = np.random.default_rng(3)
+    lens = [[int(n)] for n in rng.integers(1, 9, 1100)]
+    w, act, q, k, v = _inputs(4, 2, lens, rng.integers(1, 4, 1100).tolist(), (50, 100), 12)
+    assert 2 * (w.n_req + 1) + 2 * w.n_req > 4096
+    lay = api.Layout.from_workload(w)
+    out = torch.zeros((len(act), 4, 128), dtype=torch.bfloat16, device="cuda")
+    api.a3_fused_attention(lay, q.cuda(), idev(act), len(act), k.cuda(), v.cuda(), out, lay.workspace(len(act)))
+    _check(w, act, q, k, v, out, range(0, len(act), 3))
+
+
+def test_plan_too_large_for_lds_long_request():
+    """... and all 33008 rows of one request at 16 heads per KV head, by the plan kernel and by the selecting kernel."""
+    w, act, q, k, v = _inputs(16, 1, [[33000]], [8], (100, 100), 13)
+    n = len(act)
+    assert n == w.total_tokens and 2 * (n * 16 // 256) > 4096
+    lay = api.Layout.from_workload(w)
+    dq, dk, dv = q.cuda(), k.cuda(), v.cuda()
+    one, two = torch.zeros_like(dq), torch.zeros_like(dq)
+    ws = lay.workspace(n)
+    api.a3_fused_attention(lay, dq, idev(act), n, dk, dv, one, ws)
+    _check(w, act, q, k, v, one, [0, 1, 15, 16, 17, 63, 64, 5000, 20001, n - 9, n - 1])
+    ws.fill_(0xAB)
+    scores = torch.rand(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    rows = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    api.a3_topk_select_plan(lay, scores, idev(w.sel_start), w.total_k, rows, n, rows, ws)
+    api.a3_fused_attention_planned(lay, dq, rows, n, dk, dv, two, ws)
+    assert np.array_equal(rows.cpu().numpy(), act) and torch.equal(one, two)
+
+
 @pytest.mark.parametrize("wgs", [-1, 1, 40])
 def test_weights_sum_to_one(wgs, tuning):
     """Numerator and denominator carry the same weights, each rounded to bf16 once and summed in fp32: where every value is 1

@@ -175,3 +175,22 @@ def test_select_chunk_edges(name, n_head, n_tail):
     api.a3_select_chunk_edges(lay, n_head, n_tail, idev(start), total, out)
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy()[:total], want_idx)
+
+
+def test_evict_select_longer_than_the_registers():
+    """A context of more rows than the ranking kernel holds in registers (the scores are re-read in every pass), beside a short
+    one: system prompt, ranked rows and question of every KV head; votes with ties, and the paper's pooling."""
+    w = synth.custom(synth.ModelShape("long", "bf16", 64, 4, 2, 128, 1e4), [[40000, 30005], [700]], [6, 3])
+    lay = api.Layout.from_workload(w)
+    rng = np.random.default_rng(8)
+    votes = (rng.integers(0, 3000, (2, w.total_tokens)) / 1024.0).astype(np.float32)
+    sys_len = np.array([37, 5], np.int32)
+    for width in (1, 7):
+        want, keep_start = ev.evict_select(ev.pool_votes(votes, w.seg_start, w.ctx_len, width, "max"), w.seg_start, w.ctx_len, w.q_lens,
+                                           sys_len, 1024)
+        total = int(keep_start[-1])
+        keep = torch.full((2, total), -7, dtype=torch.int32, device="cuda")
+        ws = torch.empty(api.a3_evict_ws_bytes(lay), dtype=torch.uint8, device="cuda")
+        api.a3_evict_select(lay, torch.from_numpy(votes).cuda(), idev(sys_len), idev(keep_start), total, keep, pool_width=width,
+                            pool_mode=api.A3_POOL_MAX, ws=ws)
+        assert np.array_equal(keep.cpu().numpy(), want)
