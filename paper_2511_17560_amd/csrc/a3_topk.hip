@@ -328,24 +328,28 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
     eq_before += w < wave ? wave_b[w] : 0u;
   }
   if (n_gt + (eq_before < need ? n_eq : 0u) == 0) return;    // nothing of this wave's block is taken (no barrier follows)
-  // rows equal to tau are taken in index order until `need` of them are: min(eq_before, need) of
-  // the earlier ones were taken
+  // rows equal to tau are taken in index order until `need` of them are: min(eq_before, need) of the earlier ones were taken, and
+  // of this wave's all, none, or (in one wave at most) the first few
+  const bool some = eq_before < need && eq_before + n_eq > need;
+  const uint32_t above = !some && eq_before < need ? tau - 1u : tau;      // (tau >= 1)
   uint32_t pos = gt_before + min(eq_before, need);
-  const unsigned long long below = (1ull << lane) - 1ull;
+  // lanes below this one in a ballot, added to n
+  auto lanes_below = [](unsigned long long m, uint32_t n) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, n));
+  };
 #pragma unroll
   for (int q = 0; q < KPT / 4; ++q) {
     if (q < nq) {
       bool take[4];
-      unsigned long long eq[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        take[e] = key[4 * q + e] > tau;
-        eq[e] = __ballot(key[4 * q + e] == tau);
-      }
-      if (eq[0] | eq[1] | eq[2] | eq[3]) {
+      for (int e = 0; e < 4; ++e) take[e] = key[4 * q + e] > above;
+      if (some) {
+        unsigned long long eq[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) eq[e] = __ballot(key[4 * q + e] == tau);
         uint32_t rank = eq_before;                           // rows equal to tau before this one
 #pragma unroll
-        for (int e = 0; e < 4; ++e) rank += (uint32_t)__popcll(eq[e] & below);
+        for (int e = 0; e < 4; ++e) rank = lanes_below(eq[e], rank);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const bool is = (eq[e] >> lane) & 1;
@@ -358,7 +362,7 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const unsigned long long b = __ballot(take[e]);
-        at += (uint32_t)__popcll(b & below);
+        at = lanes_below(b, at);
         pos += (uint32_t)__popcll(b);
       }
 #pragma unroll
