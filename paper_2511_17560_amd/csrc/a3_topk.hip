@@ -248,6 +248,8 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
   for (int w = 0; w < kWaves; ++w) { mn = min(mn, wave_a[w]); mx = max(mx, wave_b[w]); }
 
   // ---- radix select inside [lo, hi]: the key of the k-th largest score ------------------
+  // Bins a multiple of 32 apart would share an LDS bank, and scores of few values fall into just such bins.
+  auto slot_of = [](uint32_t bin) { return bin ^ ((bin >> 5) & 31u); };
   // Invariant: the wanted key lies in [lo, hi] and is the need-th largest of the keys in there.  (lo >= 1: key 0 less lo
   // lies above hi - lo.)
   uint32_t lo = mn + 1u, hi = mx, need = (uint32_t)k;
@@ -257,11 +259,12 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
       const uint32_t rel = key[j] - lo;
-      if ((j >> 2) < nq && rel <= width) atomicAdd(&hist[rel >> shift], 1u);
+      if ((j >> 2) < nq && rel <= width) atomicAdd(&hist[slot_of(rel >> shift)], 1u);
     }
     __syncthreads();
     // the bin that holds the need-th largest candidate: suffix sums over the bins, two per thread
-    const uint2 c = *reinterpret_cast<const uint2 *>(hist + 2 * tid);
+    const uint2 cs = *reinterpret_cast<const uint2 *>(hist + (slot_of(2 * tid) & ~1u));
+    const uint2 c = slot_of(2 * tid) & 1 ? make_uint2(cs.y, cs.x) : cs;
     uint32_t suf = c.x + c.y;                                // sum over the lanes >= this one
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -282,7 +285,7 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
     hi = lo + min(hi - lo, (1u << shift) - 1u);
     need = sh_need;
     const uint32_t in_bin = sh_in;                           // candidates left, need of them wanted
-    if (shift == 0) break;                                   // the bin was a single key
+    if (lo == hi) break;                                     // the bin was a single key
     if (in_bin <= kRankKeys) {
       // Few candidates left (the usual case after one or two rounds): they are gathered (in any order: what follows
       // does not depend on it) and ranked directly.  The key v with fewer than `need` candidates above it and at least
