@@ -184,6 +184,7 @@ a3_status a3_kv_scatter(const a3_layout *layout, const void *k_new, const void *
  * t = act_idx[i]:  out[i, hq] = softmax(q_act[i, hq] . K'[u, hq/G] * sm_scale) V[u, hq/G] over the
  * packed rows u of the same request with u <= t (causal by global position, the row itself included).
  * q_act, out: [n_act, n_q_heads, head_dim]; act_idx: device int32 [n_act], strictly ascending.
+ * A3_BF16: K and V of one request below 4 GiB each (A3_ERR_UNSUPPORTED otherwise).
  * ws: at least a3_workspace_bytes(layout, n_act) bytes. */
 a3_status a3_fused_attention(const a3_layout *layout, const void *q_act, const int *act_idx, int n_act,
                              const void *k_fused, const void *v_fused, void *out,

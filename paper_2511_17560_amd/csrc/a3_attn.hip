@@ -696,9 +696,10 @@ static a3_status attn_launch(const a3_layout *L, const void *q_act, const int *a
   a.scale2 = a3_scale_of(L) * kLog2e;
   memset(&a.plan, 0, sizeof(a.plan));
   if (L->dtype == A3_BF16) {
-    // the kernel addresses a request's K/V rows with 32-bit byte offsets
+    // (a limit of an earlier kernel's 32-bit byte offsets; this one's bases are 64-bit per tile.  The line stays: what lies
+    // beyond it was always refused and has never been run)
     A3_REQUIRE(((long long)L->max_ctx_len + L->max_q_len + 128) * L->n_kv_heads * kD * 2 < (1LL << 32), A3_ERR_UNSUPPORTED,
-               "a3_fused_attention: a request of %d rows is too long for 32-bit cache offsets",
+               "a3_fused_attention: a request of %d rows is too long (its K and V rows must stay below 4 GiB each)",
                L->max_ctx_len + L->max_q_len);
     A3_REQUIRE(ws != nullptr, A3_ERR_WORKSPACE, "a3_fused_attention: workspace is NULL");
     A3_REQUIRE(ws_bytes >= a3_attn_ws_bytes(L, n_act), A3_ERR_WORKSPACE,

@@ -18,7 +18,7 @@ constexpr int kPlanLdsInts = 4096;  // LDS the plan kernel sets aside for the pl
 //   tile  = 256 consecutive packed (row, head) pairs of one request and one KV head group; it needs
 //           ceil(visible keys of its last row / 64) key steps
 //   The key steps of all tiles, laid end to end, are cut into P equal shares, one per workgroup of a
-//   KV head (P = workgroups per head, at most one share per 8 steps): every workgroup gets the same
+//   KV head (P = workgroups per head, at most one share per kMinSteps steps): every workgroup gets the same
 //   amount of work whatever the mix of short and long tiles.
 //   item  = the part of one share that lies in one tile: (tile, k_begin, k_end).  A tile that lies inside
 //           one share is finished by that workgroup; the others are cut into 2 or more items whose

@@ -51,9 +51,9 @@ static inline hipError_t a3_once(a3_once_per_device &o, F fn) {
 enum a3_knob {
   A3_KNOB_ATTN_WGS = 0,        // workgroups (shares) per KV head in the attention plan
   A3_KNOB_ATTN_ITEM_COST,      // start-up cost of a tile in the plan, in key steps
-  A3_KNOB_PROJ_NTW,            // row-tile width (2, 3, 4 x 64 rows) of the projection GEMM; also sends few rows there
+  A3_KNOB_PROJ_NTW,            // tile of the projection GEMM (2 .. 7: gemm_tile_of_knob); also sends few rows there
   A3_KNOB_PROJ_K64,            // no effect any more
-  A3_KNOB_GEMM_TB,             // row-tile width of the GEMMs of H(.)
+  A3_KNOB_GEMM_TB,             // tile of the GEMMs of H(.) (the same numbers), their reductions not split
   A3_KNOB_GEMM_K64,            // no effect any more
   A3_KNOB_COUNT
 };

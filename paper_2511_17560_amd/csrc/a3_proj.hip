@@ -419,7 +419,7 @@ proj_small_bf16_kernel(proj_args a) {
 // elements of one weight row or one hidden row, one for each of four instructions.  The 16 features are 8 of each half of
 // the head (8 b .. and d / 2 + 8 b ..), so both RoPE pairings stay inside the workgroup.  Small calls are latency: every load
 // of a wave's share is independent of the others.  (A tiled kernel with two barriers per 32 elements took 146 us for 32
-// rows x 512 x 512; the new one 6.)
+// rows x 512 x 512; the new one 7.)
 struct proj_args_f32 {
   const float *hidden;
   const int *row_idx;
