@@ -8,7 +8,7 @@
 // and the output is ascending.  Integer work only: the result is unique and bit-exact.
 // Requests of up to 68 K rows keep every key in a register of the lane that owns it; longer ones re-read the
 // scores from global memory in every pass.  One compute unit does all of it, so what bounds it is the instructions its 16
-// waves issue and the chain of barriers.  With the plan: 2K rows 10.8 us, 16K 21, 32K 33, 64K 49.
+// waves issue and the chain of barriers.  With the plan: 2K rows 10.2 us, 5K 11.9, 16K 20, 64K 42.
 #include <type_traits>
 
 #include "a3_internal.h"
