@@ -535,7 +535,10 @@ static a3_status proj_launch(const a3_layout *L, const void *hidden, const int *
     a.scatter_kv = scatter_kv;
     const int ntw_knob = a3_knob(A3_KNOB_PROJ_NTW);            // tuning value "proj_ntw": the GEMM kernel in this width
     if (n_rows <= 192 && L->hidden % 64 == 0 && ntw_knob < 0) {
-      // few rows: stream the weights with 4 x n_heads x ceil(rows/64) small workgroups
+      // few rows: stream the weights with 4 x n_heads x ceil(rows/64) small workgroups.  Weights from HBM, this against the GEMM
+      // in its best tile: Q, K, V of 6144 x 4096 at 64 rows 17.9 and 32.9 us, 128 rows 27.1 and 32.1, 160 rows 34.7 and 29.5, 192 rows
+      // 36.9 and 31.9; of 4608 x 3584 at 192 rows 22.2 and 27.8; Q alone at 192 rows 23.2 and 29.2, 20.7 and 19.1; K and V alone 11.9
+      // and 20.0, 8.8 and 18.1.  192 is the line that serves all but the widest call.
       const dim3 grid(4 * n_heads_total, (n_rows + 63) / 64);
       if (L->hidden % 256 == 0) {
         static a3_once_per_device small_once;
