@@ -49,11 +49,11 @@ constexpr int gemm_tile_of_knob(int v) {
   return v >= 2 && v <= 7 ? tile[v - 2] : -1;
 }
 // n_w weight rows, n_x activation rows, `slabs` slabs; up to max_splits ways to split the reduction (each costs a pass over
-// the fp32 partial results at about 3 TB/s, write and read, and a launch).
-constexpr gemm_tile_choice gemm_choose_tile(int n_w, int n_x, int slabs, int max_splits) {
-  gemm_tile_choice best{GEMM_256x256, 1};
+// the fp32 partial results at about 3 TB/s, write and read, and a launch); tiles `first` and smaller.
+constexpr gemm_tile_choice gemm_choose_tile(int n_w, int n_x, int slabs, int max_splits, int first = GEMM_256x256) {
+  gemm_tile_choice best{first, 1};
   double best_us = 1e30;
-  for (int t = 0; t < GEMM_TILES; ++t)
+  for (int t = first; t < GEMM_TILES; ++t)
     for (int sp = 1; sp <= max_splits && sp * 4 <= slabs + 3; sp *= 2) {
       const gemm_tile_cost &c = kGemmTileCost[t];
       const long wgs = (long)((n_w + c.bm - 1) / c.bm) * ((n_x + c.bn - 1) / c.bn) * sp;

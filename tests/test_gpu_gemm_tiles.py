@@ -96,3 +96,30 @@ def test_block_tail_in_every_tile_and_split(tile, n, hidden, ffn, heads, tuning)
         assert float((got_n[at] - want).abs().max() / want.abs().max()) <= 2e-2
         rest = np.setdiff1d(np.arange(T), rows.numpy())
         assert torch.equal(got_r[rest], r0.double()[rest]) and bool((got_n[rest] == 5).all())
+
+
+@pytest.mark.parametrize("n,hidden,ffn", [(1200, 2048, 8192), (1400, 3072, 14336), (600, 8192, 14336)])
+def test_block_tail_same_bits_with_and_without_room(n, hidden, ffn, tuning):
+    """The larger tiles in which one workgroup forms all shares of a split reduction (128 x 128, 128 x 192, 256 x 128; the shapes
+    above reach the smallest): bit for bit what the split product and its sum give, both within 2e-2 of the unsplit product."""
+    lay = _layout(hidden, 8, 1, n + 1)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    mk = lambda *s, std=1.0: (torch.randn(*s, device="cuda", generator=g) * std).bfloat16()
+    o, r0 = mk(n, 8, 128), mk(n + 1, hidden)
+    lw = (mk(hidden, 1024, std=0.05), 1 + mk(hidden, std=0.1), mk(ffn, hidden, std=0.02), mk(ffn, hidden, std=0.02),
+          mk(hidden, ffn, std=0.02), 1 + mk(hidden, std=0.1))
+    small = ((n * hidden * 2 + 255) // 256 + (n * ffn * 2 + 255) // 256) * 256 + 256
+    need = api.a3_block_tail_ws_bytes(lay, ffn, n)
+    assert need > small
+
+    def run(size):
+        resid, nxt = r0.clone(), torch.zeros_like(r0)
+        api.a3_block_tail(lay, o, None, n, *lw, 1e-5, resid, nxt, torch.empty(size, dtype=torch.uint8, device="cuda"))
+        return resid, nxt
+
+    split, summed = run(need), run(small)
+    tuning("gemm_tb", 4)
+    unsplit = run(small)
+    for a, b, c in zip(split, summed, unsplit):
+        assert torch.equal(a, b)
+        assert float((a.double() - c.double()).abs().max() / c.double().abs().max()) <= 2e-2
