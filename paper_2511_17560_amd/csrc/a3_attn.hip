@@ -13,10 +13,10 @@
 //                     O^T[d][m]  += V^T P^T        (A = V^T fragment from LDS, B = P^T from the S^T accumulators)
 //                 In this orientation four lanes share ONE query row m, and two blocks of S^T accumulators are
 //                 exactly one B operand of the second product.
-// What bounds the main kernel: power.  16x16x32 matrix instructions, two waves per SIMD in opposite phases: 3230 cycles
-// per 64-key tile and 256 rows against 3580 with one wave's phases overlapping by chance on 32x32x16, at 1.9 GHz;
-// 16K context at r = 10 %: 290 -> 255 us, 64K: 3411 -> 3030 us (1.18 PFLOP/s), seven heads per KV head at 32K: 1597 ->
-// 1400 us.  Leaving out the exponentials, the loads or the fragment reads gives 9, 8 and 4 %.
+// What bounds the main kernel: the vector issue port and power.  Two waves per SIMD in opposite phases on 16x16x32 matrix
+// instructions: 2660 cycles per 64-key tile and 256 rows, 2176 of them matrix time (3220 before the phases were cut to
+// what the port has room for: see the loop), at 1.75 GHz under the power limit (1.84 before).  16K context at r = 10 %: 219 -> 209
+// us with the merge, 64K: 3020 -> 2730 us (1.28 PFLOP/s), seven heads per KV head at 32K: 1340 -> 1200 us.
 // fp32 path: the fp32 matrix instruction, one workgroup per 16 packed rows.
 #include <stdlib.h>
 #include <string.h>
@@ -32,12 +32,15 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kD = 128;
 constexpr int kAttnWaves = kTM / 32;   // waves per workgroup, two groups of four in opposite phases
 constexpr int kAttnThreads = 64 * kAttnWaves;
-constexpr int kTileBytes = kTK * kD * 2;             // a K or V tile [key][d] in LDS, unpadded 256-byte rows
-constexpr int kStages = 4;                           // of the K ring and of the V ring
-constexpr int kAhead = 4;                            // fragments read ahead of their products
-constexpr int kTableItems = 16;
-constexpr size_t kRingBytes = (size_t)2 * kStages * kTileBytes;
-constexpr size_t kAttnLds = kRingBytes + (size_t)kAttnWaves * kTableItems * 32;   // 132 KB
+constexpr int kStages = 4;                           // of the LDS ring
+// A direct-to-LDS load brings four keys, 1 KB in one piece; the pieces are padded apart so that the fragment reads find 64 banks
+// at addresses that differ by constants only (no address arithmetic between the products; see the loads)
+constexpr int kKPiece = 1024 + 64, kVPiece = 1024 + 32;
+constexpr int kVAt = kTK / 4 * kKPiece, kStageBytes = kVAt + kTK / 4 * kVPiece;   // a stage: a K tile, then a V tile
+constexpr int kAhead = 4, kKAhead = 6;               // fragments of V read ahead of the phase that multiplies them, of K ahead of S
+constexpr int kTableItems = 32;                      // a multiple of 2 x 8: refilled by halves
+constexpr size_t kRingBytes = (size_t)kStages * kStageBytes;
+constexpr size_t kAttnLds = kRingBytes + (size_t)kAttnWaves * kTableItems * 32;   // 142 KB
 
 __global__ void __launch_bounds__(kPlanThreads)
 attn_plan_kernel(attn_plan p, const int *__restrict__ act_idx, int n_act, const int *__restrict__ seg_start,
@@ -55,6 +58,7 @@ struct attn_args {
   const int *tok_req;
   attn_plan plan;
   int n_act, Hq, Hkv, d;
+  uint32_t inv_G;                      // ceil(2^32 / G), G > 1: x / G = mulhi(x, inv_G) below 2^28
   float scale2;
 };
 
@@ -73,8 +77,6 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 
-struct attn_item { int k_begin, k_end, kv_len, m0, m_end, a0, base, nseg; };
-
 // One workgroup per share of a KV head's work: it runs the items of its share in order, their 64-key tiles as one stream.
 __global__ void __launch_bounds__(kAttnThreads, 1)
 attn_bf16_kernel(attn_args a) {
@@ -90,107 +92,108 @@ attn_bf16_kernel(attn_args a) {
   const bf16_t *__restrict__ Q = (const bf16_t *)a.q;
   const float c2 = a.scale2;
 
-  // ---- items of this workgroup: the first kTableItems are looked up once, into a table of the wave's own -----------------
-  auto fetch = [&](int i) {
-    const int4 it = a.plan.items[i];
-    const int4 ta = a.plan.tile_a[it.x];
-    attn_item d;
-    d.nseg = a.plan.tile_b[it.x].y;
-    d.k_begin = it.y; d.k_end = it.z; d.kv_len = ta.z; d.m0 = ta.y; d.m_end = ta.w;
-    d.a0 = a.plan.a_lo[ta.x]; d.base = a.seg_start[ta.x];
-    return d;
+  // ---- items of this workgroup, looked up ahead into a ring of the wave's own.  The stream of loads is at most three items
+  // ahead of the products: when it enters the middle of one half, the other half holds nothing that is still wanted
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) i32x4 lds_i32x4;
+  lds_i32x4 *table = (lds_i32x4 *)(lds + kRingBytes + wave * (kTableItems * sizeof(attn_item)));
+  auto table_fill = [&](int first, int n) {                  // items first .. first + n - 1 (2 n <= 64)
+    const int i = first + lane / 2;
+    if (lane < 2 * n && i < item_end) table[(i - item_begin) % kTableItems * 2 + (lane & 1)] = reinterpret_cast<const i32x4 *>(a.plan.items)[2 * i + (lane & 1)];
   };
-  attn_item *table = reinterpret_cast<attn_item *>(lds + kRingBytes + wave * (kTableItems * sizeof(attn_item)));
-  if (lane < kTableItems && item_begin + lane < item_end) table[lane] = fetch(item_begin + lane);
+  table_fill(item_begin, kTableItems);
   auto item_at = [&](int i) {
-    attn_item d = i - item_begin < kTableItems ? table[i - item_begin] : fetch(i);
-    int *f = reinterpret_cast<int *>(&d);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = __builtin_amdgcn_readfirstlane(f[e]);
-    return d;
+    const lds_i32x4 *d = table + (i - item_begin) % kTableItems * 2;
+    const i32x4 x = d[0], y = d[1];
+    attn_item it;
+    it.k_begin = __builtin_amdgcn_readfirstlane(x.x); it.k_end = __builtin_amdgcn_readfirstlane(x.y);
+    it.kv_len = __builtin_amdgcn_readfirstlane(x.z); it.m0 = __builtin_amdgcn_readfirstlane(x.w);
+    it.m_end = __builtin_amdgcn_readfirstlane(y.x); it.a0 = __builtin_amdgcn_readfirstlane(y.y);
+    it.base = __builtin_amdgcn_readfirstlane(y.z); it.whole = __builtin_amdgcn_readfirstlane(y.w);
+    return it;
   };
 
   // ---- loads: both tiles of 64 keys x 256 bytes by direct-to-LDS loads, 4 keys per wave instruction, two instructions
-  // per wave and tile.  K: slot s (16 bytes) of key r holds piece s ^ (r % 16), so that the 16 keys a quarter wave reads at
-  // one piece index touch all 64 banks once.  V: the 32-byte piece p of key r lies at p ^ (r % 8), so that the 8 keys x 32
-  // bytes a half wave hands to the transposing read do.
+  // per wave and tile; lane (l16, lg) brings 16 bytes of the lg-th of its keys to slot l16 of that key's 256 bytes.
+  // K: piece t holds keys 4 t .. + 3, slot s of key r the 16 bytes number s ^ (r % 4): the 16 keys a quarter wave reads at
+  // one place then lie at 64 (r / 4) + 16 (place ^ (r % 4)) modulo 256, all 64 banks once.
+  // V: piece t holds keys 16 (t / 4) + t % 4 + 4 j, j = 0 .. 3, with the halves of a key's row swapped for odd j: the 8 keys x 32
+  // bytes a half wave hands to the transposing read (t % 4 = 0 .. 3, two j) lie at 32 (t % 4) + 128 (j % 2), all banks once.
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
   const uint32_t pitch = (uint32_t)a.Hkv * kD * sizeof(bf16_t);
-  const int drow = 4 * wave + lg;                            // key of the lane in instruction 0; + 32 in instruction 1
-  const uint32_t key_off = (uint32_t)drow * pitch;
-  const uint32_t kpiece = 16 * (l16 ^ (drow & 15)), vpiece = 32 * ((l16 >> 1) ^ (drow & 7)) + 16 * (l16 & 1);
-  const uint32_t koff0 = key_off + kpiece, koff1 = koff0 + 32 * pitch, voff0 = key_off + vpiece, voff1 = voff0 + 32 * pitch;
-  // K of a tile is requested one tile before its V: l_* the tile whose K comes next, v_* the one before it
-  int l_item = item_begin, l_keys, l_steps, v_keys = kTK;    // visible keys and tiles of the item from this tile on
-  const char *l_kb, *l_vb, *v_vb = nullptr;
+  const uint32_t kkey_off = (uint32_t)(4 * wave + lg) * pitch;         // key of the lane in instruction 0; + 32 keys in instruction 1
+  const uint32_t vkey_off = (uint32_t)(16 * (wave >> 2) + (wave & 3) + 4 * lg) * pitch;
+  const uint32_t kpiece = 16 * (l16 ^ lg), vpiece = 16 * (l16 ^ (8 * (lg & 1)));
+  const uint32_t k_off[2] = {kkey_off + kpiece, kkey_off + 32 * pitch + kpiece}, v_off[2] = {vkey_off + vpiece, vkey_off + 32 * pitch + vpiece};
+  // K of a tile is requested one tile before its V: l_* the tile whose K comes next, v_* the one before it.  Descriptors of the
+  // request and head end behind the item's last visible key: past it the loads bring zeros (also past the last tile of the stream)
+  int l_item = item_begin, l_steps;                          // tiles of the item from this one on
+  u32x4 l_k, l_v, v_v;
+  uint32_t l_at, v_at = 0;                                   // byte offsets of the tiles
+  bool l_same = false;                                       // both tiles are of one item
   auto load_from = [&](int i) {
     const attn_item d = item_at(i);
-    l_keys = d.kv_len - d.k_begin;
     l_steps = (d.k_end - d.k_begin + kTK - 1) / kTK;
-    const size_t at = ((size_t)(d.base + d.k_begin) * a.Hkv + g) * kD;
-    l_kb = reinterpret_cast<const char *>((const bf16_t *)a.k + at);
-    l_vb = reinterpret_cast<const char *>((const bf16_t *)a.v + at);
+    l_at = (uint32_t)d.k_begin * pitch;
+    const uint32_t bytes = (uint32_t)(d.kv_len - 1) * pitch + kD * sizeof(bf16_t);
+    const uint64_t at = ((uint64_t)(uint32_t)d.base * a.Hkv + g) * (kD * sizeof(bf16_t)), pk = (uint64_t)a.k + at, pv = (uint64_t)a.v + at;
+    l_k = u32x4{(uint32_t)pk, (uint32_t)(pk >> 32) & 0xffffu, bytes, 0x00020000u};
+    l_v = u32x4{(uint32_t)pv, (uint32_t)(pv >> 32) & 0xffffu, bytes, 0x00020000u};
+  };
+  auto load_step = [&]() { v_at = l_at; l_at += kTK * pitch; };
+  auto load_on = [&]() {                                     // what else there is to do behind load_step
+    v_v = l_v;
+    l_same = --l_steps > 0;
+    if (!l_same) {
+      if (l_item + 1 < item_end) {
+        load_from(++l_item);
+        if ((l_item - item_begin) % (kTableItems / 2) == kTableItems / 4)
+          table_fill(l_item + kTableItems / 4, kTableItems / 2);
+      } else {
+        l_steps = 1 << 30;
+      }
+    }
   };
   // Inline assembly on purpose: the compiler then neither treats these as LDS writes (it would wait for all of them before
   // every LDS read) nor moves memory accesses across them; the waits for them are the explicit s_waitcnt below.
-  auto dma = [&](const char *base, uint32_t off, uint32_t to) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds_base + to), "v"(off), "s"(base) : "memory");
+  auto dma = [&](const u32x4 &base, uint32_t at, uint32_t off, uint32_t stage, uint32_t to) {
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds"
+                 :: "s"(stage), "s"(to), "v"(off), "s"(base), "s"(at) : "memory", "scc");
   };
-  // keys past the item's last visible one are clamped onto it and masked later; past the last tile of the stream that one
-  // again, unused
-  auto load_half = [&](const char *base, int keys, uint32_t off0, uint32_t off1, uint32_t piece, uint32_t to) {
-    if (keys < kTK) {
-      const uint32_t last = (uint32_t)(keys - 1) * pitch;
-      off0 = min(key_off, last) + piece;
-      off1 = min(key_off + 32 * pitch, last) + piece;
-    }
-    dma(base, off0, to);
-    dma(base, off1, to + 8192);
-  };
-  auto load_k = [&](int stage) { load_half(l_kb, l_keys, koff0, koff1, kpiece, stage * kTileBytes + wave * 1024); };
-  auto load_v = [&](int stage) { load_half(v_vb, v_keys, voff0, voff1, vpiece, (kStages + stage) * kTileBytes + wave * 1024); };
-  auto load_next = [&]() {
-    v_vb = l_vb; v_keys = l_keys;
-    if (--l_steps > 0) {
-      l_kb += kTK * pitch; l_vb += kTK * pitch; l_keys -= kTK;
-    } else if (l_item + 1 < item_end) {
-      load_from(++l_item);
-    } else {
-      l_steps = 1;
-    }
-  };
+  const uint32_t to_k = lds_base + wave * kKPiece, to_v = lds_base + kVAt + wave * kVPiece;
+  auto load_k = [&](uint32_t stage, int i) { dma(l_k, l_at, k_off[i], stage, to_k + i * 8 * kKPiece); };
+  auto load_v = [&](uint32_t stage, int i) { dma(v_v, v_at, v_off[i], stage, to_v + i * 8 * kVPiece); };
 
   // ---- rows of an item: lane (l16, lg) holds rows m0 + 32 wave + 16 rb + l16 ---------------------------------------
   bf16x8 qf[2][4];
   int limit[2], min_limit, max_limit;                        // last visible key of the rows (request-relative)
-  uint32_t out_row[2], prev_row[2];                          // row of the output, ~0: none
+  uint32_t out_row[2], prev_row[2];                          // row of the output; bit 31: not stored
   attn_item cur;
   auto load_rows = [&]() {
-    min_limit = 0x7fffffff; max_limit = -1;
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
       const int m = cur.m0 + 32 * wave + 16 * rb + l16, mc = min(m, cur.m_end - 1);
-      const int ar = mc / G, arow = cur.a0 + ar, hq = g * G + mc - ar * G;
+      const int ar = G == 1 ? mc : (int)__umulhi((uint32_t)mc, a.inv_G), arow = cur.a0 + ar, hq = g * G + mc - ar * G;
       out_row[rb] = (uint32_t)arow * a.Hq + hq;
-      const bf16_t *qp = Q + (size_t)out_row[rb] * kD + lg * 8;
+      limit[rb] = a.act_idx[arow];
+      if (m >= cur.m_end) out_row[rb] |= 1u << 31;
+    }
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+      const bf16_t *qp = Q + (size_t)(out_row[rb] & ~(1u << 31)) * kD + lg * 8;
 #pragma unroll
       for (int ds = 0; ds < 4; ++ds) qf[rb][ds] = *reinterpret_cast<const bf16x8 *>(qp + 32 * ds);
-      limit[rb] = a.act_idx[arow] - cur.base;
-      if (m >= cur.m_end) out_row[rb] = ~0u;
     }
-    int lo = min(limit[0], limit[1]), hi = max(limit[0], limit[1]);
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) {
-      lo = min(lo, __shfl_xor(lo, off, 64));
-      hi = max(hi, __shfl_xor(hi, off, 64));
-    }
-    min_limit = __builtin_amdgcn_readfirstlane(lo);
-    max_limit = __builtin_amdgcn_readfirstlane(hi);
+  };
+  auto row_limits = [&]() {                                  // limits ascend with the rows
+    limit[0] -= cur.base; limit[1] -= cur.base;
+    min_limit = __builtin_amdgcn_readlane(limit[0], 0);
+    max_limit = __builtin_amdgcn_readlane(limit[1], 15);
   };
 
   f32x4 o[8][2], st[4][2];
   uint32_t pu[2][2][4];                                      // P of the tile before, pairs of bf16, [32 keys][row block]
-  float ref[2], mx[2], nref[2] = {0.f, 0.f};                  // exponent reference and tile maximum in raw logit units; -ref c2
+  float ref[2], nref[2];                                     // exponent reference (-inf: no key seen) and what is added to an exponent
   // Row sums of P, by the matrix pipe (an all-ones V): every register.  They are fp32 sums of the weights as the product with V
   // uses them, rounded to bf16: an output is then an exact mean of the values it sees, and the weights' roundings cancel where
   // values are alike.  Relative error against float64, unrounded weights summed -> these: 8 matching rows of 100 2.04e-3
@@ -200,14 +203,15 @@ attn_bf16_kernel(attn_args a) {
   bf16x8 ones;
 #pragma unroll
   for (int e = 0; e < 8; ++e) ones[e] = (bf16_t)1.0f;
-  int prev_item = item_begin, prev_nseg = 0;
+  asm volatile("" : "+v"(ones));                             // kept in registers
+  int prev_item = item_begin, prev_whole = 0;
   auto store_rows = [&]() {
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
       const float total = osum[rb][0];
-      if (prev_nseg == 1) {
+      if (prev_whole) {
         const float inv = 1.0f / total;
-        if (prev_row[rb] != ~0u) {
+        if (prev_row[rb] < 1u << 31) {
           bf16_t *p = (bf16_t *)a.out + (size_t)prev_row[rb] * kD + 4 * lg;
 #pragma unroll
           for (int db = 0; db < 8; ++db) {
@@ -219,82 +223,65 @@ attn_bf16_kernel(attn_args a) {
         }
       } else {
         const size_t pr = ((size_t)g * a.plan.max_items + prev_item) * kTM + 32 * wave + 16 * rb + l16;
-        float *p = a.plan.part_o + pr * kD + 4 * lg;
+        f32x4 *p = reinterpret_cast<f32x4 *>(a.plan.part_o) + (((size_t)g * a.plan.max_items + prev_item) * (kTM / 16) + 2 * wave + rb) * 512 + lane;
 #pragma unroll
-        for (int db = 0; db < 8; ++db) *reinterpret_cast<f32x4 *>(p + 16 * db) = o[db][rb];
-        if (lg == 0) a.plan.part_ml[pr] = make_float2(ref[rb] * c2, total);
+        for (int db = 0; db < 8; ++db) p[64 * db] = o[db][rb];
+        if (lg == 0) a.plan.part_ml[pr] = make_float2(ref[rb], total);
       }
     }
   };
 
-  // ---- fragments: K (16 keys x 32 dims, lane = key l16, piece 4 ds + lg) by one 16-byte read, V^T (16 dims x 32 keys) by two
-  // transposing 8-byte reads: lane (l16, lg) then holds dim l16, keys 4 lg .. + 3 of two 16-key blocks, which is the order in
-  // which the S^T accumulators hold P (accumulator r of key block b: key 16 b + 4 lg + r, row l16)
-  const uint32_t kaddr = l16 * 256 + 16 * (lg ^ l16);
-  const int vkey = 4 * lg + (l16 >> 2);
-  const uint32_t vaddr = vkey * 256 + 32 * (vkey & 7) + 8 * (l16 & 3);
-#define A3_KFRAG(N) fr[(N) % kAhead] = *reinterpret_cast<const bf16x8 *>(kt + (kaddr ^ (64 * ((N) >> 2))) + 4096 * ((N) & 3));
-#define A3_VFRAG(N)                                                                                                    \
-  {                                                                                                                    \
-    typedef __attribute__((address_space(3))) s16x4 *tr_ptr;                                                           \
-    const unsigned char *p_ = vt + (vaddr ^ (32 * ((N) & 7))) + 8192 * ((N) >> 3);                                     \
-    const s16x4 x_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(p_));                                            \
-    const s16x4 y_ = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(p_ + 4096));                                     \
-    fr[(16 + (N)) % kAhead] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(x_, y_, 0, 1, 2, 3, 4, 5, 6, 7));            \
-  }
+  // ---- fragments: K (16 keys x 32 dims, lane = key l16, 16 bytes number 4 ds + lg) by one 16-byte read, V^T (16 dims x 32 keys)
+  // by two transposing 8-byte reads: lane (l16, lg) then holds dim l16, keys 4 lg .. + 3 of two 16-key blocks, which is the order
+  // in which the S^T accumulators hold P (accumulator r of key block b: key 16 b + 4 lg + r, row l16)
+  const uint32_t kaddr = (l16 >> 2) * kKPiece + (l16 & 3) * 256 + 16 * (lg ^ (l16 & 3));
+  const uint32_t vaddr = kVAt + (l16 >> 2) * kVPiece + lg * 256 + 8 * (l16 & 3);
+  const uint32_t vaddr0 = vaddr + 128 * (lg & 1), vaddr1 = vaddr + 128 * (~lg & 1);      // dims 0 .. 63, 64 .. 127
+  typedef __attribute__((address_space(3))) s16x4 *tr_ptr;
+  s16x4 va[16][2];                                           // V^T fragment N = 8 ks + block of 16 dims, its two halves
+  bf16x8 kf[16];                                             // K fragment N = 4 ds + block of 16 keys
+  const unsigned char *kp = lds + kaddr, *vp0, *vp1;
+#define A3_KREAD(N) kf[N] = *reinterpret_cast<const bf16x8 *>(kp + 64 * ((N) >> 2) + 4 * kKPiece * ((N) & 3));
+#define A3_VREAD(N, H) va[N][H] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(((N) & 4 ? vp1 : vp0) + 32 * ((N) & 3) + 4 * kVPiece * (2 * ((N) >> 3) + (H))));
+#define A3_VF(N) __builtin_bit_cast(bf16x8, __builtin_shufflevector(va[N][0], va[N][1], 0, 1, 2, 3, 4, 5, 6, 7))
+#define A3_P(KS, RB) __builtin_bit_cast(bf16x8, u32x4{pu[KS][RB][0], pu[KS][RB][1], pu[KS][RB][2], pu[KS][RB][3]})
 #define A3_FENCE __builtin_amdgcn_sched_barrier(0);
-  bf16x8 fr[kAhead];                                         // fragments in the order K 0 .. 15, V 0 .. 15
 
   cur = item_at(item_begin);
-  load_rows();
-  prev_row[0] = prev_row[1] = ~0u;
+  prev_row[0] = prev_row[1] = 1u << 31;
   load_from(item_begin);
-  __builtin_amdgcn_s_waitcnt(0);
-  load_k(0); load_next();
-  load_k(1); load_v(0); load_next();
-  load_k(2); load_v(1); load_next();
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));                              // this wave's part of K of tiles 0 and 1 has landed
+  uint32_t s0 = 0, s1 = kStageBytes, s2 = 2 * kStageBytes, s3 = 3 * kStageBytes;     // stages of tiles u .. u + 3
+  load_k(s0, 0); load_k(s0, 1); load_step(); load_on();
+  load_k(s1, 0); load_k(s1, 1); load_v(s0, 0); load_v(s0, 1); load_step(); load_on();
+  load_rows();
+  load_k(s2, 0); load_k(s2, 1); load_v(s1, 0); load_v(s1, 1); load_step(); load_on();
+  __builtin_amdgcn_s_waitcnt(0);                                         // this wave's part of tiles 0, 1 and K of tile 2 has landed
   __builtin_amdgcn_s_barrier();                                          // ... and everybody's
   if (grp == 1) __builtin_amdgcn_s_barrier();                            // one phase behind
 
   // The two waves of a SIMD belong to different groups and run in opposite phases, one barrier apart: while one has the
-  // matrix pipe (S of tile u and P V of tile u - 1), the other does the softmax of its tile on the vector unit.  Group 0
-  // multiplies tile u in phase 2 u, group 1 in phase 2 u + 1.  K of tile u + 3 and V of tile u + 2 are requested in the
-  // vector phase of tile u; at the end of phase 2 u everything up to K of tile u + 1 and V of tile u has landed, one phase
-  // before their first fragments are read.  Beside the matrix pipe a vector instruction takes about 7 cycles of its wave (10.8
-  // an exponential), so the vector phase is kept to the 32 scalings, 32 exponentials and 16 conversions: the row sums are
-  // matrix products, and the maxima are taken between the products of P V.
-  int ring = 0, k0 = cur.k_begin, item = item_begin;         // ring: tile u % 4
+  // matrix pipe (P V of tile u - 1, then S of tile u), the other does the softmax of its tile on the vector unit.  Group 0
+  // multiplies tile u in phase 2 u, group 1 in phase 2 u + 1.  K of tile u + 3 and V of tile u + 2 are requested at the end of the
+  // matrix phase of tile u, over K of tile u - 1 and V of tile u - 2, which both groups have read; at the end of the vector phase
+  // every wave waits for all but these, so that K of tile u + 1 and V of tile u are there one phase before group 0 reads them.
+  // What a phase may hold, measured in a loop of nothing else (cycles per tile of two phases):
+  //   68 products with at most one LDS read right behind each: 2250.  A read costs nothing there, but 6 - 12 cycles of its wave behind
+  //   a vector instruction or another read.
+  //   with 32 scalings, 32 exponentials, 16 conversions and 8 ors in the other wave: 2280.  A product takes 8 cycles of the SIMD's
+  //   vector issue, an exponential 8, any other vector instruction 4: 544 + 480 of the 1088 cycles, so nothing else is done
+  //   per element: the row sums are matrix products, and instead of the maxima of a tile the bits of the weights are or-ed.
+  //   barrier four products before the end of the matrix phase instead of one: 2820; fragments read ahead at the start of the vector
+  //   phase instead of its end: + 350; the four requests in the vector phase: + 120 .. 200, between products without a read: + 60;
+  //   s_setprio around the products: + 150; a scalar instruction at either end of a phase: + 9 each, between products: 0.
+  // Hence tiles with nothing special to them run in a loop of their own without a branch or a bookkeeping instruction.
+  int k0 = cur.k_begin, item = item_begin;
   bool first = true, has_prev = false;
-  bool act = k0 <= max_limit, act_prev = false;              // a wave whose rows all end before a tile leaves its products out
-  {
-    const unsigned char *kt = lds;
-#pragma unroll
-    for (int n = 0; n < kAhead; ++n) A3_KFRAG(n)
-  }
-#define A3_PV(N)                                                                                                       \
+  bool act = false, act_prev = false;                        // a wave whose rows all end before a tile leaves its products out
+  // Weights of the N-th pair of S values, N = 0 .. 15 (key block N / 4, registers 2 (N / 2 % 2) and + 1, row block N % 2)
+  // (the empty asm statement keeps the compiler from moving the arithmetic behind the products)
+#define A3_EXP(N)                                                                                                      \
   {                                                                                                                    \
-    if ((N) == 14) {                                                                                                   \
-      __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));                                                                        \
-      __builtin_amdgcn_s_barrier();                                                                                    \
-      A3_FENCE                                                                                                         \
-    }                                                                                                                  \
-    _Pragma("unroll") for (int rb = 0; rb < 2; ++rb)                                                                   \
-      o[(N) & 7][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[(16 + (N)) % kAhead], A3_P((N) >> 3, rb), o[(N) & 7][rb], 0, 0, 0); \
-    if (((N) & 7) == 4) {                                                                                              \
-      _Pragma("unroll") for (int rb = 0; rb < 2; ++rb)                                                                 \
-        osum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, A3_P((N) >> 3, rb), osum[rb], 0, 0, 0);                 \
-    }                                                                                                                  \
-    A3_FENCE                                                                                                           \
-    if ((N) + kAhead < 16) A3_VFRAG((N) + kAhead)                                                                      \
-    A3_MAX2((N) >> 1, (N) & 1)                                                                                         \
-    A3_FENCE                                                                                                           \
-  }
-  // the N-th pair of S values of a row block, N = 0 .. 7 (key block N / 2, registers 2 (N % 2) and + 1)
-  // (the empty asm statements keep the compiler from moving the arithmetic behind the products)
-#define A3_EXP2(Q)                                                                                                     \
-  {                                                                                                                    \
-    const int b_ = (Q) >> 2, r_ = (Q) & 2, rb_ = (Q) & 1;                                                              \
+    const int b_ = (N) >> 2, r_ = (N) & 2, rb_ = (N) & 1;                                                              \
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));                                                         \
     bf16x2 t_;                                                                                                         \
     t_[0] = a3_f2bf(fast_exp2(fmaf(st[b_][rb_][r_], c2, nref[rb_])));                                                  \
@@ -302,140 +289,203 @@ attn_bf16_kernel(attn_args a) {
     pu[b_ >> 1][rb_][2 * (b_ & 1) + r_ / 2] = __builtin_bit_cast(uint32_t, t_);                                        \
     asm volatile("" : "+v"(pu[b_ >> 1][rb_][2 * (b_ & 1) + r_ / 2]));                                                  \
   }
-#define A3_P(KS, RB) __builtin_bit_cast(bf16x8, u32x4{pu[KS][RB][0], pu[KS][RB][1], pu[KS][RB][2], pu[KS][RB][3]})
-#define A3_MAX2(N, RB) { mx[RB] = fmaxf(fmaxf(mx[RB], st[(N) >> 1][RB][2 * ((N) & 1)]), st[(N) >> 1][RB][2 * ((N) & 1) + 1]); asm volatile("" : "+v"(mx[RB])); }
+  // ---- matrix phase: row sums and P V of keys 0 .. 31 of the tile before, then of keys 32 .. 63; fragments of V are read 9
+  // products before their first, and the first of K at the end
+  auto pv_products = [&]() {
+#pragma unroll
+    for (int m = 0; m < 36; ++m) {
+      const int ks = m / 18, i = m % 18 - 2, rb = m & 1;
+      if (i < 0) osum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, A3_P(ks, rb), osum[rb], 0, 0, 0);
+      else o[i >> 1][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A3_VF(8 * ks + (i >> 1)), A3_P(ks, rb), o[i >> 1][rb], 0, 0, 0);
+      A3_FENCE
+      if (m < 2 * (16 - kAhead)) A3_VREAD(kAhead + (m >> 1), m & 1)
+      else if (m < 2 * (16 - kAhead) + kKAhead) A3_KREAD(m - 2 * (16 - kAhead))
+      A3_FENCE
+    }
+  };
+  // the loads of K of tile u + 3 and V of tile u + 2, and the addresses of the phases to come, in six parts
+  auto between = [&](int i) {
+    if (i == 0) load_k(s3, 0);
+    if (i == 1) load_k(s3, 1);
+    if (i == 2) load_v(s2, 0);
+    if (i == 3) load_v(s2, 1);
+    if (i == 4) { vp0 = lds + (vaddr0 + s0); vp1 = lds + (vaddr1 + s0); load_step(); }
+    if (i == 5) { const uint32_t t = s0; s0 = s1; s1 = s2; s2 = s3; s3 = t; kp = lds + (kaddr + s0); }
+  };
+  auto s_products = [&]() {
+#pragma unroll
+    for (int m = 0; m < 32; ++m) {
+      const int n = m >> 1, rb = m & 1;
+      if (m == 31) __builtin_amdgcn_s_barrier();
+      A3_FENCE
+      st[n & 3][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[n], qf[rb][n >> 2], n < 4 ? f32x4{0.f, 0.f, 0.f, 0.f} : st[n & 3][rb], 0, 0, 0);
+      A3_FENCE
+      if (!(m & 1) && kKAhead + n < 16) A3_KREAD(kKAhead + n)
+      if ((m & 1) && m >= 19 && m < 31) between((m - 19) >> 1);
+      A3_FENCE
+    }
+  };
+  // ---- vector phase
+  auto weights = [&]() -> uint32_t {                         // the or of their bits
+    uint32_t bits = 0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      A3_EXP(q)
+      if (q & 1) bits |= pu[q >> 3][0][(q >> 1) & 3] | pu[q >> 3][1][(q >> 1) & 3];
+      A3_FENCE
+    }
+    return bits;
+  };
+  auto maximum = [&](int rb) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; r += 2) mx = fmaxf(fmaxf(mx, st[b][rb][r]), st[b][rb][r + 1]);
+    return fmaf(groups_max(mx), c2, 7.0f);
+  };
+  // Lazy rescaling: the exponent reference lies 7 above the largest exponent of the row when it was set, so weights are about
+  // 2^-7 and below, and moves when one reaches 2 (a bf16 that does has bit 14 set, and only such a one: one test of the or of
+  // all bits), so the accumulators are rescaled a handful of times per row instead of whenever the maximum moves.
+  auto check = [&](uint32_t bits) {
+    if (__any((bits & 0x40004000u) != 0)) {
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        const float new_ref = fmaxf(ref[rb], maximum(rb));
+        const float alpha = new_ref == -INFINITY ? 1.0f : fast_exp2(ref[rb] - new_ref);
+        ref[rb] = new_ref;
+        nref[rb] = new_ref == -INFINITY ? 0.f : -new_ref;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          osum[rb][r] *= alpha;
+#pragma unroll
+          for (int db = 0; db < 8; ++db) o[db][rb][r] *= alpha;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 16; ++q) A3_EXP(q)
+    }
+  };
+  auto phase_end = [&](bool wait) {
+    A3_FENCE
+    if (wait) __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
+#pragma unroll
+    for (int n = 0; n < kAhead; ++n) { A3_VREAD(n, 0) A3_VREAD(n, 1) }
+    A3_FENCE
+    __builtin_amdgcn_s_barrier();
+    A3_FENCE
+  };
+
   for (;;) {
-    // ---- matrix phase
-    const unsigned char *kt = lds + ring * kTileBytes, *vt = lds + (kStages + ((ring + 3) & 3)) * kTileBytes;
-    A3_FENCE
-    __builtin_amdgcn_s_setprio(1);
-    if (act) {
-#pragma unroll
-      for (int n = 0; n < 16; ++n) {
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
-          st[n & 3][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[n % kAhead], qf[rb][n >> 2],
-                                                                  n < 4 ? f32x4{0.f, 0.f, 0.f, 0.f} : st[n & 3][rb], 0, 0, 0);
-        A3_FENCE
-        if (n + kAhead < 16) A3_KFRAG(n + kAhead) else A3_VFRAG(n + kAhead - 16)
-        A3_FENCE
-      }
-      if (k0 + kTK - 1 > min_limit) {                        // tile touches the causal boundary of some row
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-          for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (k0 + 16 * b + 4 * lg + r > limit[rb]) st[b][rb][r] = -INFINITY;
-      }
-    } else {
-#pragma unroll
-      for (int n = 0; n < kAhead; ++n) A3_VFRAG(n)
-    }
-    mx[0] = mx[1] = -INFINITY;                               // (of no meaning, and not used, when the tile is left out)
-    A3_FENCE
     if (act_prev) {
-#pragma unroll
-      for (int n = 0; n < 16; ++n) A3_PV(n)
+      pv_products();
     } else {
-      __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
-      __builtin_amdgcn_s_barrier();
 #pragma unroll
-      for (int n = 0; n < 16; ++n) A3_MAX2(n >> 1, n & 1)
+      for (int n = 0; n < kKAhead; ++n) A3_KREAD(n)
     }
-    __builtin_amdgcn_s_setprio(0);
-    A3_FENCE
-    // ---- vector phase
     if (first) {
-      if (has_prev) store_rows();
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));              // the rows of the new item
+      row_limits();
+      act = k0 <= max_limit;
+      if (has_prev) store_rows();                            // (before the loads of this tile: waits count stores too)
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) {
 #pragma unroll
         for (int db = 0; db < 8; ++db) o[db][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
         osum[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        ref[rb] = -INFINITY;
-        nref[rb] = 0.f;
       }
-      first = false;
     }
-    load_k((ring + 3) & 3);
-    load_v((ring + 2) & 3);
-    load_next();
     if (act) {
-      // Lazy rescaling: the exponent reference only has to stay within 2^8 of the running maximum, not equal to it, so the
-      // accumulators are rescaled a handful of times per row instead of whenever the maximum moves.  P ranges up to 256.
-      const bool redo = __any((mx[0] - ref[0]) * c2 > 8.0f || (mx[1] - ref[1]) * c2 > 8.0f);   // also the first visible key (-inf)
-      if (redo) {
+      s_products();
+    } else {
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
-          const float new_ref = fmaxf(ref[rb], groups_max(mx[rb]));
-          const float alpha = new_ref == -INFINITY ? 1.0f : fast_exp2((ref[rb] - new_ref) * c2);
-          ref[rb] = new_ref;
-          nref[rb] = new_ref == -INFINITY ? 0.f : -new_ref * c2;                  // no visible key yet: every P is 0
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            osum[rb][r] *= alpha;
-#pragma unroll
-            for (int db = 0; db < 8; ++db) o[db][rb][r] *= alpha;
-          }
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 16; ++q) A3_EXP2(q)
+      for (int i = 0; i < 6; ++i) between(i);
+      __builtin_amdgcn_s_barrier();
     }
-    // ---- on to the next tile
-    ring = (ring + 1) & 3;
+    A3_FENCE
+    if (k0 + kTK - 1 > min_limit) {                          // tile touches the causal boundary of some row
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        const int seen = act ? limit[rb] - k0 - 4 * lg : -1;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (16 * b + r > seen) st[b][rb][r] = -INFINITY;
+      }
+    }
+    if (first) {
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        ref[rb] = maximum(rb);
+        nref[rb] = ref[rb] == -INFINITY ? 0.f : -ref[rb];    // no visible key: every P is 0
+      }
+    }
+    check(weights());
+    load_on();
     act_prev = act;
-    bool last = false;
+    const bool fresh = first;
+    first = false;
     k0 += kTK;
     if (k0 >= cur.k_end) {
-      prev_item = item; prev_nseg = cur.nseg;
+      prev_item = item; prev_whole = cur.whole;
       prev_row[0] = out_row[0]; prev_row[1] = out_row[1];
-      has_prev = true;
+      has_prev = first = true;
       if (++item < item_end) {
         cur = item_at(item);
         load_rows();
-        __builtin_amdgcn_s_waitcnt(0);
         k0 = cur.k_begin;
-        first = true;
-      } else {
-        last = true;
       }
     }
     act = k0 <= max_limit;
-    if (grp == 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
-    {
-      const unsigned char *kt = lds + ring * kTileBytes;
-      A3_FENCE
+    phase_end(!fresh && !first);                             // (all loads up to a fresh tile's have landed before its stores)
+    if (item == item_end) break;
+    if (fresh || first) continue;
+    // Tiles of the same items here and in the stream of loads with nothing masked; then tiles that this wave only loads for
+    const int rest = l_same ? min((cur.k_end - k0 + kTK - 1) / kTK, l_steps) - 1 : 0;
+    if (act && act_prev) {
+      const int calm = min((min_limit + 1 - k0) / kTK, rest);
+      if (calm > 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // (or the compiler waits in the loop, for rows loaded long ago)
+      for (int c = 0; c < calm; ++c) {
+        pv_products();
+        s_products();
+        check(weights());
+        phase_end(true);
+      }
+      if (calm > 0) {
+        k0 += calm * kTK;
+        l_steps -= calm;
+      }
+    } else if (!act && !act_prev && rest > 0) {
+      for (int c = 0; c < rest; ++c) {
 #pragma unroll
-      for (int n = 0; n < kAhead; ++n) A3_KFRAG(n)
-      A3_FENCE
+        for (int i = 0; i < 6; ++i) between(i);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
+        __builtin_amdgcn_s_barrier();
+      }
+      k0 += rest * kTK;
+      l_steps -= rest;
     }
-    __builtin_amdgcn_s_barrier();
-    if (last) break;
   }
   // ---- P V of the last tile
   if (act_prev) {
-    const unsigned char *vt = lds + (kStages + ((ring + 3) & 3)) * kTileBytes;
 #pragma unroll
-    for (int n = 0; n < 16; ++n) {
-      A3_VFRAG(n)
+    for (int n = kAhead; n < 16; ++n) { A3_VREAD(n, 0) A3_VREAD(n, 1) }
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
-        o[n & 7][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[(16 + n) % kAhead], A3_P(n >> 3, rb), o[n & 7][rb], 0, 0, 0);
-    }
+    for (int n = 0; n < 16; ++n)
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) o[n & 7][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A3_VF(n), A3_P(n >> 3, rb), o[n & 7][rb], 0, 0, 0);
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) osum[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, A3_P(ks, rb), osum[rb], 0, 0, 0);
   }
-#undef A3_PV
 #undef A3_P
-#undef A3_EXP2
-#undef A3_MAX2
-#undef A3_KFRAG
-#undef A3_VFRAG
+#undef A3_VF
+#undef A3_EXP
+#undef A3_KREAD
+#undef A3_VREAD
 #undef A3_FENCE
   if (grp == 0) __builtin_amdgcn_s_barrier();
   store_rows();
@@ -443,9 +493,8 @@ attn_bf16_kernel(attn_args a) {
 }
 
 // Merges the partial results of tiles that were cut into key segments, in segment order.
-// One workgroup per (tile, KV head, 32 of the tile's rows); 8 lanes share a row, dims 32 i + 4 lane .. + 3 each, so that
-// one load of theirs covers 128 bytes in one piece (16 dims in a run per lane: 12.4 instead of 11.6 us at 16K, 17.4 instead
-// of 15.8 at 64K).
+// One workgroup per (tile, KV head, 32 of the tile's rows), in the order in which the lanes of the main kernel hold them: wave
+// (rb, half) merges 16 rows x 64 dims, lane (l16, lg) of it row l16, dims 16 i + 4 lg .. + 3, and every load is 1 KB in one piece.
 __global__ void __launch_bounds__(256)
 attn_combine_kernel(attn_args a) {
   const int t = blockIdx.x, g = blockIdx.y;
@@ -455,13 +504,14 @@ attn_combine_kernel(attn_args a) {
   if (nseg <= 1) return;
   const int4 ta = a.plan.tile_a[t];
   const int G = a.Hq / a.Hkv;
-  const int ml = blockIdx.z * 32 + (threadIdx.x >> 3), d0 = (threadIdx.x & 7) * 4;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4, rb = (threadIdx.x >> 6) & 1, half = threadIdx.x >> 7;
+  const int ml = blockIdx.z * 32 + 16 * rb + l16, d0 = 64 * half + 4 * lg;
   const int m = ta.y + ml;
   if (m >= ta.w) return;
   const int arow = a.plan.a_lo[ta.x] + m / G, hq = g * G + m % G;
   const size_t p0 = (size_t)g * a.plan.max_items + tb.x;
   const float2 *ml_p = a.plan.part_ml + p0 * kTM + ml;
-  const float *o_p = a.plan.part_o + (p0 * kTM + ml) * kD + d0;
+  const f32x4 *o_p = reinterpret_cast<const f32x4 *>(a.plan.part_o) + (p0 * (kTM / 16) + 2 * blockIdx.z + rb) * 512 + 256 * half + lane;
   float acc[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
@@ -475,7 +525,7 @@ attn_combine_kernel(attn_args a) {
       const size_t s = (size_t)min(s0 + u, nseg - 1) * kTM;
       st[u] = ml_p[s];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[u][i] = *reinterpret_cast<const f32x4 *>(o_p + s * kD + 32 * i);
+      for (int i = 0; i < 4; ++i) v[u][i] = o_p[s * (kD / 4) + 64 * i];
     }
     float m = M;
 #pragma unroll
@@ -500,7 +550,7 @@ attn_combine_kernel(attn_args a) {
     bf16x4 v;
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = a3_f2bf(acc[4 * i + e] * inv);
-    *reinterpret_cast<bf16x4 *>(orow + 32 * i) = v;
+    *reinterpret_cast<bf16x4 *>(orow + 16 * i) = v;
   }
 }
 
@@ -666,7 +716,7 @@ size_t a3_attn_ws_bytes(const a3_layout *L, int max_active_rows) {
   const size_t per_req = a3_align_up((size_t)(L->n_req + 1) * sizeof(int), 256);
   const size_t tiles = attn_max_tiles(L, max_active_rows), items = attn_max_items(L, max_active_rows);
   return 2 * per_req + a3_align_up(tiles * sizeof(int4), 256) + a3_align_up(tiles * sizeof(int2), 256) +
-         a3_align_up((tiles + 1) * sizeof(int), 256) + a3_align_up(items * sizeof(int4), 256) +
+         a3_align_up((tiles + 1) * sizeof(int), 256) + a3_align_up(items * 2 * sizeof(int4), 256) +
          a3_align_up((size_t)(attn_wgs_per_head(L) + 1) * sizeof(int), 256) + 256 +
          a3_align_up(items * L->n_kv_heads * kTM * kD * sizeof(float), 256) +
          a3_align_up(items * L->n_kv_heads * kTM * sizeof(float2), 256) + 2048;
@@ -694,6 +744,8 @@ static a3_status attn_launch(const a3_layout *L, const void *q_act, const int *a
   a.act_idx = act_idx; a.seg_start = L->seg_start; a.tok_req = L->tok_req;
   a.n_act = n_act; a.Hq = L->n_q_heads; a.Hkv = L->n_kv_heads; a.d = L->head_dim;
   a.scale2 = a3_scale_of(L) * kLog2e;
+  const unsigned G = (unsigned)(L->n_q_heads / L->n_kv_heads);
+  a.inv_G = G > 1 ? (uint32_t)(((1ull << 32) + G - 1) / G) : 0;
   memset(&a.plan, 0, sizeof(a.plan));
   if (L->dtype == A3_BF16) {
     // (a limit of an earlier kernel's 32-bit byte offsets; this one's bases are 64-bit per tile.  The line stays: what lies

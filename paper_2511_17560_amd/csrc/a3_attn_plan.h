@@ -23,17 +23,19 @@ constexpr int kPlanLdsInts = 4096;  // LDS the plan kernel sets aside for the pl
 //   item  = the part of one share that lies in one tile: (tile, k_begin, k_end).  A tile that lies inside
 //           one share is finished by that workgroup; the others are cut into 2 or more items whose
 //           unnormalised partial results are merged afterwards, in key order.
+struct attn_item { int k_begin, k_end, kv_len, m0, m_end, a0, base, whole; };   // whole: the tile's only item
 struct attn_plan {
   int *a_lo;         // [n_req+1] first active row of each request
   int *tile_start;   // [n_req+1] first tile of each request
   int4 *tile_a;      // [max_tiles] (request, first m, visible keys of the last row, rows*G of the request)
   int2 *tile_b;      // [max_tiles] (first item, number of items)
   int *tile_pre;     // [max_tiles+1] key steps of all earlier tiles
-  int4 *items;       // [max_items] (tile, k_begin, k_end, 0), in work order
+  int4 *items;       // [max_items][2] all the attention kernel needs of an item (attn_item), in work order
   int *wg_start;     // [max_wgs+1] first item of each workgroup of a head
   int *counters;     // n_tiles, n_items, P, max_wgs the plan was made with (first in the workspace: its place
                      // does not depend on the sizes of the other arrays)
-  float *part_o;     // [Hkv * max_items][256][128] unnormalised partial O of cut tiles
+  float *part_o;     // [Hkv * max_items][16 rows x 16][16 dims x 8][lane][4] unnormalised partial O of cut tiles: lane (l16, lg)
+                     // holds row l16, dims 4 lg .. + 3 of a block
   float2 *part_ml;   // [Hkv * max_items][256]      (exponent reference in the exp2 domain, sum)
   int max_tiles, max_items, max_wgs;
 };
@@ -110,7 +112,7 @@ __device__ __forceinline__ void attn_plan_body(const attn_plan &p, const int *ac
 
   // ---- tiles and their running cost -------------------------------------------------------
   // A tile is laid out as `item_cost` units of start-up (fetching its queries and first keys, storing its
-  // result: three to five key steps) followed by one unit per key step.
+  // result, and the steps in which its rows end) followed by one unit per key step.
   int carry = 0;
   for (int base = 0; base < n_tiles; base += kPlanThreads) {
     const int t = base + tid;
@@ -171,7 +173,9 @@ __device__ __forceinline__ void attn_plan_body(const attn_plan &p, const int *ac
     const int pre = tile_pre[t] + item_cost, nxt = tile_pre[t + 1];      // key step s of the tile sits at pre + s
     const int it_b = (int)(s_beg > pre ? s_beg - pre : 0), it_e = (int)((s_end < nxt ? s_end : nxt) - pre);
     const int kv = in_lds ? tile_kv[t] : p.tile_a[t].z;
-    p.items[idx] = make_int4(t, it_b * kTK, min(kv, it_e * kTK), 0);
+    const int r = n_req == 1 ? 0 : upper_bound_i32(tile_start, n_req, t) - 1;
+    p.items[2 * idx] = make_int4(it_b * kTK, min(kv, it_e * kTK), kv, (t - tile_start[r]) * kTM);
+    p.items[2 * idx + 1] = make_int4((a_lo[r + 1] - a_lo[r]) * G, a_lo[r], seg_start[r], it_b == 0 && s_end >= nxt);
     if (it_b == 0) p.tile_b[t].x = idx;
   }
   // items of a tile = share boundaries strictly inside it + 1; boundary q lies at floor(q W / P)
@@ -203,11 +207,13 @@ int attn_wgs_per_head(const a3_layout *L) {
   return w;
 }
 
-// Start-up cost of an item in key steps (what the share boundaries are balanced with), or the tuning
-// value "attn_item_cost".
+// Start-up cost of an item in key steps (what the share boundaries are balanced with), or the tuning value
+// "attn_item_cost".  With 4, 8 and 10: 64K context 2801, 2746 and 2722 us, seven heads per KV head at 32K 1236, 1198 and 1205, all
+// rows of 16K 1712, 1654 and 1664, 5K 51.0, 49.5 and 53.4 (the last steps of a tile, where rows end one wave after the
+// other, and the change of rows take 20 - 25 thousand cycles, a step 2660).
 int attn_item_cost() {
   const int v = a3_knob(A3_KNOB_ATTN_ITEM_COST);
-  return v >= 0 && v <= 64 ? v : 4;
+  return v >= 0 && v <= 64 ? v : 8;
 }
 
 // every tile starts an item, every share boundary inside a tile starts another
@@ -226,7 +232,7 @@ inline void attn_plan_carve(const a3_layout *L, int n_act, void *ws, size_t ws_b
   p->tile_a = (int4 *)cur.take((size_t)max_tiles * sizeof(int4));
   p->tile_b = (int2 *)cur.take((size_t)max_tiles * sizeof(int2));
   p->tile_pre = (int *)cur.take((size_t)(max_tiles + 1) * sizeof(int));
-  p->items = (int4 *)cur.take((size_t)max_items * sizeof(int4));
+  p->items = (int4 *)cur.take((size_t)max_items * 2 * sizeof(int4));
   p->wg_start = (int *)cur.take((size_t)(wgs_per_head + 1) * sizeof(int));
   p->part_o = (float *)cur.take((size_t)max_items * Hkv * kTM * 128 * sizeof(float));
   p->part_ml = (float2 *)cur.take((size_t)max_items * Hkv * kTM * sizeof(float2));
