@@ -218,16 +218,20 @@ scores_bf16_kernel(scores_args a) {
   // holds that head's Q rows and partial statistics) ----------------------------------------------------
   const int g = blockIdx.x % a.Hkv;
   int rest = blockIdx.x / a.Hkv;
-  const int t = rest % a.n_tiles, r = rest / a.n_tiles;
+  // PASS 0 of the causal denominator: one more run per request, its question keys, each row up to its own token
+  const int n_runs = PASS == 0 && !REALIGN ? a.n_tiles + a.causal_q : a.n_tiles;
+  const int t = rest % n_runs, r = rest / n_runs;
+  const bool own = PASS == 0 && !REALIGN && t == a.n_tiles;
   // (a batch of one request: its lengths are the layout's maxima, known on the host; no loads before the first keys
   // are requested)
-  const int N = a.one_ctx_len >= 0 ? a.one_ctx_len : a.ctx_len[r];
-  const int i0 = t * a.tile_keys;
-  if (i0 >= N) return;
-  const int G = a.Hq / a.Hkv;
-  const int Mg = (a.one_ctx_len >= 0 ? a.one_q_len : a.q_len[r]) * G;   // rows of this KV head: m = j * G + hh
+  const int n_ctx = a.one_ctx_len >= 0 ? a.one_ctx_len : a.ctx_len[r];
+  const int i0 = own ? 0 : t * a.tile_keys;
+  if (!own && i0 >= n_ctx) return;
+  const int G = a.Hq / a.Hkv, n_q = a.one_ctx_len >= 0 ? a.one_q_len : a.q_len[r];
+  const int Mg = n_q * G;                                      // rows of this KV head: m = j * G + hh
   if (Mg <= 0) return;
-  const int s = a.one_ctx_len >= 0 ? 0 : a.seg_start[r], qrow0 = a.one_ctx_len >= 0 ? 0 : a.q_start[r];
+  const int N = own ? n_q : n_ctx;                             // keys of the part that this run belongs to (n_q <= 256 <= tile_keys)
+  const int s = (a.one_ctx_len >= 0 ? 0 : a.seg_start[r]) + (own ? n_ctx : 0), qrow0 = a.one_ctx_len >= 0 ? 0 : a.q_start[r];
   const row_map row_of{G, a.Hq, g, qrow0, a.inv_G};
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, lhi = lane >> 5;
@@ -442,7 +446,17 @@ scores_bf16_kernel(scores_args a) {
 
   f32x16 acc[2];
   bf16x8 kfr[kD / 16];
-  float run_max[2] = {-INFINITY, -INFINITY}, run_sum[2] = {0.f, 0.f};
+  // (a row may see none of a wave's question keys: its maximum stays finite and its weights come out as exp2(-inf) = 0)
+  const float none = own ? -3.402823466e38f : -INFINITY;
+  float run_max[2] = {none, none}, run_sum[2] = {0.f, 0.f};
+  int seen[2] = {N, N};                                        // PASS 0: keys that the lane's row of block b may see
+  if (own) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const uint32_t m = rg * 64 + b * 32 + l32;
+      seen[b] = min(N, (G > 1 ? (int)__umulhi(m, a.inv_G) : (int)m) + 1);
+    }
+  }
   // the eight K fragments of this wave's block of slot I, requested together
 #define A3_KFRAGS(I)                                                                                           \
   _Pragma("unroll") for (int ks_ = 0; ks_ < kD / 16; ++ks_)                                                    \
@@ -461,11 +475,13 @@ scores_bf16_kernel(scores_args a) {
     if (PASS == 0) {                                                                                           \
       /* lane: row (column l32 of block b); registers: keys key0 + 8 (x / 4) + 4 lhi + x % 4 */                \
       if (key0_ < N) {                                           /* the block holds a real key */              \
-        if (key0_ + 31 >= N) {                                                                                 \
-          int n_real = N - key0_ - 4 * lhi;                                                                    \
-          asm volatile("" : "+v"(n_real));                                                                     \
-          _Pragma("unroll") for (int b = 0; b < 2; ++b) _Pragma("unroll") for (int x = 0; x < 16; ++x)         \
-            if (8 * (x >> 2) + (x & 3) >= n_real) acc[b][x] = -INFINITY;                                       \
+        if (own || key0_ + 31 >= N) {                                                                          \
+          _Pragma("unroll") for (int b = 0; b < 2; ++b) {                                                      \
+            int n_real = seen[b] - key0_ - 4 * lhi;                                                            \
+            asm volatile("" : "+v"(n_real));                                                                   \
+            _Pragma("unroll") for (int x = 0; x < 16; ++x)                                                     \
+              if (8 * (x >> 2) + (x & 3) >= n_real) acc[b][x] = -INFINITY;                                     \
+          }                                                                                                    \
         }                                                                                                      \
         _Pragma("unroll") for (int b = 0; b < 2; ++b) {                                                        \
           float mx = fmaxf(acc[b][0], acc[b][1]);                                                              \
@@ -938,14 +954,17 @@ static int scores_row_chunks(const a3_layout *L) {
 // bf16 path: keys per workgroup.  A multiple of the 64-key ring slot in [256, 1024], chosen so that the
 // workgroups (one per CU at a time: 150 KB of LDS) fill the 256 CUs in as few, as full rounds as possible; a
 // workgroup's fixed cost (its Q tile, the merge of the partials, the start-up of the ring) is worth about 192 keys.
-static int scores_tile_keys_bf16(const a3_layout *L) {
+// own = 1: every request has one more run, its question keys (causal denominator).  Counted with the others: 16K keys x 8 KV
+// heads in runs of 512 are 256 workgroups, and the 8 more would begin when the first of these have ended.  (Votes, retention
+// and compaction at 16K keys, 64 question tokens: 54.9 us with a kernel for the question keys' share, 10 us of it, 48.2 with the run.)
+static int scores_tile_keys_bf16(const a3_layout *L, int own) {
   // more than 256 rows per KV head: the kernel that keeps a 256-key tile in LDS and walks the rows
   if (scores_row_chunks(L) > 1) return kRowsTileKeys;
   const long long per_tile = (long long)L->n_req * L->n_kv_heads;
   long long best_cost = -1;
   int best = kMinTileKeys;
   for (int tk = kMinTileKeys; tk <= kMaxTileKeys; tk += kSlotKeys) {
-    const long long wgs = per_tile * ((L->max_ctx_len + tk - 1) / tk);
+    const long long wgs = per_tile * ((L->max_ctx_len + tk - 1) / tk + own);
     const long long cost = ((wgs + 255) / 256) * (tk + 192);
     if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = tk; }
   }
@@ -981,7 +1000,7 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
   hipStream_t st = (hipStream_t)stream;
   const bool bf16 = L->dtype == A3_BF16;
   const size_t total_rows = (size_t)L->n_req * L->max_q_len * L->n_q_heads;   // upper bound, used as row pitch
-  const int tk = bf16 ? scores_tile_keys_bf16(L) : kTileKeys;
+  const int tk = bf16 ? scores_tile_keys_bf16(L, causal_q) : kTileKeys;
   const int n_tiles = (L->max_ctx_len + tk - 1) / tk;
   const int tk_min = bf16 ? kMinTileKeys : kTileKeys;
   const int max_tiles = (L->max_ctx_len + tk_min - 1) / tk_min;               // what the workspace is sized for
@@ -1012,7 +1031,9 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
     s = a3_rope_realign(L, k_cat, k_fused, stream);
     if (s != A3_OK) return s;
   }
-  if (causal_q) {
+  // the question keys' share of the denominators: a run of the first pass itself in scores_bf16_kernel, a kernel before the others
+  const bool own_runs = causal_q && bf16 && scores_row_chunks(L) == 1;
+  if (causal_q && !own_runs) {
     const dim3 qgrid((unsigned)((total_rows + 3) / 4));
     if (bf16) hipLaunchKernelGGL(scores_question_stats_kernel<bf16_t>, qgrid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL(scores_question_stats_kernel<float>, qgrid, dim3(256), 0, st, a);
@@ -1037,8 +1058,8 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
     if (e != hipSuccess) return a3_fail(A3_ERR_HIP, "a3_question_scores: cannot raise the dynamic LDS limit: %s", hipGetErrorString(e));
     a.merged = (n_tiles > 32 || scores_row_chunks(L) > 1) ? 1 : 0;
     const long long wgs = (long long)L->n_req * n_tiles * L->n_kv_heads;
-    A3_REQUIRE(wgs < (1LL << 31), A3_ERR_UNSUPPORTED, "a3_question_scores: batch too large");
-    const dim3 grid((unsigned)wgs);
+    A3_REQUIRE(wgs + own_runs * (long long)L->n_req * L->n_kv_heads < (1LL << 31), A3_ERR_UNSUPPORTED, "a3_question_scores: batch too large");
+    const dim3 grid((unsigned)wgs), grid0((unsigned)(wgs + own_runs * (long long)L->n_req * L->n_kv_heads));
     if (scores_row_chunks(L) > 1) {
       // (tile_keys is kRowsTileKeys here; every row of a KV head in one workgroup)
       const dim3 rgrid((unsigned)n_tiles, (unsigned)L->n_kv_heads, (unsigned)L->n_req);
@@ -1048,7 +1069,7 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
       hipLaunchKernelGGL((scores_rows_bf16_kernel<1, false>), rgrid, dim3(256), kScoresRowsLds, st, a);
     } else {
       if (fuse) hipLaunchKernelGGL((scores_bf16_kernel<0, true>), grid, dim3(kScoreThreads), kScoresLds, st, a);
-      else hipLaunchKernelGGL((scores_bf16_kernel<0, false>), grid, dim3(kScoreThreads), kScoresLds, st, a);
+      else hipLaunchKernelGGL((scores_bf16_kernel<0, false>), grid0, dim3(kScoreThreads), kScoresLds, st, a);
       if (a.merged) hipLaunchKernelGGL(scores_combine_kernel, dim3((unsigned)((total_rows + 15) / 16)), dim3(256), 0, st, a);
       hipLaunchKernelGGL((scores_bf16_kernel<1, false>), grid, dim3(kScoreThreads), kScoresLds, st, a);
     }
