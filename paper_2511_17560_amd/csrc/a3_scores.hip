@@ -582,7 +582,8 @@ scores_bf16_kernel(scores_args a) {
 // in groups of 64 with their Q fragments straight from global memory (L2).  The tile arrives in four quarters
 // of 64 keys, all requested up front; the logits of a wave's first 64 rows against a quarter are formed as soon
 // as it has landed.  PASS 0 leaves (max, sum exp) per (tile, row), a small kernel merges them per row, PASS 1
-// forms the column sums of exp2(l - stat).  Same results layout as the kernel above.
+// forms the column sums of exp2(l - stat).  Same results layout as the kernel above.  (The question keys as one more tile of
+// PASS 0: votes of eight requests, 65k keys, 32 .. 128 question tokens, 205 -> 148 us, of 5120 keys and 80 tokens 45.2 -> 31.)
 // ---------------------------------------------------------------------------------------
 constexpr int kRowsTileKeys = 256;
 constexpr size_t kScoresRowsLds = (size_t)kRowsTileKeys * kKRowBytes + 4 * 64 * sizeof(float) +
@@ -596,13 +597,15 @@ scores_rows_bf16_kernel(scores_args a) {
   float *red = reinterpret_cast<float *>(St + 4 * 64);                                // [4 waves][256 keys]
 
   const int r = blockIdx.z, g = blockIdx.y;
-  const int N = a.ctx_len[r];
-  const int i0 = blockIdx.x * kRowsTileKeys;
+  // PASS 0 of the causal denominator: one more tile, the question keys (at most 256), each row up to its own token
+  const bool own = PASS == 0 && !REALIGN && (int)blockIdx.x == a.n_tiles;
+  const int nq = a.q_len[r], n_ctx = a.ctx_len[r];
+  const int N = own ? nq : n_ctx;
+  const int i0 = own ? 0 : blockIdx.x * kRowsTileKeys;
   if (i0 >= N) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, lhi = lane >> 5;
-  const int s = a.seg_start[r];
-  const int nq = a.q_len[r];
+  const int s = a.seg_start[r] + (own ? n_ctx : 0);
   const int G = a.Hq / a.Hkv;
   const int Mg = nq * G;                // rows of this KV head: m = j*G + hh
   const int qrow0 = a.q_start[r];
@@ -612,23 +615,30 @@ scores_rows_bf16_kernel(scores_args a) {
   // Q fragments of this wave's first 64 rows: requested before the K tile so that both latencies overlap
   // (rows past Mg are clamped and ignored later)
   bf16x8 qf[2][kD / 16];
-  int row_id[2];
+  int row_id[2], seen[2];                                      // seen: keys that the row may see (PASS 0)
 #define A3_LOAD_Q(RB0)                                                                                 \
   _Pragma("unroll") for (int b = 0; b < 2; ++b) {                                                      \
     const int m_ = min((RB0) + b * 32 + l32, Mg - 1);                                                  \
+    seen[b] = own ? min(N, m_ / G + 1) : N;                                                            \
     row_id[b] = (qrow0 + m_ / G) * a.Hq + g * G + m_ % G;      /* row of the [sum q_len * Hq] row space */ \
     const bf16_t *qp_ = Q + (size_t)row_id[b] * kD + lhi * 8;                                          \
     _Pragma("unroll") for (int ks = 0; ks < kD / 16; ++ks) qf[b][ks] = *reinterpret_cast<const bf16x8 *>(qp_ + ks * 16); \
   }
   if (Mg > 0) { A3_LOAD_Q(min(wave * 64, Mg - 1)) }
   const bool have_rows = wave * 64 < Mg;                       // this wave has a first group of rows
-  if (PASS == 1) {
-    // max + log2(sum) of this wave's 64 rows, read back as broadcasts below; rows past Mg contribute 0
-    const int m = wave * 64 + lane;
-    float st = INFINITY;                                       // exp2(x - inf) = 0
-    if (m < Mg) st = a.stats[(qrow0 + m / G) * a.Hq + g * G + m % G].x;
-    St[wave * 64 + lane] = st;                                 // same-wave write/read: no barrier needed
+  // PASS 1: max + log2(sum) of the rows of the lane's accumulators, once a round (read from LDS at every use they were 8 reads
+  // of 16 bytes a key block); infinite for a row past Mg, whose weights come out as exp2(-inf) = 0
+  f32x16 st[2];
+#define A3_START(RB0)                                                                                  \
+  if (PASS == 1) {                                                                                     \
+    const int m_ = (RB0) + lane;                                                                       \
+    float st_ = INFINITY;                                                                              \
+    if (m_ < Mg) st_ = a.stats[(qrow0 + m_ / G) * a.Hq + g * G + m_ % G].x;                            \
+    St[wave * 64 + lane] = st_;                                /* same-wave write/read: no barrier needed */ \
+    _Pragma("unroll") for (int b = 0; b < 2; ++b) _Pragma("unroll") for (int x = 0; x < 16; ++x)       \
+      st[b][x] = St[wave * 64 + b * 32 + 8 * (x >> 2) + 4 * lhi + (x & 3)];                            \
   }
+  A3_START(wave * 64)
 
   // The K tile arrives in four quarters of 64 keys.  Every load of the tile is issued up front; the logits
   // of the wave's first 64 rows against quarter q are formed as soon as that quarter is in LDS, while the
@@ -642,7 +652,9 @@ scores_rows_bf16_kernel(scores_args a) {
   float colsum[kKB];
 #pragma unroll
   for (int kb = 0; kb < kKB; ++kb) colsum[kb] = 0.f;
-  float run_max[2] = {-INFINITY, -INFINITY}, run_sum[2] = {0.f, 0.f};
+  // (a row may see none of a wave's question keys: its maximum stays finite and its weights come out as exp2(-inf) = 0)
+  const float none = own ? -3.402823466e38f : -INFINITY;
+  float run_max[2] = {none, none}, run_sum[2] = {0.f, 0.f};
 
   // logits of the current 64 rows (fragments in qf) against key block KB, folded into the running row
   // statistics (pass A) or into the column sums (pass B)
@@ -660,12 +672,12 @@ scores_rows_bf16_kernel(scores_args a) {
     }                                                                                                          \
     if (PASS == 0) {                                                                                           \
       /* lane: row (column l32 of block b); registers: keys i0 + 32 kb + 8(x/4) + 4 lhi + x%4 */               \
-      const bool tail = i0 + 32 * (KB) + 31 >= N;                                                              \
+      const bool tail = own || i0 + 32 * (KB) + 31 >= N;                                                       \
       _Pragma("unroll") for (int b = 0; b < 2; ++b) {                                                          \
         if (tail) {                                                                                            \
           /* (the empty statement keeps the 16 comparisons of each of the unrolled blocks here: gathered at */ \
           /* the top of the kernel their lane masks do not fit the scalar registers)                        */ \
-          int n_real = N - i0 - 32 * (KB) - 4 * lhi;                                                           \
+          int n_real = seen[b] - i0 - 32 * (KB) - 4 * lhi;                                                     \
           asm volatile("" : "+v"(n_real));                                                                     \
           _Pragma("unroll") for (int x = 0; x < 16; ++x)                                                       \
             if (8 * (x >> 2) + (x & 3) >= n_real) acc[b][x] = -INFINITY;                                       \
@@ -681,23 +693,38 @@ scores_rows_bf16_kernel(scores_args a) {
       }                                                                                                        \
     } else {                                                                                                   \
       /* lane: key l32 of block kb; registers: rows 8(x/4) + 4 lhi + x%4 of row block b */                     \
-      float part = 0.f;                                                                                        \
-      _Pragma("unroll") for (int b = 0; b < 2; ++b)                                                            \
-        _Pragma("unroll") for (int x = 0; x < 16; ++x) {                                                       \
-          const float st = St[wave * 64 + b * 32 + 8 * (x >> 2) + 4 * lhi + (x & 3)];                          \
-          part += fast_exp2(fmaf(acc[b][x], a.scale2, -st));                                                   \
-        }                                                                                                      \
-      colsum[KB] += part;                                                                                      \
+      float p0 = 0.f, p1 = 0.f;                                                                                \
+      _Pragma("unroll") for (int b = 0; b < 2; ++b) _Pragma("unroll") for (int x = 0; x < 16; x += 2) {        \
+        p0 += fast_exp2(fmaf(acc[b][x], a.scale2, -st[b][x]));                                            \
+        p1 += fast_exp2(fmaf(acc[b][x + 1], a.scale2, -st[b][x + 1]));                                    \
+      }                                                                                                        \
+      colsum[KB] += p0 + p1;                                                                                   \
     }                                                                                                          \
   }
-  // the 64 rows are done: pass A leaves their (max, sum) over this tile
-#define A3_ROWS_DONE(RB0)                                                                                      \
+  // the round is done: pass A leaves the (max, sum) of its rows over this tile; waves that share a group (by key blocks, see the
+  // further rounds) merge theirs in LDS.  One that saw no key has (max, sum) = (-inf, 0).
+  int share = 1, sub = 0, rb = wave * 64;                      // waves that share the wave's group, which of them it is, its first row
+  float2 *pair = reinterpret_cast<float2 *>(red);
+#define A3_ROWS_DONE()                                                                                         \
   if (PASS == 0) {                                                                                             \
-    _Pragma("unroll") for (int b = 0; b < 2; ++b) {                                                            \
-      const float z = halves_sum(run_sum[b]);                                                                  \
-      if (lhi == 0 && (RB0) + b * 32 + l32 < Mg)                                                               \
-        a.part[(size_t)blockIdx.x * a.total_rows + row_id[b]] = make_float2(run_max[b], z);                    \
+    float z[2];                                                                                                \
+    _Pragma("unroll") for (int b = 0; b < 2; ++b) z[b] = halves_sum(run_sum[b]);                               \
+    if (share > 1) {                                                                                           \
+      _Pragma("unroll") for (int b = 0; b < 2; ++b)                                                            \
+        if (lhi == 0) pair[wave * 64 + b * 32 + l32] = make_float2(run_max[b], z[b]);                          \
+      __syncthreads();                                                                                         \
+      _Pragma("unroll") for (int b = 0; b < 2; ++b)                                                            \
+        if (sub == 0)                                                                                          \
+          for (int w = wave + 4 / share; w < 4; w += 4 / share) {                                              \
+            const float2 o = pair[w * 64 + b * 32 + l32];                                                      \
+            const float mn = fmaxf(run_max[b], o.x);           /* sub 0 has key block 0: finite */             \
+            z[b] = z[b] * fast_exp2(run_max[b] - mn) + (o.y > 0.f ? o.y * fast_exp2(o.x - mn) : 0.f);          \
+            run_max[b] = mn;                                                                                   \
+          }                                                                                                    \
     }                                                                                                          \
+    if (sub == 0)                                                                                              \
+      _Pragma("unroll") for (int b = 0; b < 2; ++b)                                                            \
+        if (lhi == 0 && rb + b * 32 + l32 < Mg) a.part[(size_t)blockIdx.x * a.total_rows + row_id[b]] = make_float2(run_max[b], z[b]); \
   }
 
   // ---- K tile: 256 keys x 128 dims of head g, global memory -> LDS directly (16 bytes per lane, lane i
@@ -813,22 +840,29 @@ scores_rows_bf16_kernel(scores_args a) {
       }
     }
   }
-  if (have_rows) { A3_ROWS_DONE(wave * 64) }
+  if (have_rows) { A3_ROWS_DONE() }
 
-  // ---- the wave's further rows (more than 256 rows per KV head): the whole tile is in LDS by now --------------
-  for (int rb0 = wave * 64 + 256; rb0 < Mg; rb0 += 256) {      // this wave's rows rb0 .. rb0+63
-    A3_LOAD_Q(rb0)
-    if (PASS == 1) {
-      const int m = rb0 + lane;
-      float st = INFINITY;
-      if (m < Mg) st = a.stats[(qrow0 + m / G) * a.Hq + g * G + m % G].x;
-      St[wave * 64 + lane] = st;
-    }
-    run_max[0] = run_max[1] = -INFINITY;
+  // ---- the further rounds (more than 256 rows per KV head): the whole tile is in LDS by now --------------
+  // A group of 64 rows each, or, where one or two are left, for four or two waves with every fourth or second key block each:
+  // 80 question tokens x 4 heads are five groups, and the fifth on one wave alone took as long as the four before it (16K keys, both
+  // passes and the small kernels 53.9 -> 48.4 us; 64K keys, 96 tokens, 169 -> 159; 128 tokens, eight groups, as before).  Not in the
+  // first round, where a wave without rows leaves its SIMD to the other workgroup of the CU.
+  for (int rb0 = 256; rb0 < Mg; rb0 += 256) {
+    const int left = (Mg - rb0 + 63) >> 6;                     // groups
+    share = left == 1 ? 4 : left == 2 ? 2 : 1;
+    sub = left == 1 ? wave : left == 2 ? wave >> 1 : 0;
+    rb = rb0 + 64 * (left == 1 ? 0 : left == 2 ? wave & 1 : wave);
+    if (rb >= Mg) break;                                       // (a wave without rows: three groups are left, none of them shared)
+    A3_LOAD_Q(rb)
+    A3_START(rb)
+    run_max[0] = run_max[1] = none;
     run_sum[0] = run_sum[1] = 0.f;
-    for (int kb = 0; kb < n_kb; ++kb) A3_KEY_BLOCK(kb)
-    A3_ROWS_DONE(rb0)
+#pragma unroll
+    for (int kb = 0; kb < kKB; ++kb)                           // (unrolled: the column sums are registers)
+      if (kb < n_kb && (kb & (share - 1)) == sub) A3_KEY_BLOCK(kb)
+    A3_ROWS_DONE()
   }
+#undef A3_START
 #undef A3_KEY_BLOCK
 #undef A3_ROWS_DONE
 #undef A3_LOAD_Q
@@ -954,9 +988,9 @@ static int scores_row_chunks(const a3_layout *L) {
 // bf16 path: keys per workgroup.  A multiple of the 64-key ring slot in [256, 1024], chosen so that the
 // workgroups (one per CU at a time: 150 KB of LDS) fill the 256 CUs in as few, as full rounds as possible; a
 // workgroup's fixed cost (its Q tile, the merge of the partials, the start-up of the ring) is worth about 192 keys.
-// own = 1: every request has one more run, its question keys (causal denominator).  Counted with the others: 16K keys x 8 KV
-// heads in runs of 512 are 256 workgroups, and the 8 more would begin when the first of these have ended.  (Votes, retention
-// and compaction at 16K keys, 64 question tokens: 54.9 us with a kernel for the question keys' share, 10 us of it, 48.2 with the run.)
+// own = 1: every request has one more, short run in the first pass, its question keys (causal denominator), which costs as much as
+// its keys where the last round has no room for it: 16K keys x 8 KV heads take 29 runs of 576, not 32 of 512 (both passes 32.5 us and
+// 34.8 without the one more), 64K keys stay at 64 runs of 1024 (98 us; 95 runs of 704 109).
 static int scores_tile_keys_bf16(const a3_layout *L, int own) {
   // more than 256 rows per KV head: the kernel that keeps a 256-key tile in LDS and walks the rows
   if (scores_row_chunks(L) > 1) return kRowsTileKeys;
@@ -964,8 +998,9 @@ static int scores_tile_keys_bf16(const a3_layout *L, int own) {
   long long best_cost = -1;
   int best = kMinTileKeys;
   for (int tk = kMinTileKeys; tk <= kMaxTileKeys; tk += kSlotKeys) {
-    const long long wgs = per_tile * ((L->max_ctx_len + tk - 1) / tk + own);
-    const long long cost = ((wgs + 255) / 256) * (tk + 192);
+    const long long wgs = per_tile * ((L->max_ctx_len + tk - 1) / tk);
+    long long cost = 2 * ((wgs + 255) / 256) * (tk + 192);      // the two passes
+    if (own && (wgs - 1) % 256 + 1 + per_tile > 256) cost += (L->max_q_len + kSlotKeys - 1) / kSlotKeys * kSlotKeys + 192;
     if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = tk; }
   }
   return best;
@@ -1031,8 +1066,9 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
     s = a3_rope_realign(L, k_cat, k_fused, stream);
     if (s != A3_OK) return s;
   }
-  // the question keys' share of the denominators: a run of the first pass itself in scores_bf16_kernel, a kernel before the others
-  const bool own_runs = causal_q && bf16 && scores_row_chunks(L) == 1;
+  // the question keys' share of the denominators: a run of the first pass itself in bf16, up to the 256 keys of a tile; a kernel
+  // before the passes otherwise
+  const bool own_runs = causal_q && bf16 && L->max_q_len <= kRowsTileKeys;
   if (causal_q && !own_runs) {
     const dim3 qgrid((unsigned)((total_rows + 3) / 4));
     if (bf16) hipLaunchKernelGGL(scores_question_stats_kernel<bf16_t>, qgrid, dim3(256), 0, st, a);
@@ -1062,9 +1098,9 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
     const dim3 grid((unsigned)wgs), grid0((unsigned)(wgs + own_runs * (long long)L->n_req * L->n_kv_heads));
     if (scores_row_chunks(L) > 1) {
       // (tile_keys is kRowsTileKeys here; every row of a KV head in one workgroup)
-      const dim3 rgrid((unsigned)n_tiles, (unsigned)L->n_kv_heads, (unsigned)L->n_req);
+      const dim3 rgrid((unsigned)n_tiles, (unsigned)L->n_kv_heads, (unsigned)L->n_req), rgrid0((unsigned)(n_tiles + own_runs), rgrid.y, rgrid.z);
       if (fuse) hipLaunchKernelGGL((scores_rows_bf16_kernel<0, true>), rgrid, dim3(256), kScoresRowsLds, st, a);
-      else hipLaunchKernelGGL((scores_rows_bf16_kernel<0, false>), rgrid, dim3(256), kScoresRowsLds, st, a);
+      else hipLaunchKernelGGL((scores_rows_bf16_kernel<0, false>), rgrid0, dim3(256), kScoresRowsLds, st, a);
       hipLaunchKernelGGL(scores_combine_kernel, dim3((unsigned)((total_rows + 15) / 16)), dim3(256), 0, st, a);
       hipLaunchKernelGGL((scores_rows_bf16_kernel<1, false>), rgrid, dim3(256), kScoresRowsLds, st, a);
     } else {
