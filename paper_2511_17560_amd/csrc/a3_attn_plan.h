@@ -209,11 +209,15 @@ int attn_wgs_per_head(const a3_layout *L) {
 
 // Start-up cost of an item in key steps (what the share boundaries are balanced with), or the tuning value
 // "attn_item_cost".  With 4, 8 and 10: 64K context 2801, 2746 and 2722 us, seven heads per KV head at 32K 1236, 1198 and 1205, all
-// rows of 16K 1712, 1654 and 1664, 5K 51.0, 49.5 and 53.4 (the last steps of a tile, where rows end one wave after the
-// other, and the change of rows take 20 - 25 thousand cycles, a step 2660).
-int attn_item_cost() {
+// rows of 16K 1712, 1654 and 1664 (the last steps of a tile, where rows end one wave after the other, and the change of rows take
+// 20 - 25 thousand cycles, a step 2660).  Requests of few rows leave a share so few steps that a tile's start-up overlaps the
+// loads of the others: with 4 and 8, whole calls, 500 rows of context 21.3 and 23.0 us (seven heads 22.5 and 25.1), 1000 25.1 and 26.6,
+// 3000 35.8 and 37.2, 8 x 1000 55.1 and 58.2 (49.3 and 47.8), 4 x 500 29.7 and 27.8, all rows of 1100 34.1 and 36.2; 4000 43.0 and
+// 43.1 (40.0 and 40.6), 5120 52.3 and 51.0 (47.5 and 48.4), 3 x 5000 95 and 95.5 (86.5 and 84.8): the line lies between these.
+constexpr int kShortRequestRows = 4608;
+int attn_item_cost(const a3_layout *L) {
   const int v = a3_knob(A3_KNOB_ATTN_ITEM_COST);
-  return v >= 0 && v <= 64 ? v : 8;
+  return v >= 0 && v <= 64 ? v : L->max_ctx_len + L->max_q_len <= kShortRequestRows ? 4 : 8;
 }
 
 // every tile starts an item, every share boundary inside a tile starts another
