@@ -125,32 +125,32 @@ attn_bf16_kernel(attn_args a) {
   const uint32_t vkey_off = (uint32_t)(16 * (wave >> 2) + (wave & 3) + 4 * lg) * pitch;
   const uint32_t kpiece = 16 * (l16 ^ lg), vpiece = 16 * (l16 ^ (8 * (lg & 1)));
   const uint32_t k_off[2] = {kkey_off + kpiece, kkey_off + 32 * pitch + kpiece}, v_off[2] = {vkey_off + vpiece, vkey_off + 32 * pitch + vpiece};
-  // K of a tile is requested one tile before its V: l_* the tile whose K comes next, v_* the one before it.  Descriptors of the
-  // request and head end behind the item's last visible key: past it the loads bring zeros (also past the last tile of the stream)
-  int l_item = item_begin, l_steps;                          // tiles of the item from this one on
+  // The descriptors of a request and head end behind the item's last visible key: past it the loads bring zeros.  l_k, l_v: of
+  // the tile whose K comes next, v_v: of the one before it
+  int l_item = item_begin;
   u32x4 l_k, l_v, v_v;
-  uint32_t l_at, v_at = 0;                                   // byte offsets of the tiles
+  attn_stream ld = {0, 0, 0};
   bool l_same = false;                                       // both tiles are of one item
+  constexpr uint32_t kRowBytes = kD * sizeof(bf16_t);
   auto load_from = [&](int i) {
     const attn_item d = item_at(i);
-    l_steps = (d.k_end - d.k_begin + kTK - 1) / kTK;
-    l_at = (uint32_t)d.k_begin * pitch;
-    const uint32_t bytes = (uint32_t)(d.kv_len - 1) * pitch + kD * sizeof(bf16_t);
-    const uint64_t at = ((uint64_t)(uint32_t)d.base * a.Hkv + g) * (kD * sizeof(bf16_t)), pk = (uint64_t)a.k + at, pv = (uint64_t)a.v + at;
+    ld.enter(d.k_begin, d.k_end, pitch);
+    const uint32_t bytes = attn_stream::bytes(d.kv_len, pitch, kRowBytes);
+    const uint64_t at = ((uint64_t)(uint32_t)d.base * a.Hkv + g) * kRowBytes, pk = (uint64_t)a.k + at, pv = (uint64_t)a.v + at;
     l_k = u32x4{(uint32_t)pk, (uint32_t)(pk >> 32) & 0xffffu, bytes, 0x00020000u};
     l_v = u32x4{(uint32_t)pv, (uint32_t)(pv >> 32) & 0xffffu, bytes, 0x00020000u};
   };
-  auto load_step = [&]() { v_at = l_at; l_at += kTK * pitch; };
+  auto load_step = [&]() { ld.step(pitch, l_k[2], kRowBytes); };
   auto load_on = [&]() {                                     // what else there is to do behind load_step
     v_v = l_v;
-    l_same = --l_steps > 0;
+    l_same = ld.same();
     if (!l_same) {
       if (l_item + 1 < item_end) {
         load_from(++l_item);
         if ((l_item - item_begin) % (kTableItems / 2) == kTableItems / 4)
           table_fill(l_item + kTableItems / 4, kTableItems / 2);
       } else {
-        l_steps = 1 << 30;
+        ld.end();
       }
     }
   };
@@ -161,8 +161,8 @@ attn_bf16_kernel(attn_args a) {
                  :: "s"(stage), "s"(to), "v"(off), "s"(base), "s"(at) : "memory", "scc");
   };
   const uint32_t to_k = lds_base + wave * kKPiece, to_v = lds_base + kVAt + wave * kVPiece;
-  auto load_k = [&](uint32_t stage, int i) { dma(l_k, l_at, k_off[i], stage, to_k + i * 8 * kKPiece); };
-  auto load_v = [&](uint32_t stage, int i) { dma(v_v, v_at, v_off[i], stage, to_v + i * 8 * kVPiece); };
+  auto load_k = [&](uint32_t stage, int i) { dma(l_k, ld.at, k_off[i], stage, to_k + i * 8 * kKPiece); };
+  auto load_v = [&](uint32_t stage, int i) { dma(v_v, ld.v_at, v_off[i], stage, to_v + i * 8 * kVPiece); };
 
   // ---- rows of an item: lane (l16, lg) holds rows m0 + 32 wave + 16 rb + l16 ---------------------------------------
   bf16x8 qf[2][4];
@@ -442,7 +442,7 @@ attn_bf16_kernel(attn_args a) {
     if (item == item_end) break;
     if (fresh || first) continue;
     // Tiles of the same items here and in the stream of loads with nothing masked; then tiles that this wave only loads for
-    const int rest = l_same ? min((cur.k_end - k0 + kTK - 1) / kTK, l_steps) - 1 : 0;
+    const int rest = l_same ? ld.calm((cur.k_end - k0 + kTK - 1) / kTK) : 0;
     if (act && act_prev) {
       const int calm = min((min_limit + 1 - k0) / kTK, rest);
       if (calm > 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // (or the compiler waits in the loop, for rows loaded long ago)
@@ -454,7 +454,7 @@ attn_bf16_kernel(attn_args a) {
       }
       if (calm > 0) {
         k0 += calm * kTK;
-        l_steps -= calm;
+        ld.pass(calm);
       }
     } else if (!act && !act_prev && rest > 0) {
       for (int c = 0; c < rest; ++c) {
@@ -465,7 +465,7 @@ attn_bf16_kernel(attn_args a) {
         __builtin_amdgcn_s_barrier();
       }
       k0 += rest * kTK;
-      l_steps -= rest;
+      ld.pass(rest);
     }
   }
   // ---- P V of the last tile

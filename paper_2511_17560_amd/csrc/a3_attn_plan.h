@@ -4,12 +4,12 @@
 // a3_attn.hip and a3_topk.hip; device code is inlined into both (no relocatable device code).
 #pragma once
 
+#include "a3_attn_stream.h"
 #include "a3_internal.h"
 
 namespace {
 
 constexpr int kTM = 256;            // packed (row, head) pairs per work item: 32 per wave of the attention kernel
-constexpr int kTK = 64;             // keys per tile
 constexpr int kMinSteps = 4;        // key steps of a share, at least (2K context: 37 us with 8, 33 with 4 or less)
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanLdsInts = 4096;  // LDS the plan kernel sets aside for the plan's small arrays (16 KB)
