@@ -262,8 +262,8 @@ attn_bf16_kernel(attn_args a) {
   // The two waves of a SIMD belong to different groups and run in opposite phases, one barrier apart: while one has the
   // matrix pipe (P V of tile u - 1, then S of tile u), the other does the softmax of its tile on the vector unit.  Group 0
   // multiplies tile u in phase 2 u, group 1 in phase 2 u + 1.  K of tile u + 3 and V of tile u + 2 are requested at the end of the
-  // matrix phase of tile u, over K of tile u - 1 and V of tile u - 2, which both groups have read; at the end of the vector phase
-  // every wave waits for all but these, so that K of tile u + 1 and V of tile u are there one phase before group 0 reads them.
+  // matrix phase of tile u, over K of tile u - 1 and V of tile u - 2, which both groups have read; in the vector phase every wave
+  // waits for all but these (attn_waits_behind), so that K of tile u + 2 and V of tile u + 1 are there when group 0 reads them.
   // What a phase may hold, measured in a loop of nothing else (cycles per tile of two phases):
   //   68 products with at most one LDS read right behind each: 2250.  A read costs nothing there, but 6 - 12 cycles of its wave behind
   //   a vector instruction or another read.
@@ -366,9 +366,16 @@ attn_bf16_kernel(attn_args a) {
       for (int q = 0; q < 16; ++q) A3_EXP(q)
     }
   };
-  auto phase_end = [&](bool wait) {
+  // all but the four requests of this tile have landed; memory accesses stay on their side of it
+  auto landed = [&]() {
+    asm volatile("" ::: "memory");
     A3_FENCE
-    if (wait) __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));
+    A3_FENCE
+    asm volatile("" ::: "memory");
+  };
+  auto phase_end = [&]() {
+    A3_FENCE
 #pragma unroll
     for (int n = 0; n < kAhead; ++n) { A3_VREAD(n, 0) A3_VREAD(n, 1) }
     A3_FENCE
@@ -427,7 +434,8 @@ attn_bf16_kernel(attn_args a) {
     const bool fresh = first;
     first = false;
     k0 += kTK;
-    if (k0 >= cur.k_end) {
+    if (attn_waits_behind(fresh, k0 >= cur.k_end)) landed();
+    if (k0 >= cur.k_end) {                                   // (the rows are requested behind the wait, which does not count them)
       prev_item = item; prev_whole = cur.whole;
       prev_row[0] = out_row[0]; prev_row[1] = out_row[1];
       has_prev = first = true;
@@ -438,7 +446,7 @@ attn_bf16_kernel(attn_args a) {
       }
     }
     act = k0 <= max_limit;
-    phase_end(!fresh && !first);                             // (all loads up to a fresh tile's have landed before its stores)
+    phase_end();
     if (item == item_end) break;
     if (fresh || first) continue;
     // Tiles of the same items here and in the stream of loads with nothing masked; then tiles that this wave only loads for
@@ -450,7 +458,8 @@ attn_bf16_kernel(attn_args a) {
         pv_products();
         s_products();
         check(weights());
-        phase_end(true);
+        landed();
+        phase_end();
       }
       if (calm > 0) {
         k0 += calm * kTK;

@@ -34,3 +34,8 @@ struct attn_stream {
   constexpr int calm(int tiles) const { return (tiles < left ? tiles : left) - 1; }
   constexpr void pass(int tiles) { left -= tiles; }
 };
+
+// Behind the softmax of a tile and before it requests the rows of the next item, a wave waits for all but the tile's own requests (K of
+// tile u + 3 and V of tile u + 2): V of tile u + 1, which every wave reads two phases later, has then landed.  The first tile of an
+// item needs no wait here: it waits for everything in its matrix phase, before its stores and its requests.
+constexpr bool attn_waits_behind(bool first_of_item, bool /*last_of_item*/) { return !first_of_item; }

@@ -1,7 +1,8 @@
 """The attention's stream of loads (csrc/a3_attn_stream.h), compiled for the CPU and walked as the kernel walks it: K of every tile
 of every item in order and V one request later, stretches of tiles in steps alone included; no request, also not those behind the
 stream's last tile, starts behind the last visible key of its descriptor, and no lane's offset passes 32 bits at the longest request
-that is accepted."""
+that is accepted.  And the kernel's phases: what a phase reads of K and V has been waited for by the waves that requested it, with a barrier
+between, whatever the lengths of the items; and no request overwrites a tile that is still to be read."""
 import os
 import shutil
 import subprocess
@@ -79,13 +80,77 @@ int main() {
 }
 """
 
+PHASES = r"""
+#include <cstdio>
+#include <deque>
+#include <map>
+#include <random>
+#include <vector>
+#include "a3_attn_stream.h"
+// Group g multiplies tile u (and reads K of u, V of u - 1) in phase 2 u + g and reads V of u at the end of phase 2 u + 1 + g.
+static int check(const std::vector<int> &items) {            // tiles of each
+  std::vector<char> first, last;
+  for (int n : items)
+    for (int i = 0; i < n; ++i) { first.push_back(i == 0); last.push_back(i == n - 1); }
+  const int tiles = (int)first.size();
+  enum { K, V, OTHER };
+  std::map<int, int> landed[2][2], asked[2][2];              // [group][K, V] of a tile: phase in which it was waited for, requested
+  for (int g = 0; g < 2; ++g) {
+    std::deque<std::pair<int, int>> open;                    // requests in order
+    auto ask = [&](int what, int tile, int n, int phase) {
+      for (int i = 0; i < n; ++i) open.push_back({what, tile});
+      if (what != OTHER) asked[g][what][tile] = phase;
+    };
+    auto wait = [&](size_t leave, int phase) {
+      for (; open.size() > leave; open.pop_front())
+        if (open.front().first != OTHER) landed[g][open.front().first][open.front().second] = phase;
+    };
+    ask(K, 0, 2, -1); ask(K, 1, 2, -1); ask(V, 0, 2, -1); ask(OTHER, 0, 10, -1); ask(K, 2, 2, -1); ask(V, 1, 2, -1);
+    wait(0, -1);
+    for (int u = 0; u < tiles; ++u) {
+      if (first[u]) { wait(0, 2 * u + g); ask(OTHER, 0, u ? 18 : 0, 2 * u + g); }
+      ask(K, u + 3, 2, 2 * u + g); ask(V, u + 2, 2, 2 * u + g);
+      if (attn_waits_behind(first[u], last[u])) wait(4, 2 * u + 1 + g);
+      if (last[u]) ask(OTHER, 0, 10, 2 * u + 1 + g);
+    }
+  }
+  for (int from = 0; from < 2; ++from)                       // group that requests, group that reads
+    for (int g = 0; g < 2; ++g)
+      for (int t = 0; t < tiles; ++t) {
+        auto there = [&](int what, int phase) { return landed[from][what].count(t) && landed[from][what][t] < phase; };
+        if (!there(K, 2 * t + g) || !there(V, 2 * t + 1 + g))
+          return std::printf("tile %d of %d: the part of group %d is read by group %d before it was waited for\n", t, tiles, from, g), 1;
+        if ((asked[from][K].count(t + 4) && asked[from][K][t + 4] <= 2 * t + g) || (asked[from][V].count(t + 4) && asked[from][V][t + 4] <= 2 * t + 2 + g))
+          return std::printf("tile %d of %d: overwritten by group %d before group %d has read it\n", t, tiles, from, g), 1;
+      }
+  return 0;
+}
+int main() {
+  std::mt19937 rng(2);
+  for (int trial = 0; trial < 3000; ++trial) {
+    std::vector<int> items(1 + rng() % 7);
+    for (int &n : items) n = 1 + rng() % 5;
+    if (check(items)) return 1;
+  }
+  return 0;
+}
+"""
+
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no C++ compiler")
 
 
-def test_requests_stay_inside_their_descriptors(tmp_path):
+def _run(tmp_path, program):
     src, exe = tmp_path / "stream.cpp", tmp_path / "stream"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2511_17560_amd", "csrc"), str(src), "-o", str(exe)],
                    check=True)
     res = subprocess.run([str(exe)], capture_output=True, text=True)
     assert res.returncode == 0, res.stdout
+
+
+def test_requests_stay_inside_their_descriptors(tmp_path):
+    _run(tmp_path, PROGRAM)
+
+
+def test_what_a_phase_reads_has_landed(tmp_path):
+    _run(tmp_path, PHASES)

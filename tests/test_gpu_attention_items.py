@@ -29,6 +29,17 @@ def test_many_short_items_in_one_workgroup(hq, hkv, tuning):
     _check(w, act, q, k, v, _attend(w, act, q, k, v), range(0, len(act), 7))
 
 
+def test_items_of_a_few_tiles_in_one_workgroup(tuning):
+    """Items of two to seven tiles of keys, one behind the other: V of the tile behind a change of item is requested two tiles
+    before it and has no other wait than the one in front of the next item's rows."""
+    rng = np.random.default_rng(6)
+    lens = [[int(n)] for n in rng.integers(66, 420, 40)]
+    w, act, q, k, v = _inputs(8, 2, lens, rng.integers(1, 9, 40).tolist(), (30, 100), 18)
+    v *= torch.exp2((torch.arange(w.total_tokens) // 64 % 5).float())[:, None, None].bfloat16()      # another size from tile to tile
+    tuning("attn_wgs", 1)
+    _check(w, act, q, k, v, _attend(w, act, q, k, v), range(0, len(act), 5))
+
+
 def test_growing_logits_move_the_reference():
     """The exponent reference only moves when a weight reaches 2 against it: logits that grow by a few powers of two from tile to
     tile of keys, that jump far at one key, that fall steeply, and single large ones."""
