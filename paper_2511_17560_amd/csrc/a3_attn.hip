@@ -347,6 +347,9 @@ attn_bf16_kernel(attn_args a) {
   // Lazy rescaling: the exponent reference lies 7 above the largest exponent of the row when it was set, so weights are about
   // 2^-7 and below, and moves when one reaches 2 (a bf16 that does has bit 14 set, and only such a one: one test of the or of
   // all bits), so the accumulators are rescaled a handful of times per row instead of whenever the maximum moves.
+  // A row that has seen nothing but logits of -inf has no reference yet: what is added to its exponents then leaves -inf a weight of
+  // 0 and makes that of its first finite logit infinite, however small the logit, so that the reference is set there.
+  constexpr float kUnset = 3.402823466e38f;
   auto check = [&](uint32_t bits) {
     if (__any((bits & 0x40004000u) != 0)) {
 #pragma unroll
@@ -354,7 +357,7 @@ attn_bf16_kernel(attn_args a) {
         const float new_ref = fmaxf(ref[rb], maximum(rb));
         const float alpha = new_ref == -INFINITY ? 1.0f : fast_exp2(ref[rb] - new_ref);
         ref[rb] = new_ref;
-        nref[rb] = new_ref == -INFINITY ? 0.f : -new_ref;
+        nref[rb] = new_ref == -INFINITY ? kUnset : -new_ref;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           osum[rb][r] *= alpha;
@@ -425,7 +428,7 @@ attn_bf16_kernel(attn_args a) {
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) {
         ref[rb] = maximum(rb);
-        nref[rb] = ref[rb] == -INFINITY ? 0.f : -ref[rb];    // no visible key: every P is 0
+        nref[rb] = ref[rb] == -INFINITY ? kUnset : -ref[rb];
       }
     }
     check(weights());

@@ -52,6 +52,25 @@ def test_growing_logits_move_the_reference():
         _check(w, act, qq, kk, v, _attend(w, act, qq, kk, v), list(range(0, len(act), 17)) + [len(act) - 1])
 
 
+@pytest.mark.parametrize("wgs", [-1, 1, 7])
+@pytest.mark.parametrize("logit", [-1.0, -100.0, "up"])
+@pytest.mark.parametrize("pattern", ["first 64", "first 100", "first 128", "every other tile", "three tiles of four"])
+def test_keys_with_infinite_logits_before_small_ones(pattern, logit, wgs, tuning):
+    """A row whose first tiles of keys, of the request or of a share of it, have weight 0 altogether (logits of -inf): the exponent
+    reference is that of the first finite logit, also of one that is small or far below zero."""
+    tuning("attn_wgs", wgs)
+    w, act, q, k, v = _inputs(8, 2, [[1500]], [20], (30, 100), 19)
+    t = torch.arange(w.total_tokens)
+    none = {"first 64": t < 64, "first 100": t < 100, "first 128": t < 128, "every other tile": t // 64 % 2 == 0,
+            "three tiles of four": t // 64 % 4 < 3}[pattern]
+    want = torch.where(t % 400 < 300, -1.0, 3.0) if logit == "up" else torch.full(t.shape, logit)
+    qq, kk = 0.1 * q, k.clone()
+    qq[:, :, 0] = 8.0
+    kk[:, :, 0] = torch.where(none, -torch.inf, want * 128 ** 0.5 / 8.0).bfloat16()[:, None]
+    seen = [i for i in range(len(act)) if bool((~none[:int(act[i]) + 1]).any())]
+    _check(w, act, qq, kk, v, _attend(w, act, qq, kk, v), seen[::23] + seen[-1:])
+
+
 def test_rows_behind_the_last_visible_key_stay_out():
     """Keys and values behind the last one that a tile of rows sees are not multiplied: not finite there, finite outputs."""
     w, _, _, k, v = _inputs(8, 2, [[700]], [3], (0, 100), 17)
