@@ -517,7 +517,7 @@ attn_combine_kernel(attn_args a) {
   const int4 ta = a.plan.tile_a[t];
   const int G = a.Hq / a.Hkv;
   const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4, rb = (threadIdx.x >> 6) & 1, half = threadIdx.x >> 7;
-  const int ml = blockIdx.z * 32 + 16 * rb + l16, d0 = 64 * half + 4 * lg;
+  const int ml = blockIdx.z * 32 + 16 * rb + l16;
   const int m = ta.y + ml;
   if (m >= ta.w) return;
   const int arow = a.plan.a_lo[ta.x] + m / G, hq = g * G + m % G;
@@ -556,13 +556,26 @@ attn_combine_kernel(attn_args a) {
     }
   }
   const float inv = 1.0f / L;
-  bf16_t *orow = (bf16_t *)a.out + ((size_t)arow * a.Hq + hq) * kD + d0;
+  bf16_t *orow = (bf16_t *)a.out + ((size_t)arow * a.Hq + hq) * kD + 64 * half;
+  // by lane-row swaps of two blocks of 16 dims lane group lg gets dims 8 lg .. + 7 of them
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    bf16x4 v;
+  for (int h = 0; h < 2; ++h) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 w[2];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = a3_f2bf(acc[4 * i + e] * inv);
-    *reinterpret_cast<bf16x4 *>(orow + 16 * i) = v;
+    for (int i = 0; i < 2; ++i) {
+      bf16x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = a3_f2bf(acc[8 * h + 4 * i + e] * inv);
+      w[i] = __builtin_bit_cast(u32x2, v);
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      auto r = __builtin_amdgcn_permlane32_swap(w[0][e], w[1][e], false, false);
+      r = __builtin_amdgcn_permlane16_swap(r[0], r[1], false, false);
+      w[0][e] = r[0]; w[1][e] = r[1];
+    }
+    *reinterpret_cast<u32x4 *>(orow + 32 * h + 8 * lg) = u32x4{w[0][0], w[0][1], w[1][0], w[1][1]};
   }
 }
 
