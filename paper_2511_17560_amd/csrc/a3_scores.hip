@@ -446,8 +446,9 @@ scores_bf16_kernel(scores_args a) {
 
   f32x16 acc[2];
   bf16x8 kfr[kD / 16];
-  // (a row may see none of a wave's question keys: its maximum stays finite and its weights come out as exp2(-inf) = 0)
-  const float none = own ? -3.402823466e38f : -INFINITY;
+  // (a wave's first keys may all have logits of -inf for a row, masked question keys or by their values: the row's maximum stays finite
+  // and the weights come out as exp2(-inf) = 0)
+  constexpr float none = -3.402823466e38f;
   float run_max[2] = {none, none}, run_sum[2] = {0.f, 0.f};
   int seen[2] = {N, N};                                        // PASS 0: keys that the lane's row of block b may see
   if (own) {
@@ -549,7 +550,7 @@ scores_bf16_kernel(scores_args a) {
         const int m = m_base + rg * 64 + b * 32 + l32;
         if (m < Mg) {
           const float2 o = pair[rg * 64 + b * 32 + l32];
-          const float mn = fmaxf(run_max[b], o.x);             // keys 0 .. 31 of slot 0 are real: run_max is finite
+          const float mn = fmaxf(run_max[b], o.x);
           const float zz = z[b] * fast_exp2(run_max[b] - mn) + (o.y > 0.f ? o.y * fast_exp2(o.x - mn) : 0.f);
           a.part[(size_t)t * a.total_rows + row_of(m)] = make_float2(mn, zz);
         }
@@ -652,8 +653,9 @@ scores_rows_bf16_kernel(scores_args a) {
   float colsum[kKB];
 #pragma unroll
   for (int kb = 0; kb < kKB; ++kb) colsum[kb] = 0.f;
-  // (a row may see none of a wave's question keys: its maximum stays finite and its weights come out as exp2(-inf) = 0)
-  const float none = own ? -3.402823466e38f : -INFINITY;
+  // (a wave's first keys may all have logits of -inf for a row, masked question keys or by their values: the row's maximum stays finite
+  // and the weights come out as exp2(-inf) = 0)
+  constexpr float none = -3.402823466e38f;
   float run_max[2] = {none, none}, run_sum[2] = {0.f, 0.f};
 
   // logits of the current 64 rows (fragments in qf) against key block KB, folded into the running row
@@ -702,7 +704,7 @@ scores_rows_bf16_kernel(scores_args a) {
     }                                                                                                          \
   }
   // the round is done: pass A leaves the (max, sum) of its rows over this tile; waves that share a group (by key blocks, see the
-  // further rounds) merge theirs in LDS.  One that saw no key has (max, sum) = (-inf, 0).
+  // further rounds) merge theirs in LDS.  One that saw no key has a sum of 0.
   int share = 1, sub = 0, rb = wave * 64;                      // waves that share the wave's group, which of them it is, its first row
   float2 *pair = reinterpret_cast<float2 *>(red);
 #define A3_ROWS_DONE()                                                                                         \
@@ -717,7 +719,7 @@ scores_rows_bf16_kernel(scores_args a) {
         if (sub == 0)                                                                                          \
           for (int w = wave + 4 / share; w < 4; w += 4 / share) {                                              \
             const float2 o = pair[w * 64 + b * 32 + l32];                                                      \
-            const float mn = fmaxf(run_max[b], o.x);           /* sub 0 has key block 0: finite */             \
+            const float mn = fmaxf(run_max[b], o.x);                                                           \
             z[b] = z[b] * fast_exp2(run_max[b] - mn) + (o.y > 0.f ? o.y * fast_exp2(o.x - mn) : 0.f);          \
             run_max[b] = mn;                                                                                   \
           }                                                                                                    \
