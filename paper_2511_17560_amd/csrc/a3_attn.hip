@@ -790,7 +790,7 @@ static a3_status attn_launch(const a3_layout *L, const void *q_act, const int *a
     const int wgs_per_head = a.plan.max_wgs, max_tiles = a.plan.max_tiles, Hkv = L->n_kv_heads;
     if (parts & 1)
       hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(kPlanThreads), 0, st, a.plan, act_idx, n_act, L->seg_start,
-                         L->n_req, L->n_q_heads / L->n_kv_heads, wgs_per_head, attn_item_cost(L));
+                         L->n_req, L->n_q_heads / L->n_kv_heads, wgs_per_head, attn_item_cost(L, n_act));
     if (parts & 2) {
       // blockIdx % Hkv = KV head, so with 8 KV heads each XCD's L2 serves the K/V of one head
       if (ev_begin) (void)hipEventRecord(ev_begin, st);

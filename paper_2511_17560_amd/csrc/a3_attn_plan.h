@@ -225,16 +225,24 @@ int attn_wgs_per_head(const a3_layout *L) {
 }
 
 // Start-up cost of an item in key steps (what the share boundaries are balanced with), or the tuning value
-// "attn_item_cost".  With 4, 8 and 10: 64K context 2801, 2746 and 2722 us, seven heads per KV head at 32K 1236, 1198 and 1205, all
-// rows of 16K 1712, 1654 and 1664 (the last steps of a tile, where rows end one wave after the other, and the change of rows take
-// 20 - 25 thousand cycles, a step 2660).  Requests of few rows leave a share so few steps that a tile's start-up overlaps the
-// loads of the others: with 4 and 8, whole calls, 500 rows of context 21.3 and 23.0 us (seven heads 22.5 and 25.1), 1000 25.1 and 26.6,
-// 3000 35.8 and 37.2, 8 x 1000 55.1 and 58.2 (49.3 and 47.8), 4 x 500 29.7 and 27.8, all rows of 1100 34.1 and 36.2; 4000 43.0 and
-// 43.1 (40.0 and 40.6), 5120 52.3 and 51.0 (47.5 and 48.4), 3 x 5000 95 and 95.5 (86.5 and 84.8): the line lies between these.
-constexpr int kShortRequestRows = 4608;
-int attn_item_cost(const a3_layout *L) {
-  const int v = a3_knob(A3_KNOB_ATTN_ITEM_COST);
-  return v >= 0 && v <= 64 ? v : L->max_ctx_len + L->max_q_len <= kShortRequestRows ? 4 : 8;
+// "attn_item_cost".  Long shares, with 4, 8 and 10: 64K context 2801, 2746 and 2722 us, seven heads per KV head at 32K 1236, 1198 and
+// 1205, all rows of 16K 1712, 1654 and 1664 (the last steps of a tile, where rows end one wave after the other, and the change of
+// rows take 20 - 25 thousand cycles, a step 2660); all rows of 5000 217 and 205, 3 x 5000 130 and 125.
+// In shares of few steps a tile's start-up overlaps the loads of the others, and 4 is no slower.  Whole calls of 15 % of the
+// rows with 4 and 8 (seven heads per KV head): 500 rows 27.3 and 28.3 us (25.7, 27.8), 3000 41.8 and 42.3 (38.5, 39.2), 5000 60.2 and
+// 61.2 (54.0, 54.6), 5500 62.8 and 63.8 (59.1, 60.0), 6000 72.6 and 72.7 (63.0, 64.2), but 6500 79.9 and 77.6 (70.5, 69.5), 8000 99.1
+// and 97.9 (91.0, 89.3): the line lies at 22 steps a share, rows taken to see half of the longest request each.
+// Requests of up to 4608 rows keep 4 also in longer shares.  Some batches of them would be faster with 8 (8 x 1000 rows 56.5 and 48.3,
+// seven heads 51.7 and 52.5; 16 x 500 63.8 and 59.5, 42.8 and 42.8; 4 x 2000 63.1 and 59.8, 57.6 and 55.5), but fewer cuts of
+// these short rows mean a larger error against float64, nowhere a smaller one: 500 rows 1.732e-3 and 1.750e-3, with a few large
+// weights 1.858e-3 and 1.881e-3; 8 x 1000 2.017e-3 and 2.021e-3, 1.951e-3 and 1.968e-3; 4 x 2000 1.992e-3 and 1.993e-3, 1.994e-3 and
+// 2.011e-3.  Longer ones differ by less, both ways (8000 rows 2.006e-3 and 2.003e-3, 16K 2.035e-3 and 2.036e-3).
+constexpr int kShortRequestRows = 4608, kShortShareSteps = 22;
+int attn_item_cost(const a3_layout *L, int n_act) {
+  const int v = a3_knob(A3_KNOB_ATTN_ITEM_COST), len = L->max_ctx_len + L->max_q_len;
+  if (v >= 0 && v <= 64) return v;
+  const double steps = (double)n_act * (L->n_q_heads / L->n_kv_heads) / kTM * len / kTK / 2 / attn_wgs_per_head(L);
+  return len <= kShortRequestRows || steps < kShortShareSteps ? 4 : 8;
 }
 
 // every tile starts an item, every share boundary inside a tile starts another

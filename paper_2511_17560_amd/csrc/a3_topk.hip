@@ -589,7 +589,7 @@ extern "C" a3_status a3_topk_select_plan(const a3_layout *L, const float *scores
   const int G = L->n_q_heads / L->n_kv_heads;
   with_keys_per_lane(L->max_ctx_len, [&](auto kpt) {
     hipLaunchKernelGGL(topk_select_plan_kernel<kpt.value>, dim3(1), dim3(kBlock), 0, (hipStream_t)stream, scores, prob,
-                       sel_idx, act_idx, n_act, plan, G, plan.max_wgs, attn_item_cost(L));
+                       sel_idx, act_idx, n_act, plan, G, plan.max_wgs, attn_item_cost(L, n_act));
   });
   A3_CHECK_LAUNCH("a3_topk_select_plan");
   return A3_OK;
