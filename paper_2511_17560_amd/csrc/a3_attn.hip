@@ -773,8 +773,8 @@ static a3_status attn_launch(const a3_layout *L, const void *q_act, const int *a
   a.inv_G = G > 1 ? (uint32_t)(((1ull << 32) + G - 1) / G) : 0;
   memset(&a.plan, 0, sizeof(a.plan));
   if (L->dtype == A3_BF16) {
-    // (a limit of an earlier kernel's 32-bit byte offsets; this one's bases are 64-bit per tile.  The line stays: what lies
-    // beyond it was always refused and has never been run)
+    // Required: offsets of a request's tiles and the sizes of its descriptors are 32-bit byte counts (attn_stream).  The furthest lane
+    // of a load lies 63 rows behind the last visible key; 128 rows are kept in hand
     A3_REQUIRE(((long long)L->max_ctx_len + L->max_q_len + 128) * L->n_kv_heads * kD * 2 < (1LL << 32), A3_ERR_UNSUPPORTED,
                "a3_fused_attention: a request of %d rows is too long (its K and V rows must stay below 4 GiB each)",
                L->max_ctx_len + L->max_q_len);
