@@ -557,7 +557,8 @@ attn_combine_kernel(attn_args a) {
   }
   const float inv = 1.0f / L;
   bf16_t *orow = (bf16_t *)a.out + ((size_t)arow * a.Hq + hq) * kD + 64 * half;
-  // by lane-row swaps of two blocks of 16 dims lane group lg gets dims 8 lg .. + 7 of them
+  // by lane-row swaps of two blocks of 16 dims lane group lg gets dims 8 lg .. + 7 of them (a lane's own dims, stored as 8 bytes, 32 in
+  // one piece: merge of eight requests of 1000 rows 10.7 us, now 9.6; of 64K context 17.9 and 16.4)
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
