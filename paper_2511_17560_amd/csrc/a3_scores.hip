@@ -23,6 +23,9 @@
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
+// Where a row's maximum starts.  The first keys that a lane, wave or tile sees may all have logits of -inf for a row, by their values or
+// as masked question keys: the maximum is finite all the same, and their weights come out as exp2(-inf) = 0
+constexpr float kLeast = -3.402823466e38f;
 
 // largest i in [0, n) with a[i] <= x (a ascending, a[0] <= x)
 __device__ __forceinline__ int find_segment(const int *__restrict__ a, int n, int x) {
@@ -78,7 +81,7 @@ scores_question_stats_kernel(scores_args a) {
   const T *__restrict__ Q = (const T *)a.q + (size_t)row * a.d;
   const T *__restrict__ K = (const T *)a.k;
   const int key0 = a.seg_start[r] + a.ctx_len[r];
-  float m = -INFINITY, z = 0.f;
+  float m = kLeast, z = 0.f;
   for (int u = lane; u <= j; u += 64) {
     // 16-byte loads of both rows (element by element this kernel took 28 us for 64 question tokens x 32 heads)
     constexpr int V = a3_elem<T>::kVec;
@@ -94,7 +97,7 @@ scores_question_stats_kernel(scores_args a) {
     }
     const float l = dot * a.scale2;
     const float mn = fmaxf(m, l);
-    z = z * exp2f(m - mn) + exp2f(l - mn);                     // m = -inf, z = 0 on the first key: 0 * 0
+    z = z * exp2f(m - mn) + exp2f(l - mn);                     // first key: 0 * 0
     m = mn;
   }
 #pragma unroll
@@ -118,7 +121,7 @@ scores_combine_kernel(scores_args a) {
   // one row per 16 lanes: the lanes split the row's tiles, then merge pairwise (fixed tree)
   const int row = blockIdx.x * 16 + (threadIdx.x >> 4);
   const int slice = threadIdx.x & 15;
-  float m = -INFINITY, z = 0.f;
+  float m = kLeast, z = 0.f;
   if (row < a.total_rows) {
     const int jq = row / a.Hq;
     const int r = find_segment(a.q_start, a.n_req, jq);
@@ -446,10 +449,7 @@ scores_bf16_kernel(scores_args a) {
 
   f32x16 acc[2];
   bf16x8 kfr[kD / 16];
-  // (a wave's first keys may all have logits of -inf for a row, masked question keys or by their values: the row's maximum stays finite
-  // and the weights come out as exp2(-inf) = 0)
-  constexpr float none = -3.402823466e38f;
-  float run_max[2] = {none, none}, run_sum[2] = {0.f, 0.f};
+  float run_max[2] = {kLeast, kLeast}, run_sum[2] = {0.f, 0.f};
   int seen[2] = {N, N};                                        // PASS 0: keys that the lane's row of block b may see
   if (own) {
 #pragma unroll
@@ -653,10 +653,7 @@ scores_rows_bf16_kernel(scores_args a) {
   float colsum[kKB];
 #pragma unroll
   for (int kb = 0; kb < kKB; ++kb) colsum[kb] = 0.f;
-  // (a wave's first keys may all have logits of -inf for a row, masked question keys or by their values: the row's maximum stays finite
-  // and the weights come out as exp2(-inf) = 0)
-  constexpr float none = -3.402823466e38f;
-  float run_max[2] = {none, none}, run_sum[2] = {0.f, 0.f};
+  float run_max[2] = {kLeast, kLeast}, run_sum[2] = {0.f, 0.f};
 
   // logits of the current 64 rows (fragments in qf) against key block KB, folded into the running row
   // statistics (pass A) or into the column sums (pass B)
@@ -857,7 +854,7 @@ scores_rows_bf16_kernel(scores_args a) {
     if (rb >= Mg) break;                                       // (a wave without rows: three groups are left, none of them shared)
     A3_LOAD_Q(rb)
     A3_START(rb)
-    run_max[0] = run_max[1] = none;
+    run_max[0] = run_max[1] = kLeast;
     run_sum[0] = run_sum[1] = 0.f;
 #pragma unroll
     for (int kb = 0; kb < kKB; ++kb)                           // (unrolled: the column sums are registers)
@@ -956,9 +953,9 @@ scores_f32_kernel(scores_args a) {
       if (lg == 0) red[wave][l16] = make_float2(mx, z);
       __syncthreads();
       if (threadIdx.x < 16 && m < Mg) {
-        float mm = -INFINITY, zz = 0.f;
+        float mm = kLeast, zz = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) mm = fmaxf(mm, red[w][l16].x);   // the first key of a tile is always real
+        for (int w = 0; w < 4; ++w) mm = fmaxf(mm, red[w][l16].x);
 #pragma unroll
         for (int w = 0; w < 4; ++w) zz += red[w][l16].y * exp2f(red[w][l16].x - mm);
         a.part[(size_t)blockIdx.x * a.total_rows + row] = make_float2(mm, zz);
