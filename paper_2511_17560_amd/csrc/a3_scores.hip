@@ -126,11 +126,17 @@ scores_combine_kernel(scores_args a) {
     const int jq = row / a.Hq;
     const int r = find_segment(a.q_start, a.n_req, jq);
     const int tiles = (a.ctx_len[r] + a.tile_keys - 1) / a.tile_keys;
-    for (int t = slice; t < tiles; t += 16) {
-      float2 p = a.part[(size_t)t * a.total_rows + row];
-      float mn = fmaxf(m, p.x);
-      z = z * exp2f(m - mn) + p.y * exp2f(p.x - mn);
-      m = mn;
+    for (int t = slice; t < tiles; t += 64) {                  // the loads of four tiles together
+      float2 p[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) p[u] = a.part[(size_t)min(t + 16 * u, tiles - 1) * a.total_rows + row];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (t + 16 * u < tiles) {
+          const float mn = fmaxf(m, p[u].x);
+          z = z * exp2f(m - mn) + p[u].y * exp2f(p[u].x - mn);
+          m = mn;
+        }
     }
     if (a.causal_q && slice == 15) {                           // the question keys' share (slice 15 has the fewest tiles)
       float2 p = a.part[(size_t)a.n_tiles * a.total_rows + row];
@@ -879,17 +885,23 @@ scores_rows_bf16_kernel(scores_args a) {
   }
 }
 
-// scores[t] = sum over KV heads of their column sums, in head order; question rows get -inf
+// scores[t] = sum over KV heads of their column sums, in head order; question rows get -inf.  Nothing but the latency of its loads, so
+// those of eight heads and of the row's chunk are requested together (one after the other 3.3 us for 544 rows and 8 heads, now 1.9; a layer
+// pass of 2K rows 117.5 -> 115.9).
 __global__ void __launch_bounds__(256)
 scores_head_sum_kernel(scores_args a, const int *__restrict__ tok_chunk) {
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= a.T) return;
-  float v = -INFINITY;
-  if (tok_chunk[t] >= 0) {
-    v = 0.f;
-    for (int g = 0; g < a.Hkv; ++g) v += a.part_scores[(size_t)g * a.T + t];
+  const int chunk = tok_chunk[t];
+  float v = 0.f;
+  for (int g0 = 0; g0 < a.Hkv; g0 += 8) {
+    float p[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) p[u] = a.part_scores[(size_t)min(g0 + u, a.Hkv - 1) * a.T + t];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v = g0 + u < a.Hkv ? v + p[u] : v;
   }
-  a.scores[t] = v;
+  a.scores[t] = chunk >= 0 ? v : -INFINITY;
 }
 
 // ---------------------------------------------------------------------------------------
