@@ -57,22 +57,23 @@ __device__ __forceinline__ int upper_bound_i32(const int *a, int n, int x) {
   return lo;
 }
 
-// exclusive prefix sum over the workgroup (threads in tid order); *total receives the sum
+// Barrier between the steps of the plan: what they hand on lies in LDS, or in the workspace
+template <bool in_lds>
+__device__ __forceinline__ void plan_barrier() {
+  if constexpr (in_lds) A3_LDS_BARRIER();
+  else __syncthreads();
+}
+
+// exclusive prefix sum over the workgroup (threads in tid order); *total receives the sum.  wave_tot: [kPlanThreads / 64]
+template <bool in_lds>
 __device__ __forceinline__ int plan_scan(int v, int *wave_tot, int *total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    int x = __shfl_up(inc, off, 64);
-    if (lane >= off) inc += x;
-  }
-  __syncthreads();               // wave_tot may still be read by a previous scan
+  const int inc = a3_wave_prefix(v);
+  plan_barrier<in_lds>();        // wave_tot may still be read by a previous scan
   if (lane == 63) wave_tot[wave] = inc;
-  __syncthreads();
-  int before = 0, all = 0;
-  for (int w2 = 0; w2 < kPlanThreads / 64; ++w2) { if (w2 < wave) before += wave_tot[w2]; all += wave_tot[w2]; }
-  *total = all;
-  return before + inc - v;
+  plan_barrier<in_lds>();
+  static_assert(kPlanThreads == 16 * 64, "16 waves");
+  return a3_waves_before(wave_tot, *total) + inc - v;
 }
 
 // The whole plan, by one workgroup of kPlanThreads threads.  wave_tot: [kPlanThreads / 64] ints of LDS.
@@ -83,8 +84,9 @@ __device__ __forceinline__ int plan_scan(int v, int *wave_tot, int *total) {
 // to be of LDS: one that might be of memory waits for the stores of the item before it (plan of eight requests of 8000 rows 18.2 ->
 // 14.5 us, of 64K context 12.7 -> 10.7, of 16 x 500 rows 11.8 -> 9.3; the request of an item taken from its tile instead of a
 // bisection is 2.0, 0.3 and 0.6 us of that).
-template <bool in_lds>
-__device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *act_idx, int n_act,
+// row(i): act_idx[i].
+template <bool in_lds, class Row>
+__device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *act_idx, Row row, int n_act,
                                                  const int *__restrict__ seg_start, int n_req, int G, int wgs_per_head,
                                                  int item_cost, int *wave_tot, int *lds) {
   const int tid = threadIdx.x;
@@ -106,8 +108,16 @@ __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *
       if (n_req > 1 && r < n_req) req_base[r] = seg_start[r];
     }
   }
-  __syncthreads();
-  if (tid == 0) {
+  plan_barrier<in_lds>();
+  if (n_req < 64) {
+    if (tid < 64) {
+      const int n = tid < n_req ? ((a_lo[tid + 1] - a_lo[tid]) * G + kTM - 1) / kTM : 0, t = a3_wave_prefix(n) - n;
+      if (tid <= n_req) {
+        tile_start[tid] = t;
+        if (in_lds) p.tile_start[tid] = t;
+      }
+    }
+  } else if (tid == 0) {
     int t = 0;
     for (int r = 0; r < n_req; ++r) {
       tile_start[r] = t;
@@ -117,7 +127,7 @@ __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *
     tile_start[n_req] = t;
     if (in_lds) p.tile_start[n_req] = t;
   }
-  __syncthreads();
+  plan_barrier<in_lds>();
   const int n_tiles = min(tile_start[n_req], p.max_tiles);
 
   // ---- tiles and their running cost -------------------------------------------------------
@@ -133,13 +143,13 @@ __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *
       const int nr = a_lo[r + 1] - a_lo[r];
       int last = ((j + 1) * kTM - 1) / G;
       if (last > nr - 1) last = nr - 1;
-      const int kv = act_idx[a_lo[r] + last] - base_of(r) + 1;
+      const int kv = row(a_lo[r] + last) - base_of(r) + 1;
       steps = (kv + kTK - 1) / kTK;
       p.tile_a[t] = make_int4(r, j * kTM, kv, nr * G);
       if (in_lds) { tile_kv[t] = kv; tile_req[t] = r; }
     }
     int total;
-    const int before = plan_scan(t < n_tiles ? steps + item_cost : 0, wave_tot, &total);
+    const int before = plan_scan<in_lds>(t < n_tiles ? steps + item_cost : 0, wave_tot, &total);
     if (t < n_tiles) {
       tile_pre[t] = carry + before;
       if (in_lds) p.tile_pre[t] = carry + before;
@@ -151,7 +161,7 @@ __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *
     tile_pre[n_tiles] = W;
     if (in_lds) p.tile_pre[n_tiles] = W;
   }
-  __syncthreads();
+  plan_barrier<in_lds>();
 
   // ---- equal shares ------------------------------------------------------------------------
   int P = (W - n_tiles * item_cost + kMinSteps - 1) / kMinSteps;
@@ -167,14 +177,30 @@ __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *
     s_beg = quotient((long long)tid * W, P);
     s_end = quotient((long long)(tid + 1) * W, P);
     if (s_end > s_beg) {
-      t0 = upper_bound_i32(tile_pre, n_tiles + 1, (int)s_beg) - 1;      // tile that holds position s_beg
-      const int t1 = lower_bound_i32(tile_pre, n_tiles + 1, (int)s_end) - 1;     // ... and position s_end - 1
+      // tiles that hold positions s_beg and s_end - 1: the last with a start <= s_beg, and < s_end (both searches at once)
+      int hi0 = n_tiles + 1, t1 = 0, hi1 = n_tiles + 1;
+      while (t0 < hi0 || t1 < hi1) {
+        const int m0 = (t0 + hi0) >> 1, m1 = (t1 + hi1) >> 1;
+        const int p0 = tile_pre[min(m0, n_tiles)], p1 = tile_pre[min(m1, n_tiles)];
+        if (t0 < hi0) { if (p0 <= (int)s_beg) t0 = m0 + 1; else hi0 = m0; }
+        if (t1 < hi1) { if (p1 < (int)s_end) t1 = m1 + 1; else hi1 = m1; }
+      }
+      t0 -= 1;
+      t1 -= 1;
       // the last tile only counts if the share reaches past its start-up units
       cnt = t1 - t0 + 1 - (s_end <= (long long)tile_pre[t1] + item_cost ? 1 : 0);
     }
   }
+  // (waves that have no share begin)
+  // items of a tile = share boundaries strictly inside it + 1; boundary q lies at floor(q W / P)
+  for (int t = (tid + kPlanThreads / 2) % kPlanThreads; t < n_tiles; t += kPlanThreads) {
+    const long long x = (long long)tile_pre[t] + item_cost, y = tile_pre[t + 1];
+    const long long ub = quotient((x + 1) * P + W - 1, W);   // first q with floor(q W / P) > x
+    const long long lb = quotient(y * P + W - 1, W);         // first q with floor(q W / P) >= y
+    p.tile_b[t].y = (int)(lb > ub ? lb - ub : 0) + 1;
+  }
   int n_items;
-  const int first = plan_scan(cnt, wave_tot, &n_items);
+  const int first = plan_scan<in_lds>(cnt, wave_tot, &n_items);
   if (tid < P) p.wg_start[tid] = min(first, p.max_items);
   if (tid == 0) p.wg_start[P] = min(n_items, p.max_items);
   for (int i = 0; i < cnt; ++i) {
@@ -188,13 +214,6 @@ __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *
     p.items[2 * idx + 1] = make_int4((a_lo[r + 1] - a_lo[r]) * G, a_lo[r], base_of(r), it_b == 0 && s_end >= nxt);
     if (it_b == 0) p.tile_b[t].x = idx;
   }
-  // items of a tile = share boundaries strictly inside it + 1; boundary q lies at floor(q W / P)
-  for (int t = tid; t < n_tiles; t += kPlanThreads) {
-    const long long x = (long long)tile_pre[t] + item_cost, y = tile_pre[t + 1];
-    const long long ub = quotient((x + 1) * P + W - 1, W);   // first q with floor(q W / P) > x
-    const long long lb = quotient(y * P + W - 1, W);         // first q with floor(q W / P) >= y
-    p.tile_b[t].y = (int)(lb > ub ? lb - ub : 0) + 1;
-  }
   if (tid == 0) {
     p.counters[0] = n_tiles;
     p.counters[1] = min(n_items, p.max_items);
@@ -202,12 +221,96 @@ __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *
     p.counters[3] = p.max_wgs;
   }
 }
-__device__ __forceinline__ void attn_plan_body(const attn_plan &p, const int *act_idx, int n_act,
+// The same plan of one request by one wave, without barriers: a lane takes consecutive tiles, then a share.  What bounds the plan is the chain
+// of its steps (LDS round trips, scans), not their number: with all 16 waves in step, a barrier on either side of every scan and bisections and
+// divisions for each tile's number of items, it took 10.1 thousand cycles behind the selection of 2K rows, like this 4.7.
+constexpr int kOneTiles = 512, kOneShares = 64;
+template <class Row>
+__device__ __forceinline__ void attn_plan_one(const attn_plan &p, Row row, int n_act, int base, int G, int wgs_per_head, int item_cost, int *lds) {
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x;
+  int *pre = lds, *kvs = pre + kOneTiles + 1, *parts = kvs + kOneTiles;   // running cost, visible keys, items of a tile
+  auto wave_sync = [&]() {                                   // LDS in program order over the lanes
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  const int rows = n_act * G, n_tiles = min((rows + kTM - 1) / kTM, p.max_tiles), per = (n_tiles + 63) / 64;
+  int sum = 0;
+  for (int u = 0; u < per; ++u) {
+    const int t = lane * per + u;
+    if (t >= n_tiles) break;
+    const int kv = row(min(((t + 1) * kTM - 1) / G, n_act - 1)) - base + 1;
+    kvs[t] = kv;
+    parts[t] = 0;
+    p.tile_a[t] = make_int4(0, t * kTM, kv, rows);
+    pre[t] = sum;
+    sum += (kv + kTK - 1) / kTK + item_cost;
+  }
+  const int upto = a3_wave_prefix(sum), W = __builtin_amdgcn_readlane(upto, 63);     // cost of one head
+  for (int u = 0; u < per; ++u)
+    if (lane * per + u < n_tiles) pre[lane * per + u] += upto - sum;
+  if (lane == 0) {
+    pre[n_tiles] = W;
+    p.a_lo[0] = p.tile_start[0] = 0;
+    p.a_lo[1] = n_act;
+    p.tile_start[1] = n_tiles;
+  }
+  wave_sync();
+  const int P = max(1, min((W - n_tiles * item_cost + kMinSteps - 1) / kMinSteps, min(wgs_per_head, p.max_wgs)));
+  // share q: positions floor(q W / P) .. floor((q + 1) W / P) - 1
+  const uint32_t each = (uint32_t)W / (uint32_t)P, rest = (uint32_t)W - each * (uint32_t)P;
+  const int s_beg = (int)((uint32_t)lane * each + (uint32_t)lane * rest / (uint32_t)P);
+  const int s_end = (int)((uint32_t)(lane + 1) * each + (uint32_t)(lane + 1) * rest / (uint32_t)P);
+  int t0 = 0, cnt = 0;
+  if (lane < P && s_end > s_beg) {
+    // tiles that hold positions s_beg and s_end - 1: the last with a start <= s_beg, and < s_end (both searches at once)
+    int hi0 = n_tiles + 1, t1 = 0, hi1 = n_tiles + 1;
+    while (t0 < hi0 || t1 < hi1) {
+      const int m0 = (t0 + hi0) >> 1, m1 = (t1 + hi1) >> 1;
+      const int p0 = pre[min(m0, n_tiles)], p1 = pre[min(m1, n_tiles)];
+      if (t0 < hi0) { if (p0 <= s_beg) t0 = m0 + 1; else hi0 = m0; }
+      if (t1 < hi1) { if (p1 < s_end) t1 = m1 + 1; else hi1 = m1; }
+    }
+    t0 -= 1;
+    t1 -= 1;
+    // the last tile only counts if the share reaches past its start-up units
+    cnt = t1 - t0 + 1 - (s_end <= pre[t1] + item_cost ? 1 : 0);
+  }
+  const int all = a3_wave_prefix(cnt), first = all - cnt, n_items = min(__builtin_amdgcn_readlane(all, 63), p.max_items);
+  if (lane < P) p.wg_start[lane] = min(first, p.max_items);
+  if (lane == 0) {
+    p.wg_start[P] = n_items;
+    p.counters[0] = n_tiles;
+    p.counters[1] = n_items;
+    p.counters[2] = P;
+    p.counters[3] = p.max_wgs;
+  }
+  for (int i = 0; i < cnt; ++i) {
+    const int t = t0 + i, idx = first + i;
+    if (idx >= p.max_items) break;
+    const int at = pre[t] + item_cost, nxt = pre[t + 1], kv = kvs[t];    // key step s of the tile sits at `at` + s
+    const int it_b = max(s_beg - at, 0), it_e = min(s_end, nxt) - at;
+    p.items[2 * idx] = make_int4(it_b * kTK, min(kv, it_e * kTK), kv, t * kTM);
+    p.items[2 * idx + 1] = make_int4(rows, 0, base, it_b == 0 && s_end >= nxt);
+    if (it_b == 0) p.tile_b[t].x = idx;
+    atomicAdd(&parts[t], 1);
+  }
+  wave_sync();
+  for (int t = lane; t < n_tiles; t += 64) p.tile_b[t].y = parts[t];
+}
+
+template <class Row>
+__device__ __forceinline__ void attn_plan_body(const attn_plan &p, const int *act_idx, Row row, int n_act,
                                                const int *__restrict__ seg_start, int n_req, int G, int wgs_per_head,
                                                int item_cost, int *wave_tot, int *lds, int lds_ints) {
+  if (n_req == 1 && ((long long)n_act * G + kTM - 1) / kTM <= kOneTiles && wgs_per_head <= kOneShares && p.max_wgs <= kOneShares &&
+      3 * kOneTiles + 1 <= lds_ints) {
+    attn_plan_one(p, row, n_act, seg_start[0], G, wgs_per_head, item_cost, lds);
+    return;
+  }
   const bool fits = 3 * (n_req + 1) + 3 * p.max_tiles + 1 <= lds_ints;
-  if (fits) attn_plan_layout<true>(p, act_idx, n_act, seg_start, n_req, G, wgs_per_head, item_cost, wave_tot, lds);
-  else attn_plan_layout<false>(p, act_idx, n_act, seg_start, n_req, G, wgs_per_head, item_cost, wave_tot, lds);
+  if (fits) attn_plan_layout<true>(p, act_idx, row, n_act, seg_start, n_req, G, wgs_per_head, item_cost, wave_tot, lds);
+  else attn_plan_layout<false>(p, act_idx, row, n_act, seg_start, n_req, G, wgs_per_head, item_cost, wave_tot, lds);
 }
 
 

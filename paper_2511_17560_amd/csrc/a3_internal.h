@@ -76,6 +76,42 @@ __device__ __forceinline__ void a3_rotate_pair(float x0, float x1, float2 cs, fl
   y1 = __fmaf_rn(x0, cs.y, __fmul_rn(x1, cs.x));
 }
 
+// ---- wave and workgroup primitives ----------------------------------------------------------
+// Inclusive prefix sum over the 64 lanes of a wave by data-parallel moves (8 cycles or so each; the six shuffles through LDS
+// that it replaces take some 130 each).
+__device__ __forceinline__ int a3_wave_prefix(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);       // row_shr:1, 2, 4, 8 (rows of 16 lanes)
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);       // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);       // row_bcast:31 into rows 2 and 3
+  return x;
+}
+// The same over the 16 lanes of a row: what 16 waves left in LDS, one number a lane, is summed with one read (all 16 read by every lane,
+// four at a time, occupied LDS for 500 cycles of a workgroup of 16 waves).
+__device__ __forceinline__ int a3_row_prefix(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  return x;
+}
+// tot: one number of each of 16 waves, in LDS.  Sum over the waves before this one; all: over all of them
+__device__ __forceinline__ int a3_waves_before(const int *tot, int &all) {
+  const int x = tot[threadIdx.x & 15], wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), sum = a3_row_prefix(x);
+  all = __builtin_amdgcn_readlane(sum, 15);
+  return __builtin_amdgcn_readlane(sum, wave) - __builtin_amdgcn_readlane(x, wave);
+}
+// Workgroup barrier that orders LDS traffic only: this wave's LDS accesses are complete before it, none of the later ones
+// starts ahead of it.  (__syncthreads() also waits for every global access in flight.)
+#define A3_LDS_BARRIER()                                        \
+  do {                                                          \
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local"); \
+    __builtin_amdgcn_s_barrier();                               \
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local"); \
+  } while (0)
+
 template <typename T> struct a3_elem;
 template <> struct a3_elem<float> {
   static constexpr int kVec = 4;   // elements per 16-byte vector

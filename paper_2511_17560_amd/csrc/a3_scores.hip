@@ -198,13 +198,6 @@ __device__ __forceinline__ float halves_sum(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-// Workgroup barrier that orders LDS traffic only: this wave's LDS accesses are complete before it, none of the
-// later ones starts ahead of it.  (__syncthreads() would also wait for every global access in flight, i.e. for
-// the whole ring of keys.)
-#define A3_LDS_BARRIER()                                        \
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local"); \
-  __builtin_amdgcn_s_barrier();                                 \
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local")
 // vmcnt(n) alone (the other counters open): n = 0 .. 63
 #define A3_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | (7 << 4) | (15 << 8))
 
@@ -580,7 +573,6 @@ scores_bf16_kernel(scores_args a) {
   }
 }
 #undef A3_VMCNT
-#undef A3_LDS_BARRIER
 
 // ---------------------------------------------------------------------------------------
 // bf16 MFMA kernel for more than 256 rows per KV head (long questions, wide query groups, batches of them).

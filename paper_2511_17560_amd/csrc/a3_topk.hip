@@ -8,7 +8,10 @@
 // and the output is ascending.  Integer work only: the result is unique and bit-exact.
 // Requests of up to 68 K rows keep every key in a register of the lane that owns it; longer ones re-read the
 // scores from global memory in every pass.  One compute unit does all of it, so what bounds it is the instructions its 16
-// waves issue and the chain of barriers.  With the plan: 2K rows 10.2 us, 5K 11.9, 16K 20, 64K 42.
+// waves issue and the chain of barriers and LDS round trips between them: sums over lanes are data-parallel moves, a wave's part of a sum
+// over waves is one read, barriers wait for LDS alone, and the rows leave through LDS in whole lines.  From the first instruction to
+// the last, plan included, us (with shuffles, 16 reads a sum and full barriers -> now): 2K rows 9.0 -> 6.1, 5K 10.9 -> 8.0, 16K 16.8 -> 12.3,
+// 64K 39.4 -> 33.4.
 #include <type_traits>
 
 #include "a3_internal.h"
@@ -21,9 +24,8 @@ constexpr int kWaves = kBlock / 64;
 
 // Monotone map float -> uint32 (larger float <=> larger key); -0 is folded onto +0.
 __device__ __forceinline__ uint32_t score_key(float s) {
-  uint32_t b = __float_as_uint(s);
-  if (b == 0x80000000u) b = 0u;
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+  const uint32_t b = __float_as_uint(s + 0.0f);
+  return b ^ ((uint32_t)((int)b >> 31) | 0x80000000u);
 }
 
 // Exclusive prefix sum of one int per thread over the workgroup (threads in tid order).
@@ -196,12 +198,37 @@ topk_select_kernel(const float *__restrict__ scores, topk_problem prob, int *__r
 // reach over an end of the request are loaded element by element.
 constexpr int kBins = 2048;
 constexpr uint32_t kRankKeys = 256;      // candidates that are ranked directly instead of by another round
+static_assert(kBlock == 4 * kRankKeys && kWaves % 4 == 0, "a quarter of the candidates to each 256 threads");
 
+// Maximum over a wave, in every lane
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+#define A3_STEP(CTRL, ROWS) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, ROWS, 0xf, false))
+  A3_STEP(0x111, 0xf); A3_STEP(0x112, 0xf); A3_STEP(0x114, 0xf); A3_STEP(0x118, 0xf);   // as in a3_wave_prefix
+  A3_STEP(0x142, 0xa); A3_STEP(0x143, 0xc);
+#undef A3_STEP
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+// Maximum over the numbers of 16 waves
+__device__ __forceinline__ uint32_t waves_max(const uint32_t *v) {
+  uint32_t x = v[threadIdx.x & 15];
+#define A3_STEP(CTRL) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xf, 0xf, false))
+  A3_STEP(0x111); A3_STEP(0x112); A3_STEP(0x114); A3_STEP(0x118);
+#undef A3_STEP
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 15);
+}
+
+// Rows taken and kept in LDS until all are known: they leave in whole lines
+constexpr int kListRows = 6656;
+
+// list: LDS, [kListRows]: receives the rows instead of rg.out where they fit.
 template <int KPT>
-__device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
+__device__ __forceinline__ void topk_select_reg_body(const topk_range &rg, int *list) {
   __shared__ __align__(16) uint32_t hist[kBins];
-  __shared__ uint32_t wave_a[kWaves], wave_b[kWaves];
-  __shared__ uint32_t sh_bin, sh_need, sh_in, sh_key;
+  __shared__ __align__(16) uint32_t wave_a[kWaves], wave_b[kWaves];
+  __shared__ __align__(16) uint32_t cand[kRankKeys];
+  __shared__ uint32_t above_of[kWaves / 4][kRankKeys];       // candidates above and at or above one, by shares of them
+  __shared__ __align__(16) uint4 sh_found;                   // the bin (or key), how many of it are wanted, how many there are
+  __shared__ uint32_t sh_cand;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = rg.N, k = rg.k;
@@ -233,26 +260,30 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
     }
   }
   for (int i = tid; i < kBins; i += kBlock) hist[i] = 0;
+  if (tid < (int)kRankKeys) cand[tid] = 0;
+  if (tid == 0) sh_cand = 0;
   uint32_t mn = 0xffffffffu, mx = 0u;
 #pragma unroll
   for (int j = 0; j < KPT; ++j)
     if ((j >> 2) < nq) { mn = min(mn, key[j] - 1u); mx = max(mx, key[j]); }     // (0 - 1: no minimum)
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    mn = min(mn, (uint32_t)__shfl_xor((int)mn, off, 64));
-    mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
-  }
-  if (lane == 0) { wave_a[wave] = mn; wave_b[wave] = mx; }
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) { mn = min(mn, wave_a[w]); mx = max(mx, wave_b[w]); }
+  mn = ~wave_max(~mn);
+  mx = wave_max(mx);
+  if (lane == 0) { wave_a[wave] = ~mn; wave_b[wave] = mx; }
+  A3_LDS_BARRIER();
+  mn = ~waves_max(wave_a);
+  mx = waves_max(wave_b);
 
+  // lanes below this one in a ballot, added to n
+  auto lanes_below = [](unsigned long long m, uint32_t n) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, n));
+  };
   // ---- radix select inside [lo, hi]: the key of the k-th largest score ------------------
   // Bins a multiple of 32 apart would share an LDS bank, and scores of few values fall into just such bins.
   auto slot_of = [](uint32_t bin) { return bin ^ ((bin >> 5) & 31u); };
   // Invariant: the wanted key lies in [lo, hi] and is the need-th largest of the keys in there.  (lo >= 1: key 0 less lo
   // lies above hi - lo.)
   uint32_t lo = mn + 1u, hi = mx, need = (uint32_t)k;
+  bool exact = false;                                        // all rows equal to the k-th largest are taken
   while (hi != lo) {                                         // (equal: every candidate is the same key)
     const uint32_t width = hi - lo;
     const int shift = max(0, 21 - __clz((int)width));        // (width >> shift) < kBins
@@ -261,117 +292,134 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
       const uint32_t rel = key[j] - lo;
       if ((j >> 2) < nq && rel <= width) atomicAdd(&hist[slot_of(rel >> shift)], 1u);
     }
-    __syncthreads();
+    A3_LDS_BARRIER();
     // the bin that holds the need-th largest candidate: suffix sums over the bins, two per thread
     const uint2 cs = *reinterpret_cast<const uint2 *>(hist + (slot_of(2 * tid) & ~1u));
     const uint2 c = slot_of(2 * tid) & 1 ? make_uint2(cs.y, cs.x) : cs;
-    uint32_t suf = c.x + c.y;                                // sum over the lanes >= this one
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t x = __shfl_down(suf, off, 64);
-      if (lane + off < 64) suf += x;
-    }
-    if (lane == 0) wave_a[wave] = suf;
-    __syncthreads();
-    uint32_t above = suf - c.x - c.y;                        // candidates in higher bins
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) above += w > wave ? wave_a[w] : 0u;
-    if (above < need && above + c.y >= need) { sh_bin = 2 * tid + 1; sh_need = need - above; sh_in = c.y; }
-    above += c.y;
-    if (above < need && above + c.x >= need) { sh_bin = 2 * tid; sh_need = need - above; sh_in = c.x; }
+    const int upto = a3_wave_prefix((int)(c.x + c.y));       // sum over the lanes <= this one
+    A3_LDS_BARRIER();                                        // (wave_a has been read)
+    if (lane == 63) wave_a[wave] = (uint32_t)upto;
     *reinterpret_cast<uint2 *>(hist + 2 * tid) = make_uint2(0u, 0u);           // for the next round
-    __syncthreads();
-    lo += sh_bin << shift;
+    A3_LDS_BARRIER();
+    int all;
+    const int before = a3_waves_before(reinterpret_cast<const int *>(wave_a), all);
+    uint32_t above = (uint32_t)(all - before - upto);        // candidates in higher bins
+    if (above < need && above + c.y >= need) sh_found = make_uint4(2 * tid + 1, need - above, c.y, 0);
+    above += c.y;
+    if (above < need && above + c.x >= need) sh_found = make_uint4(2 * tid, need - above, c.x, 0);
+    A3_LDS_BARRIER();
+    const uint4 found = sh_found;
+    lo += found.x << shift;
     hi = lo + min(hi - lo, (1u << shift) - 1u);
-    need = sh_need;
-    const uint32_t in_bin = sh_in;                           // candidates left, need of them wanted
+    need = found.y;
+    const uint32_t in_bin = found.z;                         // candidates left, need of them wanted
+    exact = in_bin == need;
     if (lo == hi) break;                                     // the bin was a single key
     if (in_bin <= kRankKeys) {
       // Few candidates left (the usual case after one or two rounds): they are gathered (in any order: what follows
       // does not depend on it) and ranked directly.  The key v with fewer than `need` candidates above it and at least
       // `need` at or above it is the wanted one.
-      uint32_t *cand = hist;
-      __syncthreads();                                       // sh_bin and sh_need have been read
-      if (tid == 0) sh_bin = 0;
-      __syncthreads();
 #pragma unroll
       for (int j = 0; j < KPT; ++j)
-        if ((j >> 2) < nq && key[j] - lo <= hi - lo) cand[atomicAdd(&sh_bin, 1u)] = key[j];
-      __syncthreads();
-      if (tid < (int)kRankKeys && (wave << 6) < (int)in_bin) {
-        const uint32_t mine = tid < (int)in_bin ? cand[tid] : 0u;
-        uint32_t gt = 0, ge = 0;
-        for (uint32_t i = 0; i < in_bin; ++i) { const uint32_t x = cand[i]; gt += x > mine; ge += x >= mine; }
-        // (several lanes hold the wanted key when it occurs more than once: they store the same two numbers)
-        if (tid < (int)in_bin && gt < need && need <= ge) { sh_key = mine; sh_need = need - gt; }
+        if ((j >> 2) < nq && key[j] - lo <= hi - lo) cand[atomicAdd(&sh_cand, 1u)] = key[j];
+      A3_LDS_BARRIER();
+      // 256 threads, one a candidate, count against a quarter of them each; behind the last candidate cand holds zeros, which are
+      // above nothing
+      const int c = tid & ((int)kRankKeys - 1), part = wave / 4, per = ((int)in_bin + 15) / 16 * 4;
+      const uint32_t mine = cand[c];
+      uint32_t gt = 0, ge = 0;
+#pragma unroll 4
+      for (int i = part * per; i < part * per + per; i += 4) {
+        const uint4 x = *reinterpret_cast<const uint4 *>(cand + i);
+        gt += (x.x > mine) + (x.y > mine) + (x.z > mine) + (x.w > mine);
+        ge += (x.x >= mine) + (x.y >= mine) + (x.z >= mine) + (x.w >= mine);
       }
-      __syncthreads();
-      lo = hi = sh_key;
-      need = sh_need;
+      above_of[part][c] = gt | ge << 16;
+      A3_LDS_BARRIER();
+      if (tid < (int)in_bin) {
+        uint32_t sum = 0;
+#pragma unroll
+        for (int u = 0; u < kWaves / 4; ++u) sum += above_of[u][tid];
+        gt = sum & 0xffffu;
+        ge = sum >> 16;
+        // (several lanes hold the wanted key when it occurs more than once: they store the same numbers)
+        if (gt < need && need <= ge) sh_found = make_uint4(mine, need - gt, ge - gt, 0);
+      }
+      A3_LDS_BARRIER();
+      lo = hi = sh_found.x;
+      need = sh_found.y;
+      exact = sh_found.z == need;
       break;
     }
   }
   const uint32_t tau = lo;               // key of the k-th largest; `need` rows equal to it are taken
 
   // ---- ordered compaction: rows above tau and equal to tau per wave, then every row's place from the ballots -------
+  // (where all of the latter are taken, which is the rule, there is nothing to count but the rows at or above tau)
+  const uint32_t top = exact ? tau - 1u : tau;               // (tau >= 1)
   uint32_t n_gt = 0, n_eq = 0;
 #pragma unroll
   for (int j = 0; j < KPT; ++j)
-    if ((j >> 2) < nq) {
-      n_gt += (uint32_t)__popcll(__ballot(key[j] > tau));
-      n_eq += (uint32_t)__popcll(__ballot(key[j] == tau));
-    }
-  __syncthreads();                                           // wave_a, wave_b: free
-  if (lane == 0) { wave_a[wave] = n_gt; wave_b[wave] = n_eq; }
-  __syncthreads();
-  uint32_t gt_before = 0, eq_before = 0;
+    if ((j >> 2) < nq) n_gt += (uint32_t)__popcll(__ballot(key[j] > top));
+  if (!exact) {
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    gt_before += w < wave ? wave_a[w] : 0u;
-    eq_before += w < wave ? wave_b[w] : 0u;
+    for (int j = 0; j < KPT; ++j)
+      if ((j >> 2) < nq) n_eq += (uint32_t)__popcll(__ballot(key[j] == tau));
   }
-  if (n_gt + (eq_before < need ? n_eq : 0u) == 0) return;    // nothing of this wave's block is taken (no barrier follows)
+  if (exact) need = 0;
+  A3_LDS_BARRIER();                                          // wave_a, wave_b: free
+  if (lane == 0) { wave_a[wave] = n_gt; wave_b[wave] = n_eq; }
+  A3_LDS_BARRIER();
+  int all;
+  const uint32_t gt_before = (uint32_t)a3_waves_before(reinterpret_cast<const int *>(wave_a), all);
+  uint32_t eq_before = exact ? 0u : (uint32_t)a3_waves_before(reinterpret_cast<const int *>(wave_b), all);
   // rows equal to tau are taken in index order until `need` of them are: min(eq_before, need) of the earlier ones were taken, and
   // of this wave's all, none, or (in one wave at most) the first few
   const bool some = eq_before < need && eq_before + n_eq > need;
-  const uint32_t above = !some && eq_before < need ? tau - 1u : tau;      // (tau >= 1)
+  const uint32_t above = !some && eq_before < need ? tau - 1u : top;
   uint32_t pos = gt_before + min(eq_before, need);
-  // lanes below this one in a ballot, added to n
-  auto lanes_below = [](unsigned long long m, uint32_t n) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, n));
-  };
+  auto emit = [&](auto put) {
+    if (n_gt + (eq_before < need ? n_eq : 0u) == 0) return;  // nothing of this wave's block is taken
 #pragma unroll
-  for (int q = 0; q < KPT / 4; ++q) {
-    if (q < nq) {
-      bool take[4];
+    for (int q = 0; q < KPT / 4; ++q) {
+      if (q < nq) {
+        bool take[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) take[e] = key[4 * q + e] > above;
-      if (some) {
-        unsigned long long eq[4];
+        for (int e = 0; e < 4; ++e) take[e] = key[4 * q + e] > above;
+        if (some) {
+          unsigned long long eq[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) eq[e] = __ballot(key[4 * q + e] == tau);
-        uint32_t rank = eq_before;                           // rows equal to tau before this one
+          for (int e = 0; e < 4; ++e) eq[e] = __ballot(key[4 * q + e] == tau);
+          uint32_t rank = eq_before;                           // rows equal to tau before this one
 #pragma unroll
-        for (int e = 0; e < 4; ++e) rank = lanes_below(eq[e], rank);
+          for (int e = 0; e < 4; ++e) rank = lanes_below(eq[e], rank);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bool is = (eq[e] >> lane) & 1;
+            take[e] = take[e] || (is && rank < need);
+            rank += is;
+            eq_before += (uint32_t)__popcll(eq[e]);
+          }
+        }
+        uint32_t at = pos;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const bool is = (eq[e] >> lane) & 1;
-          take[e] = take[e] || (is && rank < need);
-          rank += is;
-          eq_before += (uint32_t)__popcll(eq[e]);
+          const unsigned long long b = __ballot(take[e]);
+          at = lanes_below(b, at);
+          pos += (uint32_t)__popcll(b);
         }
-      }
-      uint32_t at = pos;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const unsigned long long b = __ballot(take[e]);
-        at = lanes_below(b, at);
-        pos += (uint32_t)__popcll(b);
+        for (int e = 0; e < 4; ++e)
+          if (take[e]) put(at++, rg.s + A3_ROW(4 * q + e));
       }
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (take[e]) out[at++] = rg.s + A3_ROW(4 * q + e);
     }
+  };
+  if (k <= kListRows) {
+    emit([&](uint32_t at, int row) { list[at] = row; });
+    A3_LDS_BARRIER();
+    for (int i = tid; i < k; i += kBlock) out[i] = list[i];
+  } else {
+    emit([&](uint32_t at, int row) { out[at] = row; });
   }
 #undef A3_ROW
 }
@@ -379,8 +427,9 @@ __device__ __forceinline__ void topk_select_reg_body(const topk_range &rg) {
 template <int KPT>
 __global__ void __launch_bounds__(kBlock)
 topk_select_reg_kernel(const float *__restrict__ scores, topk_problem prob, int *__restrict__ sel_idx) {
+  __shared__ int list[kListRows];
   if (prob.skip) write_fixed_rows(prob, sel_idx);
-  topk_select_reg_body<KPT>(topk_range_of(prob, scores, sel_idx));
+  topk_select_reg_body<KPT>(topk_range_of(prob, scores, sel_idx), list);
 }
 
 // Step 3, the active rows [Re, Q] and the layout of the attention's work in one launch, for a batch of one
@@ -390,19 +439,29 @@ template <int KPT>
 __global__ void __launch_bounds__(kBlock)
 topk_select_plan_kernel(const float *__restrict__ scores, topk_problem prob, int *__restrict__ sel_idx,
                         int *act_idx, int n_act, attn_plan plan, int G, int wgs_per_head, int item_cost) {
-  __shared__ int wave_tot[kPlanThreads / 64];
-  __shared__ int small[kPlanLdsInts];
+  __shared__ __align__(16) int wave_tot[kPlanThreads / 64];
+  __shared__ int small[kPlanLdsInts], list[kListRows];
   static_assert(kPlanThreads == kBlock, "one workgroup shape for both parts");
-  topk_select_reg_body<KPT>(topk_range_of(prob, scores, sel_idx));
-  __syncthreads();                                           // the selection is written (and has left this CU's L1 path)
+  topk_select_reg_body<KPT>(topk_range_of(prob, scores, sel_idx), list);
   const int k = prob.one_N >= 0 ? prob.one_k : prob.sel_start[1] - prob.sel_start[0];
   const int s = prob.one_N >= 0 ? 0 : prob.seg_start[0], N = prob.one_N >= 0 ? prob.one_N : prob.ctx_len[0];
-  if (sel_idx != act_idx)
-    for (int i = threadIdx.x; i < k; i += kBlock) act_idx[i] = sel_idx[i];
-  for (int i = threadIdx.x; k + i < n_act; i += kBlock) act_idx[k + i] = s + N + i;   // the question rows
-  __threadfence_block();
-  __syncthreads();
-  attn_plan_body(plan, act_idx, n_act, prob.seg_start, 1, G, wgs_per_head, item_cost, wave_tot, small, kPlanLdsInts);
+  const int first_q = s + N - k;                             // row i >= k of the list: first_q + i
+  for (int i = threadIdx.x; k + i < n_act; i += kBlock) act_idx[k + i] = first_q + k + i;   // the question rows
+  // The plan reads the selected rows in LDS where they fit: nothing then waits for a store
+  const bool listed = k <= min(N, kListRows);
+  if (!listed || sel_idx != act_idx) {
+    __syncthreads();                                         // the selection is written (and has left this CU's L1 path)
+    if (sel_idx != act_idx)
+      for (int i = threadIdx.x; i < k; i += kBlock) act_idx[i] = sel_idx[i];
+    __threadfence_block();
+    __syncthreads();
+  }
+  if (listed)
+    attn_plan_body(plan, act_idx, [&](int i) { return i < k ? list[i] : first_q + i; }, n_act, prob.seg_start, 1, G, wgs_per_head, item_cost,
+                   wave_tot, small, kPlanLdsInts);
+  else
+    attn_plan_body(plan, act_idx, [&](int i) { return act_idx[i]; }, n_act, prob.seg_start, 1, G, wgs_per_head, item_cost,
+                   wave_tot, small, kPlanLdsInts);
 }
 
 constexpr int kMaxRegKeys = 68 * 1024 - 3;   // rows of a request in registers, from whatever alignment it starts
