@@ -581,18 +581,19 @@ attn_combine_kernel(attn_args a) {
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32: one workgroup per 16 packed (row, head) pairs of a KV head; its eight waves take every eighth block of 16 keys
+// fp32: one workgroup per 16 packed (row, head) pairs of a KV head; its eight or sixteen waves take the blocks of 16 keys in turn
 // and merge at the end
 // ---------------------------------------------------------------------------------------
 // fp32 matrix instruction (16x16x4), fragments straight from memory.  S^T[key][m]: register r of lane (l16, lg) is key
 // 4 lg + r, pair l16 - which is the B operand of the r-th product of O^T[d][m] += V^T P^T when lane group lg supplies key
 // 4 lg + r of V; its lane l16 loads coordinates 4 l16 .. + 3 at once, so block e of O holds coordinates 4 (row) + e.
 // (One workgroup per row and head with a thread per key took 50 us for 108 rows x 8 heads x up to 544 keys.)
-constexpr int kF32Waves = 8;
-constexpr size_t kF32Lds(int d) { return (size_t)kF32Waves * 16 * (d * sizeof(float) + sizeof(float2)); }
+constexpr int f32_waves(int d) { return d == 64 ? 16 : 8; }        // (128 coordinates do not fit the registers of 16)
+constexpr size_t kF32Lds(int d) { return (size_t)f32_waves(d) * 16 * (d * sizeof(float) + sizeof(float2)); }
 template <int D>
-__global__ void __launch_bounds__(64 * kF32Waves)
+__global__ void __launch_bounds__(64 * f32_waves(D))
 attn_f32_kernel(attn_args a) {
+  constexpr int kF32Waves = f32_waves(D);
   extern __shared__ __align__(16) float lds_f[];               // [wave][D / 4 rows of 16 pairs] O as float4, then (ref, sum)
   f32x4 *lds_o = reinterpret_cast<f32x4 *>(lds_f);
   float2 *lds_ml = reinterpret_cast<float2 *>(lds_f + (size_t)kF32Waves * 16 * D);
@@ -609,15 +610,17 @@ attn_f32_kernel(attn_args a) {
 #pragma unroll
     for (int c = 0; c < D / 16; ++c) qf[c] = qp[4 * c];
   }
-  const int t = a.act_idx[arow], req = a.tok_req[t];
-  // the rows of one request at a time (rows are ascending: nearly always all of them)
+  const int t = a.act_idx[arow], req = a.tok_req ? a.tok_req[t] : 0;
+  const int first_key = a.seg_start[req];
+  // the rows of one request at a time (rows are ascending: nearly always all of them), found in the lanes that hold them: lane x of a
+  // group belongs to row a0 + x / G, the last ones to the last row
   for (int b0 = a0; b0 < a_end;) {
-    const int r = a.tok_req[a.act_idx[b0]], base = a.seg_start[r];
-    int b1 = b0;
-    while (b1 < a_end && a.tok_req[a.act_idx[b1]] == r) ++b1;
+    const int r = __builtin_amdgcn_readlane(req, (b0 - a0) * G), base = __builtin_amdgcn_readlane(first_key, (b0 - a0) * G);
+    const uint32_t later = ((uint32_t)__ballot(req != r) & 0xffffu) >> ((b0 - a0) * G);
+    const int b1 = later ? b0 + (int)__builtin_ctz(later) / G : a_end;
     const bool mine = req == r && l16 < (a_end - a0) * G;
     const int limit = mine ? t - base : -1;                    // last visible key (request-relative)
-    const int n_keys = a.act_idx[b1 - 1] - base + 1;
+    const int n_keys = __builtin_amdgcn_readlane(t, (b1 - 1 - a0) * G) - base + 1;
     // The product O^T += V^T P^T gives every pair every key of a block, with weight 0 where it sees none: no harm unless V is
     // infinite or NaN there.  That shows in O, and the wave starts over with each pair adding the keys it sees one by one.
     f32x4 o[D / 16];
@@ -767,7 +770,7 @@ static a3_status attn_launch(const a3_layout *L, const void *q_act, const int *a
   hipStream_t st = (hipStream_t)stream;
   attn_args a;
   a.q = q_act; a.k = k_fused; a.v = v_fused; a.out = out;
-  a.act_idx = act_idx; a.seg_start = L->seg_start; a.tok_req = L->tok_req;
+  a.act_idx = act_idx; a.seg_start = L->seg_start; a.tok_req = L->n_req > 1 ? L->tok_req : nullptr;
   a.n_act = n_act; a.Hq = L->n_q_heads; a.Hkv = L->n_kv_heads; a.d = L->head_dim;
   a.scale2 = a3_scale_of(L) * kLog2e;
   const unsigned G = (unsigned)(L->n_q_heads / L->n_kv_heads);
@@ -804,11 +807,13 @@ static a3_status attn_launch(const a3_layout *L, const void *q_act, const int *a
     const dim3 grid((n_act + rows - 1) / rows, L->n_kv_heads);
     static a3_once_per_device lds_once;
     const hipError_t e = a3_once(lds_once, []() {
-      return hipFuncSetAttribute((const void *)attn_f32_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kF32Lds(128));
+      const hipError_t e64 = hipFuncSetAttribute((const void *)attn_f32_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kF32Lds(64));
+      return e64 != hipSuccess ? e64
+                               : hipFuncSetAttribute((const void *)attn_f32_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kF32Lds(128));
     });
     if (e != hipSuccess) return a3_fail(A3_ERR_HIP, "a3_fused_attention: %s", hipGetErrorString(e));
-    if (L->head_dim == 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64 * kF32Waves), kF32Lds(64), st, a);
-    else hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(64 * kF32Waves), kF32Lds(128), st, a);
+    if (L->head_dim == 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64 * f32_waves(64)), kF32Lds(64), st, a);
+    else hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(64 * f32_waves(128)), kF32Lds(128), st, a);
   }
   A3_CHECK_LAUNCH("a3_fused_attention");
   return A3_OK;

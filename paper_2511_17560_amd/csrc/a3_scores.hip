@@ -17,6 +17,7 @@
 // folded into the scale.
 // fp32: the same two passes on the fp32 matrix instruction.
 #include <mutex>
+#include <type_traits>
 
 #include "a3_internal.h"
 
@@ -903,11 +904,14 @@ scores_head_sum_kernel(scores_args a, const int *__restrict__ tok_chunk) {
 // 16x16x4 products: a lane's 16-byte load holds four consecutive coordinates of one key or row, one for each of four
 // instructions (which coordinate goes to which does not matter as long as both operands agree).  C[key][row]: register
 // r of lane (l16, lg) is key 4 lg + r, row l16.  (One thread per key and row slice, 64 coordinates deep, took 280 +
-// 188 us for 512 keys x 256 rows.)
-template <int PASS, int D>
+// 188 us for 512 keys x 256 rows.)  Small calls are launches and latency: with REALIGN the first pass turns the stale keys itself (a lane holds
+// whole pairs of either layout) and stores them, and the second merges the row statistics of up to 32 tiles and 1024 rows itself (512 keys, 32 rows per head: four launches of 3 - 5 us -> two of 5 - 6).
+constexpr int kF32MergeTiles = 32, kF32MergeRows = 1024;
+template <int PASS, int D, bool REALIGN>
 __global__ void __launch_bounds__(256)
 scores_f32_kernel(scores_args a) {
   __shared__ float2 red[4][16];                                // PASS 0: (max, sum) of the rows over a wave's keys
+  __shared__ float stats[PASS == 1 ? kF32MergeRows : 1];
   const int r = blockIdx.z, g = blockIdx.y;
   const int N = a.ctx_len[r], i0 = blockIdx.x * kTileKeys;
   if (i0 >= N) return;
@@ -917,9 +921,42 @@ scores_f32_kernel(scores_args a) {
   const int key0 = i0 + 16 * wave;                             // first key of the wave
   f32x4 kf[D / 16];
   {
-    const f32x4 *kp = reinterpret_cast<const f32x4 *>((const float *)a.k + ((size_t)min(s + key0 + l16, a.T - 1) * a.Hkv + g) * D) + lg;
+    const size_t at = ((size_t)min(s + key0 + l16, a.T - 1) * a.Hkv + g) * (D / 4) + lg;
+    const f32x4 *kp = reinterpret_cast<const f32x4 *>(REALIGN ? a.k_cat : a.k) + at;
 #pragma unroll
     for (int c = 0; c < D / 16; ++c) kf[c] = kp[4 * c];
+    if (REALIGN && key0 + l16 < N) {
+      // coordinates 16 c + 4 lg .. + 3: two pairs of the interleaved layout, or the first members of pairs with fragment c + D / 32
+      const int chunk = a.tok_chunk[s + key0 + l16];
+      if (chunk < 0) {                                         // (a row of no chunk: it stays what it is)
+        const f32x4 *kp0 = reinterpret_cast<const f32x4 *>(a.k) + at;
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) kf[c] = kp0[4 * c];
+      } else {
+        const float2 *tab = a.chunk_cs + (size_t)chunk * (D / 2);
+        if (a.rope_layout == A3_ROPE_INTERLEAVED) {
+#pragma unroll
+          for (int c = 0; c < D / 16; ++c) {
+            float y[4];
+            a3_rotate_pair(kf[c][0], kf[c][1], tab[8 * c + 2 * lg], y[0], y[1]);
+            a3_rotate_pair(kf[c][2], kf[c][3], tab[8 * c + 2 * lg + 1], y[2], y[3]);
+            kf[c] = f32x4{y[0], y[1], y[2], y[3]};
+          }
+        } else {
+#pragma unroll
+          for (int c = 0; c < D / 32; ++c) {
+            float lo[4], hi[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a3_rotate_pair(kf[c][e], kf[c + D / 32][e], tab[16 * c + 4 * lg + e], lo[e], hi[e]);
+            kf[c] = f32x4{lo[0], lo[1], lo[2], lo[3]};
+            kf[c + D / 32] = f32x4{hi[0], hi[1], hi[2], hi[3]};
+          }
+        }
+        f32x4 *ko = reinterpret_cast<f32x4 *>(a.k_out) + at;
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) ko[4 * c] = kf[c];
+      }
+    }
   }
   auto row_of = [&](int m) { return (qrow0 + m / G) * a.Hq + g * G + m % G; };
   f32x4 qf[D / 16];
@@ -930,9 +967,32 @@ scores_f32_kernel(scores_args a) {
   };
   f32x4 colsum = {0.f, 0.f, 0.f, 0.f};
   if (Mg > 0) load_q(0);
+  const bool merge = PASS == 1 && !a.merged;
+  if (merge) {                                                 // at most kF32MergeTiles tiles, kF32MergeRows rows
+    for (int m = threadIdx.x; m < Mg; m += 256) {
+      const float2 *pp = a.part + row_of(m);
+      const int tiles = (N + kTileKeys - 1) / kTileKeys;
+      const float2 own = a.causal_q ? pp[(size_t)a.n_tiles * a.total_rows] : make_float2(kLeast, 0.f);
+      float mx = own.x, z = own.y;
+      for (int t0 = 0; t0 < tiles; t0 += 8) {
+        float2 p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) p[u] = pp[(size_t)min(t0 + u, tiles - 1) * a.total_rows];
+        float mn = mx;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) mn = fmaxf(mn, p[u].x);
+        z *= exp2f(mx - mn);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) z += t0 + u < tiles ? p[u].y * exp2f(p[u].x - mn) : 0.f;
+        mx = mn;
+      }
+      stats[m] = z > 0.f ? mx + log2f(z) : INFINITY;
+    }
+    __syncthreads();
+  }
   for (int m0 = 0; m0 < Mg; m0 += 16) {
     const int m = m0 + l16, row = row_of(min(m, Mg - 1));
-    const float stat = PASS == 1 ? a.stats[row].x : 0.f;
+    const float stat = PASS == 0 ? 0.f : merge ? stats[min(m, Mg - 1)] : a.stats[row].x;
     f32x4 c4[4];                                               // four chains, so that no product waits for the one before
 #pragma unroll
     for (int e = 0; e < 4; ++e) c4[e] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1064,7 +1124,7 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
   a.one_q_len = one ? L->max_q_len : -1;
   a.k_cat = k_cat; a.k_out = k_fused; a.tok_chunk = L->tok_chunk; a.chunk_cs = (const float2 *)L->rope_chunk_cs;
   a.rope_layout = L->rope_layout;
-  const bool fuse = k_cat != nullptr && bf16 && L->n_chunks > 0;
+  const bool fuse = k_cat != nullptr && L->n_chunks > 0;
   if (k_cat != nullptr && !fuse) {
     s = a3_rope_realign(L, k_cat, k_fused, stream);
     if (s != A3_OK) return s;
@@ -1114,11 +1174,16 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
     }
   } else {
     const dim3 grid(n_tiles, L->n_kv_heads, L->n_req), cgrid((unsigned)((total_rows + 15) / 16));
-    if (L->head_dim == 64) hipLaunchKernelGGL((scores_f32_kernel<0, 64>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((scores_f32_kernel<0, 128>), grid, dim3(256), 0, st, a);
-    hipLaunchKernelGGL(scores_combine_kernel, cgrid, dim3(256), 0, st, a);
-    if (L->head_dim == 64) hipLaunchKernelGGL((scores_f32_kernel<1, 64>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((scores_f32_kernel<1, 128>), grid, dim3(256), 0, st, a);
+    a.merged = n_tiles > kF32MergeTiles || L->max_q_len * G > kF32MergeRows ? 1 : 0;
+    auto launch = [&](auto dim) {
+      constexpr int D = decltype(dim)::value;
+      if (fuse) hipLaunchKernelGGL((scores_f32_kernel<0, D, true>), grid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((scores_f32_kernel<0, D, false>), grid, dim3(256), 0, st, a);
+      if (a.merged) hipLaunchKernelGGL(scores_combine_kernel, cgrid, dim3(256), 0, st, a);
+      hipLaunchKernelGGL((scores_f32_kernel<1, D, false>), grid, dim3(256), 0, st, a);
+    };
+    if (L->head_dim == 64) launch(std::integral_constant<int, 64>{});
+    else launch(std::integral_constant<int, 128>{});
   }
   if (scores)
     hipLaunchKernelGGL(scores_head_sum_kernel, dim3((L->total_tokens + 255) / 256), dim3(256), 0, st, a, L->tok_chunk);

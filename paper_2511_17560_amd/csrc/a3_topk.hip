@@ -432,7 +432,7 @@ topk_select_reg_kernel(const float *__restrict__ scores, topk_problem prob, int 
   topk_select_reg_body<KPT>(topk_range_of(prob, scores, sel_idx), list);
 }
 
-// Step 3, the active rows [Re, Q] and the layout of the attention's work in one launch, for a batch of one
+// Step 3, the active rows [Re, Q] and (bf16) the layout of the attention's work in one launch, for a batch of one
 // request (one workgroup ranks it anyway): the selection goes to sel_idx and to the head of act_idx, the question
 // rows behind it, and the same workgroup then lays out the attention (a3_attn_plan.h) from the list it just wrote.
 template <int KPT>
@@ -447,6 +447,13 @@ topk_select_plan_kernel(const float *__restrict__ scores, topk_problem prob, int
   const int s = prob.one_N >= 0 ? 0 : prob.seg_start[0], N = prob.one_N >= 0 ? prob.one_N : prob.ctx_len[0];
   const int first_q = s + N - k;                             // row i >= k of the list: first_q + i
   for (int i = threadIdx.x; k + i < n_act; i += kBlock) act_idx[k + i] = first_q + k + i;   // the question rows
+  if (plan.max_tiles == 0) {                                 // fp32: the attention needs no plan
+    if (sel_idx != act_idx) {
+      __syncthreads();
+      for (int i = threadIdx.x; i < k; i += kBlock) act_idx[i] = sel_idx[i];
+    }
+    return;
+  }
   // The plan reads the selected rows in LDS where they fit: nothing then waits for a store
   const bool listed = k <= min(N, kListRows);
   if (!listed || sel_idx != act_idx) {
@@ -618,7 +625,7 @@ extern "C" a3_status a3_topk_select_plan(const a3_layout *L, const float *scores
              "a3_topk_select_plan: total_k %d, n_act %d (of %d rows)", total_k, n_act, L->total_tokens);
   A3_REQUIRE(scores && sel_start && act_idx && (sel_idx || total_k == 0), A3_ERR_INVALID_ARG,
              "a3_topk_select_plan: NULL argument");
-  const bool one = L->n_req == 1 && L->dtype == A3_BF16 && L->max_ctx_len <= kMaxRegKeys && total_k > 0 && n_act > 0;
+  const bool one = L->n_req == 1 && L->max_ctx_len <= kMaxRegKeys && total_k > 0 && n_act > 0;
   if (!one) {
     A3_REQUIRE(sel_idx != act_idx || L->n_req == 1, A3_ERR_INVALID_ARG,
                "a3_topk_select_plan: sel_idx may only be act_idx itself in a batch of one request");
@@ -636,10 +643,12 @@ extern "C" a3_status a3_topk_select_plan(const a3_layout *L, const float *scores
   }
   A3_REQUIRE((long long)total_k <= (long long)L->max_ctx_len, A3_ERR_INVALID_ARG,
              "a3_topk_select_plan: total_k %d exceeds the number of context rows", total_k);
-  A3_REQUIRE(ws != nullptr && ws_bytes >= a3_attn_ws_bytes(L, n_act), A3_ERR_WORKSPACE,
-             "a3_topk_select_plan: workspace %zu bytes, need %zu", ws_bytes, a3_attn_ws_bytes(L, n_act));
-  attn_plan plan;
-  attn_plan_carve(L, n_act, ws, ws_bytes, &plan);
+  attn_plan plan{};
+  if (L->dtype == A3_BF16) {
+    A3_REQUIRE(ws != nullptr && ws_bytes >= a3_attn_ws_bytes(L, n_act), A3_ERR_WORKSPACE,
+               "a3_topk_select_plan: workspace %zu bytes, need %zu", ws_bytes, a3_attn_ws_bytes(L, n_act));
+    attn_plan_carve(L, n_act, ws, ws_bytes, &plan);
+  }
   topk_problem prob{L->seg_start, L->ctx_len, sel_start, nullptr, nullptr, 0, 0};
   if (L->max_ctx_len + L->max_q_len == L->total_tokens) {   // the one request's lengths are the layout's maxima
     prob.one_N = L->max_ctx_len;
