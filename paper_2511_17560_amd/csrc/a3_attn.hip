@@ -82,10 +82,16 @@ __global__ void __launch_bounds__(kAttnThreads, 1)
 attn_bf16_kernel(attn_args a) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int g = blockIdx.x % a.Hkv, wg = blockIdx.x / a.Hkv;
-  // a plan made with another number of workgroups per head lies elsewhere in the workspace: touch nothing
-  if (a.plan.counters[3] != a.plan.max_wgs || wg >= a.plan.counters[2]) return;
+  // What the workgroup is to do, its first item included, is requested at once: one look-up behind the other they were three round trips
+  // to what another XCD has just written, in front of the first keys (layer pass of 2K rows 110.8 -> 108.5 us with the merge, of 5K 155 -> 153.7)
+  const int max_wgs = a.plan.counters[3], n_wgs = a.plan.counters[2];
   const int item_begin = a.plan.wg_start[wg], item_end = a.plan.wg_start[wg + 1];
-  if (item_begin >= item_end) return;
+  attn_item first_item = {};
+  if (a.plan.wg_first) first_item = reinterpret_cast<const attn_item *>(a.plan.wg_first)[wg];
+  asm volatile("" :: "s"(max_wgs), "s"(n_wgs), "s"(item_begin), "s"(item_end), "s"(first_item.k_begin), "s"(first_item.m_end));
+  // a plan made with another number of workgroups per head lies elsewhere in the workspace: touch nothing
+  if (max_wgs != a.plan.max_wgs || wg >= n_wgs || item_begin >= item_end) return;
+  if (!a.plan.wg_first) first_item = reinterpret_cast<const attn_item *>(a.plan.items)[item_begin];
   const int G = a.Hq / a.Hkv;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, lg = lane >> 4, grp = wave >> 2;
@@ -97,11 +103,12 @@ attn_bf16_kernel(attn_args a) {
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) i32x4 lds_i32x4;
   lds_i32x4 *table = (lds_i32x4 *)(lds + kRingBytes + wave * (kTableItems * sizeof(attn_item)));
-  auto table_fill = [&](int first, int n) {                  // items first .. first + n - 1 (2 n <= 64)
+  auto table_load = [&](int first) { return reinterpret_cast<const i32x4 *>(a.plan.items)[2 * min(first + lane / 2, item_end - 1) + (lane & 1)]; };
+  auto table_store = [&](int first, int n, const i32x4 &x) { // items first .. first + n - 1 (2 n <= 64)
     const int i = first + lane / 2;
-    if (lane < 2 * n && i < item_end) table[(i - item_begin) % kTableItems * 2 + (lane & 1)] = reinterpret_cast<const i32x4 *>(a.plan.items)[2 * i + (lane & 1)];
+    if (lane < 2 * n && i < item_end) table[(i - item_begin) % kTableItems * 2 + (lane & 1)] = x;
   };
-  table_fill(item_begin, kTableItems);
+  const i32x4 first_items = table_load(item_begin);
   auto item_at = [&](int i) {
     const lds_i32x4 *d = table + (i - item_begin) % kTableItems * 2;
     const i32x4 x = d[0], y = d[1];
@@ -132,8 +139,7 @@ attn_bf16_kernel(attn_args a) {
   attn_stream ld = {0, 0, 0};
   bool l_same = false;                                       // both tiles are of one item
   constexpr uint32_t kRowBytes = kD * sizeof(bf16_t);
-  auto load_from = [&](int i) {
-    const attn_item d = item_at(i);
+  auto load_from = [&](const attn_item &d) {
     ld.enter(d.k_begin, d.k_end, pitch);
     const uint32_t bytes = attn_stream::bytes(d.kv_len, pitch, kRowBytes);
     const uint64_t at = ((uint64_t)(uint32_t)d.base * a.Hkv + g) * kRowBytes, pk = (uint64_t)a.k + at, pv = (uint64_t)a.v + at;
@@ -146,9 +152,9 @@ attn_bf16_kernel(attn_args a) {
     l_same = ld.same();
     if (!l_same) {
       if (l_item + 1 < item_end) {
-        load_from(++l_item);
+        load_from(item_at(++l_item));
         if ((l_item - item_begin) % (kTableItems / 2) == kTableItems / 4)
-          table_fill(l_item + kTableItems / 4, kTableItems / 2);
+          table_store(l_item + kTableItems / 4, kTableItems / 2, table_load(l_item + kTableItems / 4));
       } else {
         ld.end();
       }
@@ -247,14 +253,19 @@ attn_bf16_kernel(attn_args a) {
 #define A3_P(KS, RB) __builtin_bit_cast(bf16x8, u32x4{pu[KS][RB][0], pu[KS][RB][1], pu[KS][RB][2], pu[KS][RB][3]})
 #define A3_FENCE __builtin_amdgcn_sched_barrier(0);
 
-  cur = item_at(item_begin);
+  cur = first_item;
   prev_row[0] = prev_row[1] = 1u << 31;
-  load_from(item_begin);
+  load_from(first_item);
+  // the looked-up items are needed below only where the first has fewer than three tiles: else nothing waits for them before the keys are requested
+  const bool at_once = ld.left >= 3;
+  if (!at_once) table_store(item_begin, kTableItems, first_items);
   uint32_t s0 = 0, s1 = kStageBytes, s2 = 2 * kStageBytes, s3 = 3 * kStageBytes;     // stages of tiles u .. u + 3
   load_k(s0, 0); load_k(s0, 1); load_step(); load_on();
   load_k(s1, 0); load_k(s1, 1); load_v(s0, 0); load_v(s0, 1); load_step(); load_on();
   load_rows();
-  load_k(s2, 0); load_k(s2, 1); load_v(s1, 0); load_v(s1, 1); load_step(); load_on();
+  load_k(s2, 0); load_k(s2, 1); load_v(s1, 0); load_v(s1, 1); load_step();
+  if (at_once) table_store(item_begin, kTableItems, first_items);
+  load_on();
   __builtin_amdgcn_s_waitcnt(0);                                         // this wave's part of tiles 0, 1 and K of tile 2 has landed
   __builtin_amdgcn_s_barrier();                                          // ... and everybody's
   if (grp == 1) __builtin_amdgcn_s_barrier();                            // one phase behind
@@ -510,17 +521,19 @@ attn_bf16_kernel(attn_args a) {
 __global__ void __launch_bounds__(256)
 attn_combine_kernel(attn_args a) {
   const int t = blockIdx.x, g = blockIdx.y;
-  if (a.plan.counters[3] != a.plan.max_wgs || t >= a.plan.counters[0]) return;
+  // (all of it looked up at once: the merge of 2K context 7.5 -> 7.2 us)
   const int2 tb = a.plan.tile_b[t];
-  const int nseg = tb.y;
-  if (nseg <= 1) return;
   const int4 ta = a.plan.tile_a[t];
+  const int n_tiles = a.plan.counters[0], max_wgs = a.plan.counters[3];
+  asm volatile("" :: "s"(tb.x), "s"(tb.y), "s"(ta.x), "s"(ta.y), "s"(ta.w), "s"(n_tiles), "s"(max_wgs));
+  const int nseg = tb.y;
+  if (max_wgs != a.plan.max_wgs || t >= n_tiles || nseg <= 1) return;
   const int G = a.Hq / a.Hkv;
   const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4, rb = (threadIdx.x >> 6) & 1, half = threadIdx.x >> 7;
   const int ml = blockIdx.z * 32 + 16 * rb + l16;
   const int m = ta.y + ml;
   if (m >= ta.w) return;
-  const int arow = a.plan.a_lo[ta.x] + m / G, hq = g * G + m % G;
+  const int ar = G == 1 ? m : (int)__umulhi((uint32_t)m, a.inv_G), arow = ta.x + ar, hq = g * G + m - ar * G;
   const size_t p0 = (size_t)g * a.plan.max_items + tb.x;
   const float2 *ml_p = a.plan.part_ml + p0 * kTM + ml;
   const f32x4 *o_p = reinterpret_cast<const f32x4 *>(a.plan.part_o) + (p0 * (kTM / 16) + 2 * blockIdx.z + rb) * 512 + 256 * half + lane;

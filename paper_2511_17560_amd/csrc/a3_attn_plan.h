@@ -12,6 +12,7 @@ namespace {
 constexpr int kTM = 256;            // packed (row, head) pairs per work item: 32 per wave of the attention kernel
 constexpr int kMinSteps = 4;        // key steps of a share, at least (2K context: 37 us with 8, 33 with 4 or less)
 constexpr int kPlanThreads = 1024;
+constexpr int kOneShares = 64;      // shares that one wave can lay out
 constexpr int kPlanLdsInts = 6144;  // LDS the plan kernel sets aside for the plan's small arrays (24 KB)
 
 // Work decomposition written by the plan kernel.
@@ -27,11 +28,13 @@ struct attn_item { int k_begin, k_end, kv_len, m0, m_end, a0, base, whole; };   
 struct attn_plan {
   int *a_lo;         // [n_req+1] first active row of each request
   int *tile_start;   // [n_req+1] first tile of each request
-  int4 *tile_a;      // [max_tiles] (request, first m, visible keys of the last row, rows*G of the request)
+  int4 *tile_a;      // [max_tiles] (first active row of the request, first m, visible keys of the last row, rows*G of the request)
   int2 *tile_b;      // [max_tiles] (first item, number of items)
   int *tile_pre;     // [max_tiles+1] key steps of all earlier tiles
   int4 *items;       // [max_items][2] all the attention kernel needs of an item (attn_item), in work order
   int *wg_start;     // [max_wgs+1] first item of each workgroup of a head
+  int4 *wg_first;    // [max_wgs][2] that item again, at a place that a workgroup knows without looking wg_start up; NULL above
+                     // kOneShares workgroups
   int *counters;     // n_tiles, n_items, P, max_wgs the plan was made with (first in the workspace: its place
                      // does not depend on the sizes of the other arrays)
   float *part_o;     // [Hkv * max_items][16 rows x 16][16 dims x 8][lane][4] unnormalised partial O of cut tiles: lane (l16, lg)
@@ -145,7 +148,7 @@ __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *
       if (last > nr - 1) last = nr - 1;
       const int kv = row(a_lo[r] + last) - base_of(r) + 1;
       steps = (kv + kTK - 1) / kTK;
-      p.tile_a[t] = make_int4(r, j * kTM, kv, nr * G);
+      p.tile_a[t] = make_int4(a_lo[r], j * kTM, kv, nr * G);
       if (in_lds) { tile_kv[t] = kv; tile_req[t] = r; }
     }
     int total;
@@ -209,9 +212,12 @@ __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *
     const int pre = tile_pre[t] + item_cost, nxt = tile_pre[t + 1];      // key step s of the tile sits at pre + s
     const int it_b = (int)(s_beg > pre ? s_beg - pre : 0), it_e = (int)((s_end < nxt ? s_end : nxt) - pre);
     const int kv = in_lds ? tile_kv[t] : p.tile_a[t].z;
-    const int r = n_req == 1 ? 0 : in_lds ? tile_req[t] : p.tile_a[t].x;
-    p.items[2 * idx] = make_int4(it_b * kTK, min(kv, it_e * kTK), kv, (t - tile_start[r]) * kTM);
-    p.items[2 * idx + 1] = make_int4((a_lo[r + 1] - a_lo[r]) * G, a_lo[r], base_of(r), it_b == 0 && s_end >= nxt);
+    const int r = n_req == 1 ? 0 : in_lds ? tile_req[t] : upper_bound_i32(tile_start, n_req, t) - 1;
+    const int4 x = make_int4(it_b * kTK, min(kv, it_e * kTK), kv, (t - tile_start[r]) * kTM);
+    const int4 y = make_int4((a_lo[r + 1] - a_lo[r]) * G, a_lo[r], base_of(r), it_b == 0 && s_end >= nxt);
+    p.items[2 * idx] = x;
+    p.items[2 * idx + 1] = y;
+    if (i == 0 && p.wg_first) { p.wg_first[2 * tid] = x; p.wg_first[2 * tid + 1] = y; }
     if (it_b == 0) p.tile_b[t].x = idx;
   }
   if (tid == 0) {
@@ -224,7 +230,7 @@ __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *
 // The same plan of one request by one wave, without barriers: a lane takes consecutive tiles, then a share.  What bounds the plan is the chain
 // of its steps (LDS round trips, scans), not their number: with all 16 waves in step, a barrier on either side of every scan and bisections and
 // divisions for each tile's number of items, it took 10.1 thousand cycles behind the selection of 2K rows, like this 4.7.
-constexpr int kOneTiles = 512, kOneShares = 64;
+constexpr int kOneTiles = 512;
 template <class Row>
 __device__ __forceinline__ void attn_plan_one(const attn_plan &p, Row row, int n_act, int base, int G, int wgs_per_head, int item_cost, int *lds) {
   if (threadIdx.x >= 64) return;
@@ -290,8 +296,10 @@ __device__ __forceinline__ void attn_plan_one(const attn_plan &p, Row row, int n
     if (idx >= p.max_items) break;
     const int at = pre[t] + item_cost, nxt = pre[t + 1], kv = kvs[t];    // key step s of the tile sits at `at` + s
     const int it_b = max(s_beg - at, 0), it_e = min(s_end, nxt) - at;
-    p.items[2 * idx] = make_int4(it_b * kTK, min(kv, it_e * kTK), kv, t * kTM);
-    p.items[2 * idx + 1] = make_int4(rows, 0, base, it_b == 0 && s_end >= nxt);
+    const int4 x = make_int4(it_b * kTK, min(kv, it_e * kTK), kv, t * kTM), y = make_int4(rows, 0, base, it_b == 0 && s_end >= nxt);
+    p.items[2 * idx] = x;
+    p.items[2 * idx + 1] = y;
+    if (i == 0) { p.wg_first[2 * lane] = x; p.wg_first[2 * lane + 1] = y; }
     if (it_b == 0) p.tile_b[t].x = idx;
     atomicAdd(&parts[t], 1);
   }
@@ -368,6 +376,7 @@ inline void attn_plan_carve(const a3_layout *L, int n_act, void *ws, size_t ws_b
   p->wg_start = (int *)cur.take((size_t)(wgs_per_head + 1) * sizeof(int));
   p->part_o = (float *)cur.take((size_t)max_items * Hkv * kTM * 128 * sizeof(float));
   p->part_ml = (float2 *)cur.take((size_t)max_items * Hkv * kTM * sizeof(float2));
+  p->wg_first = wgs_per_head <= kOneShares ? (int4 *)cur.take((size_t)wgs_per_head * 2 * sizeof(int4)) : nullptr;     // 2 KB at most
   p->max_tiles = max_tiles; p->max_items = max_items; p->max_wgs = wgs_per_head;
 }
 
