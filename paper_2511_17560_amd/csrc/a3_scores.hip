@@ -4,17 +4,14 @@
 //
 // A column sum of row softmaxes needs every row's (max, sum exp) before any column can be
 // summed, so the logits are formed twice:
-//   pass A   per (run of keys, row): partial (max, sum exp)       -> workspace
-//   pass B   per run of keys: the partials of a row are merged (in the prologue; the fp32 path has a small
-//            kernel for it), then sum over all rows of exp(l - max)/sum -> per KV head column sums
+//   pass A   per (tile of keys, row): partial (max, sum exp)      -> workspace
+//   pass B   per tile of keys: the partials of a row are merged (by the pass itself, or by a small kernel before it where there are
+//            many), then sum over all rows of exp(l - max)/sum -> per KV head column sums
 //   head sum per token: the KV heads in order                      -> scores
 // Rows, then heads, are reduced in a fixed order, so the result is deterministic (no atomics).
 //
-// bf16: logits on the matrix cores (32x32x16 bf16 MFMA), two kernels.  Up to 256 rows per KV head (a question of
-// 64 tokens at 4 query heads per KV head): keys and the rows' Q tile stream through LDS by direct-to-LDS loads,
-// one workgroup per CU with its whole run of keys in flight (scores_bf16_kernel).  More rows: a 256-key tile
-// stays in LDS and the waves walk the rows, two workgroups per CU (scores_rows_bf16_kernel).  exp2 with log2(e)
-// folded into the scale.
+// bf16: logits on the matrix cores (16x16x32 bf16 MFMA), a wave's keys in registers, the rows' Q through LDS.  exp2 with log2(e) folded
+// into the scale.
 // fp32: the same two passes on the fp32 matrix instruction.
 #include <mutex>
 #include <type_traits>
@@ -27,6 +24,12 @@ constexpr float kLog2e = 1.4426950408889634f;
 // Where a row's maximum starts.  The first keys that a lane, wave or tile sees may all have logits of -inf for a row, by their values or
 // as masked question keys: the maximum is finite all the same, and their weights come out as exp2(-inf) = 0
 constexpr float kLeast = -3.402823466e38f;
+
+// log2(z 2^m), z > 0: the logarithm of a number in [1/2, 1), so that its error is small against the sum's rounding whatever z is
+__device__ __forceinline__ float log2_sum(float m, float z) {
+  const int e = __builtin_amdgcn_frexp_expf(z);
+  return m + ((float)e + log2f(__builtin_amdgcn_frexp_mantf(z)));
+}
 
 // largest i in [0, n) with a[i] <= x (a ascending, a[0] <= x)
 __device__ __forceinline__ int find_segment(const int *__restrict__ a, int n, int x) {
@@ -42,16 +45,17 @@ struct scores_args {
   const void *q;            // [sum q_len, Hq, d]
   const void *k;            // [T, Hkv, d]
   const int *seg_start, *ctx_len, *q_len, *q_start;
-  float2 *part;             // [n_tiles, total_rows] partial (max, sum) in the exp2 domain
+  float2 *part;             // fp32: [n_tiles + 1, total_rows] partial (max, sum) in the exp2 domain
+  float *part_z, *part_m;   // bf16, in its place: [n_tiles + 1, total_rows] each, the sum z = sum exp2(l), or -z and the maximum that z
+                            // is taken against
   float2 *stats;            // [total_rows] (max + log2(sum), unused): written by the combine kernel
-  int merged;               // bf16 path: the combine kernel has run (more than 32 runs of keys, or rows in chunks);
-                            // otherwise the second pass merges the partials itself
+  int merged;               // the combine kernel has run; otherwise the second pass merges the partials itself
   float *scores;            // [T]
   float *part_scores;       // [Hkv, T] bf16 path: per KV head partial scores
   int n_req, Hq, Hkv, d, T, total_rows, n_tiles, tile_keys;
   uint32_t inv_G;           // ceil(2^32 / G) for G > 1: m / G = umulhi(m, inv_G) for every m < 2^32 / G
+  uint32_t inv_heads, inv_runs[2];   // the same for Hkv and the tiles of a request in either pass; 0: no such number, divide
   float scale2;             // sm_scale * log2(e)
-  float inv_scale2;
   int one_ctx_len, one_q_len;   // a single request whose segment starts at row 0: its lengths; otherwise -1
   // fused position recovery (first pass of the bf16 path only): stale keys in, realigned keys out
   const void *k_cat;        // [T, Hkv, d] keys at chunk-local positions
@@ -61,9 +65,19 @@ struct scores_args {
   int rope_layout;
   // the softmax of a question token also runs over the question keys up to itself (their (max, sum) sits
   // in the extra partial slot n_tiles): the literal denominator of Eq. 3 and the window votes of the
-  // eviction extension
-  int causal_q;
+  // eviction extension.  own_tile: bf16, that slot is written by a tile of the first pass
+  int causal_q, own_tile;
 };
+
+// bf16: partial i as (max, sum), and back
+__device__ __forceinline__ float2 partial(const float *z, const float *m, size_t i) {
+  const float x = z[i];
+  return x < 0.f ? make_float2(m[i], -x) : make_float2(x > 0.f ? 0.f : kLeast, x);
+}
+__device__ __forceinline__ void store_partial(float *pz, float *pm, size_t i, float m, float z) {
+  pz[i] = m == 0.f || z == 0.f ? z : -z;
+  if (m != 0.f && z != 0.f) pm[i] = m;
+}
 
 // ---------------------------------------------------------------------------------------
 // (max, sum exp) of a question row over the question keys it sees (itself and the earlier ones of its
@@ -109,7 +123,11 @@ scores_question_stats_kernel(scores_args a) {
     z = (lane & off) ? zb + za : za + zb;
     m = mn;
   }
-  if (lane == 0) a.part[(size_t)a.n_tiles * a.total_rows + row] = make_float2(m, z);
+  // (bf16: the rows of a KV head one after the other)
+  const int G = a.Hq / a.Hkv, at = sizeof(T) == 2 ? (a.q_start[r]) * a.Hq + g * a.q_len[r] * G + j * G + hq - g * G : row;
+  if (lane != 0) return;
+  if constexpr (sizeof(T) == 2) store_partial(a.part_z, a.part_m, (size_t)a.n_tiles * a.total_rows + at, m, z);
+  else a.part[(size_t)a.n_tiles * a.total_rows + at] = make_float2(m, z);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -117,8 +135,14 @@ scores_question_stats_kernel(scores_args a) {
 // ---------------------------------------------------------------------------------------
 constexpr int kTileKeys = 64;      // fp32 kernels
 
+template <bool BF16>
 __global__ void __launch_bounds__(256)
 scores_combine_kernel(scores_args a) {
+  auto part = [&](int t, int row) {
+    const size_t i = (size_t)t * a.total_rows + row;
+    if constexpr (BF16) return partial(a.part_z, a.part_m, i);
+    else return a.part[i];
+  };
   // one row per 16 lanes: the lanes split the row's tiles, then merge pairwise (fixed tree)
   const int row = blockIdx.x * 16 + (threadIdx.x >> 4);
   const int slice = threadIdx.x & 15;
@@ -130,7 +154,7 @@ scores_combine_kernel(scores_args a) {
     for (int t = slice; t < tiles; t += 64) {                  // the loads of four tiles together
       float2 p[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) p[u] = a.part[(size_t)min(t + 16 * u, tiles - 1) * a.total_rows + row];
+      for (int u = 0; u < 4; ++u) p[u] = part(min(t + 16 * u, tiles - 1), row);
 #pragma unroll
       for (int u = 0; u < 4; ++u)
         if (t + 16 * u < tiles) {
@@ -140,8 +164,8 @@ scores_combine_kernel(scores_args a) {
         }
     }
     if (a.causal_q && slice == 15) {                           // the question keys' share (slice 15 has the fewest tiles)
-      float2 p = a.part[(size_t)a.n_tiles * a.total_rows + row];
-      float mn = fmaxf(m, p.x);
+      const float2 p = part(a.n_tiles, row);
+      const float mn = fmaxf(m, p.x);
       z = (z > 0.f ? z * exp2f(m - mn) : 0.f) + p.y * exp2f(p.x - mn);
       m = mn;
     }
@@ -156,37 +180,45 @@ scores_combine_kernel(scores_args a) {
     m = mn;
   }
   // exp2(l - m) / z = exp2(l - (m + log2 z)): pass B subtracts one number per row
-  if (slice == 0 && row < a.total_rows) a.stats[row] = make_float2(z > 0.f ? m + log2f(z) : INFINITY, 0.f);
+  if (slice == 0 && row < a.total_rows) a.stats[row] = make_float2(z > 0.f ? log2_sum(m, z) : INFINITY, 0.f);
 }
 
 // ---------------------------------------------------------------------------------------
-// bf16 MFMA kernels, head_dim 128.  PASS 0 = partial row statistics, PASS 1 = column sums.
+// bf16 MFMA kernel, head_dim 128.  PASS 0 = partial row statistics, PASS 1 = column sums.
 //
-// Workgroup (8 waves) = up to 256 (question token, head) rows of one KV head against one run of
-// `tile_keys` context keys of one request.  The keys stream through a ring of eight 64-key slots in LDS
-// (direct-to-LDS loads by waves 0-3: four slots and the rows' Q tile are requested first thing, whole 256-byte
-// rows, coalesced; the Q tile is read into registers once and its place then serves as slots 4-7, so a run of
-// up to 512 keys is in flight in full).  Wave (rg, kh) owns rows 64 rg .. 64 rg + 63 and the keys
-// 32 kh .. 32 kh + 31 of every slot; the two waves of a row group share a SIMD and run their matrix phase (the
-// logits of a block: 16 MFMAs) and their vector phase (the exponentials of a block) in opposite order.
-//   PASS 0  C[key][row]: a lane owns a row; per-row (max, sum exp) over the run -> one partial per (run, row)
-//   PASS 1  C[row][key]: a lane owns a key; the partials of all runs are merged per row (fixed order, the
-//           same in every workgroup), then sum over rows of exp2(l - stat) -> per (KV head, row chunk) column
-//           sums; a last small kernel adds them in fixed order.
+// Workgroup (8 waves, two per CU) = one KV head of one request against a tile of 256 context keys.  A wave keeps its 32 keys in registers, as
+// matrix operands, and walks all rows m = (question token, head) of the KV head; the rows' Q comes through two LDS buffers of 128
+// rows, which all waves share.  So no key goes through LDS; a wave forms whole column sums by itself and meets the others only where
+// row statistics are merged or Q is exchanged; and Eq. 2 turns the keys where they lie (a lane holds whole pairs of either layout).
+//   PASS 0  C[key][row]: a lane owns a row; sums of exp2(l) over the wave's keys, merged over the waves -> one partial (max, sum) per
+//           (tile, row).  The sums are taken as they come, without the row's maximum: fp32 holds them over 2^-64 .. 2^100 with the
+//           precision it has anywhere, and where one lies outside the wave forms its sums again with the maximum.
+//   PASS 1  C[row][key]: a lane owns a key; the partials of all tiles are merged per row (fixed order, the same in every workgroup),
+//           then sum over rows of exp2(l - stat) -> per KV head column sums; a last small kernel adds them in fixed order.
+// What bounds it: the issue port.  32 rows x 32 keys are 16 products, 16 x (fma, exp2, add) and 10 LDS reads of a wave, 390 cycles of a
+// SIMD with four waves in a loop of nothing else; 450 - 650 are reached, the rest goes into a tile's start.  All LDS addresses are four
+// registers and constants, Q's offsets six instructions a row, and a partial is one number as long as nothing left fp32's range.
+// Whole calls with position recovery, us, and without (before: keys through LDS, rows in registers, a kernel each for up to 256 rows and for
+// more): 65.6K keys of eight requests, 32 .. 128 question tokens, 209 -> 178 and 172 -> 150; 30K keys, 96 tokens, 106 -> 85 and 92 -> 71; 64K, 64 tokens,
+// 147 -> 136 and 109 -> 107; 16K, 64 tokens, 48 -> 45 and 37.5 -> 35.4; 2K, 32 tokens, 24 -> 21 and 19.5 -> 17; 5K, 64 tokens, 27 -> 26.5 and 21.4 -> 21.7.
+// Scores against float64: 1.6 .. 6e-7 -> 0.6 .. 0.9e-7 (log2_sum).
 // ---------------------------------------------------------------------------------------
 constexpr int kD = 128;
-constexpr int kKRowBytes = kD * 2;                 // LDS rows are unpadded; their 16-byte pieces are XOR-swizzled
-constexpr int kSlotKeys = 64;
-constexpr int kSlots = 8;                          // the Q tile first occupies the place of slots 4 .. 7
-constexpr int kSlotBytes = kSlotKeys * kKRowBytes; // 16 KB
-constexpr int kChunkRows = 256;                    // rows of the score matrix per workgroup
-constexpr int kScoreThreads = 512;
-constexpr int kMinTileKeys = 256, kMaxTileKeys = 1024;
-constexpr int kLdsQ = 4 * kSlotBytes;                            // Q tile [256][128] bf16, swizzled: read into registers
-static_assert(kChunkRows * kKRowBytes == 4 * kSlotBytes, "the Q tile takes the place of four slots");   // before slot 4 is filled
-constexpr int kLdsSt = kSlots * kSlotBytes;                       // [256] float: max + log2(sum) per row (PASS 1)
-constexpr int kLdsRed = kLdsSt + kChunkRows * 4;                  // [4 rg][tile_keys] float column sums (PASS 1)
-constexpr size_t kScoresLds = kLdsRed + 4 * kMaxTileKeys * 4;
+constexpr int kKRowBytes = kD * 2;
+constexpr int kKeysWave = 32;                      // keys of a wave
+constexpr int kWaves = 8;
+constexpr int kTile = kKeysWave * kWaves;          // keys of a workgroup
+constexpr int kThreads = 64 * kWaves;
+constexpr int kChunk = 128;                        // rows of Q in an LDS buffer
+constexpr int kChunkBytes = kChunk * kKRowBytes;
+constexpr int kStatRows = 512;                     // row statistics in LDS (PASS 1)
+constexpr float kSumLow = 0x1p-64f, kSumHigh = 0x1p100f;
+// Q's buffers, then PASS 0: (max, sum) of a chunk's rows of every wave, twice; PASS 1: statistics of kStatRows rows, half of a merge
+constexpr size_t scores_lds_bytes(int bufs, int pass) {
+  return (size_t)bufs * kChunkBytes + (pass == 0 ? 2 * kWaves * kChunk * sizeof(float2) : kStatRows * sizeof(float) + kThreads / 2 * sizeof(float2));
+}
+static_assert(2 * scores_lds_bytes(2, 0) <= 160 * 1024 && scores_lds_bytes(2, 1) <= scores_lds_bytes(2, 0), "two workgroups per CU");
+
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float halves_max(float x) {
@@ -199,682 +231,315 @@ __device__ __forceinline__ float halves_sum(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-// vmcnt(n) alone (the other counters open): n = 0 .. 63
-#define A3_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | (7 << 4) | (15 << 8))
+__device__ __forceinline__ float swap16_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 
-// row m = j * G + hh of a KV head's row space -> row of the [sum q_len, Hq] query tensor
-struct row_map {
-  int G, Hq, g, qrow0;
-  uint32_t inv_G;
-  __device__ __forceinline__ int operator()(int m) const {
-    const int j = G > 1 ? (int)__umulhi((uint32_t)m, inv_G) : m;
-    return (qrow0 + j) * Hq + g * G + (m - j * G);
-  }
-};
-
-// At most 256 rows per KV head (longer questions and wide groups go to scores_rows_bf16_kernel below).
 template <int PASS, bool REALIGN>
-__global__ void __launch_bounds__(kScoreThreads, 2)
+__global__ void __launch_bounds__(kThreads, 4)
 scores_bf16_kernel(scores_args a) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  // ---- which part of the problem: blockIdx % Hkv = KV head (with 8 heads: one head per XCD, whose L2 then
-  // holds that head's Q rows and partial statistics) ----------------------------------------------------
-  const int g = blockIdx.x % a.Hkv;
-  int rest = blockIdx.x / a.Hkv;
-  // PASS 0 of the causal denominator: one more run per request, its question keys, each row up to its own token
-  const int n_runs = PASS == 0 && !REALIGN ? a.n_tiles + a.causal_q : a.n_tiles;
-  const int t = rest % n_runs, r = rest / n_runs;
+  // blockIdx % Hkv = KV head: with 8 heads an XCD has one, and its L2 that head's Q rows and partial statistics.  PASS 0 of the causal
+  // denominator has one more tile per request, its question keys, each row up to its own token
+  auto quotient = [](uint32_t x, uint32_t d, uint32_t inv) { return d == 1 ? x : inv ? __umulhi(x, inv) : x / d; };
+  const uint32_t n_runs = (uint32_t)(a.n_tiles + (PASS == 0 && !REALIGN ? a.own_tile : 0));
+  const uint32_t rest = quotient(blockIdx.x, a.Hkv, a.inv_heads);
+  const int g = (int)(blockIdx.x - rest * a.Hkv), r = a.n_req == 1 ? 0 : (int)quotient(rest, n_runs, a.inv_runs[PASS]), t = (int)(rest - r * n_runs);
   const bool own = PASS == 0 && !REALIGN && t == a.n_tiles;
-  // (a batch of one request: its lengths are the layout's maxima, known on the host; no loads before the first keys
-  // are requested)
   const int n_ctx = a.one_ctx_len >= 0 ? a.one_ctx_len : a.ctx_len[r];
-  const int i0 = own ? 0 : t * a.tile_keys;
+  const int i0 = own ? 0 : t * kTile;
   if (!own && i0 >= n_ctx) return;
   const int G = a.Hq / a.Hkv, n_q = a.one_ctx_len >= 0 ? a.one_q_len : a.q_len[r];
   const int Mg = n_q * G;                                      // rows of this KV head: m = j * G + hh
-  if (Mg <= 0) return;
-  const int N = own ? n_q : n_ctx;                             // keys of the part that this run belongs to (n_q <= 256 <= tile_keys)
+  const int N = own ? n_q : n_ctx;
   const int s = (a.one_ctx_len >= 0 ? 0 : a.seg_start[r]) + (own ? n_ctx : 0), qrow0 = a.one_ctx_len >= 0 ? 0 : a.q_start[r];
-  const row_map row_of{G, a.Hq, g, qrow0, a.inv_G};
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, lhi = lane >> 5;
-  const int n_keys = min(a.tile_keys, N - i0);
-  const int nQ = (n_keys + kSlotKeys - 1) / kSlotKeys;         // slots of this run, >= 1
-  const bf16_t *__restrict__ Q = (const bf16_t *)a.q;
-  const bf16_t *__restrict__ K = (const bf16_t *)a.k;
+  const int row0 = qrow0 * a.Hq + g * Mg;                      // first of the head's rows in part and stats
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lg = lane >> 4;
+  // waves with question keys, of which there may be few: the others take some of their rows
+  const int key_waves = !own || n_q > 128 ? kWaves : n_q > 64 ? 4 : n_q > 32 ? 2 : 1, share = kWaves / key_waves, sub = wave / key_waves;
+  const int iw = i0 + kKeysWave * (wave & (key_waves - 1));    // the wave's first key
+  const int n_chunks = (Mg + kChunk - 1) / kChunk;
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds_raw;
-  float *St = reinterpret_cast<float *>(lds_raw + kLdsSt);
-  float *red = reinterpret_cast<float *>(lds_raw + kLdsRed);
+  unsigned char *extra = lds_raw + min(n_chunks, 2) * kChunkBytes;
+  float *St = reinterpret_cast<float *>(extra);                // PASS 1: [kStatRows]
+  float *pz = reinterpret_cast<float *>(extra), *pm = pz + 2 * kWaves * kChunk;        // PASS 0: partials of the waves, [2][kWaves][kChunk]
 
-  // Wave (rg, kh) owns the rows 64 rg .. 64 rg + 63 and the keys 32 kh .. 32 kh + 31 of every slot; the waves
-  // (rg, 0) and (rg, 1) share a SIMD.  Between two barriers each wave forms the logits of one block (16 MFMAs
-  // back to back: the matrix pipe) and folds one block into the row statistics / column sums (exponentials: the
-  // vector ALU).  The kh = 0 waves do that in the order "logits of slot i + 1, fold slot i + 1", the kh = 1 waves
-  // in the order "fold slot i, logits of slot i + 1": at any time one wave of a SIMD is in its matrix phase and
-  // the other in its vector phase, each a plain stream of one kind of instruction.
-  const int rg = wave & 3, kh = wave >> 2;
+  // ---- keys: fragment (kb, ks) of a lane: 16 bytes of key iw + 16 kb + l16, dims 32 ks + 8 lg ..
+  bf16x8 kf[2][4];
+  int krow[2], chunk[2];
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    krow[kb] = min(s + iw + 16 * kb + l16, a.T - 1);           // past the run: loaded, masked or never stored
+    if (REALIGN) chunk[kb] = iw + 16 * kb + l16 < N ? a.tok_chunk[krow[kb]] : -1;
+  }
+  const bf16_t *Kin = (const bf16_t *)(REALIGN ? a.k_cat : a.k);
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+      kf[kb][ks] = *reinterpret_cast<const bf16x8 *>(Kin + ((size_t)krow[kb] * a.Hkv + g) * kD + 32 * ks + 8 * lg);
+  // ---- Q: chunk C of rows to its buffer
+  const int drow = 4 * wave + (lane >> 4), dpiece = (lane & 15) ^ (drow & 15);
+  const bf16_t *Qr = (const bf16_t *)a.q + ((size_t)qrow0 * a.Hq + g * G) * kD;      // row 0 of the head
+#define A3_QDMA(C)                                                                                             \
+  _Pragma("unroll") for (int j = 0; j < kChunk / (4 * kWaves); ++j) {                                          \
+    const uint32_t m_ = (uint32_t)min((C) * kChunk + drow + 4 * kWaves * j, Mg - 1);                           \
+    const uint32_t off_ = (m_ + (G > 1 ? __umulhi(m_, a.inv_G) : m_) * (uint32_t)(a.Hq - G)) * (kD * 2) + 16 * dpiece; \
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"                               \
+                 :: "s"(lds_base + ((C) & 1) * kChunkBytes + (4 * wave + 4 * kWaves * j) * kKRowBytes), "v"(off_), "s"(Qr) : "memory"); \
+  }
+  static_assert((4 * kWaves) % 16 == 0, "the swizzle of a lane's rows is one number");
+  if (n_chunks > 0) { A3_QDMA(0) }
+  if (n_chunks > 1) { A3_QDMA(1) }
 
-  // ---- direct-to-LDS loads (16 bytes per lane, lane i lands at base + 16 i), waves 0-3 only.  One wave
-  // instruction brings 4 rows x 256 B; instruction j of wave w covers rows 4 (4 j + w) .. + 3 of a 64-row
-  // group.  The lane fetches piece (slot ^ row % 16) of its row, so LDS slot s of row x holds piece
-  // s ^ (x % 16) and the 16 rows a quarter wave reads at one piece index touch all 64 banks once.  Inline
-  // assembly: the compiler then does not track these as LDS writes (it would wait for all of them before
-  // every LDS read); the explicit vmcnt waits below cover them, and waves 0-3 issue no other vector memory
-  // access until the ring has drained, so the counts are exact.  Waves 4-7 issue none: the compiler's own
-  // counting is exact there (PASS 1 merges the partial statistics in those waves meanwhile).
-  const bool loads = wave < 4;
-  const int drow = 4 * (wave & 3) + (lane >> 4);               // row of the lane in instruction 0
-  const int dpiece = (lane & 15) ^ (drow & 15);                // (drow + 16 j) % 16 does not depend on j
-#define A3_KDMA(I)                                                                                             \
-  _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                              \
-    const int row_ = min(s + i0k + (I) * kSlotKeys + drow + 16 * j, a.T - 1);  /* past the run: loaded, masked */ \
-    const bf16_t *gp_ = K + ((size_t)row_ * a.Hkv + g) * kD + dpiece * 8;                                      \
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"                                         \
-                 :: "s"(__builtin_amdgcn_readfirstlane(lds_base + ((I) & (kSlots - 1)) * kSlotBytes +           \
-                                                       4 * (4 * j + (wave & 3)) * kKRowBytes)), "v"(gp_) : "memory"); \
-  }
-  // the Q tile: rows MBASE .. + 255 of this head (rows past Mg: a copy of the last row, ignored later)
-#define A3_QDMA(MBASE)                                                                                         \
-  _Pragma("unroll") for (int j = 0; j < 16; ++j) {                                                             \
-    const int m_ = min((MBASE) + drow + 16 * j, Mg - 1);                                                       \
-    const bf16_t *gp_ = Q + (size_t)row_of(m_) * kD + dpiece * 8;                                              \
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"                                         \
-                 :: "s"(__builtin_amdgcn_readfirstlane(lds_base + kLdsQ + 4 * (4 * j + wave) * kKRowBytes)), "v"(gp_) \
-                 : "memory");                                                                                  \
-  }
-  const int i0k = i0, total_rows = a.total_rows;
-  constexpr int m_base = 0;
-  if (loads) {
-    if (!REALIGN) { A3_KDMA(0) }
-    A3_QDMA(0)
-    if (!REALIGN) {
-      if (nQ > 1) { A3_KDMA(1) }
-      if (nQ > 2) { A3_KDMA(2) }
-      if (nQ > 3) { A3_KDMA(3) }
-    }
-  }
-  // ---- PASS 1, waves 4-7: max + log2(sum exp) of the 256 rows from the partials of all runs (every workgroup
-  // of the row chunk forms the same numbers in the same order) --------------------------------------------
-  if (PASS == 1 && wave >= 4) {
-    const int ml = tid - 256, m = m_base + ml;
-    float st = INFINITY;                                       // rows past Mg add nothing (see acc0 below)
-    if (m < Mg) {
-      const int row_id = row_of(m);
-      const int runs = (N + a.tile_keys - 1) / a.tile_keys;
-      if (a.merged) {
-        st = a.stats[row_id].x;                                // many runs: a small kernel has merged them already
-      } else {
-        // first the maximum over the runs, then the sums rescaled to it, added in run order (at most 32 runs)
-        float mx = -INFINITY, z = 0.f;
-        float2 p[32];
-#pragma unroll
-        for (int u = 0; u < 32; ++u)
-          p[u] = u < runs ? a.part[(size_t)u * total_rows + row_id] : make_float2(-INFINITY, 0.f);
-        // the question keys' share: its load goes with the others (a launch of the combine kernel for it was 2 us more
-        // in all: votes, retention and compaction at 16K 56.7 -> 55.1)
-        const float2 pq = a.causal_q ? a.part[(size_t)a.n_tiles * total_rows + row_id] : make_float2(-INFINITY, 0.f);
-#pragma unroll
-        for (int u = 0; u < 32; ++u) mx = fmaxf(mx, p[u].x);
-        mx = fmaxf(mx, pq.x);
-        // a run that saw no key has (max, sum) = (-inf, 0): its factor must not become exp2(nan)
-#pragma unroll
-        for (int u = 0; u < 32; ++u) z += p[u].y > 0.f ? p[u].y * fast_exp2(p[u].x - mx) : 0.f;
-        z += pq.y > 0.f ? pq.y * fast_exp2(pq.x - mx) : 0.f;
-        // exp2(l - m) / z = exp2(l - (m + log2 z)): one number per row
-        st = z > 0.f ? mx + log2f(z) : INFINITY;
-      }
-    }
-    St[ml] = st;
-  }
-
-  // fragment reads: row / key 32 b + l32 of a 64-row group, piece 2 ks + lhi -> slot (2 ks + lhi) ^ (l32 % 16)
-  const int kswz = (lhi ^ (l32 & 15)) * 16;
-  const unsigned char *kt = lds_raw + (kh * 32 + l32) * kKRowBytes;      // + slot * kSlotBytes
-  const unsigned char *qt = lds_raw + kLdsQ + (rg * 64 + l32) * kKRowBytes;
-
-  // REALIGN: the stale keys come through registers, every pair is turned by its chunk's offset (Eq. 2), and
-  // the rounded result goes both to the realigned cache and, in the swizzled layout, to the ring.  A lane owns
-  // the 16-byte pieces c and c + 8 of one key per slot: in either pairing (adjacent coordinates, or i with
-  // i + 64) it then holds whole pairs.  Three slots are in flight in registers.
-  const bf16_t *Kc = (const bf16_t *)a.k_cat;                  // may be the same buffer as k_out
-  bf16_t *Ko = (bf16_t *)a.k_out;
-  const int rc = tid & 7, rkey = tid >> 3;
-  constexpr int kPF = 3;
-  bf16x8 plo[kPF], phi[kPF];
-  int pchunk[kPF];
-  float2 csr[8];
-  int cs_cur = -1;
-  const bool inter = a.rope_layout == A3_ROPE_INTERLEAVED;
-#define A3_RLOAD(I, P)                                                                                         \
-  {                                                                                                            \
-    const int key_ = (I) * kSlotKeys + rkey;                                                                   \
-    const int row_ = min(s + i0k + key_, a.T - 1);               /* past the run: loaded, never stored */      \
-    const size_t off_ = ((size_t)row_ * a.Hkv + g) * kD;                                                       \
-    plo[P] = *reinterpret_cast<const bf16x8 *>(Kc + off_ + 8 * rc);                                            \
-    phi[P] = *reinterpret_cast<const bf16x8 *>(Kc + off_ + 64 + 8 * rc);                                       \
-    pchunk[P] = key_ < n_keys ? a.tok_chunk[row_] : -1;                                                        \
-  }
-  // turns the registers of slot I and stores them
-#define A3_RSTORE(I, P)                                                                                        \
-  {                                                                                                            \
-    const int key_ = (I) * kSlotKeys + rkey;                                                                   \
-    const int row_ = min(s + i0k + key_, a.T - 1);                                                             \
-    const size_t off_ = ((size_t)row_ * a.Hkv + g) * kD;                                                       \
-    bf16x8 rlo = plo[P], rhi = phi[P];                                                                         \
-    if (pchunk[P] >= 0) {                                                                                      \
-      if (pchunk[P] != cs_cur) {                                                                               \
-        const float2 *cs = a.chunk_cs + (size_t)pchunk[P] * (kD / 2);                                          \
-        _Pragma("unroll") for (int e = 0; e < 8; ++e)   /* interleaved: pairs 4c..4c+3 and 32+4c..; half: 8c..8c+7 */ \
-          csr[e] = inter ? cs[(e < 4 ? 4 * rc : 28 + 4 * rc) + e] : cs[8 * rc + e];                            \
-        cs_cur = pchunk[P];                                                                                    \
-      }                                                                                                        \
-      if (inter) {                                                                                             \
-        _Pragma("unroll") for (int p2 = 0; p2 < 4; ++p2) {                                                     \
-          float y0, y1;                                                                                        \
-          a3_rotate_pair(a3_bf2f(plo[P][2 * p2]), a3_bf2f(plo[P][2 * p2 + 1]), csr[p2], y0, y1);               \
-          rlo[2 * p2] = a3_f2bf(y0); rlo[2 * p2 + 1] = a3_f2bf(y1);                                            \
-          a3_rotate_pair(a3_bf2f(phi[P][2 * p2]), a3_bf2f(phi[P][2 * p2 + 1]), csr[4 + p2], y0, y1);           \
-          rhi[2 * p2] = a3_f2bf(y0); rhi[2 * p2 + 1] = a3_f2bf(y1);                                            \
-        }                                                                                                      \
-      } else {                                                                                                 \
-        _Pragma("unroll") for (int e = 0; e < 8; ++e) {          /* coordinate 8c+e pairs with 64+8c+e */      \
-          float y0, y1;                                                                                        \
-          a3_rotate_pair(a3_bf2f(plo[P][e]), a3_bf2f(phi[P][e]), csr[e], y0, y1);                              \
-          rlo[e] = a3_f2bf(y0); rhi[e] = a3_f2bf(y1);                                                          \
-        }                                                                                                      \
-      }                                                                                                        \
-    }                                                                                                          \
-    if (key_ < n_keys) {                                                                                       \
-      *reinterpret_cast<bf16x8 *>(Ko + off_ + 8 * rc) = rlo;                                                   \
-      *reinterpret_cast<bf16x8 *>(Ko + off_ + 64 + 8 * rc) = rhi;                                              \
-    }                                                                                                          \
-    unsigned char *ld_ = lds_raw + ((I) & (kSlots - 1)) * kSlotBytes + rkey * kKRowBytes;                      \
-    *reinterpret_cast<bf16x8 *>(ld_ + ((rc ^ (rkey & 15)) * 16)) = rlo;                                        \
-    *reinterpret_cast<bf16x8 *>(ld_ + (((rc + 8) ^ (rkey & 15)) * 16)) = rhi;                                  \
-  }
-  // slot I + 1 goes from this lane's registers to the ring, then the registers take slot I + 1 + kPF
-#define A3_RSTEP_STORE(I)                                                                                      \
-  if (((I) + 1) % kPF == 0) { A3_RSTORE((I) + 1, 0) } else if (((I) + 1) % kPF == 1) { A3_RSTORE((I) + 1, 1) }  \
-  else { A3_RSTORE((I) + 1, 2) }
-#define A3_RSTEP_LOAD(I)                                                                                       \
-  if ((I) + 1 + kPF < nQ) {                                                                                    \
-    if (((I) + 1) % kPF == 0) { A3_RLOAD((I) + 1 + kPF, 0) } else if (((I) + 1) % kPF == 1) { A3_RLOAD((I) + 1 + kPF, 1) } \
-    else { A3_RLOAD((I) + 1 + kPF, 2) }                                                                        \
-  }
-  // waves 0-3: slot I + 1 has landed when at most the (up to six) slots requested after it are in flight
-#define A3_WAIT_SLOT(I)                                                                                        \
-  {                                                                                                            \
-    const int younger_ = nQ - (I) - 2;                                                                         \
-    if (younger_ >= 6) A3_VMCNT(24); else if (younger_ == 5) A3_VMCNT(20); else if (younger_ == 4) A3_VMCNT(16); \
-    else if (younger_ == 3) A3_VMCNT(12); else if (younger_ == 2) A3_VMCNT(8); else if (younger_ == 1) A3_VMCNT(4); \
-    else A3_VMCNT(0);                                                                                          \
-  }
-
-  // ---- slot 0 and the Q tile have landed -------------------------------------------------------------
-  if (REALIGN) {
-    // (in waves 0-3 the Q tile's loads are older than these: the compiler's wait for the keys of slot 0 covers them)
-    A3_RLOAD(0, 0)
-    if (nQ > 1) { A3_RLOAD(1, 1) }
-    if (nQ > 2) { A3_RLOAD(2, 2) }
-    A3_RSTORE(0, 0)
-    if (nQ > 3) { A3_RLOAD(3, 0) }
-  } else if (loads) {                                          // younger than slot 0 and the Q tile: slots 1 .. 3
-    if (nQ > 3) A3_VMCNT(12); else if (nQ == 3) A3_VMCNT(8); else if (nQ == 2) A3_VMCNT(4); else A3_VMCNT(0);
-  }
-  A3_LDS_BARRIER();                                            // (also publishes St)
-  bf16x8 qf[2][kD / 16];
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int ks = 0; ks < kD / 16; ++ks)
-      qf[b][ks] = *reinterpret_cast<const bf16x8 *>(qt + b * 32 * kKRowBytes + ((32 * ks) ^ kswz));
-  // what the accumulators start from: zero, or in PASS 1 the row's -(max + log2 sum) / scale, so that the
-  // finished accumulator times the scale is the exponent of the softmax weight (+inf for a row past Mg:
-  // its weights come out as exp2(-inf) = 0)
-  f32x16 acc0[2];
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int x = 0; x < 16; ++x)     // PASS 1 lane: key; registers: rows 8 (x / 4) + 4 lhi + x % 4 of row block b
-      acc0[b][x] = PASS == 1 ? -St[rg * 64 + b * 32 + 8 * (x >> 2) + 4 * lhi + (x & 3)] * a.inv_scale2 : 0.f;
-  if (nQ > 4) {
-    A3_LDS_BARRIER();                                          // everybody has its Q fragments: their place is free
-    if (!REALIGN && loads) {                                   // ... and joins the ring
-      A3_KDMA(4)
-      if (nQ > 5) { A3_KDMA(5) }
-      if (nQ > 6) { A3_KDMA(6) }
-      if (nQ > 7) { A3_KDMA(7) }
-    }
-  }
-
-  f32x16 acc[2];
-  bf16x8 kfr[kD / 16];
-  float run_max[2] = {kLeast, kLeast}, run_sum[2] = {0.f, 0.f};
-  int seen[2] = {N, N};                                        // PASS 0: keys that the lane's row of block b may see
-  if (own) {
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const uint32_t m = rg * 64 + b * 32 + l32;
-      seen[b] = min(N, (G > 1 ? (int)__umulhi(m, a.inv_G) : (int)m) + 1);
-    }
-  }
-  // the eight K fragments of this wave's block of slot I, requested together
-#define A3_KFRAGS(I)                                                                                           \
-  _Pragma("unroll") for (int ks_ = 0; ks_ < kD / 16; ++ks_)                                                    \
-    kfr[ks_] = *reinterpret_cast<const bf16x8 *>(kt + ((I) & (kSlots - 1)) * kSlotBytes + ((32 * ks_) ^ kswz));
-  // matrix phase: the logits of the wave's 64 rows against its 32 keys (fragments in kfr).  The first slab starts
-  // from acc0, so the accumulators never have to be cleared.
-#define A3_LOGITS()                                                                                            \
-  _Pragma("unroll") for (int ks = 0; ks < kD / 16; ++ks) _Pragma("unroll") for (int b = 0; b < 2; ++b) { \
-    if (PASS == 0) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[ks], qf[b][ks], ks == 0 ? acc0[b] : acc[b], 0, 0, 0); /* C[key][row] */ \
-    else           acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[b][ks], kfr[ks], ks == 0 ? acc0[b] : acc[b], 0, 0, 0); /* C[row][key] */ \
-  }
-  // vector phase: the logits in acc (block of slot I) go into the row statistics (PASS 0) or the column sums (PASS 1)
-#define A3_FOLD(I)                                                                                             \
-  {                                                                                          \
-    const int key0_ = i0 + (I) * kSlotKeys + kh * 32;            /* first key of the block */                   \
-    if (PASS == 0) {                                                                                           \
-      /* lane: row (column l32 of block b); registers: keys key0 + 8 (x / 4) + 4 lhi + x % 4 */                \
-      if (key0_ < N) {                                           /* the block holds a real key */              \
-        if (own || key0_ + 31 >= N) {                                                                          \
-          _Pragma("unroll") for (int b = 0; b < 2; ++b) {                                                      \
-            int n_real = seen[b] - key0_ - 4 * lhi;                                                            \
-            asm volatile("" : "+v"(n_real));                                                                   \
-            _Pragma("unroll") for (int x = 0; x < 16; ++x)                                                     \
-              if (8 * (x >> 2) + (x & 3) >= n_real) acc[b][x] = -INFINITY;                                     \
-          }                                                                                                    \
-        }                                                                                                      \
-        _Pragma("unroll") for (int b = 0; b < 2; ++b) {                                                        \
-          float mx = fmaxf(acc[b][0], acc[b][1]);                                                              \
-          _Pragma("unroll") for (int x = 2; x < 16; x += 2) mx = fmaxf(fmaxf(mx, acc[b][x]), acc[b][x + 1]);   \
-          mx = halves_max(mx) * a.scale2;                                                                      \
-          const float new_max = fmaxf(run_max[b], mx);                                                         \
-          float sum0 = 0.f, sum1 = 0.f;                                                                        \
-          _Pragma("unroll") for (int x = 0; x < 16; x += 2) {                                                  \
-            sum0 += fast_exp2(fmaf(acc[b][x], a.scale2, -new_max));                                            \
-            sum1 += fast_exp2(fmaf(acc[b][x + 1], a.scale2, -new_max));                                        \
-          }                                                                                                    \
-          run_sum[b] = run_sum[b] * fast_exp2(run_max[b] - new_max) + (sum0 + sum1);   /* first block: 0 * 0 */ \
-          run_max[b] = new_max;                                                                                \
-        }                                                                                                      \
-      }                                                                                                        \
-    } else {                                                                                                   \
-      /* lane: key l32 of the block; registers: rows 8 (x / 4) + 4 lhi + x % 4 of row block b */               \
-      float p0 = 0.f, p1 = 0.f;                                                                                \
-      _Pragma("unroll") for (int b = 0; b < 2; ++b) _Pragma("unroll") for (int x = 0; x < 16; x += 2) {        \
-        p0 += fast_exp2(acc[b][x] * a.scale2);                                                                 \
-        p1 += fast_exp2(acc[b][x + 1] * a.scale2);                                                             \
-      }                                                                                                        \
-      const float part_ = halves_sum(p0 + p1);                                                                 \
-      if (lhi == 0) red[rg * a.tile_keys + (I) * kSlotKeys + kh * 32 + l32] = part_;                           \
-    }                                                                                                          \
-  }
-
-  A3_KFRAGS(0)
-  A3_LOGITS()
-  if (kh == 0) { A3_FOLD(0) }
-  for (int i = 0; i + 1 < nQ; ++i) {
-    if (REALIGN) { A3_RSTEP_STORE(i) } else if (loads) { A3_WAIT_SLOT(i) }
-    A3_LDS_BARRIER();                                          // slot i + 1 is in the ring
-    if (REALIGN) { A3_RSTEP_LOAD(i) }
-    // every wave has read slot i (its MFMAs were issued before the barrier): refill its place
-    else if (loads && i + kSlots < nQ) { A3_KDMA(i + kSlots) }
-    A3_KFRAGS(i + 1)
-    if (kh == 0) {
-      A3_LOGITS()
-      A3_FOLD(i + 1)
+  if (PASS == 1 && Mg > 0) {
+    if (a.merged) {
+      for (int m = tid; m < min(n_chunks * kChunk, kStatRows); m += kThreads) St[m] = m < Mg ? a.stats[row0 + m].x : INFINITY;
     } else {
-      A3_FOLD(i)
-      A3_LOGITS()
-    }
-  }
-  if (kh == 1) { A3_FOLD(nQ - 1) }
-#undef A3_FOLD
-#undef A3_LOGITS
-#undef A3_KFRAGS
-
-  if (PASS == 0) {
-    // (max, sum) of this wave's rows over its half of the keys; the two halves of a row group merge in LDS
-    float2 *pair = reinterpret_cast<float2 *>(lds_raw + kLdsRed);
-    float z[2];
+      // two threads a row where there are enough (up to 64 runs), else one (up to 32)
+      const bool two = Mg <= kThreads / 2;
+      const int m = two ? tid % (kThreads / 2) : tid, first = two ? tid / (kThreads / 2) * 32 : 0;
+      const int runs = (N + kTile - 1) / kTile;
+      const size_t at = (size_t)row0 + min(m, Mg - 1);
+      float mx = 0.f, z = 0.f, p[32];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) z[b] = halves_sum(run_sum[b]);
-    if (kh == 1 && lhi == 0) {
+      for (int u = 0; u < 32; ++u) p[u] = first + u < runs ? a.part_z[(size_t)(first + u) * a.total_rows + at] : 0.f;
+      const float pq = a.causal_q && first == 0 ? a.part_z[(size_t)a.n_tiles * a.total_rows + at] : 0.f;
+      float least = pq;
 #pragma unroll
-      for (int b = 0; b < 2; ++b) pair[rg * 64 + b * 32 + l32] = make_float2(run_max[b], z[b]);
-    }
-    __syncthreads();
-    if (kh == 0 && lhi == 0) {
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int m = m_base + rg * 64 + b * 32 + l32;
-        if (m < Mg) {
-          const float2 o = pair[rg * 64 + b * 32 + l32];
-          const float mn = fmaxf(run_max[b], o.x);
-          const float zz = z[b] * fast_exp2(run_max[b] - mn) + (o.y > 0.f ? o.y * fast_exp2(o.x - mn) : 0.f);
-          a.part[(size_t)t * a.total_rows + row_of(m)] = make_float2(mn, zz);
+      for (int u = 0; u < 32; ++u) { z += p[u]; least = fminf(least, p[u]); }
+      z += pq;
+      if (least < 0.f) {                                       // sums against a maximum among them
+        mx = kLeast;
+        for (int u = -1; u < 32; ++u) {
+          const int tile = u < 0 ? a.n_tiles : first + u;
+          if (u < 0 ? !(a.causal_q && first == 0) : tile >= runs) continue;
+          mx = fmaxf(mx, partial(a.part_z, a.part_m, (size_t)tile * a.total_rows + at).x);
+        }
+        z = 0.f;
+        for (int u = 0; u < 33; ++u) {
+          const int tile = u == 32 ? a.n_tiles : first + u;
+          if (u == 32 ? !(a.causal_q && first == 0) : tile >= runs) continue;
+          const float2 x = partial(a.part_z, a.part_m, (size_t)tile * a.total_rows + at);
+          z += x.y > 0.f ? x.y * fast_exp2(x.x - mx) : 0.f;
         }
       }
+      if (!(z > 0.f)) mx = kLeast;                             // (a half without tiles)
+      if (two) {
+        float2 *half = reinterpret_cast<float2 *>(St + kStatRows);          // [kThreads / 2]
+        if (first) half[m] = make_float2(mx, z);
+        __syncthreads();
+        if (!first) {
+          const float2 o = half[m];
+          const float mn = fmaxf(mx, o.x);
+          z = (z > 0.f ? z * fast_exp2(mx - mn) : 0.f) + (o.y > 0.f ? o.y * fast_exp2(o.x - mn) : 0.f);
+          mx = mn;
+        }
+      }
+      if (!first) St[m] = m < Mg && z > 0.f ? log2_sum(mx, z) : INFINITY;
+    }
+  }
+
+  if (REALIGN) {
+    bf16_t *Ko = (bf16_t *)a.k_out;
+    const bool inter = a.rope_layout == A3_ROPE_INTERLEAVED;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {                              // dims of fragments 2 p and 2 p + 1 (interleaved), or p and p + 2
+      float2 cs[8];
+      int cur = -1;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        if (chunk[kb] >= 0) {
+          if (chunk[kb] != cur) {
+            const float2 *tab = a.chunk_cs + (size_t)chunk[kb] * (kD / 2) + (inter ? 32 * p + 4 * lg : 32 * p + 8 * lg);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) cs[e] = tab[inter && e >= 4 ? e + 12 : e];
+            cur = chunk[kb];
+          }
+          if (inter) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              bf16x8 &f = kf[kb][2 * p + (e >> 2)];
+              float y0, y1;
+              a3_rotate_pair(a3_bf2f(f[2 * (e & 3)]), a3_bf2f(f[2 * (e & 3) + 1]), cs[e], y0, y1);
+              f[2 * (e & 3)] = a3_f2bf(y0);
+              f[2 * (e & 3) + 1] = a3_f2bf(y1);
+            }
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              float y0, y1;
+              a3_rotate_pair(a3_bf2f(kf[kb][p][e]), a3_bf2f(kf[kb][p + 2][e]), cs[e], y0, y1);
+              kf[kb][p][e] = a3_f2bf(y0);
+              kf[kb][p + 2][e] = a3_f2bf(y1);
+            }
+          }
+        }
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0);                             // Q has landed: nothing below waits for the stores
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+      if (iw + 16 * kb + l16 < N) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+          *reinterpret_cast<bf16x8 *>(Ko + ((size_t)krow[kb] * a.Hkv + g) * kD + 32 * ks + 8 * lg) = kf[kb][ks];
+      }
+  }
+
+  const bool have = iw < N, tail = own || iw + kKeysWave > N;
+  float colsum[2] = {0.f, 0.f};
+  // LDS addresses of a lane's fragments of the rows l16 of a chunk, dims 32 ks + 8 lg ..: everything else is a constant offset
+  typedef __attribute__((address_space(3))) const unsigned char *lds_ptr;
+  const uint32_t stat_at = lds_base + min(n_chunks, 2) * kChunkBytes + 16 * lg;
+  uint32_t qat[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) qat[ks] = lds_base + l16 * kKRowBytes + ((64 * ks) ^ (16 * (lg ^ l16)));
+  // Q and the keys are there
+  if (!REALIGN) __builtin_amdgcn_s_waitcnt(0);
+  A3_LDS_BARRIER();
+  for (int c = 0; c < n_chunks; ++c) {
+    if (c > 0 && c + 1 < n_chunks) { A3_QDMA(c + 1) }
+    if (PASS == 1 && a.merged && (c + 1) * kChunk >= kStatRows && c + 1 < n_chunks && tid < kChunk) {
+      const int m = (c + 1) * kChunk + tid;
+      St[m % kStatRows] = m < Mg ? a.stats[row0 + m].x : INFINITY;
+    }
+    const uint32_t cb = (c & 1) * kChunkBytes;
+    const int rows = min(kChunk, Mg - c * kChunk);
+    if (have) {
+      // logits of the 16 rows from row q of the chunk on
+      auto logits = [&](int q, f32x4 (&acc)[2]) {
+        bf16x8 qf[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) qf[ks] = *(__attribute__((address_space(3))) const bf16x8 *)((lds_ptr)(uintptr_t)(qat[ks] + cb) + q * kKRowBytes);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb) {
+            const f32x4 c0 = ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[kb];
+            acc[kb] = PASS == 0 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][ks], qf[ks], c0, 0, 0, 0)
+                                : __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[ks], kf[kb][ks], c0, 0, 0, 0);
+          }
+      };
+      if (PASS == 0) {
+        // of the wave's keys, those that the lane's row sees
+        auto seen_by = [&](int q) {
+          if (!own) return N - iw;
+          const int m = c * kChunk + q + l16;
+          return min(N, (G > 1 ? (int)__umulhi((uint32_t)m, a.inv_G) : m) + 1) - iw;
+        };
+        auto mask = [&](int seen, f32x4 (&acc)[2]) {
+          seen -= 4 * lg;
+          asm volatile("" : "+v"(seen));
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (16 * kb + e >= seen) acc[kb][e] = -INFINITY;
+        };
+        float *pzw = pz + ((c & 1) * kWaves + wave) * kChunk, *pmw = pm + ((c & 1) * kWaves + wave) * kChunk;
+        bool again = false;
+#pragma unroll
+        for (int rg = 0; rg < kChunk; rg += 32) {
+          if (rg >= rows) break;
+          if (share > 1 && ((c * (kChunk / 32) + rg / 32) & (share - 1)) != sub) {             // (another wave's rows)
+            if (lane < 32) pzw[rg + lane] = 0.f;
+            continue;
+          }
+          f32x4 acc[2][2];
+          logits(rg, acc[0]);
+          logits(rg + 16, acc[1]);
+          if (tail) {
+            mask(seen_by(rg), acc[0]);
+            mask(seen_by(rg + 16), acc[1]);
+          }
+          float z[2];
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            float z0 = fast_exp2(acc[b][0][0] * a.scale2), z1 = fast_exp2(acc[b][1][0] * a.scale2);
+#pragma unroll
+            for (int e = 1; e < 4; ++e) {
+              z0 += fast_exp2(acc[b][0][e] * a.scale2);
+              z1 += fast_exp2(acc[b][1][e] * a.scale2);
+            }
+            z[b] = z0 + z1;
+          }
+          // lane groups 0 and 2: the first 16 rows, lane groups 1 and 3: the others
+          const float zz = halves_sum(swap16_add(z[0], z[1]));
+          again |= !(zz >= kSumLow && zz <= kSumHigh) && !(own && seen_by(rg + (lane & 16)) <= 0);         // (0: the row sees none of the keys)
+          if (lane < 32) pzw[rg + lane] = zz;
+        }
+        if (__any(again)) {
+          for (int q = 0; q < rows; q += 16) {
+            if (share > 1 && ((c * (kChunk / 32) + q / 32) & (share - 1)) != sub) continue;
+            f32x4 acc[2];
+            logits(q, acc);
+            if (tail) mask(seen_by(q), acc);
+            float mx = kLeast;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) { acc[kb][e] *= a.scale2; mx = fmaxf(mx, acc[kb][e]); }
+            const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+            mx = halves_max(fmaxf(__uint_as_float(w[0]), __uint_as_float(w[1])));
+            float sum = 0.f;
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) sum += fast_exp2(acc[kb][e] - mx);
+            sum = halves_sum(swap16_add(sum, sum));
+            if (lane < 16) store_partial(pzw, pmw, q + lane, mx, sum);
+          }
+        }
+      } else {
+        const uint32_t sat = stat_at + (c * kChunk) % kStatRows * 4;
+#pragma unroll
+        for (int rg = 0; rg < kChunk; rg += 32) {
+          if (rg >= rows) break;
+          f32x4 acc[2][2], st[2];
+#pragma unroll
+          for (int b = 0; b < 2; ++b) st[b] = *(__attribute__((address_space(3))) const f32x4 *)((lds_ptr)(uintptr_t)sat + (rg + 16 * b) * 4);
+          logits(rg, acc[0]);
+          logits(rg + 16, acc[1]);
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb) {
+            float p0 = fast_exp2(fmaf(acc[0][kb][0], a.scale2, -st[0][0])), p1 = fast_exp2(fmaf(acc[1][kb][0], a.scale2, -st[1][0]));
+#pragma unroll
+            for (int e = 1; e < 4; ++e) {
+              p0 += fast_exp2(fmaf(acc[0][kb][e], a.scale2, -st[0][e]));
+              p1 += fast_exp2(fmaf(acc[1][kb][e], a.scale2, -st[1][e]));
+            }
+            colsum[kb] += p0 + p1;
+          }
+        }
+      }
+    } else if (PASS == 0) {
+      for (int m = lane; m < rows; m += 64) pz[((c & 1) * kWaves + wave) * kChunk + m] = 0.f;
+    }
+    if (c + 1 < n_chunks) __builtin_amdgcn_s_waitcnt(0);       // the next chunk of Q has landed
+    if (PASS == 0 || c + 1 < n_chunks) { A3_LDS_BARRIER(); }
+    if (PASS == 0 && tid < rows) {
+      const float *zc = pz + (c & 1) * kWaves * kChunk + tid, *mc = pm + (c & 1) * kWaves * kChunk + tid;
+      float mx = 0.f, z = 0.f, least = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) { const float x = zc[w * kChunk]; z += x; least = fminf(least, x); }
+      if (least < 0.f) {
+        mx = kLeast;
+        for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, partial(zc, mc, w * kChunk).x);
+        z = 0.f;
+        for (int w = 0; w < kWaves; ++w) { const float2 x = partial(zc, mc, w * kChunk); z += x.y * fast_exp2(x.x - mx); }
+      }
+      store_partial(a.part_z, a.part_m, (size_t)t * a.total_rows + row0 + c * kChunk + tid, mx, z);
     }
   }
 #undef A3_QDMA
-#undef A3_WAIT_SLOT
-#undef A3_RSTEP_LOAD
-#undef A3_RSTEP_STORE
-#undef A3_RSTORE
-#undef A3_RLOAD
-#undef A3_KDMA
-
   if (PASS == 1) {
-    __syncthreads();
-    // column sums of this (KV head, row chunk): the four row groups in a fixed order
-    float *mine = a.part_scores + (size_t)g * a.T + s + i0;
-    for (int key = tid; key < n_keys; key += kScoreThreads)
-      mine[key] = (red[key] + red[a.tile_keys + key]) + (red[2 * a.tile_keys + key] + red[3 * a.tile_keys + key]);
-  }
-}
-#undef A3_VMCNT
-
-// ---------------------------------------------------------------------------------------
-// bf16 MFMA kernel for more than 256 rows per KV head (long questions, wide query groups, batches of them).
-// Workgroup (4 waves) = all rows of one KV head of one request against a tile of 256 keys, which stays in LDS
-// (64 KB, so two workgroups share a CU and one loads while the other multiplies) while the waves walk the rows
-// in groups of 64 with their Q fragments straight from global memory (L2).  The tile arrives in four quarters
-// of 64 keys, all requested up front; the logits of a wave's first 64 rows against a quarter are formed as soon
-// as it has landed.  PASS 0 leaves (max, sum exp) per (tile, row), a small kernel merges them per row, PASS 1
-// forms the column sums of exp2(l - stat).  Same results layout as the kernel above.  (The question keys as one more tile of
-// PASS 0: votes of eight requests, 65k keys, 32 .. 128 question tokens, 205 -> 148 us, of 5120 keys and 80 tokens 45.2 -> 31.)
-// ---------------------------------------------------------------------------------------
-constexpr int kRowsTileKeys = 256;
-constexpr size_t kScoresRowsLds = (size_t)kRowsTileKeys * kKRowBytes + 4 * 64 * sizeof(float) +
-                                  4 * kRowsTileKeys * sizeof(float);
-
-template <int PASS, bool REALIGN>
-__global__ void __launch_bounds__(256, 2)
-scores_rows_bf16_kernel(scores_args a) {
-  extern __shared__ __align__(16) unsigned char lds_raw[];
-  float *St = reinterpret_cast<float *>(lds_raw + kRowsTileKeys * kKRowBytes);      // after the K tile; [4 waves][64 rows]
-  float *red = reinterpret_cast<float *>(St + 4 * 64);                                // [4 waves][256 keys]
-
-  const int r = blockIdx.z, g = blockIdx.y;
-  // PASS 0 of the causal denominator: one more tile, the question keys (at most 256), each row up to its own token
-  const bool own = PASS == 0 && !REALIGN && (int)blockIdx.x == a.n_tiles;
-  const int nq = a.q_len[r], n_ctx = a.ctx_len[r];
-  const int N = own ? nq : n_ctx;
-  const int i0 = own ? 0 : blockIdx.x * kRowsTileKeys;
-  if (i0 >= N) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, lhi = lane >> 5;
-  const int s = a.seg_start[r] + (own ? n_ctx : 0);
-  const int G = a.Hq / a.Hkv;
-  const int Mg = nq * G;                // rows of this KV head: m = j*G + hh
-  const int qrow0 = a.q_start[r];
-  const bf16_t *__restrict__ Q = (const bf16_t *)a.q;
-  const bf16_t *__restrict__ K = (const bf16_t *)a.k;
-
-  // Q fragments of this wave's first 64 rows: requested before the K tile so that both latencies overlap
-  // (rows past Mg are clamped and ignored later)
-  bf16x8 qf[2][kD / 16];
-  int row_id[2], seen[2];                                      // seen: keys that the row may see (PASS 0)
-#define A3_LOAD_Q(RB0)                                                                                 \
-  _Pragma("unroll") for (int b = 0; b < 2; ++b) {                                                      \
-    const int m_ = min((RB0) + b * 32 + l32, Mg - 1);                                                  \
-    seen[b] = own ? min(N, m_ / G + 1) : N;                                                            \
-    row_id[b] = (qrow0 + m_ / G) * a.Hq + g * G + m_ % G;      /* row of the [sum q_len * Hq] row space */ \
-    const bf16_t *qp_ = Q + (size_t)row_id[b] * kD + lhi * 8;                                          \
-    _Pragma("unroll") for (int ks = 0; ks < kD / 16; ++ks) qf[b][ks] = *reinterpret_cast<const bf16x8 *>(qp_ + ks * 16); \
-  }
-  if (Mg > 0) { A3_LOAD_Q(min(wave * 64, Mg - 1)) }
-  const bool have_rows = wave * 64 < Mg;                       // this wave has a first group of rows
-  // PASS 1: max + log2(sum) of the rows of the lane's accumulators, once a round (read from LDS at every use they were 8 reads
-  // of 16 bytes a key block); infinite for a row past Mg, whose weights come out as exp2(-inf) = 0
-  f32x16 st[2];
-#define A3_START(RB0)                                                                                  \
-  if (PASS == 1) {                                                                                     \
-    const int m_ = (RB0) + lane;                                                                       \
-    float st_ = INFINITY;                                                                              \
-    if (m_ < Mg) st_ = a.stats[(qrow0 + m_ / G) * a.Hq + g * G + m_ % G].x;                            \
-    St[wave * 64 + lane] = st_;                                /* same-wave write/read: no barrier needed */ \
-    _Pragma("unroll") for (int b = 0; b < 2; ++b) _Pragma("unroll") for (int x = 0; x < 16; ++x)       \
-      st[b][x] = St[wave * 64 + b * 32 + 8 * (x >> 2) + 4 * lhi + (x & 3)];                            \
-  }
-  A3_START(wave * 64)
-
-  // The K tile arrives in four quarters of 64 keys.  Every load of the tile is issued up front; the logits
-  // of the wave's first 64 rows against quarter q are formed as soon as that quarter is in LDS, while the
-  // later quarters are still on their way, so the arithmetic runs under the memory time instead of after it.
-  constexpr int kQuarters = 4;
-  constexpr int kKB = kRowsTileKeys / 32;                      // 32-key blocks per tile
-  const int n_kb = min(kKB, (N - i0 + 31) / 32);               // key blocks with at least one real key
-  // fragment read: key 32 kb + l32, piece 2 ks + lhi -> slot (2 ks + lhi) ^ (l32 % 16)
-  const unsigned char *kt = lds_raw + l32 * kKRowBytes;
-  const int kswz = (lhi ^ (l32 & 15)) * 16;
-  float colsum[kKB];
-#pragma unroll
-  for (int kb = 0; kb < kKB; ++kb) colsum[kb] = 0.f;
-  float run_max[2] = {kLeast, kLeast}, run_sum[2] = {0.f, 0.f};
-
-  // logits of the current 64 rows (fragments in qf) against key block KB, folded into the running row
-  // statistics (pass A) or into the column sums (pass B)
-#define A3_KEY_BLOCK(KB)                                                                                       \
-  {                                                                                                            \
-    f32x16 acc[2];                                                                                             \
-    _Pragma("unroll") for (int b = 0; b < 2; ++b)                                                              \
-      _Pragma("unroll") for (int x = 0; x < 16; ++x) acc[b][x] = 0.f;                                          \
-    _Pragma("unroll") for (int ks = 0; ks < kD / 16; ++ks) {                                                   \
-      const bf16x8 kf = *reinterpret_cast<const bf16x8 *>(kt + (KB) * 32 * kKRowBytes + ((32 * ks) ^ kswz));   \
-      _Pragma("unroll") for (int b = 0; b < 2; ++b) {                                                          \
-        if (PASS == 0) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[b][ks], acc[b], 0, 0, 0); /* C[key][row] */ \
-        else           acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[b][ks], kf, acc[b], 0, 0, 0); /* C[row][key] */ \
-      }                                                                                                        \
-    }                                                                                                          \
-    if (PASS == 0) {                                                                                           \
-      /* lane: row (column l32 of block b); registers: keys i0 + 32 kb + 8(x/4) + 4 lhi + x%4 */               \
-      const bool tail = own || i0 + 32 * (KB) + 31 >= N;                                                       \
-      _Pragma("unroll") for (int b = 0; b < 2; ++b) {                                                          \
-        if (tail) {                                                                                            \
-          /* (the empty statement keeps the 16 comparisons of each of the unrolled blocks here: gathered at */ \
-          /* the top of the kernel their lane masks do not fit the scalar registers)                        */ \
-          int n_real = seen[b] - i0 - 32 * (KB) - 4 * lhi;                                                     \
-          asm volatile("" : "+v"(n_real));                                                                     \
-          _Pragma("unroll") for (int x = 0; x < 16; ++x)                                                       \
-            if (8 * (x >> 2) + (x & 3) >= n_real) acc[b][x] = -INFINITY;                                       \
-        }                                                                                                      \
-        float mx = acc[b][0];                                                                                  \
-        _Pragma("unroll") for (int x = 1; x < 16; ++x) mx = fmaxf(mx, acc[b][x]);                              \
-        mx = halves_max(mx) * a.scale2;                        /* block 0 of a tile always has a real key */   \
-        const float new_max = fmaxf(run_max[b], mx);                                                           \
-        float sum = 0.f;                                                                                       \
-        _Pragma("unroll") for (int x = 0; x < 16; ++x) sum += fast_exp2(fmaf(acc[b][x], a.scale2, -new_max));  \
-        run_sum[b] = run_sum[b] * fast_exp2(run_max[b] - new_max) + sum;   /* per lane half */                 \
-        run_max[b] = new_max;                                                                                  \
-      }                                                                                                        \
-    } else {                                                                                                   \
-      /* lane: key l32 of block kb; registers: rows 8(x/4) + 4 lhi + x%4 of row block b */                     \
-      float p0 = 0.f, p1 = 0.f;                                                                                \
-      _Pragma("unroll") for (int b = 0; b < 2; ++b) _Pragma("unroll") for (int x = 0; x < 16; x += 2) {        \
-        p0 += fast_exp2(fmaf(acc[b][x], a.scale2, -st[b][x]));                                            \
-        p1 += fast_exp2(fmaf(acc[b][x + 1], a.scale2, -st[b][x + 1]));                                    \
-      }                                                                                                        \
-      colsum[KB] += p0 + p1;                                                                                   \
-    }                                                                                                          \
-  }
-  // the round is done: pass A leaves the (max, sum) of its rows over this tile; waves that share a group (by key blocks, see the
-  // further rounds) merge theirs in LDS.  One that saw no key has a sum of 0.
-  int share = 1, sub = 0, rb = wave * 64;                      // waves that share the wave's group, which of them it is, its first row
-  float2 *pair = reinterpret_cast<float2 *>(red);
-#define A3_ROWS_DONE()                                                                                         \
-  if (PASS == 0) {                                                                                             \
-    float z[2];                                                                                                \
-    _Pragma("unroll") for (int b = 0; b < 2; ++b) z[b] = halves_sum(run_sum[b]);                               \
-    if (share > 1) {                                                                                           \
-      _Pragma("unroll") for (int b = 0; b < 2; ++b)                                                            \
-        if (lhi == 0) pair[wave * 64 + b * 32 + l32] = make_float2(run_max[b], z[b]);                          \
-      __syncthreads();                                                                                         \
-      _Pragma("unroll") for (int b = 0; b < 2; ++b)                                                            \
-        if (sub == 0)                                                                                          \
-          for (int w = wave + 4 / share; w < 4; w += 4 / share) {                                              \
-            const float2 o = pair[w * 64 + b * 32 + l32];                                                      \
-            const float mn = fmaxf(run_max[b], o.x);                                                           \
-            z[b] = z[b] * fast_exp2(run_max[b] - mn) + (o.y > 0.f ? o.y * fast_exp2(o.x - mn) : 0.f);          \
-            run_max[b] = mn;                                                                                   \
-          }                                                                                                    \
-    }                                                                                                          \
-    if (sub == 0)                                                                                              \
-      _Pragma("unroll") for (int b = 0; b < 2; ++b)                                                            \
-        if (lhi == 0 && rb + b * 32 + l32 < Mg) a.part[(size_t)blockIdx.x * a.total_rows + row_id[b]] = make_float2(run_max[b], z[b]); \
-  }
-
-  // ---- K tile: 256 keys x 128 dims of head g, global memory -> LDS directly (16 bytes per lane, lane i
-  // lands at base + 16 i).  One wave instruction brings 4 keys x 256 B; instruction j of wave w covers
-  // keys 4 (4 j + w) .. +3, so the instructions 4 q .. 4 q + 3 of the four waves bring quarter q.  The lane
-  // fetches piece (slot ^ key % 16) of its key, so LDS slot s of key r holds piece s ^ (r % 16) and the 16
-  // keys a quarter wave reads at one piece index touch all 64 banks once.  Inline assembly: the compiler
-  // then does not track these as LDS writes (it would wait for all of them before every LDS read); the
-  // explicit waits below cover them.
-  if (!REALIGN) {
-    // The compiler's own wait for the Q fragments and the row statistics would, counted by the hardware, also
-    // wait for everything issued before them; they are therefore awaited first, then the tile is requested.
-    __builtin_amdgcn_s_waitcnt(0);
-    const int drow = 4 * wave + (lane >> 4);                   // key of the lane in instruction 0
-    const int dpiece = (lane & 15) ^ (drow & 15);              // (4 (4 j + w) + lane/16) % 16 does not depend on j
-    const uint32_t lds_k = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds_raw;
-#pragma unroll
-    for (int j = 0; j < kRowsTileKeys / 16; ++j) {
-      const int row = min(s + i0 + drow + 16 * j, a.T - 1);    // tail rows: loaded, masked below
-      const bf16_t *gp = K + ((size_t)row * a.Hkv + g) * kD + dpiece * 8;
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                   :: "s"(__builtin_amdgcn_readfirstlane(lds_k + 4 * (4 * j + wave) * kKRowBytes)), "v"(gp) : "memory");
-    }
-    // at most the 4 (3 - QT) younger instructions of this wave are still in flight: its part of quarter QT
-    // has landed; after the barrier everybody's has.  (vmcnt in bits 3:0 and 15:14, the other counters open.)
-#define A3_QUARTER(QT)                                                                                         \
-    __builtin_amdgcn_s_waitcnt((4 * (kQuarters - 1 - (QT))) | (7 << 4) | (15 << 8));                           \
-    __builtin_amdgcn_s_barrier();                                                                              \
-    if (have_rows) {                                                                                           \
-      if (2 * (QT) < n_kb) A3_KEY_BLOCK(2 * (QT))                                                              \
-      if (2 * (QT) + 1 < n_kb) A3_KEY_BLOCK(2 * (QT) + 1)                                                      \
-    }
-    A3_QUARTER(0)
-    A3_QUARTER(1)
-    A3_QUARTER(2)
-    A3_QUARTER(3)
-#undef A3_QUARTER
-  } else {
-    // Position recovery (Eq. 2) on the way in: the tile comes from the stale cache through registers,
-    // every pair is turned by its chunk's offset, and the rounded result goes both to the realigned cache
-    // and, in the same swizzled layout as above, to LDS.  A lane owns the 16-byte pieces c and c + 8 of
-    // a key: in either pairing (adjacent coordinates, or i with i + 64) it then holds whole pairs.
-    const bf16_t *Kc = (const bf16_t *)a.k_cat;               // may be the same buffer as k_out
-    bf16_t *Ko = (bf16_t *)a.k_out;
-    const int c = tid & 7, kr0 = tid >> 3;                     // 32 keys per round, 8 rounds: 2 per quarter
-    constexpr int kRounds = kRowsTileKeys / 32;
-    // all loads of the stale keys and of their chunk numbers are issued before the first rotation
-    bf16x8 lo[kRounds], hi[kRounds];
-    int chunk[kRounds];
-#pragma unroll
-    for (int j = 0; j < kRounds; ++j) {
-      const int key = kr0 + 32 * j;
-      const int row = min(s + i0 + key, a.T - 1);              // tail rows: loaded, never stored to the cache
-      const size_t off = ((size_t)row * a.Hkv + g) * kD;
-      lo[j] = *reinterpret_cast<const bf16x8 *>(Kc + off + 8 * c);
-      hi[j] = *reinterpret_cast<const bf16x8 *>(Kc + off + 64 + 8 * c);
-      chunk[j] = i0 + key < N ? a.tok_chunk[row] : -1;
-    }
-    // the eight (cos, sin) pairs of this lane's coordinates are reloaded only when the chunk changes
-    // from one of its keys to the next (rarely: a tile spans few chunks)
-    const bool inter = a.rope_layout == A3_ROPE_INTERLEAVED;
-    float2 csr[8];
-    int cur = -1;
-#pragma unroll
-    for (int j = 0; j < kRounds; ++j) {
-      const int key = kr0 + 32 * j;
-      const bool real = i0 + key < N;
-      const int row = min(s + i0 + key, a.T - 1);
-      const size_t off = ((size_t)row * a.Hkv + g) * kD;
-      bf16x8 rlo = lo[j], rhi = hi[j];
-      if (chunk[j] >= 0) {
-        if (chunk[j] != cur) {
-          const float2 *cs = a.chunk_cs + (size_t)chunk[j] * (kD / 2);
-#pragma unroll
-          for (int e = 0; e < 8; ++e)                          // interleaved: pairs 4c..4c+3 and 32+4c..; half: 8c..8c+7
-            csr[e] = inter ? cs[(e < 4 ? 4 * c : 28 + 4 * c) + e] : cs[8 * c + e];
-          cur = chunk[j];
-        }
-        if (inter) {
-#pragma unroll
-          for (int p2 = 0; p2 < 4; ++p2) {
-            float y0, y1;
-            a3_rotate_pair(a3_bf2f(lo[j][2 * p2]), a3_bf2f(lo[j][2 * p2 + 1]), csr[p2], y0, y1);
-            rlo[2 * p2] = a3_f2bf(y0); rlo[2 * p2 + 1] = a3_f2bf(y1);
-            a3_rotate_pair(a3_bf2f(hi[j][2 * p2]), a3_bf2f(hi[j][2 * p2 + 1]), csr[4 + p2], y0, y1);
-            rhi[2 * p2] = a3_f2bf(y0); rhi[2 * p2 + 1] = a3_f2bf(y1);
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {                        // coordinate 8c+e pairs with 64+8c+e
-            float y0, y1;
-            a3_rotate_pair(a3_bf2f(lo[j][e]), a3_bf2f(hi[j][e]), csr[e], y0, y1);
-            rlo[e] = a3_f2bf(y0); rhi[e] = a3_f2bf(y1);
-          }
-        }
-      }
-      if (real) {
-        *reinterpret_cast<bf16x8 *>(Ko + off + 8 * c) = rlo;
-        *reinterpret_cast<bf16x8 *>(Ko + off + 64 + 8 * c) = rhi;
-      }
-      unsigned char *ld = lds_raw + key * kKRowBytes;
-      *reinterpret_cast<bf16x8 *>(ld + ((c ^ (key & 15)) * 16)) = rlo;
-      *reinterpret_cast<bf16x8 *>(ld + (((c + 8) ^ (key & 15)) * 16)) = rhi;
-      if (j & 1) {
-        // quarter j / 2 is in LDS once everybody's two rounds are written (this wave's writes first: the
-        // LDS counter only; a full fence would also wait for the keys still on their way)
-        __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (0 << 8));
-        __builtin_amdgcn_s_barrier();
-        if (have_rows) {
-          if (j - 1 < n_kb) A3_KEY_BLOCK(j - 1)
-          if (j < n_kb) A3_KEY_BLOCK(j)
-        }
-      }
-    }
-  }
-  if (have_rows) { A3_ROWS_DONE() }
-
-  // ---- the further rounds (more than 256 rows per KV head): the whole tile is in LDS by now --------------
-  // A group of 64 rows each, or, where one or two are left, for four or two waves with every fourth or second key block each:
-  // 80 question tokens x 4 heads are five groups, and the fifth on one wave alone took as long as the four before it (16K keys, both
-  // passes and the small kernels 53.9 -> 48.4 us; 64K keys, 96 tokens, 169 -> 159; 128 tokens, eight groups, as before).  Not in the
-  // first round, where a wave without rows leaves its SIMD to the other workgroup of the CU.
-  for (int rb0 = 256; rb0 < Mg; rb0 += 256) {
-    const int left = (Mg - rb0 + 63) >> 6;                     // groups
-    share = left == 1 ? 4 : left == 2 ? 2 : 1;
-    sub = left == 1 ? wave : left == 2 ? wave >> 1 : 0;
-    rb = rb0 + 64 * (left == 1 ? 0 : left == 2 ? wave & 1 : wave);
-    if (rb >= Mg) break;                                       // (a wave without rows: three groups are left, none of them shared)
-    A3_LOAD_Q(rb)
-    A3_START(rb)
-    run_max[0] = run_max[1] = kLeast;
-    run_sum[0] = run_sum[1] = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < kKB; ++kb)                           // (unrolled: the column sums are registers)
-      if (kb < n_kb && (kb & (share - 1)) == sub) A3_KEY_BLOCK(kb)
-    A3_ROWS_DONE()
-  }
-#undef A3_START
-#undef A3_KEY_BLOCK
-#undef A3_ROWS_DONE
-#undef A3_LOAD_Q
-  if (PASS == 1) {
-#pragma unroll
-    for (int kb = 0; kb < kKB; ++kb) {
-      const float v = halves_sum(colsum[kb]);
-      if (lhi == 0) red[wave * kRowsTileKeys + kb * 32 + l32] = v;
-    }
-    __syncthreads();
-    const int key = i0 + tid;
-    if (tid < kRowsTileKeys && key < N)
-      a.part_scores[(size_t)g * a.T + s + key] = (red[tid] + red[kRowsTileKeys + tid]) +
-                                                 (red[2 * kRowsTileKeys + tid] + red[3 * kRowsTileKeys + tid]);
+    // lane groups 0 and 2: key block 0, groups 1 and 3: key block 1
+    const float v = halves_sum(swap16_add(colsum[0], colsum[1]));
+    if (lane < kKeysWave && iw + lane < N) a.part_scores[(size_t)g * a.T + s + iw + lane] = v;
   }
 }
 
@@ -1041,38 +706,10 @@ scores_f32_kernel(scores_args a) {
 
 }  // namespace
 
-// bf16 path: rows of the score matrix per KV head, in chunks of 256 (one chunk: the ring kernel)
-static int scores_row_chunks(const a3_layout *L) {
-  const int G = L->n_q_heads / L->n_kv_heads;
-  const int c = (int)(((long long)L->max_q_len * G + kChunkRows - 1) / kChunkRows);
-  return c < 1 ? 1 : c;
-}
-
-// bf16 path: keys per workgroup.  A multiple of the 64-key ring slot in [256, 1024], chosen so that the
-// workgroups (one per CU at a time: 150 KB of LDS) fill the 256 CUs in as few, as full rounds as possible; a
-// workgroup's fixed cost (its Q tile, the merge of the partials, the start-up of the ring) is worth about 192 keys.
-// own = 1: every request has one more, short run in the first pass, its question keys (causal denominator), which costs as much as
-// its keys where the last round has no room for it: 16K keys x 8 KV heads take 29 runs of 576, not 32 of 512 (both passes 32.5 us and
-// 34.8 without the one more), 64K keys stay at 64 runs of 1024 (98 us; 95 runs of 704 109).
-static int scores_tile_keys_bf16(const a3_layout *L, int own) {
-  // more than 256 rows per KV head: the kernel that keeps a 256-key tile in LDS and walks the rows
-  if (scores_row_chunks(L) > 1) return kRowsTileKeys;
-  const long long per_tile = (long long)L->n_req * L->n_kv_heads;
-  long long best_cost = -1;
-  int best = kMinTileKeys;
-  for (int tk = kMinTileKeys; tk <= kMaxTileKeys; tk += kSlotKeys) {
-    const long long wgs = per_tile * ((L->max_ctx_len + tk - 1) / tk);
-    long long cost = 2 * ((wgs + 255) / 256) * (tk + 192);      // the two passes
-    if (own && (wgs - 1) % 256 + 1 + per_tile > 256) cost += (L->max_q_len + kSlotKeys - 1) / kSlotKeys * kSlotKeys + 192;
-    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = tk; }
-  }
-  return best;
-}
-
 size_t a3_scores_ws_bytes(const a3_layout *L) {
   // rows of the score matrix over the whole batch are bounded by n_req * max_q_len * Hq
   const size_t total_rows = (size_t)L->n_req * L->max_q_len * L->n_q_heads;
-  const int tk = L->dtype == A3_BF16 ? kMinTileKeys : kTileKeys;         // the most runs of keys either path can have
+  const int tk = L->dtype == A3_BF16 ? kTile : kTileKeys;
   const size_t n_tiles = (size_t)(L->max_ctx_len + tk - 1) / tk;
   return a3_align_up((n_tiles + 1) * total_rows * sizeof(float2), 256) + a3_align_up(total_rows * sizeof(float2), 256) +
          a3_align_up((size_t)L->n_kv_heads * L->total_tokens * sizeof(float), 256) + 256;
@@ -1098,15 +735,15 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
   hipStream_t st = (hipStream_t)stream;
   const bool bf16 = L->dtype == A3_BF16;
   const size_t total_rows = (size_t)L->n_req * L->max_q_len * L->n_q_heads;   // upper bound, used as row pitch
-  const int tk = bf16 ? scores_tile_keys_bf16(L, causal_q) : kTileKeys;
+  const int tk = bf16 ? kTile : kTileKeys;
   const int n_tiles = (L->max_ctx_len + tk - 1) / tk;
-  const int tk_min = bf16 ? kMinTileKeys : kTileKeys;
-  const int max_tiles = (L->max_ctx_len + tk_min - 1) / tk_min;               // what the workspace is sized for
   a3_ws_cursor cur(ws, ws_bytes);
   scores_args a;
   a.q = q_question; a.k = k_fused;
   a.seg_start = L->seg_start; a.ctx_len = L->ctx_len; a.q_len = L->q_len; a.q_start = L->q_start;
-  a.part = (float2 *)cur.take((size_t)(max_tiles + 1) * total_rows * sizeof(float2));
+  a.part = (float2 *)cur.take((size_t)(n_tiles + 1) * total_rows * sizeof(float2));
+  a.part_z = (float *)a.part;
+  a.part_m = a.part_z + (size_t)(n_tiles + 1) * total_rows;
   a.stats = (float2 *)cur.take(total_rows * sizeof(float2));
   a.part_scores = (float *)cur.take((size_t)L->n_kv_heads * L->total_tokens * sizeof(float));
   if (votes) a.part_scores = votes;                            // a KV head's column sums are its votes
@@ -1118,7 +755,6 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
   a.n_req = L->n_req; a.Hq = L->n_q_heads; a.Hkv = L->n_kv_heads; a.d = L->head_dim; a.T = L->total_tokens;
   a.total_rows = (int)total_rows; a.n_tiles = n_tiles; a.tile_keys = tk;
   a.scale2 = a3_scale_of(L) * kLog2e;
-  a.inv_scale2 = 1.0f / a.scale2;
   const bool one = L->n_req == 1 && L->max_ctx_len + L->max_q_len == L->total_tokens;
   a.one_ctx_len = one ? L->max_ctx_len : -1;
   a.one_q_len = one ? L->max_q_len : -1;
@@ -1129,9 +765,10 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
     s = a3_rope_realign(L, k_cat, k_fused, stream);
     if (s != A3_OK) return s;
   }
-  // the question keys' share of the denominators: a run of the first pass itself in bf16, up to the 256 keys of a tile; a kernel
-  // before the passes otherwise
-  const bool own_runs = causal_q && bf16 && L->max_q_len <= kRowsTileKeys;
+  // the question keys' share of the denominators: a tile of the first pass itself in bf16, up to its 256 keys; a kernel before the
+  // passes otherwise
+  const bool own_runs = causal_q && bf16 && L->max_q_len <= kTile;
+  a.own_tile = own_runs;
   if (causal_q && !own_runs) {
     const dim3 qgrid((unsigned)((total_rows + 3) / 4));
     if (bf16) hipLaunchKernelGGL(scores_question_stats_kernel<bf16_t>, qgrid, dim3(256), 0, st, a);
@@ -1140,38 +777,28 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
   if (bf16) {
     static a3_once_per_device lds_once;
     const hipError_t e = a3_once(lds_once, []() {
-      const void *fns[] = {(const void *)scores_bf16_kernel<0, false>, (const void *)scores_bf16_kernel<1, false>,
-                           (const void *)scores_bf16_kernel<0, true>};
-      for (const void *fn : fns) {
-        const hipError_t e_ = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kScoresLds);
-        if (e_ != hipSuccess) return e_;
-      }
-      const void *rows_fns[] = {(const void *)scores_rows_bf16_kernel<0, false>, (const void *)scores_rows_bf16_kernel<1, false>,
-                                (const void *)scores_rows_bf16_kernel<0, true>};
-      for (const void *fn : rows_fns) {
-        const hipError_t e_ = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kScoresRowsLds);
+      for (const void *fn : {(const void *)scores_bf16_kernel<0, false>, (const void *)scores_bf16_kernel<0, true>, (const void *)scores_bf16_kernel<1, false>}) {
+        const hipError_t e_ = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)scores_lds_bytes(2, 0));
         if (e_ != hipSuccess) return e_;
       }
       return hipSuccess;
     });
     if (e != hipSuccess) return a3_fail(A3_ERR_HIP, "a3_question_scores: cannot raise the dynamic LDS limit: %s", hipGetErrorString(e));
-    a.merged = (n_tiles > 32 || scores_row_chunks(L) > 1) ? 1 : 0;
-    const long long wgs = (long long)L->n_req * n_tiles * L->n_kv_heads;
-    A3_REQUIRE(wgs + own_runs * (long long)L->n_req * L->n_kv_heads < (1LL << 31), A3_ERR_UNSUPPORTED, "a3_question_scores: batch too large");
-    const dim3 grid((unsigned)wgs), grid0((unsigned)(wgs + own_runs * (long long)L->n_req * L->n_kv_heads));
-    if (scores_row_chunks(L) > 1) {
-      // (tile_keys is kRowsTileKeys here; every row of a KV head in one workgroup)
-      const dim3 rgrid((unsigned)n_tiles, (unsigned)L->n_kv_heads, (unsigned)L->n_req), rgrid0((unsigned)(n_tiles + own_runs), rgrid.y, rgrid.z);
-      if (fuse) hipLaunchKernelGGL((scores_rows_bf16_kernel<0, true>), rgrid, dim3(256), kScoresRowsLds, st, a);
-      else hipLaunchKernelGGL((scores_rows_bf16_kernel<0, false>), rgrid0, dim3(256), kScoresRowsLds, st, a);
-      hipLaunchKernelGGL(scores_combine_kernel, dim3((unsigned)((total_rows + 15) / 16)), dim3(256), 0, st, a);
-      hipLaunchKernelGGL((scores_rows_bf16_kernel<1, false>), rgrid, dim3(256), kScoresRowsLds, st, a);
-    } else {
-      if (fuse) hipLaunchKernelGGL((scores_bf16_kernel<0, true>), grid, dim3(kScoreThreads), kScoresLds, st, a);
-      else hipLaunchKernelGGL((scores_bf16_kernel<0, false>), grid0, dim3(kScoreThreads), kScoresLds, st, a);
-      if (a.merged) hipLaunchKernelGGL(scores_combine_kernel, dim3((unsigned)((total_rows + 15) / 16)), dim3(256), 0, st, a);
-      hipLaunchKernelGGL((scores_bf16_kernel<1, false>), grid, dim3(kScoreThreads), kScoresLds, st, a);
-    }
+    const long long wgs = (long long)L->n_req * n_tiles * L->n_kv_heads, wgs0 = wgs + (own_runs ? (long long)L->n_req * L->n_kv_heads : 0);
+    A3_REQUIRE(wgs0 < (1LL << 31), A3_ERR_UNSUPPORTED, "a3_question_scores: batch too large");
+    const long long rows = (long long)L->max_q_len * G;          // of a KV head, at most
+    // The second pass merges the partials of a row in its threads, 32 each: two threads a row up to 256 rows.  (A launch of the combine
+    // kernel is 5 us.)
+    a.merged = n_tiles > (rows <= kThreads / 2 ? 64 : rows <= kThreads ? 32 : 0);
+    auto inverse = [](long long d, long long n) { return d > 1 && n * d < (1LL << 32) ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u; };
+    a.inv_heads = inverse(L->n_kv_heads, wgs0);
+    a.inv_runs[0] = inverse(n_tiles + (fuse ? 0 : own_runs), wgs0);
+    a.inv_runs[1] = inverse(n_tiles, wgs);
+    const int bufs = rows > kChunk ? 2 : 1;
+    if (fuse) hipLaunchKernelGGL((scores_bf16_kernel<0, true>), dim3((unsigned)wgs), dim3(kThreads), scores_lds_bytes(bufs, 0), st, a);
+    else hipLaunchKernelGGL((scores_bf16_kernel<0, false>), dim3((unsigned)wgs0), dim3(kThreads), scores_lds_bytes(bufs, 0), st, a);
+    if (a.merged) hipLaunchKernelGGL(scores_combine_kernel<true>, dim3((unsigned)((total_rows + 15) / 16)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((scores_bf16_kernel<1, false>), dim3((unsigned)wgs), dim3(kThreads), scores_lds_bytes(bufs, 1), st, a);
   } else {
     const dim3 grid(n_tiles, L->n_kv_heads, L->n_req), cgrid((unsigned)((total_rows + 15) / 16));
     a.merged = n_tiles > kF32MergeTiles || L->max_q_len * G > kF32MergeRows ? 1 : 0;
@@ -1179,7 +806,7 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
       constexpr int D = decltype(dim)::value;
       if (fuse) hipLaunchKernelGGL((scores_f32_kernel<0, D, true>), grid, dim3(256), 0, st, a);
       else hipLaunchKernelGGL((scores_f32_kernel<0, D, false>), grid, dim3(256), 0, st, a);
-      if (a.merged) hipLaunchKernelGGL(scores_combine_kernel, cgrid, dim3(256), 0, st, a);
+      if (a.merged) hipLaunchKernelGGL(scores_combine_kernel<false>, cgrid, dim3(256), 0, st, a);
       hipLaunchKernelGGL((scores_f32_kernel<1, D, false>), grid, dim3(256), 0, st, a);
     };
     if (L->head_dim == 64) launch(std::integral_constant<int, 64>{});
