@@ -623,8 +623,9 @@ attn_f32_kernel(attn_args a) {
 #pragma unroll
     for (int c = 0; c < D / 16; ++c) qf[c] = qp[4 * c];
   }
+  const int first = a.seg_start[0];                            // of one request: read beside the row number, not behind it (13.0 -> 12.6 us)
   const int t = a.act_idx[arow], req = a.tok_req ? a.tok_req[t] : 0;
-  const int first_key = a.seg_start[req];
+  const int first_key = a.tok_req ? a.seg_start[req] : first;
   // the rows of one request at a time (rows are ascending: nearly always all of them), found in the lanes that hold them: lane x of a
   // group belongs to row a0 + x / G, the last ones to the last row
   for (int b0 = a0; b0 < a_end;) {
