@@ -57,7 +57,7 @@ struct scores_args {
   uint32_t inv_heads, inv_runs[2];   // the same for Hkv and the tiles of a request in either pass; 0: no such number, divide
   float scale2;             // sm_scale * log2(e)
   int one_ctx_len, one_q_len;   // a single request whose segment starts at row 0: its lengths; otherwise -1
-  // fused position recovery (first pass of the bf16 path only): stale keys in, realigned keys out
+  // fused position recovery (first pass): stale keys in, realigned keys out
   const void *k_cat;        // [T, Hkv, d] keys at chunk-local positions
   void *k_out;              // [T, Hkv, d] realigned keys (may be k_cat itself)
   const int *tok_chunk;     // [T] chunk of a context row, -1 for question rows
@@ -715,8 +715,7 @@ size_t a3_scores_ws_bytes(const a3_layout *L) {
          a3_align_up((size_t)L->n_kv_heads * L->total_tokens * sizeof(float), 256) + 256;
 }
 
-// k_cat != nullptr: the first pass of the bf16 path also realigns (k_cat -> k_fused); the fp32 path runs the
-// realign kernel first.
+// k_cat != nullptr: the first pass also realigns (k_cat -> k_fused).
 // causal_q: the question keys a question token sees join its softmax denominator.  votes != nullptr: the per
 // KV head column sums [Hkv, T] go there; scores may then be NULL (no sum over heads).
 static a3_status scores_launch(const a3_layout *L, const void *q_question, const void *k_cat, void *k_fused,
