@@ -450,30 +450,21 @@ proj_f32_kernel(proj_args_f32 a) {
     const int m = min(row0 + 16 * j + l16, a.n_rows - 1);      // clamp: computed but never stored
     xp[j] = reinterpret_cast<const f32x4 *>(a.hidden + (size_t)(a.row_idx ? a.row_idx[m] : m) * a.K) + lg;
   }
-  // what a thread needs at the end for its pair of coordinates of its row: three loads one behind the other
-  const int i = tid >> 3, q = tid & 7, tok = row0 + i;
-  const bool inter = a.rope_layout == A3_ROPE_INTERLEAVED;
-  const int fa = inter ? 2 * q : q, fb = inter ? 2 * q + 1 : q + 8;              // MFMA rows of the pair
-  const int ca = (fa < 8 ? 0 : half - 8) + 8 * b + fa, cb = (fb < 8 ? 0 : half - 8) + 8 * b + fb;   // coordinates in the head
-  const int tokc = min(tok, a.n_rows - 1), src = a.row_idx ? a.row_idx[tokc] : tokc;
-  float2 turn = make_float2(1.f, 0.f);
-  // 16-element chunks of the reduction: wave w takes chunks w, w + 4, ..., eight at a time
-  constexpr int kAtOnce = 8;
+  // 16-element chunks of the reduction: wave w takes chunks w, w + 4, ..., four at a time
   const int chunks = a.K / 16;
   f32x4 acc[2][2] = {};                                        // [row block][parity of the chunk]: two chains each
-  for (int c0 = wave; c0 < chunks; c0 += 4 * kAtOnce) {
-    f32x4 wf[kAtOnce], xf[2][kAtOnce];
+  for (int c0 = wave; c0 < chunks; c0 += 16) {
+    f32x4 wf[4], xf[2][4];
 #pragma unroll
-    for (int u = 0; u < kAtOnce; ++u) {
+    for (int u = 0; u < 4; ++u) {
       const int c = c0 + 4 * u;
       const bool on = c < chunks;
       wf[u] = on ? wp[4 * c] : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int j = 0; j < 2; ++j) xf[j][u] = on ? xp[j][4 * c] : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    if (c0 == wave && hs.which != 2) turn = a.pos_cs[(size_t)a.tok_pos[src] * half + (inter ? ca / 2 : ca)];
 #pragma unroll
-    for (int u = 0; u < kAtOnce; ++u)
+    for (int u = 0; u < 4; ++u)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -487,15 +478,21 @@ proj_f32_kernel(proj_args_f32 a) {
   __syncthreads();
   // one pair of coordinates of one row per thread: features 8 b + .. of the first half with those of the second (halves), or
   // neighbours of either half (interleaved)
+  const int i = tid >> 3, q = tid & 7, tok = row0 + i;
   if (tok >= a.n_rows) return;
+  const bool inter = a.rope_layout == A3_ROPE_INTERLEAVED;
+  const int fa = inter ? 2 * q : q, fb = inter ? 2 * q + 1 : q + 8;              // MFMA rows of the pair
   float xa = 0.f, xb = 0.f;
 #pragma unroll
   for (int w = 0; w < 4; ++w) { xa += red[w][i >> 4][i & 15][fa]; xb += red[w][i >> 4][i & 15][fb]; }
+  const int ca = (fa < 8 ? 0 : half - 8) + 8 * b + fa, cb = (fb < 8 ? 0 : half - 8) + 8 * b + fb;   // coordinates in the head
   const float *bias = a.bias[hs.which];
   if (bias) { xa += bias[hs.head * d + ca]; xb += bias[hs.head * d + cb]; }
+  const int src = a.row_idx ? a.row_idx[tok] : tok;
   if (hs.which != 2) {
-    const float ya = xa * turn.x - xb * turn.y;
-    xb = xa * turn.y + xb * turn.x;
+    const float2 t = a.pos_cs[(size_t)a.tok_pos[src] * half + (inter ? ca / 2 : ca)];
+    const float ya = xa * t.x - xb * t.y;
+    xb = xa * t.y + xb * t.x;
     xa = ya;
   }
   float *orow = out + ((size_t)((a.scatter_kv && hs.which != 0) ? src : tok) * hs.heads_out + hs.head) * d;
