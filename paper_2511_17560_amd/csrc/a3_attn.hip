@@ -44,10 +44,10 @@ constexpr size_t kAttnLds = kRingBytes + (size_t)kAttnWaves * kTableItems * 32; 
 
 __global__ void __launch_bounds__(kPlanThreads)
 attn_plan_kernel(attn_plan p, const int *__restrict__ act_idx, int n_act, const int *__restrict__ seg_start,
-                 int n_req, int G, int wgs_per_head, int item_cost, int min_steps) {
+                 int n_req, int G, int wgs_per_head, int item_cost) {
   __shared__ __align__(16) int wave_tot[kPlanThreads / 64];
   __shared__ int small[kPlanLdsInts];
-  attn_plan_body(p, act_idx, [&](int i) { return act_idx[i]; }, n_act, seg_start, n_req, G, wgs_per_head, item_cost, min_steps, wave_tot, small, kPlanLdsInts);
+  attn_plan_body(p, act_idx, [&](int i) { return act_idx[i]; }, n_act, seg_start, n_req, G, wgs_per_head, item_cost, wave_tot, small, kPlanLdsInts);
 }
 
 struct attn_args {
@@ -808,7 +808,7 @@ static a3_status attn_launch(const a3_layout *L, const void *q_act, const int *a
     const int wgs_per_head = a.plan.max_wgs, max_tiles = a.plan.max_tiles, Hkv = L->n_kv_heads;
     if (parts & 1)
       hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(kPlanThreads), 0, st, a.plan, act_idx, n_act, L->seg_start,
-                         L->n_req, L->n_q_heads / L->n_kv_heads, wgs_per_head, attn_item_cost(L, n_act), attn_min_steps(L));
+                         L->n_req, L->n_q_heads / L->n_kv_heads, wgs_per_head, attn_item_cost(L, n_act));
     if (parts & 2) {
       // blockIdx % Hkv = KV head, so with 8 KV heads each XCD's L2 serves the K/V of one head
       if (ev_begin) (void)hipEventRecord(ev_begin, st);

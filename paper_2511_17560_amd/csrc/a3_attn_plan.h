@@ -10,6 +10,10 @@
 namespace {
 
 constexpr int kTM = 256;            // packed (row, head) pairs per work item: 32 per wave of the attention kernel
+// Key steps of a share, at least (2K context: 37 us with 8, 33 with 4 or less).  Two for requests of up to 768 rows were faster (500 rows at
+// 15 % 19.1 -> 15.8 us, 512 in a chunk's precompute 24.0 -> 18.7) but give other cuts, whose error against float64 is larger in places:
+// 4 x 400 rows 1.963e-3 -> 1.978e-3, 1.799e-3 -> 1.823e-3 with a few large weights, precompute of 200 rows 7.026e-3 -> 7.037e-3
+constexpr int kMinSteps = 4;
 constexpr int kPlanThreads = 1024;
 constexpr int kOneShares = 64;      // shares that one wave can lay out
 constexpr int kPlanLdsInts = 6144;  // LDS the plan kernel sets aside for the plan's small arrays (24 KB)
@@ -18,7 +22,7 @@ constexpr int kPlanLdsInts = 6144;  // LDS the plan kernel sets aside for the pl
 //   tile  = 256 consecutive packed (row, head) pairs of one request and one KV head group; it needs
 //           ceil(visible keys of its last row / 64) key steps
 //   The key steps of all tiles, laid end to end, are cut into P equal shares, one per workgroup of a
-//   KV head (P = workgroups per head, at most one share per min_steps steps): every workgroup gets the same
+//   KV head (P = workgroups per head, at most one share per kMinSteps steps): every workgroup gets the same
 //   amount of work whatever the mix of short and long tiles.
 //   item  = the part of one share that lies in one tile: (tile, k_begin, k_end).  A tile that lies inside
 //           one share is finished by that workgroup; the others are cut into 2 or more items whose
@@ -90,7 +94,7 @@ __device__ __forceinline__ int plan_scan(int v, int *wave_tot, int *total) {
 template <bool in_lds, class Row>
 __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *act_idx, Row row, int n_act,
                                                  const int *__restrict__ seg_start, int n_req, int G, int wgs_per_head,
-                                                 int item_cost, int min_steps, int *wave_tot, int *lds) {
+                                                 int item_cost, int *wave_tot, int *lds) {
   const int tid = threadIdx.x;
   int *a_lo = in_lds ? lds : p.a_lo;
   int *tile_start = in_lds ? lds + (n_req + 1) : p.tile_start;
@@ -166,7 +170,7 @@ __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *
   plan_barrier<in_lds>();
 
   // ---- equal shares ------------------------------------------------------------------------
-  int P = (W - n_tiles * item_cost + min_steps - 1) / min_steps;
+  int P = (W - n_tiles * item_cost + kMinSteps - 1) / kMinSteps;
   if (P > wgs_per_head) P = wgs_per_head;
   if (P > p.max_wgs) P = p.max_wgs;
   if (P < 1) P = 1;
@@ -231,7 +235,7 @@ __device__ __forceinline__ void attn_plan_layout(const attn_plan &p, const int *
 // divisions for each tile's number of items, it took 10.1 thousand cycles behind the selection of 2K rows, like this 4.7.
 constexpr int kOneTiles = 512;
 template <class Row>
-__device__ __forceinline__ void attn_plan_one(const attn_plan &p, Row row, int n_act, int base, int G, int wgs_per_head, int item_cost, int min_steps, int *lds) {
+__device__ __forceinline__ void attn_plan_one(const attn_plan &p, Row row, int n_act, int base, int G, int wgs_per_head, int item_cost, int *lds) {
   if (threadIdx.x >= 64) return;
   const int lane = threadIdx.x;
   int *pre = lds, *kvs = pre + kOneTiles + 1, *parts = kvs + kOneTiles;   // running cost, visible keys, items of a tile
@@ -261,7 +265,7 @@ __device__ __forceinline__ void attn_plan_one(const attn_plan &p, Row row, int n
     p.tile_start[1] = n_tiles;
   }
   wave_sync();
-  const int P = max(1, min((W - n_tiles * item_cost + min_steps - 1) / min_steps, min(wgs_per_head, p.max_wgs)));
+  const int P = max(1, min((W - n_tiles * item_cost + kMinSteps - 1) / kMinSteps, min(wgs_per_head, p.max_wgs)));
   // share q: positions floor(q W / P) .. floor((q + 1) W / P) - 1
   const uint32_t each = (uint32_t)W / (uint32_t)P, rest = (uint32_t)W - each * (uint32_t)P;
   const int s_beg = (int)((uint32_t)lane * each + (uint32_t)lane * rest / (uint32_t)P);
@@ -309,15 +313,15 @@ __device__ __forceinline__ void attn_plan_one(const attn_plan &p, Row row, int n
 template <class Row>
 __device__ __forceinline__ void attn_plan_body(const attn_plan &p, const int *act_idx, Row row, int n_act,
                                                const int *__restrict__ seg_start, int n_req, int G, int wgs_per_head,
-                                               int item_cost, int min_steps, int *wave_tot, int *lds, int lds_ints) {
+                                               int item_cost, int *wave_tot, int *lds, int lds_ints) {
   if (n_req == 1 && ((long long)n_act * G + kTM - 1) / kTM <= kOneTiles && wgs_per_head <= kOneShares && p.max_wgs <= kOneShares &&
       3 * kOneTiles + 1 <= lds_ints) {
-    attn_plan_one(p, row, n_act, seg_start[0], G, wgs_per_head, item_cost, min_steps, lds);
+    attn_plan_one(p, row, n_act, seg_start[0], G, wgs_per_head, item_cost, lds);
     return;
   }
   const bool fits = 3 * (n_req + 1) + 3 * p.max_tiles + 1 <= lds_ints;
-  if (fits) attn_plan_layout<true>(p, act_idx, row, n_act, seg_start, n_req, G, wgs_per_head, item_cost, min_steps, wave_tot, lds);
-  else attn_plan_layout<false>(p, act_idx, row, n_act, seg_start, n_req, G, wgs_per_head, item_cost, min_steps, wave_tot, lds);
+  if (fits) attn_plan_layout<true>(p, act_idx, row, n_act, seg_start, n_req, G, wgs_per_head, item_cost, wave_tot, lds);
+  else attn_plan_layout<false>(p, act_idx, row, n_act, seg_start, n_req, G, wgs_per_head, item_cost, wave_tot, lds);
 }
 
 
@@ -354,13 +358,6 @@ int attn_item_cost(const a3_layout *L, int n_act) {
   const double steps = (double)n_act * (L->n_q_heads / L->n_kv_heads) / kTM * len / kTK / 2 / attn_wgs_per_head(L);
   return len <= kShortRequestRows || steps < kShortShareSteps ? 4 : 8;
 }
-
-// Key steps of a share, at least.  Fewer mean more workgroups with less to do and more segments to merge: requests of up to 768 rows have few
-// tiles of few steps and leave the chip half empty with 4 (calls of 15 % of the rows, and of all, with 4 and 2: 300 rows 17.5 and 15.0 us,
-// 500 19.1 and 15.8, 4 x 400 22.8 and 20.7; 200 20.9 and 17.5, 512 24.1 and 23.7, in a chunk's precompute 24.0 and 18.7 for the main kernel; 1
-// instead of 2: 300 rows 14.3, 500 17.0, 512 23.7).  Longer ones differ by up to 8 % either way (1000 rows at 5 % 19.4 and 18.5, at 15 %
-// 21.2 and 21.8, 2000 at 5 % 24.3 and 25.8: more segments to merge) and are cut by the number of workgroups from 2000 rows at 15 % on.
-int attn_min_steps(const a3_layout *L) { return L->max_ctx_len + L->max_q_len <= 768 ? 2 : 4; }
 
 // every tile starts an item, every share boundary inside a tile starts another
 int attn_max_items(const a3_layout *L, int n_act) { return attn_max_tiles(L, n_act) + attn_wgs_per_head(L); }

@@ -438,7 +438,7 @@ topk_select_reg_kernel(const float *__restrict__ scores, topk_problem prob, int 
 template <int KPT>
 __global__ void __launch_bounds__(kBlock)
 topk_select_plan_kernel(const float *__restrict__ scores, topk_problem prob, int *__restrict__ sel_idx,
-                        int *act_idx, int n_act, attn_plan plan, int G, int wgs_per_head, int item_cost, int min_steps) {
+                        int *act_idx, int n_act, attn_plan plan, int G, int wgs_per_head, int item_cost) {
   __shared__ __align__(16) int wave_tot[kPlanThreads / 64];
   __shared__ int small[kPlanLdsInts], list[kListRows];
   static_assert(kPlanThreads == kBlock, "one workgroup shape for both parts");
@@ -464,11 +464,9 @@ topk_select_plan_kernel(const float *__restrict__ scores, topk_problem prob, int
     __syncthreads();
   }
   if (listed)
-    attn_plan_body(plan, act_idx, [&](int i) { return i < k ? list[i] : first_q + i; }, n_act, prob.seg_start, 1, G, wgs_per_head, item_cost, min_steps,
-                   wave_tot, small, kPlanLdsInts);
+    attn_plan_body(plan, act_idx, [&](int i) { return i < k ? list[i] : first_q + i; }, n_act, prob.seg_start, 1, G, wgs_per_head, item_cost, wave_tot, small, kPlanLdsInts);
   else
-    attn_plan_body(plan, act_idx, [&](int i) { return act_idx[i]; }, n_act, prob.seg_start, 1, G, wgs_per_head, item_cost, min_steps,
-                   wave_tot, small, kPlanLdsInts);
+    attn_plan_body(plan, act_idx, [&](int i) { return act_idx[i]; }, n_act, prob.seg_start, 1, G, wgs_per_head, item_cost, wave_tot, small, kPlanLdsInts);
 }
 
 constexpr int kMaxRegKeys = 68 * 1024 - 3;   // rows of a request in registers, from whatever alignment it starts
@@ -658,7 +656,7 @@ extern "C" a3_status a3_topk_select_plan(const a3_layout *L, const float *scores
   const int G = L->n_q_heads / L->n_kv_heads;
   with_keys_per_lane(L->max_ctx_len, [&](auto kpt) {
     hipLaunchKernelGGL(topk_select_plan_kernel<kpt.value>, dim3(1), dim3(kBlock), 0, (hipStream_t)stream, scores, prob,
-                       sel_idx, act_idx, n_act, plan, G, plan.max_wgs, attn_item_cost(L, n_act), attn_min_steps(L));
+                       sel_idx, act_idx, n_act, plan, G, plan.max_wgs, attn_item_cost(L, n_act));
   });
   A3_CHECK_LAUNCH("a3_topk_select_plan");
   return A3_OK;

@@ -12,10 +12,10 @@ from gpu_util import idev
 
 pytestmark = pytest.mark.gpu
 
-COST, TM, TK = 4, 256, 64
+COST, TM, TK, MIN_STEPS = 4, 256, 64, 4
 
 
-def _plan(act, group, shares, min_steps):
+def _plan(act, group, shares):
     """(items, first item of each share, (first item, items) of each tile)"""
     rows = len(act) * group
     tiles = -(-rows // TM)
@@ -23,7 +23,7 @@ def _plan(act, group, shares, min_steps):
     steps = [-(-k // TK) for k in kv]
     pre = np.concatenate([[0], np.cumsum([s + COST for s in steps])])
     total = int(pre[-1])
-    p = max(1, min(-(-(total - tiles * COST) // min_steps), shares))
+    p = max(1, min(-(-(total - tiles * COST) // MIN_STEPS), shares))
     items, starts = [], []
     for q in range(p):
         beg, end = q * total // p, (q + 1) * total // p
@@ -49,7 +49,7 @@ def test_plan_of_one_request(group, n, ctx, shares, tuning):
     rng = np.random.default_rng(n)
     act = np.concatenate([np.sort(rng.permutation(ctx)[:n - 1]), [ctx]]).astype(np.int32)
     lay = api.Layout.from_workload(w)
-    items, starts, of_tile = _plan(act, group, wgs, 2 if ctx + 1 <= 768 else 4)
+    items, starts, of_tile = _plan(act, group, wgs)
     max_tiles = -(-n * group // TM) + 1
     sizes = [4, 2, 2, 4 * max_tiles, 2 * max_tiles, max_tiles + 1, 8 * (max_tiles + wgs), wgs + 1]     # 32-bit words of the arrays, in order
 
