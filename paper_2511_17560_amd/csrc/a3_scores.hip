@@ -280,15 +280,19 @@ scores_bf16_kernel(scores_args a) {
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
       kf[kb][ks] = *reinterpret_cast<const bf16x8 *>(Kin + ((size_t)krow[kb] * a.Hkv + g) * kD + 32 * ks + 8 * lg);
-  // ---- Q: chunk C of rows to its buffer
+  // ---- Q: chunk C of rows to its buffer, as 32-bit offsets from the first token that it reaches into (of the request they would end at 4 GiB)
   const int drow = 4 * wave + (lane >> 4), dpiece = (lane & 15) ^ (drow & 15);
   const bf16_t *Qr = (const bf16_t *)a.q + ((size_t)qrow0 * a.Hq + g * G) * kD;      // row 0 of the head
 #define A3_QDMA(C)                                                                                             \
-  _Pragma("unroll") for (int j = 0; j < kChunk / (4 * kWaves); ++j) {                                          \
-    const uint32_t m_ = (uint32_t)min((C) * kChunk + drow + 4 * kWaves * j, Mg - 1);                           \
-    const uint32_t off_ = (m_ + (G > 1 ? __umulhi(m_, a.inv_G) : m_) * (uint32_t)(a.Hq - G)) * (kD * 2) + 16 * dpiece; \
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"                               \
-                 :: "s"(lds_base + ((C) & 1) * kChunkBytes + (4 * wave + 4 * kWaves * j) * kKRowBytes), "v"(off_), "s"(Qr) : "memory"); \
+  {                                                                                                            \
+    const uint32_t j0_ = G > 1 ? __umulhi((uint32_t)((C) * kChunk), a.inv_G) : (uint32_t)((C) * kChunk);       \
+    const bf16_t *qc_ = Qr + (size_t)j0_ * a.Hq * kD;                                                          \
+    _Pragma("unroll") for (int j = 0; j < kChunk / (4 * kWaves); ++j) {                                        \
+      const uint32_t m_ = (uint32_t)min((C) * kChunk + drow + 4 * kWaves * j, Mg - 1);                         \
+      const uint32_t off_ = (m_ + (G > 1 ? __umulhi(m_, a.inv_G) : m_) * (uint32_t)(a.Hq - G) - j0_ * a.Hq) * (kD * 2) + 16 * dpiece; \
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"                             \
+                   :: "s"(lds_base + ((C) & 1) * kChunkBytes + (4 * wave + 4 * kWaves * j) * kKRowBytes), "v"(off_), "s"(qc_) : "memory"); \
+    }                                                                                                          \
   }
   static_assert((4 * kWaves) % 16 == 0, "the swizzle of a lane's rows is one number");
   if (n_chunks > 0) { A3_QDMA(0) }
