@@ -594,19 +594,21 @@ attn_combine_kernel(attn_args a) {
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32: one workgroup per 16 packed (row, head) pairs of a KV head; its eight or sixteen waves take the blocks of 16 keys in turn
+// fp32: one workgroup per 16 packed (row, head) pairs of a KV head; its eight waves take every eighth block of 16 keys
 // and merge at the end
 // ---------------------------------------------------------------------------------------
 // fp32 matrix instruction (16x16x4), fragments straight from memory.  S^T[key][m]: register r of lane (l16, lg) is key
 // 4 lg + r, pair l16 - which is the B operand of the r-th product of O^T[d][m] += V^T P^T when lane group lg supplies key
 // 4 lg + r of V; its lane l16 loads coordinates 4 l16 .. + 3 at once, so block e of O holds coordinates 4 (row) + e.
 // (One workgroup per row and head with a thread per key took 50 us for 108 rows x 8 heads x up to 544 keys.)
-constexpr int f32_waves(int d) { return d == 64 ? 16 : 8; }        // (128 coordinates do not fit the registers of 16)
-constexpr size_t kF32Lds(int d) { return (size_t)f32_waves(d) * 16 * (d * sizeof(float) + sizeof(float2)); }
+// Sixteen waves (64 coordinates) merge twice as much for blocks half as many: 108 rows x 8 heads x 544 keys 10.9 -> 12.3 us, 32 query heads
+// on 8 57 -> 65 for 339 rows of 2048 keys, 85 -> 115 for 3 x 346 of 1096; only above some 4000 keys, with as many workgroups as run at
+// once, are they faster (1264 rows of 8064 keys, 2 KV heads, 206 -> 178; 8 KV heads 193 -> 198).
+constexpr int kF32Waves = 8;
+constexpr size_t kF32Lds(int d) { return (size_t)kF32Waves * 16 * (d * sizeof(float) + sizeof(float2)); }
 template <int D>
-__global__ void __launch_bounds__(64 * f32_waves(D))
+__global__ void __launch_bounds__(64 * kF32Waves)
 attn_f32_kernel(attn_args a) {
-  constexpr int kF32Waves = f32_waves(D);
   extern __shared__ __align__(16) float lds_f[];               // [wave][D / 4 rows of 16 pairs] O as float4, then (ref, sum)
   f32x4 *lds_o = reinterpret_cast<f32x4 *>(lds_f);
   float2 *lds_ml = reinterpret_cast<float2 *>(lds_f + (size_t)kF32Waves * 16 * D);
@@ -623,11 +625,11 @@ attn_f32_kernel(attn_args a) {
 #pragma unroll
     for (int c = 0; c < D / 16; ++c) qf[c] = qp[4 * c];
   }
-  const int first = a.seg_start[0];                            // of one request: read beside the row number, not behind it (13.0 -> 12.6 us)
+  const int first = a.seg_start[0];                            // of one request: read beside the row number, not behind it
   const int t = a.act_idx[arow], req = a.tok_req ? a.tok_req[t] : 0;
   const int first_key = a.tok_req ? a.seg_start[req] : first;
   // the rows of one request at a time (rows are ascending: nearly always all of them), found in the lanes that hold them: lane x of a
-  // group belongs to row a0 + x / G, the last ones to the last row
+  // group belongs to row a0 + x / G, the last ones to the last row (with a loop over the rows' requests in memory 108 rows x 544 keys took 13.3 us, now 10.9)
   for (int b0 = a0; b0 < a_end;) {
     const int r = __builtin_amdgcn_readlane(req, (b0 - a0) * G), base = __builtin_amdgcn_readlane(first_key, (b0 - a0) * G);
     const uint32_t later = ((uint32_t)__ballot(req != r) & 0xffffu) >> ((b0 - a0) * G);
@@ -821,13 +823,11 @@ static a3_status attn_launch(const a3_layout *L, const void *q_act, const int *a
     const dim3 grid((n_act + rows - 1) / rows, L->n_kv_heads);
     static a3_once_per_device lds_once;
     const hipError_t e = a3_once(lds_once, []() {
-      const hipError_t e64 = hipFuncSetAttribute((const void *)attn_f32_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kF32Lds(64));
-      return e64 != hipSuccess ? e64
-                               : hipFuncSetAttribute((const void *)attn_f32_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kF32Lds(128));
+      return hipFuncSetAttribute((const void *)attn_f32_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kF32Lds(128));
     });
     if (e != hipSuccess) return a3_fail(A3_ERR_HIP, "a3_fused_attention: %s", hipGetErrorString(e));
-    if (L->head_dim == 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64 * f32_waves(64)), kF32Lds(64), st, a);
-    else hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(64 * f32_waves(128)), kF32Lds(128), st, a);
+    if (L->head_dim == 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64 * kF32Waves), kF32Lds(64), st, a);
+    else hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(64 * kF32Waves), kF32Lds(128), st, a);
   }
   A3_CHECK_LAUNCH("a3_fused_attention");
   return A3_OK;
