@@ -574,13 +574,23 @@ scores_head_sum_kernel(scores_args a, const int *__restrict__ tok_chunk) {
 // instructions (which coordinate goes to which does not matter as long as both operands agree).  C[key][row]: register
 // r of lane (l16, lg) is key 4 lg + r, row l16.  (One thread per key and row slice, 64 coordinates deep, took 280 +
 // 188 us for 512 keys x 256 rows.)  Small calls are launches and latency: with REALIGN the first pass turns the stale keys itself (a lane holds
-// whole pairs of either layout) and stores them, and the second merges the row statistics of up to 32 tiles and 1024 rows itself (512 keys, 32 rows per head: four launches of 3 - 5 us -> two of 5 - 6).
-constexpr int kF32MergeTiles = 32, kF32MergeRows = 1024;
-template <int PASS, int D, bool REALIGN>
+// whole pairs of either layout) and stores them, and the second (MERGE) merges the row statistics itself (512 keys, 32 rows per head: four launches of 3 - 5 us
+// -> two of 5 - 6).
+constexpr int kF32MergeRows = 1024;              // row statistics in LDS
+// Every workgroup merges tiles x rows partials where the combine kernel would merge them once, for a launch of 3 to 5 us.  Calls with the merge in
+// the pass and with the kernel, us: 8 tiles 154 and 165 (1024 rows, 384 workgroups), 759 and 772 (1536); 16 tiles, 256 workgroups 112 and 119
+// (1024 rows), 768 workgroups 39 and 41 (128 rows), 66 and 67 (256), 232 and 221 (1024), 512 workgroups of 128 coordinates 48.3 and 48.2 (128),
+// 84 and 80 (256); 32 tiles, 256 workgroups 36 and 37 (256), 62 and 60 (512), 121 and 107 (1024), 512 workgroups 33 and 32 (128), 52 and
+// 49 (256).  Many workgroups of few rows lose as well: 16 tiles, 1536 workgroups, 8 rows 24.6 and 23.7.
+constexpr bool f32_merges(long long tiles, long long workgroups, long long rows) {
+  if (rows > kF32MergeRows) return false;
+  return tiles <= 8 || (tiles <= 16 && (workgroups <= 256 || (workgroups <= 768 && rows <= 128))) || (tiles <= 32 && workgroups <= 256 && rows <= 256);
+}
+template <int PASS, int D, bool REALIGN, bool MERGE>
 __global__ void __launch_bounds__(256)
 scores_f32_kernel(scores_args a) {
   __shared__ float2 red[4][16];                                // PASS 0: (max, sum) of the rows over a wave's keys
-  __shared__ float stats[PASS == 1 ? kF32MergeRows : 1];
+  __shared__ float stats[MERGE ? kF32MergeRows : 1];
   const int r = blockIdx.z, g = blockIdx.y;
   const int N = a.ctx_len[r], i0 = blockIdx.x * kTileKeys;
   if (i0 >= N) return;
@@ -636,8 +646,7 @@ scores_f32_kernel(scores_args a) {
   };
   f32x4 colsum = {0.f, 0.f, 0.f, 0.f};
   if (Mg > 0) load_q(0);
-  const bool merge = PASS == 1 && !a.merged;
-  if (merge) {                                                 // at most kF32MergeTiles tiles, kF32MergeRows rows
+  if constexpr (MERGE) {                                       // at most kF32MergeRows rows
     for (int m = threadIdx.x; m < Mg; m += 256) {
       const float2 *pp = a.part + row_of(m);
       const int tiles = (N + kTileKeys - 1) / kTileKeys;
@@ -661,7 +670,7 @@ scores_f32_kernel(scores_args a) {
   }
   for (int m0 = 0; m0 < Mg; m0 += 16) {
     const int m = m0 + l16, row = row_of(min(m, Mg - 1));
-    const float stat = PASS == 0 ? 0.f : merge ? stats[min(m, Mg - 1)] : a.stats[row].x;
+    const float stat = PASS == 0 ? 0.f : MERGE ? stats[min(m, Mg - 1)] : a.stats[row].x;
     f32x4 c4[4];                                               // four chains, so that no product waits for the one before
 #pragma unroll
     for (int e = 0; e < 4; ++e) c4[e] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -804,13 +813,17 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
     hipLaunchKernelGGL((scores_bf16_kernel<1, false>), dim3((unsigned)wgs), dim3(kThreads), scores_lds_bytes(bufs, 1), st, a);
   } else {
     const dim3 grid(n_tiles, L->n_kv_heads, L->n_req), cgrid((unsigned)((total_rows + 15) / 16));
-    a.merged = n_tiles > kF32MergeTiles || L->max_q_len * G > kF32MergeRows ? 1 : 0;
+    a.merged = !f32_merges(n_tiles, (long long)n_tiles * L->n_kv_heads * L->n_req, (long long)L->max_q_len * G);
     auto launch = [&](auto dim) {
       constexpr int D = decltype(dim)::value;
-      if (fuse) hipLaunchKernelGGL((scores_f32_kernel<0, D, true>), grid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((scores_f32_kernel<0, D, false>), grid, dim3(256), 0, st, a);
-      if (a.merged) hipLaunchKernelGGL(scores_combine_kernel<false>, cgrid, dim3(256), 0, st, a);
-      hipLaunchKernelGGL((scores_f32_kernel<1, D, false>), grid, dim3(256), 0, st, a);
+      if (fuse) hipLaunchKernelGGL((scores_f32_kernel<0, D, true, false>), grid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((scores_f32_kernel<0, D, false, false>), grid, dim3(256), 0, st, a);
+      if (a.merged) {
+        hipLaunchKernelGGL(scores_combine_kernel<false>, cgrid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((scores_f32_kernel<1, D, false, false>), grid, dim3(256), 0, st, a);
+      } else {
+        hipLaunchKernelGGL((scores_f32_kernel<1, D, false, true>), grid, dim3(256), 0, st, a);
+      }
     };
     if (L->head_dim == 64) launch(std::integral_constant<int, 64>{});
     else launch(std::integral_constant<int, 128>{});
