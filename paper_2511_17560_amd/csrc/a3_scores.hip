@@ -69,11 +69,7 @@ struct scores_args {
   int causal_q, own_tile;
 };
 
-// bf16: partial i as (max, sum), and back
-__device__ __forceinline__ float2 partial(const float *z, const float *m, size_t i) {
-  const float x = z[i];
-  return x < 0.f ? make_float2(m[i], -x) : make_float2(x > 0.f ? 0.f : kLeast, x);
-}
+// bf16: a partial (max, sum) as the sum alone, or minus the sum and the maximum
 __device__ __forceinline__ void store_partial(float *pz, float *pm, size_t i, float m, float z) {
   pz[i] = m == 0.f || z == 0.f ? z : -z;
   if (m != 0.f && z != 0.f) pm[i] = m;
@@ -140,8 +136,14 @@ __global__ void __launch_bounds__(256)
 scores_combine_kernel(scores_args a) {
   auto part = [&](int t, int row) {
     const size_t i = (size_t)t * a.total_rows + row;
-    if constexpr (BF16) return partial(a.part_z, a.part_m, i);
+    if constexpr (BF16) return make_float2(0.f, a.part_z[i]);
     else return a.part[i];
+  };
+  auto maximum = [&](int t, int row, float2 &p) {              // bf16: the maximum of a partial, looked up where there is one
+    if constexpr (BF16) {
+      p.x = p.y < 0.f ? a.part_m[(size_t)t * a.total_rows + row] : p.y > 0.f ? 0.f : kLeast;
+      p.y = fabsf(p.y);
+    }
   };
   // one row per 16 lanes: the lanes split the row's tiles, then merge pairwise (fixed tree)
   const int row = blockIdx.x * 16 + (threadIdx.x >> 4);
@@ -156,6 +158,8 @@ scores_combine_kernel(scores_args a) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) p[u] = part(min(t + 16 * u, tiles - 1), row);
 #pragma unroll
+      for (int u = 0; u < 4; ++u) maximum(min(t + 16 * u, tiles - 1), row, p[u]);
+#pragma unroll
       for (int u = 0; u < 4; ++u)
         if (t + 16 * u < tiles) {
           const float mn = fmaxf(m, p[u].x);
@@ -164,7 +168,8 @@ scores_combine_kernel(scores_args a) {
         }
     }
     if (a.causal_q && slice == 15) {                           // the question keys' share (slice 15 has the fewest tiles)
-      const float2 p = part(a.n_tiles, row);
+      float2 p = part(a.n_tiles, row);
+      maximum(a.n_tiles, row, p);
       const float mn = fmaxf(m, p.x);
       z = (z > 0.f ? z * exp2f(m - mn) : 0.f) + p.y * exp2f(p.x - mn);
       m = mn;
@@ -192,7 +197,9 @@ scores_combine_kernel(scores_args a) {
 // row statistics are merged or Q is exchanged; and Eq. 2 turns the keys where they lie (a lane holds whole pairs of either layout).
 //   PASS 0  C[key][row]: a lane owns a row; sums of exp2(l) over the wave's keys, merged over the waves -> one partial (max, sum) per
 //           (tile, row).  The sums are taken as they come, without the row's maximum: fp32 holds them over 2^-64 .. 2^100 with the
-//           precision it has anywhere, and where one lies outside the wave forms its sums again with the maximum.
+//           precision it has anywhere.  Where one lies outside, the wave takes those of the 32 rows at hand against their maximum, and
+//           from there on all of them: the check costs calls of many rows 1 - 2 % (28 query heads on 4, eight requests of 8000 keys, 32 .. 128 question
+//           tokens 112 -> 114 us), one check per 128 rows, with another pass over these rows, costs calls outside the range 10 - 20 % more.
 //   PASS 1  C[row][key]: a lane owns a key; the partials of all tiles are merged per row (fixed order, the same in every workgroup),
 //           then sum over rows of exp2(l - stat) -> per KV head column sums; a last small kernel adds them in fixed order.
 // What bounds it: the issue port.  32 rows x 32 keys are 16 products, 16 x (fma, exp2, add) and 10 LDS reads of a wave, 390 cycles of a
@@ -315,19 +322,20 @@ scores_bf16_kernel(scores_args a) {
 #pragma unroll
       for (int u = 0; u < 32; ++u) { z += p[u]; least = fminf(least, p[u]); }
       z += pq;
-      if (least < 0.f) {                                       // sums against a maximum among them
-        mx = kLeast;
-        for (int u = -1; u < 32; ++u) {
-          const int tile = u < 0 ? a.n_tiles : first + u;
-          if (u < 0 ? !(a.causal_q && first == 0) : tile >= runs) continue;
-          mx = fmaxf(mx, partial(a.part_z, a.part_m, (size_t)tile * a.total_rows + at).x);
-        }
-        z = 0.f;
-        for (int u = 0; u < 33; ++u) {
-          const int tile = u == 32 ? a.n_tiles : first + u;
-          if (u == 32 ? !(a.causal_q && first == 0) : tile >= runs) continue;
-          const float2 x = partial(a.part_z, a.part_m, (size_t)tile * a.total_rows + at);
-          z += x.y > 0.f ? x.y * fast_exp2(x.x - mx) : 0.f;
+      if (least < 0.f) {                                       // sums against a maximum among them: those of 16 tiles requested together
+        mx = pq < 0.f ? a.part_m[(size_t)a.n_tiles * a.total_rows + at] : pq > 0.f ? 0.f : kLeast;
+        z = fabsf(pq);
+#pragma unroll
+        for (int u0 = 0; u0 < 32; u0 += 16) {
+          float m[16], mn = mx;
+#pragma unroll
+          for (int u = 0; u < 16; ++u) m[u] = p[u0 + u] < 0.f ? a.part_m[(size_t)(first + u0 + u) * a.total_rows + at] : p[u0 + u] > 0.f ? 0.f : kLeast;
+#pragma unroll
+          for (int u = 0; u < 16; ++u) mn = fmaxf(mn, m[u]);
+          z *= fast_exp2(mx - mn);
+#pragma unroll
+          for (int u = 0; u < 16; ++u) z += fabsf(p[u0 + u]) * fast_exp2(m[u] - mn);
+          mx = mn;
         }
       }
       if (!(z > 0.f)) mx = kLeast;                             // (a half without tiles)
@@ -395,6 +403,7 @@ scores_bf16_kernel(scores_args a) {
   }
 
   const bool have = iw < N, tail = own || iw + kKeysWave > N;
+  bool careful = false;                                        // PASS 0: the wave takes its sums against their maximum
   float colsum[2] = {0.f, 0.f};
   // LDS addresses of a lane's fragments of the rows l16 of a chunk, dims 32 ks + 8 lg ..: everything else is a constant offset
   typedef __attribute__((address_space(3))) const unsigned char *lds_ptr;
@@ -445,7 +454,6 @@ scores_bf16_kernel(scores_args a) {
               if (16 * kb + e >= seen) acc[kb][e] = -INFINITY;
         };
         float *pzw = pz + ((c & 1) * kWaves + wave) * kChunk, *pmw = pm + ((c & 1) * kWaves + wave) * kChunk;
-        bool again = false;
 #pragma unroll
         for (int rg = 0; rg < kChunk; rg += 32) {
           if (rg >= rows) break;
@@ -460,42 +468,40 @@ scores_bf16_kernel(scores_args a) {
             mask(seen_by(rg), acc[0]);
             mask(seen_by(rg + 16), acc[1]);
           }
-          float z[2];
+          // both sums over the wave's keys: lane groups 0 and 2 get the first 16 rows', lane groups 1 and 3 the others'
+          auto sums = [&](auto power) {
+            float z[2];
 #pragma unroll
-          for (int b = 0; b < 2; ++b) {
-            float z0 = fast_exp2(acc[b][0][0] * a.scale2), z1 = fast_exp2(acc[b][1][0] * a.scale2);
+            for (int b = 0; b < 2; ++b) {
+              float z0 = power(b, acc[b][0][0]), z1 = power(b, acc[b][1][0]);
 #pragma unroll
-            for (int e = 1; e < 4; ++e) {
-              z0 += fast_exp2(acc[b][0][e] * a.scale2);
-              z1 += fast_exp2(acc[b][1][e] * a.scale2);
+              for (int e = 1; e < 4; ++e) {
+                z0 += power(b, acc[b][0][e]);
+                z1 += power(b, acc[b][1][e]);
+              }
+              z[b] = z0 + z1;
             }
-            z[b] = z0 + z1;
+            return halves_sum(swap16_add(z[0], z[1]));
+          };
+          if (!careful) {
+            const float zz = sums([&](int, float x) { return fast_exp2(x * a.scale2); });
+            careful = __any(!(zz >= kSumLow && zz <= kSumHigh) && !(own && seen_by(rg + (lane & 16)) <= 0));   // (0: the row sees none of the keys)
+            if (!careful && lane < 32) pzw[rg + lane] = zz;
           }
-          // lane groups 0 and 2: the first 16 rows, lane groups 1 and 3: the others
-          const float zz = halves_sum(swap16_add(z[0], z[1]));
-          again |= !(zz >= kSumLow && zz <= kSumHigh) && !(own && seen_by(rg + (lane & 16)) <= 0);         // (0: the row sees none of the keys)
-          if (lane < 32) pzw[rg + lane] = zz;
-        }
-        if (__any(again)) {
-          for (int q = 0; q < rows; q += 16) {
-            if (share > 1 && ((c * (kChunk / 32) + q / 32) & (share - 1)) != sub) continue;
-            f32x4 acc[2];
-            logits(q, acc);
-            if (tail) mask(seen_by(q), acc);
-            float mx = kLeast;
+          if (careful) {
+            float mx[2];
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+            for (int b = 0; b < 2; ++b) {
+              mx[b] = fmaxf(acc[b][0][0], acc[b][1][0]);
 #pragma unroll
-              for (int e = 0; e < 4; ++e) { acc[kb][e] *= a.scale2; mx = fmaxf(mx, acc[kb][e]); }
-            const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-            mx = halves_max(fmaxf(__uint_as_float(w[0]), __uint_as_float(w[1])));
-            float sum = 0.f;
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-              for (int e = 0; e < 4; ++e) sum += fast_exp2(acc[kb][e] - mx);
-            sum = halves_sum(swap16_add(sum, sum));
-            if (lane < 16) store_partial(pzw, pmw, q + lane, mx, sum);
+              for (int e = 1; e < 4; ++e) mx[b] = fmaxf(fmaxf(mx[b], acc[b][0][e]), acc[b][1][e]);
+            }
+            const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx[0]), __float_as_uint(mx[1]), false, false);
+            const float own_mx = fmaxf(halves_max(fmaxf(__uint_as_float(w[0]), __uint_as_float(w[1]))) * a.scale2, kLeast);
+            const auto u = __builtin_amdgcn_permlane16_swap(__float_as_uint(own_mx), __float_as_uint(own_mx), false, false);
+            const float of[2] = {__uint_as_float(u[0]), __uint_as_float(u[1])};
+            const float zz = sums([&](int b, float x) { return fast_exp2(fmaf(x, a.scale2, -of[b])); });
+            if (lane < 32) store_partial(pzw, pmw, rg + lane, own_mx, zz);
           }
         }
       } else {
@@ -527,14 +533,19 @@ scores_bf16_kernel(scores_args a) {
     if (PASS == 0 || c + 1 < n_chunks) { A3_LDS_BARRIER(); }
     if (PASS == 0 && tid < rows) {
       const float *zc = pz + (c & 1) * kWaves * kChunk + tid, *mc = pm + (c & 1) * kWaves * kChunk + tid;
-      float mx = 0.f, z = 0.f, least = 0.f;
+      float mx = 0.f, z = 0.f, least = 0.f, x[kWaves];
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) { const float x = zc[w * kChunk]; z += x; least = fminf(least, x); }
+      for (int w = 0; w < kWaves; ++w) { x[w] = zc[w * kChunk]; z += x[w]; least = fminf(least, x[w]); }
       if (least < 0.f) {
+        float xm[kWaves];
         mx = kLeast;
-        for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, partial(zc, mc, w * kChunk).x);
         z = 0.f;
-        for (int w = 0; w < kWaves; ++w) { const float2 x = partial(zc, mc, w * kChunk); z += x.y * fast_exp2(x.x - mx); }
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) xm[w] = mc[w * kChunk];
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) { xm[w] = x[w] < 0.f ? xm[w] : x[w] > 0.f ? 0.f : kLeast; mx = fmaxf(mx, xm[w]); }
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) z += fabsf(x[w]) * fast_exp2(xm[w] - mx);
       }
       store_partial(a.part_z, a.part_m, (size_t)t * a.total_rows + row0 + c * kChunk + tid, mx, z);
     }
