@@ -764,7 +764,7 @@ size_t a3_attn_ws_bytes(const a3_layout *L, int max_active_rows) {
          a3_align_up((tiles + 1) * sizeof(int), 256) + a3_align_up(items * 2 * sizeof(int4), 256) +
          a3_align_up((size_t)(attn_wgs_per_head(L) + 1) * sizeof(int), 256) + 256 +
          a3_align_up(items * L->n_kv_heads * kTM * kD * sizeof(float), 256) +
-         a3_align_up(items * L->n_kv_heads * kTM * sizeof(float2), 256) + 2048;
+         a3_align_up(items * L->n_kv_heads * kTM * sizeof(float2), 256) + a3_align_up(kFirstBytes, 256);
 }
 
 // parts & 1: lay out the work (plan kernel); parts & 2: attend and merge.  The plan only depends on the list of

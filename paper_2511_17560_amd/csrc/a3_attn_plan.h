@@ -16,6 +16,7 @@ constexpr int kTM = 256;            // packed (row, head) pairs per work item: 3
 constexpr int kMinSteps = 4;
 constexpr int kPlanThreads = 1024;
 constexpr int kOneShares = 64;      // shares that one wave can lay out
+constexpr size_t kFirstBytes = (size_t)kOneShares * 2 * sizeof(int4);      // room for their first items (attn_plan::wg_first)
 constexpr int kPlanLdsInts = 6144;  // LDS the plan kernel sets aside for the plan's small arrays (24 KB)
 
 // Work decomposition written by the plan kernel.
@@ -379,7 +380,7 @@ inline void attn_plan_carve(const a3_layout *L, int n_act, void *ws, size_t ws_b
   p->wg_start = (int *)cur.take((size_t)(wgs_per_head + 1) * sizeof(int));
   p->part_o = (float *)cur.take((size_t)max_items * Hkv * kTM * 128 * sizeof(float));
   p->part_ml = (float2 *)cur.take((size_t)max_items * Hkv * kTM * sizeof(float2));
-  p->wg_first = wgs_per_head <= kOneShares ? (int4 *)cur.take((size_t)wgs_per_head * 2 * sizeof(int4)) : nullptr;     // 2 KB at most
+  p->wg_first = wgs_per_head <= kOneShares ? (int4 *)cur.take((size_t)wgs_per_head * 2 * sizeof(int4)) : nullptr;     // kFirstBytes at most
   p->max_tiles = max_tiles; p->max_items = max_items; p->max_wgs = wgs_per_head;
 }
 
