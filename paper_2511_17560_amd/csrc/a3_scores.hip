@@ -208,7 +208,12 @@ scores_combine_kernel(scores_args a) {
 // Whole calls with position recovery, us, and without (before: keys through LDS, rows in registers, a kernel each for up to 256 rows and for
 // more): 65.6K keys of eight requests, 32 .. 128 question tokens, 209 -> 178 and 172 -> 150; 30K keys, 96 tokens, 106 -> 85 and 92 -> 71; 64K, 64 tokens,
 // 147 -> 136 and 109 -> 107; 16K, 64 tokens, 48 -> 45 and 37.5 -> 35.4; 2K, 32 tokens, 24 -> 21 and 19.5 -> 17; 5K, 64 tokens, 27 -> 26.5 and 21.4 -> 21.7.
-// Scores against float64: 1.6 .. 6e-7 -> 0.6 .. 0.9e-7 (log2_sum).
+// Slower are calls of 129 .. 256 rows per KV head that leave most CUs idle, whose second chunk is one more chain of latencies: 500 keys, 32 tokens, 28 query
+// heads on 4, 20.3 -> 22.4 and 19.0 -> 19.9; four requests of 500 keys, 32 .. 64 tokens, 22.7 -> 24.2 and 20.8 -> 21.7 (no gain: Q's second
+// chunk requested behind the first, no barrier between the two).
+// Scores against float64: 1.6 .. 6e-7 -> 0.8 .. 2.8e-7 (log2_sum; 2-norm, keys of which a tenth stand out by 6 in the logit, the rest alike). With
+// all logits at +-40 or more the products themselves are that large and their rounding counts: 2-norm 0.2 .. 8e-6, 0.6 .. 1.3 of before, largest error
+// of one key up to 2.2 times what it was up to 256 rows per KV head, where the second pass used to start its products from the statistics.
 // ---------------------------------------------------------------------------------------
 constexpr int kD = 128;
 constexpr int kKRowBytes = kD * 2;

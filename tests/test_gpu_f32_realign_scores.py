@@ -1,5 +1,5 @@
 """fp32: position recovery inside the first scoring pass (its keys against a3_rope_realign bit for bit, also in place), the row statistics
-merged by the second pass up to 32 tiles of 64 keys and 1024 rows per KV head and by a kernel of their own beyond, and the row list made
+merged by the second pass or by a kernel in front of it (32 and 33 tiles of 64 keys, 1024 and 1026 rows per KV head), and the row list made
 by the kernel that selects.  Scores against a float64 softmax of the realigned keys, 2e-5 element by element as in test_gpu_parity.py."""
 import numpy as np
 import pytest
