@@ -191,8 +191,8 @@ scores_combine_kernel(scores_args a) {
 // ---------------------------------------------------------------------------------------
 // bf16 MFMA kernel, head_dim 128.  PASS 0 = partial row statistics, PASS 1 = column sums.
 //
-// Workgroup (8 waves, two per CU) = one KV head of one request against a tile of 256 context keys.  A wave keeps its 32 keys in registers, as
-// matrix operands, and walks all rows m = (question token, head) of the KV head; the rows' Q comes through two LDS buffers of 128
+// Workgroup (8 waves, two per CU) = one KV head of one request against a tile of 256 context keys (or 288, scores_tile_keys).  A wave keeps its 32 keys
+// in registers, as matrix operands, and walks all rows m = (question token, head) of the KV head; the rows' Q comes through two LDS buffers of 128
 // rows, which all waves share.  So no key goes through LDS; a wave forms whole column sums by itself and meets the others only where
 // row statistics are merged or Q is exchanged; and Eq. 2 turns the keys where they lie (a lane holds whole pairs of either layout).
 //   PASS 0  C[key][row]: a lane owns a row; sums of exp2(l) over the wave's keys, merged over the waves -> one partial (max, sum) per
@@ -210,7 +210,8 @@ scores_combine_kernel(scores_args a) {
 // 147 -> 136 and 109 -> 107; 16K, 64 tokens, 48 -> 45 and 37.5 -> 35.4; 2K, 32 tokens, 24 -> 21 and 19.5 -> 17; 5K, 64 tokens, 27 -> 26.5 and 21.4 -> 21.7.
 // Slower are calls of 129 .. 256 rows per KV head that leave most CUs idle, whose second chunk is one more chain of latencies: 500 keys, 32 tokens, 28 query
 // heads on 4, 20.3 -> 22.4 and 19.0 -> 19.9; four requests of 500 keys, 32 .. 64 tokens, 22.7 -> 24.2 and 20.8 -> 21.7 (no gain: Q's second
-// chunk requested behind the first, no barrier between the two).
+// chunk requested behind the first, no barrier between the two); and of such rows a little behind 256 or 512 workgroups where
+// scores_tile_keys keeps 256 keys: 10K keys, 64 tokens, 32 heads on 8, 23.9 -> 26.8 and (realign + scores) 32.0 -> 36.4.
 // Scores against float64: 1.6 .. 6e-7 -> 0.8 .. 2.8e-7 (log2_sum; 2-norm, keys of which a tenth stand out by 6 in the logit, the rest alike). With
 // all logits at +-40 or more the products themselves are that large and their rounding counts: 2-norm 0.2 .. 8e-6, 0.6 .. 1.3 of before, largest error
 // of one key up to 2.2 times what it was up to 256 rows per KV head, where the second pass used to start its products from the statistics.
@@ -229,6 +230,7 @@ constexpr float kSumLow = 0x1p-64f, kSumHigh = 0x1p100f;
 constexpr size_t scores_lds_bytes(int bufs, int pass) {
   return (size_t)bufs * kChunkBytes + (pass == 0 ? 2 * kWaves * kChunk * sizeof(float2) : kStatRows * sizeof(float) + kThreads / 2 * sizeof(float2));
 }
+static_assert(kWaves * kKeysWave * sizeof(float) <= kThreads / 2 * sizeof(float2), "the other keys' column sums take the place of half of a merge");
 static_assert(2 * scores_lds_bytes(2, 0) <= 160 * 1024 && scores_lds_bytes(2, 1) <= scores_lds_bytes(2, 0), "two workgroups per CU");
 
 
@@ -248,9 +250,12 @@ __device__ __forceinline__ float swap16_add(float a, float b) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-template <int PASS, bool REALIGN>
+// MORE: tiles of 288 keys, two chunks of rows at most.  Once through the rows with 256 keys, then with the other 32, which every wave holds, for an eighth of
+// the rows each.
+template <int PASS, bool REALIGN, bool MORE>
 __global__ void __launch_bounds__(kThreads, 4)
 scores_bf16_kernel(scores_args a) {
+  constexpr int kKeys = MORE ? kTile + kKeysWave : kTile;
   extern __shared__ __align__(16) unsigned char lds_raw[];
   // blockIdx % Hkv = KV head: with 8 heads an XCD has one, and its L2 that head's Q rows and partial statistics.  PASS 0 of the causal
   // denominator has one more tile per request, its question keys, each row up to its own token
@@ -260,7 +265,7 @@ scores_bf16_kernel(scores_args a) {
   const int g = (int)(blockIdx.x - rest * a.Hkv), r = a.n_req == 1 ? 0 : (int)quotient(rest, n_runs, a.inv_runs[PASS]), t = (int)(rest - r * n_runs);
   const bool own = PASS == 0 && !REALIGN && t == a.n_tiles;
   const int n_ctx = a.one_ctx_len >= 0 ? a.one_ctx_len : a.ctx_len[r];
-  const int i0 = own ? 0 : t * kTile;
+  const int i0 = own ? 0 : t * kKeys;
   if (!own && i0 >= n_ctx) return;
   const int G = a.Hq / a.Hkv, n_q = a.one_ctx_len >= 0 ? a.one_q_len : a.q_len[r];
   const int Mg = n_q * G;                                      // rows of this KV head: m = j * G + hh
@@ -270,28 +275,32 @@ scores_bf16_kernel(scores_args a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, lg = lane >> 4;
   // waves with question keys, of which there may be few: the others take some of their rows
-  const int key_waves = !own || n_q > 128 ? kWaves : n_q > 64 ? 4 : n_q > 32 ? 2 : 1, share = kWaves / key_waves, sub = wave / key_waves;
-  const int iw = i0 + kKeysWave * (wave & (key_waves - 1));    // the wave's first key
+  const int key_waves = !own || n_q > 128 ? kWaves : n_q > 64 ? 4 : n_q > 32 ? 2 : 1;
+  int share = kWaves / key_waves, sub = wave / key_waves;
+  int iw = i0 + kKeysWave * (wave & (key_waves - 1));          // the wave's first key
   const int n_chunks = (Mg + kChunk - 1) / kChunk;
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds_raw;
   unsigned char *extra = lds_raw + min(n_chunks, 2) * kChunkBytes;
   float *St = reinterpret_cast<float *>(extra);                // PASS 1: [kStatRows]
   float *pz = reinterpret_cast<float *>(extra), *pm = pz + 2 * kWaves * kChunk;        // PASS 0: partials of the waves, [2][kWaves][kChunk]
 
-  // ---- keys: fragment (kb, ks) of a lane: 16 bytes of key iw + 16 kb + l16, dims 32 ks + 8 lg ..
+  // ---- keys from i on: fragment (kb, ks) of a lane: 16 bytes of key i + 16 kb + l16, dims 32 ks + 8 lg ..
   bf16x8 kf[2][4];
   int krow[2], chunk[2];
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
-    krow[kb] = min(s + iw + 16 * kb + l16, a.T - 1);           // past the run: loaded, masked or never stored
-    if (REALIGN) chunk[kb] = iw + 16 * kb + l16 < N ? a.tok_chunk[krow[kb]] : -1;
-  }
   const bf16_t *Kin = (const bf16_t *)(REALIGN ? a.k_cat : a.k);
+  auto load_keys = [&](int i) {
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
+    for (int kb = 0; kb < 2; ++kb) {
+      krow[kb] = min(s + i + 16 * kb + l16, a.T - 1);          // past the run: loaded, masked or never stored
+      if (REALIGN) chunk[kb] = i + 16 * kb + l16 < N ? a.tok_chunk[krow[kb]] : -1;
+    }
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      kf[kb][ks] = *reinterpret_cast<const bf16x8 *>(Kin + ((size_t)krow[kb] * a.Hkv + g) * kD + 32 * ks + 8 * lg);
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        kf[kb][ks] = *reinterpret_cast<const bf16x8 *>(Kin + ((size_t)krow[kb] * a.Hkv + g) * kD + 32 * ks + 8 * lg);
+  };
+  load_keys(iw);
   // ---- Q: chunk C of rows to its buffer, as 32-bit offsets from the first token that it reaches into (of the request they would end at 4 GiB)
   const int drow = 4 * wave + (lane >> 4), dpiece = (lane & 15) ^ (drow & 15);
   const bf16_t *Qr = (const bf16_t *)a.q + ((size_t)qrow0 * a.Hq + g * G) * kD;      // row 0 of the head
@@ -317,7 +326,7 @@ scores_bf16_kernel(scores_args a) {
       // two threads a row where there are enough (up to 64 runs), else one (up to 32)
       const bool two = Mg <= kThreads / 2;
       const int m = two ? tid % (kThreads / 2) : tid, first = two ? tid / (kThreads / 2) * 32 : 0;
-      const int runs = (N + kTile - 1) / kTile;
+      const int runs = (N + kKeys - 1) / kKeys;
       const size_t at = (size_t)row0 + min(m, Mg - 1);
       float mx = 0.f, z = 0.f, p[32];
 #pragma unroll
@@ -359,8 +368,7 @@ scores_bf16_kernel(scores_args a) {
     }
   }
 
-  if (REALIGN) {
-    bf16_t *Ko = (bf16_t *)a.k_out;
+  auto turn_keys = [&]() {
     const bool inter = a.rope_layout == A3_ROPE_INTERLEAVED;
 #pragma unroll
     for (int p = 0; p < 2; ++p) {                              // dims of fragments 2 p and 2 p + 1 (interleaved), or p and p + 2
@@ -398,16 +406,22 @@ scores_bf16_kernel(scores_args a) {
     }
     __builtin_amdgcn_s_waitcnt(0);                             // Q has landed: nothing below waits for the stores
     asm volatile("" ::: "memory");
+  };
+  auto store_keys = [&](int i) {
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
-      if (iw + 16 * kb + l16 < N) {
+      if (i + 16 * kb + l16 < N) {
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
-          *reinterpret_cast<bf16x8 *>(Ko + ((size_t)krow[kb] * a.Hkv + g) * kD + 32 * ks + 8 * lg) = kf[kb][ks];
+          *reinterpret_cast<bf16x8 *>((bf16_t *)a.k_out + ((size_t)krow[kb] * a.Hkv + g) * kD + 32 * ks + 8 * lg) = kf[kb][ks];
       }
+  };
+  if (REALIGN) {
+    turn_keys();
+    store_keys(iw);
   }
 
-  const bool have = iw < N, tail = own || iw + kKeysWave > N;
+  bool have = iw < N, tail = own || iw + kKeysWave > N;
   bool careful = false;                                        // PASS 0: the wave takes its sums against their maximum
   float colsum[2] = {0.f, 0.f};
   // LDS addresses of a lane's fragments of the rows l16 of a chunk, dims 32 ks + 8 lg ..: everything else is a constant offset
@@ -419,147 +433,197 @@ scores_bf16_kernel(scores_args a) {
   // Q and the keys are there
   if (!REALIGN) __builtin_amdgcn_s_waitcnt(0);
   A3_LDS_BARRIER();
-  for (int c = 0; c < n_chunks; ++c) {
-    if (c > 0 && c + 1 < n_chunks) { A3_QDMA(c + 1) }
-    if (PASS == 1 && a.merged && (c + 1) * kChunk >= kStatRows && c + 1 < n_chunks && tid < kChunk) {
-      const int m = (c + 1) * kChunk + tid;
-      St[m % kStatRows] = m < Mg ? a.stats[row0 + m].x : INFINITY;
+  const int i1 = i0 + kTile, n_more = own ? 0 : min(kKeysWave, N - i1);       // MORE: the other keys
+  for (int part = 0; part < (MORE ? 2 : 1); ++part) {
+    if (MORE && part == 1) {
+      if (n_more > 0) {
+        load_keys(i1);
+        if (REALIGN) {
+          turn_keys();
+          A3_LDS_BARRIER();                                      // (in place: every wave has read the keys)
+          if (wave == 0) store_keys(i1);
+        }
+      }
+      iw = i1;
+      share = kWaves;
+      sub = wave;
+      have = n_more > 0;
+      tail = iw + kKeysWave > N;
+      colsum[0] = colsum[1] = 0.f;
     }
-    const uint32_t cb = (c & 1) * kChunkBytes;
-    const int rows = min(kChunk, Mg - c * kChunk);
-    if (have) {
-      // logits of the 16 rows from row q of the chunk on
-      auto logits = [&](int q, f32x4 (&acc)[2]) {
-        bf16x8 qf[4];
+    for (int c = 0; c < n_chunks; ++c) {
+      if (c > 0 && c + 1 < n_chunks) { A3_QDMA(c + 1) }
+      if (PASS == 1 && a.merged && (c + 1) * kChunk >= kStatRows && c + 1 < n_chunks && tid < kChunk) {
+        const int m = (c + 1) * kChunk + tid;
+        St[m % kStatRows] = m < Mg ? a.stats[row0 + m].x : INFINITY;
+      }
+      const uint32_t cb = (c & 1) * kChunkBytes;
+      const int rows = min(kChunk, Mg - c * kChunk);
+      if (have) {
+        // logits of the 16 rows from row q of the chunk on
+        auto logits = [&](int q, f32x4 (&acc)[2]) {
+          bf16x8 qf[4];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) qf[ks] = *(__attribute__((address_space(3))) const bf16x8 *)((lds_ptr)(uintptr_t)(qat[ks] + cb) + q * kKRowBytes);
+          for (int ks = 0; ks < 4; ++ks) qf[ks] = *(__attribute__((address_space(3))) const bf16x8 *)((lds_ptr)(uintptr_t)(qat[ks] + cb) + q * kKRowBytes);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
+          for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-          for (int kb = 0; kb < 2; ++kb) {
-            const f32x4 c0 = ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[kb];
-            acc[kb] = PASS == 0 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][ks], qf[ks], c0, 0, 0, 0)
-                                : __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[ks], kf[kb][ks], c0, 0, 0, 0);
-          }
-      };
-      if (PASS == 0) {
-        // of the wave's keys, those that the lane's row sees
-        auto seen_by = [&](int q) {
-          if (!own) return N - iw;
-          const int m = c * kChunk + q + l16;
-          return min(N, (G > 1 ? (int)__umulhi((uint32_t)m, a.inv_G) : m) + 1) - iw;
+            for (int kb = 0; kb < 2; ++kb) {
+              const f32x4 c0 = ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[kb];
+              acc[kb] = PASS == 0 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][ks], qf[ks], c0, 0, 0, 0)
+                                  : __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[ks], kf[kb][ks], c0, 0, 0, 0);
+            }
         };
-        auto mask = [&](int seen, f32x4 (&acc)[2]) {
-          seen -= 4 * lg;
-          asm volatile("" : "+v"(seen));
+        if (PASS == 0) {
+          // of the wave's keys, those that the lane's row sees
+          auto seen_by = [&](int q) {
+            if (!own) return N - iw;
+            const int m = c * kChunk + q + l16;
+            return min(N, (G > 1 ? (int)__umulhi((uint32_t)m, a.inv_G) : m) + 1) - iw;
+          };
+          auto mask = [&](int seen, f32x4 (&acc)[2]) {
+            seen -= 4 * lg;
+            asm volatile("" : "+v"(seen));
 #pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (16 * kb + e >= seen) acc[kb][e] = -INFINITY;
-        };
-        float *pzw = pz + ((c & 1) * kWaves + wave) * kChunk, *pmw = pm + ((c & 1) * kWaves + wave) * kChunk;
+              for (int e = 0; e < 4; ++e)
+                if (16 * kb + e >= seen) acc[kb][e] = -INFINITY;
+          };
+          float *pzw = pz + ((c & 1) * kWaves + wave) * kChunk, *pmw = pm + ((c & 1) * kWaves + wave) * kChunk;
+          auto add = [&](int m, float mx, float z) {             // onto what the wave has of row m
+            const float z0 = pzw[m];
+            if (z0 >= 0.f && mx == 0.f) {
+              pzw[m] = z0 + z;
+            } else {
+              const float m0 = z0 < 0.f ? pmw[m] : z0 > 0.f ? 0.f : kLeast, mn = fmaxf(m0, mx);
+              store_partial(pzw, pmw, m, mn, fabsf(z0) * fast_exp2(m0 - mn) + z * fast_exp2(mx - mn));
+            }
+          };
 #pragma unroll
-        for (int rg = 0; rg < kChunk; rg += 32) {
-          if (rg >= rows) break;
-          if (share > 1 && ((c * (kChunk / 32) + rg / 32) & (share - 1)) != sub) {             // (another wave's rows)
-            if (lane < 32) pzw[rg + lane] = 0.f;
-            continue;
+          for (int rg = 0; rg < kChunk; rg += 32) {
+            if (rg >= rows) break;
+            if (share > 1 && ((c * (kChunk / 32) + rg / 32) & (share - 1)) != sub) {             // (another wave's rows)
+              if (!(MORE && part == 1) && lane < 32) pzw[rg + lane] = 0.f;
+              continue;
+            }
+            f32x4 acc[2][2];
+            logits(rg, acc[0]);
+            logits(rg + 16, acc[1]);
+            if (tail) {
+              mask(seen_by(rg), acc[0]);
+              mask(seen_by(rg + 16), acc[1]);
+            }
+            // both sums over the wave's keys: lane groups 0 and 2 get the first 16 rows', lane groups 1 and 3 the others'
+            auto sums = [&](auto power) {
+              float z[2];
+#pragma unroll
+              for (int b = 0; b < 2; ++b) {
+                float z0 = power(b, acc[b][0][0]), z1 = power(b, acc[b][1][0]);
+#pragma unroll
+                for (int e = 1; e < 4; ++e) {
+                  z0 += power(b, acc[b][0][e]);
+                  z1 += power(b, acc[b][1][e]);
+                }
+                z[b] = z0 + z1;
+              }
+              return halves_sum(swap16_add(z[0], z[1]));
+            };
+            if (!careful) {
+              const float zz = sums([&](int, float x) { return fast_exp2(x * a.scale2); });
+              careful = __any(!(zz >= kSumLow && zz <= kSumHigh) && !(own && seen_by(rg + (lane & 16)) <= 0));   // (0: the row sees none of the keys)
+              if (MORE && part == 1) {
+                if (!careful && lane < 32) add(rg + lane, 0.f, zz);
+              } else if (!careful && lane < 32) {
+                pzw[rg + lane] = zz;
+              }
+            }
+            if (careful) {
+              float mx[2];
+#pragma unroll
+              for (int b = 0; b < 2; ++b) {
+                mx[b] = fmaxf(acc[b][0][0], acc[b][1][0]);
+#pragma unroll
+                for (int e = 1; e < 4; ++e) mx[b] = fmaxf(fmaxf(mx[b], acc[b][0][e]), acc[b][1][e]);
+              }
+              const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx[0]), __float_as_uint(mx[1]), false, false);
+              const float own_mx = fmaxf(halves_max(fmaxf(__uint_as_float(w[0]), __uint_as_float(w[1]))) * a.scale2, kLeast);
+              const auto u = __builtin_amdgcn_permlane16_swap(__float_as_uint(own_mx), __float_as_uint(own_mx), false, false);
+              const float of[2] = {__uint_as_float(u[0]), __uint_as_float(u[1])};
+              const float zz = sums([&](int b, float x) { return fast_exp2(fmaf(x, a.scale2, -of[b])); });
+              if (MORE && part == 1) {
+                if (lane < 32) add(rg + lane, own_mx, zz);
+              } else if (lane < 32) {
+                store_partial(pzw, pmw, rg + lane, own_mx, zz);
+              }
+            }
           }
-          f32x4 acc[2][2];
-          logits(rg, acc[0]);
-          logits(rg + 16, acc[1]);
-          if (tail) {
-            mask(seen_by(rg), acc[0]);
-            mask(seen_by(rg + 16), acc[1]);
-          }
-          // both sums over the wave's keys: lane groups 0 and 2 get the first 16 rows', lane groups 1 and 3 the others'
-          auto sums = [&](auto power) {
-            float z[2];
+        } else {
+          const uint32_t sat = stat_at + (c * kChunk) % kStatRows * 4;
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-              float z0 = power(b, acc[b][0][0]), z1 = power(b, acc[b][1][0]);
+          for (int rg = 0; rg < kChunk; rg += 32) {
+            if (rg >= rows) break;
+            if (MORE && part == 1 && c * (kChunk / 32) + rg / 32 != wave) continue;
+            f32x4 acc[2][2], st[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) st[b] = *(__attribute__((address_space(3))) const f32x4 *)((lds_ptr)(uintptr_t)sat + (rg + 16 * b) * 4);
+            logits(rg, acc[0]);
+            logits(rg + 16, acc[1]);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+              float p0 = fast_exp2(fmaf(acc[0][kb][0], a.scale2, -st[0][0])), p1 = fast_exp2(fmaf(acc[1][kb][0], a.scale2, -st[1][0]));
 #pragma unroll
               for (int e = 1; e < 4; ++e) {
-                z0 += power(b, acc[b][0][e]);
-                z1 += power(b, acc[b][1][e]);
+                p0 += fast_exp2(fmaf(acc[0][kb][e], a.scale2, -st[0][e]));
+                p1 += fast_exp2(fmaf(acc[1][kb][e], a.scale2, -st[1][e]));
               }
-              z[b] = z0 + z1;
+              colsum[kb] += p0 + p1;
             }
-            return halves_sum(swap16_add(z[0], z[1]));
-          };
-          if (!careful) {
-            const float zz = sums([&](int, float x) { return fast_exp2(x * a.scale2); });
-            careful = __any(!(zz >= kSumLow && zz <= kSumHigh) && !(own && seen_by(rg + (lane & 16)) <= 0));   // (0: the row sees none of the keys)
-            if (!careful && lane < 32) pzw[rg + lane] = zz;
-          }
-          if (careful) {
-            float mx[2];
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-              mx[b] = fmaxf(acc[b][0][0], acc[b][1][0]);
-#pragma unroll
-              for (int e = 1; e < 4; ++e) mx[b] = fmaxf(fmaxf(mx[b], acc[b][0][e]), acc[b][1][e]);
-            }
-            const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx[0]), __float_as_uint(mx[1]), false, false);
-            const float own_mx = fmaxf(halves_max(fmaxf(__uint_as_float(w[0]), __uint_as_float(w[1]))) * a.scale2, kLeast);
-            const auto u = __builtin_amdgcn_permlane16_swap(__float_as_uint(own_mx), __float_as_uint(own_mx), false, false);
-            const float of[2] = {__uint_as_float(u[0]), __uint_as_float(u[1])};
-            const float zz = sums([&](int b, float x) { return fast_exp2(fmaf(x, a.scale2, -of[b])); });
-            if (lane < 32) store_partial(pzw, pmw, rg + lane, own_mx, zz);
           }
         }
-      } else {
-        const uint32_t sat = stat_at + (c * kChunk) % kStatRows * 4;
-#pragma unroll
-        for (int rg = 0; rg < kChunk; rg += 32) {
-          if (rg >= rows) break;
-          f32x4 acc[2][2], st[2];
-#pragma unroll
-          for (int b = 0; b < 2; ++b) st[b] = *(__attribute__((address_space(3))) const f32x4 *)((lds_ptr)(uintptr_t)sat + (rg + 16 * b) * 4);
-          logits(rg, acc[0]);
-          logits(rg + 16, acc[1]);
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb) {
-            float p0 = fast_exp2(fmaf(acc[0][kb][0], a.scale2, -st[0][0])), p1 = fast_exp2(fmaf(acc[1][kb][0], a.scale2, -st[1][0]));
-#pragma unroll
-            for (int e = 1; e < 4; ++e) {
-              p0 += fast_exp2(fmaf(acc[0][kb][e], a.scale2, -st[0][e]));
-              p1 += fast_exp2(fmaf(acc[1][kb][e], a.scale2, -st[1][e]));
-            }
-            colsum[kb] += p0 + p1;
-          }
-        }
+      } else if (PASS == 0 && !(MORE && part == 1)) {
+        for (int m = lane; m < rows; m += 64) pz[((c & 1) * kWaves + wave) * kChunk + m] = 0.f;
       }
-    } else if (PASS == 0) {
-      for (int m = lane; m < rows; m += 64) pz[((c & 1) * kWaves + wave) * kChunk + m] = 0.f;
+      if (MORE && part == 0) continue;                           // (all of Q is in LDS, the rows are merged behind the other keys)
+      if (c + 1 < n_chunks) __builtin_amdgcn_s_waitcnt(0);       // the next chunk of Q has landed
+      if (PASS == 0 || c + 1 < n_chunks) { A3_LDS_BARRIER(); }
+      if (PASS == 0 && tid < rows) {
+        const float *zc = pz + (c & 1) * kWaves * kChunk + tid, *mc = pm + (c & 1) * kWaves * kChunk + tid;
+        float mx = 0.f, z = 0.f, least = 0.f, x[kWaves];
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) { x[w] = zc[w * kChunk]; z += x[w]; least = fminf(least, x[w]); }
+        if (least < 0.f) {
+          float xm[kWaves];
+          mx = kLeast;
+          z = 0.f;
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) xm[w] = mc[w * kChunk];
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) { xm[w] = x[w] < 0.f ? xm[w] : x[w] > 0.f ? 0.f : kLeast; mx = fmaxf(mx, xm[w]); }
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) z += fabsf(x[w]) * fast_exp2(xm[w] - mx);
+        }
+        store_partial(a.part_z, a.part_m, (size_t)t * a.total_rows + row0 + c * kChunk + tid, mx, z);
+      }
     }
-    if (c + 1 < n_chunks) __builtin_amdgcn_s_waitcnt(0);       // the next chunk of Q has landed
-    if (PASS == 0 || c + 1 < n_chunks) { A3_LDS_BARRIER(); }
-    if (PASS == 0 && tid < rows) {
-      const float *zc = pz + (c & 1) * kWaves * kChunk + tid, *mc = pm + (c & 1) * kWaves * kChunk + tid;
-      float mx = 0.f, z = 0.f, least = 0.f, x[kWaves];
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) { x[w] = zc[w * kChunk]; z += x[w]; least = fminf(least, x[w]); }
-      if (least < 0.f) {
-        float xm[kWaves];
-        mx = kLeast;
-        z = 0.f;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) xm[w] = mc[w * kChunk];
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) { xm[w] = x[w] < 0.f ? xm[w] : x[w] > 0.f ? 0.f : kLeast; mx = fmaxf(mx, xm[w]); }
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) z += fabsf(x[w]) * fast_exp2(xm[w] - mx);
-      }
-      store_partial(a.part_z, a.part_m, (size_t)t * a.total_rows + row0 + c * kChunk + tid, mx, z);
+    if (PASS == 1 && part == 0) {
+      // lane groups 0 and 2: key block 0, groups 1 and 3: key block 1
+      const float v = halves_sum(swap16_add(colsum[0], colsum[1]));
+      if (lane < kKeysWave && iw + lane < N) a.part_scores[(size_t)g * a.T + s + iw + lane] = v;
     }
   }
 #undef A3_QDMA
-  if (PASS == 1) {
-    // lane groups 0 and 2: key block 0, groups 1 and 3: key block 1
+  if (MORE && PASS == 1) {
+    float *red = St + kStatRows;                               // [kWaves][kKeysWave] column sums of the other keys (the merge's place)
     const float v = halves_sum(swap16_add(colsum[0], colsum[1]));
-    if (lane < kKeysWave && iw + lane < N) a.part_scores[(size_t)g * a.T + s + iw + lane] = v;
+    if (lane < kKeysWave) red[wave * kKeysWave + lane] = v;
+    A3_LDS_BARRIER();
+    if (tid < n_more) {
+      float sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) sum += red[w * kKeysWave + tid];
+      a.part_scores[(size_t)g * a.T + s + i1 + tid] = sum;
+    }
   }
 }
 
@@ -744,6 +808,25 @@ size_t a3_scores_ws_bytes(const a3_layout *L) {
          a3_align_up((size_t)L->n_kv_heads * L->total_tokens * sizeof(float), 256) + 256;
 }
 
+// Keys of a tile of the bf16 passes.  A pass lasts as long as the CUs with the most workgroups: where a few more than 256, or than 512, would be left
+// over, each takes 32 more keys, up to 256 rows per KV head (all of Q in LDS).  Votes and realign + scores with 256 and 288 keys, us, 8 KV heads:
+// 256 rows, 280 workgroups 28.0 and 22.7, 36.3 and 32.2; 528 40.1 and 33.5, 52.0 and 48.0; 552 40.6 and 34.6, 52.0 and 48.6.
+// 64 rows, 272 workgroups 16.6 and 15.7, 27.1 and 25.8.
+// Lines: behind 256, context for 264 workgroups up to one and a half chunks (for 258 64 rows 14.4 and 15.5, 22.5 and 25.2; 256 rows 24.5 and 22.5,
+// 32.3 and 32.1).  Behind 512, room for one workgroup more per KV head (256 rows, 576 and 504: votes 39.6 and 42.6); votes from the second chunk on (64
+// rows, 528: 23.8 and 24.9); scores, which may realign, from 520 (256 rows, 514: 45.0 and 47.4 in one run, 48.9 and 47.9 in another) and 192 rows (160
+// rows, 528 of two requests: votes 33.5 and 29.8, realign + scores 43.5 and 44.8).  Inside them the worst that was seen is realign + scores of 36000 keys
+// on 4 KV heads, 252 rows: 50.7 and 52.0.
+// heads: KV heads of all requests, one workgroup each per tile.  own: votes, whose question keys have workgroups of their own.  The same
+// for scores with and without position recovery: they give the same bits.
+constexpr int scores_tile_keys(int max_ctx_len, long long heads, long long rows, bool own) {
+  const long long now = heads * ((max_ctx_len + kTile - 1) / kTile), less = heads * ((max_ctx_len + kTile + kKeysWave - 1) / (kTile + kKeysWave));
+  const bool many = rows > kChunk + kChunk / 2;
+  const bool first = now > 256 && less + (own ? heads : 0) <= 256 && (many || heads * max_ctx_len >= 264LL * kTile);
+  const bool second = less + heads <= 512 && (own ? now > 512 && rows > kChunk : many && heads * max_ctx_len >= 520LL * kTile);
+  return rows <= 2 * kChunk && (first || second) ? kTile + kKeysWave : kTile;
+}
+
 // k_cat != nullptr: the first pass also realigns (k_cat -> k_fused).
 // causal_q: the question keys a question token sees join its softmax denominator.  votes != nullptr: the per
 // KV head column sums [Hkv, T] go there; scores may then be NULL (no sum over heads).
@@ -763,7 +846,11 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
   hipStream_t st = (hipStream_t)stream;
   const bool bf16 = L->dtype == A3_BF16;
   const size_t total_rows = (size_t)L->n_req * L->max_q_len * L->n_q_heads;   // upper bound, used as row pitch
-  const int tk = bf16 ? kTile : kTileKeys;
+  const int G = L->n_q_heads / L->n_kv_heads;
+  // the question keys' share of the denominators: a tile of the first pass itself in bf16, up to its 256 keys; a kernel before the
+  // passes otherwise
+  const bool own_runs = causal_q && bf16 && L->max_q_len <= kTile;
+  const int tk = bf16 ? scores_tile_keys(L->max_ctx_len, (long long)L->n_req * L->n_kv_heads, (long long)L->max_q_len * G, own_runs) : kTileKeys;
   const int n_tiles = (L->max_ctx_len + tk - 1) / tk;
   a3_ws_cursor cur(ws, ws_bytes);
   scores_args a;
@@ -775,7 +862,6 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
   a.stats = (float2 *)cur.take(total_rows * sizeof(float2));
   a.part_scores = (float *)cur.take((size_t)L->n_kv_heads * L->total_tokens * sizeof(float));
   if (votes) a.part_scores = votes;                            // a KV head's column sums are its votes
-  const int G = L->n_q_heads / L->n_kv_heads;
   a.inv_G = G > 1 ? (uint32_t)(((1ull << 32) + G - 1) / G) : 0u;
   a.causal_q = causal_q;
   a.merged = 0;
@@ -793,9 +879,6 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
     s = a3_rope_realign(L, k_cat, k_fused, stream);
     if (s != A3_OK) return s;
   }
-  // the question keys' share of the denominators: a tile of the first pass itself in bf16, up to its 256 keys; a kernel before the
-  // passes otherwise
-  const bool own_runs = causal_q && bf16 && L->max_q_len <= kTile;
   a.own_tile = own_runs;
   if (causal_q && !own_runs) {
     const dim3 qgrid((unsigned)((total_rows + 3) / 4));
@@ -805,7 +888,8 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
   if (bf16) {
     static a3_once_per_device lds_once;
     const hipError_t e = a3_once(lds_once, []() {
-      for (const void *fn : {(const void *)scores_bf16_kernel<0, false>, (const void *)scores_bf16_kernel<0, true>, (const void *)scores_bf16_kernel<1, false>}) {
+      for (const void *fn : {(const void *)scores_bf16_kernel<0, false, false>, (const void *)scores_bf16_kernel<0, true, false>, (const void *)scores_bf16_kernel<1, false, false>,
+                             (const void *)scores_bf16_kernel<0, false, true>, (const void *)scores_bf16_kernel<0, true, true>, (const void *)scores_bf16_kernel<1, false, true>}) {
         const hipError_t e_ = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)scores_lds_bytes(2, 0));
         if (e_ != hipSuccess) return e_;
       }
@@ -823,10 +907,15 @@ static a3_status scores_launch(const a3_layout *L, const void *q_question, const
     a.inv_runs[0] = inverse(n_tiles + (fuse ? 0 : own_runs), wgs0);
     a.inv_runs[1] = inverse(n_tiles, wgs);
     const int bufs = rows > kChunk ? 2 : 1;
-    if (fuse) hipLaunchKernelGGL((scores_bf16_kernel<0, true>), dim3((unsigned)wgs), dim3(kThreads), scores_lds_bytes(bufs, 0), st, a);
-    else hipLaunchKernelGGL((scores_bf16_kernel<0, false>), dim3((unsigned)wgs0), dim3(kThreads), scores_lds_bytes(bufs, 0), st, a);
-    if (a.merged) hipLaunchKernelGGL(scores_combine_kernel<true>, dim3((unsigned)((total_rows + 15) / 16)), dim3(256), 0, st, a);
-    hipLaunchKernelGGL((scores_bf16_kernel<1, false>), dim3((unsigned)wgs), dim3(kThreads), scores_lds_bytes(bufs, 1), st, a);
+    auto passes = [&](auto more) {
+      constexpr bool kMore = decltype(more)::value;
+      if (fuse) hipLaunchKernelGGL((scores_bf16_kernel<0, true, kMore>), dim3((unsigned)wgs), dim3(kThreads), scores_lds_bytes(bufs, 0), st, a);
+      else hipLaunchKernelGGL((scores_bf16_kernel<0, false, kMore>), dim3((unsigned)wgs0), dim3(kThreads), scores_lds_bytes(bufs, 0), st, a);
+      if (a.merged) hipLaunchKernelGGL(scores_combine_kernel<true>, dim3((unsigned)((total_rows + 15) / 16)), dim3(256), 0, st, a);
+      hipLaunchKernelGGL((scores_bf16_kernel<1, false, kMore>), dim3((unsigned)wgs), dim3(kThreads), scores_lds_bytes(bufs, 1), st, a);
+    };
+    if (tk > kTile) passes(std::true_type{});
+    else passes(std::false_type{});
   } else {
     const dim3 grid(n_tiles, L->n_kv_heads, L->n_req), cgrid((unsigned)((total_rows + 15) / 16));
     a.merged = !f32_merges(n_tiles, (long long)n_tiles * L->n_kv_heads * L->n_req, (long long)L->max_q_len * G);
